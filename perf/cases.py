@@ -201,15 +201,15 @@ def listed():
         {"name": "layer_8x22b_b128_k6", "kind": "layer", "shape": "8x22b", "B": 128, "k": 6, "ctx": 707},
         # the smallest program: tiny f32 model, four sequences; launches and latency
         {"name": "round_tiny_b4_k4", "kind": "round", "shape": "tiny", "layers": 2, "B": 4, "k": 4, "prompt": 32},
-        # a whole draft/verify round with everything in HBM: draft steps, target layer, LM head, accept, commit
-        {"name": "round_8x7b_b32_k6", "kind": "round", "shape": "8x7b", "layers": 1, "B": 32, "k": 6, "prompt": 300},
+        # a whole draft/verify round with everything in HBM: draft steps, target layers, LM head, accept, commit
+        {"name": "round_8x7b_b32_k6", "kind": "round", "shape": "8x7b", "layers": 4, "B": 32, "k": 6, "prompt": 300},
         # the same round when the second layer does not fit the weight budget and streams from host memory
         {"name": "round_streamed_b64_k4", "kind": "round", "shape": "8x7b", "layers": 2, "B": 64, "k": 4, "prompt": 64,
          "streamed": True},
         # time to first token of one request
-        {"name": "prefill_8x7b_b1", "kind": "prefill", "shape": "8x7b", "layers": 1, "B": 1, "lo": 333, "hi": 333},
+        {"name": "prefill_8x7b_b1", "kind": "prefill", "shape": "8x7b", "layers": 4, "B": 1, "lo": 333, "hi": 333},
         # prefill of an offline batch of ragged prompts
-        {"name": "prefill_8x7b_b48", "kind": "prefill", "shape": "8x7b", "layers": 1, "B": 48, "lo": 256, "hi": 1024},
+        {"name": "prefill_8x7b_b48", "kind": "prefill", "shape": "8x7b", "layers": 4, "B": 48, "lo": 256, "hi": 1024},
         # stochastic acceptance of a large batch at the benchmark's vocabulary
         {"name": "accept_b256_k6_v32000", "kind": "accept", "B": 256, "k": 6, "V": 32000, "greedy": False},
         # a small batch with a large vocabulary of odd size
@@ -231,12 +231,12 @@ def draw(rng):
         which = rng.choice(["tiny", "8x7b", "8x7b", "streamed"])
         if which == "tiny":
             return {"kind": kind, "shape": "tiny", "layers": 2, "B": _log(rng, 1, 16), "k": rng.randint(1, 8), "prompt": _log(rng, 2, 96)}
-        c = {"kind": kind, "shape": "8x7b", "layers": 1, "B": _log(rng, 1, 64), "k": rng.randint(1, 8), "prompt": _log(rng, 8, 600)}
+        c = {"kind": kind, "shape": "8x7b", "layers": 4, "B": _log(rng, 1, 64), "k": rng.randint(1, 8), "prompt": _log(rng, 8, 600)}
         return c if which == "8x7b" else dict(c, layers=2, prompt=_log(rng, 8, 100), streamed=True)
     if kind == "prefill":
         B = _log(rng, 1, 32)
         lo = _log(rng, 4, 512)
-        return {"kind": kind, "shape": "8x7b", "layers": 1, "B": B, "lo": lo, "hi": min(1024, lo + rng.randint(0, 2 * lo))}
+        return {"kind": kind, "shape": "8x7b", "layers": 4, "B": B, "lo": lo, "hi": min(1024, lo + rng.randint(0, 2 * lo))}
     V = rng.choice([32000, 32768, _log(rng, 500, 100000), _log(rng, 500, 100000)])
     k = rng.randint(1, 8)
     B = _log(rng, 1, max(1, min(256, 256 * 13 * 32000 // ((2 * k + 1) * V))))
@@ -397,7 +397,8 @@ def tolerance(case):
         return {"rel": 0.0, "differ": 0.01}
     if case["shape"] == "tiny":
         return {"rel": 4e-6}
-    return {"rel": 1e-2}
+    # (bf16 activations: one layer is 1.6e-3 to 3.3e-3 off its 64-bit result, a whole pass up to 4.4e-3)
+    return {"rel": 1e-2 if case["kind"] == "layer" else 1.5e-2}
 
 
 # ---- 64-bit reference ---------------------------------------------------------------------------------------------
