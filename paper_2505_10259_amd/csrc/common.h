@@ -127,6 +127,7 @@ struct GemmArgs {
 // launchers (kernels_*.hip) -------------------------------------------------------------------
 hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st);
 hipError_t launch_gemm_mfma_bf16(const GemmArgs& a, hipStream_t st);   // gemm_mfma.hip
+bool qkv_unfused_pays(int M, int N, int K);
 
 struct AttnArgs {
     const void* q;            // [T, Hq*dh] model dtype
@@ -161,6 +162,9 @@ hipError_t launch_rope_table(const int32_t* row_pos, float2* cs, int T, int half
 hipError_t launch_rope_kv(const float* qkv, const float2* cs, const int32_t* row_pos,
                           const int32_t* page_table, void* q_out, void* kv_layer, KvGeom geom,
                           int T, int n_new, int n_q_heads, int dtype, hipStream_t st);
+// bf16, head_dim 128 (the MFMA path's buffer): the arithmetic of EPI_ROPE_KV on f32 projections
+hipError_t launch_rope_kv_bf16(const float* qkv, const float2* cs, const int32_t* row_pos, const int32_t* page_table,
+                               void* q_out, void* kv_layer, KvGeom geom, int T, int n_new, int n_q_heads, hipStream_t st);
 hipError_t launch_router(const void* h, const void* wr, int32_t* ids, float* wts, int T, int d,
                          int E, const int32_t* forced, const int32_t* row_pos, int dtype, hipStream_t st);
 // counting sort of the 2T (token, choice) pairs by expert: offsets[E+1], perm[2T] (sorted row ->

@@ -444,10 +444,17 @@ int layer_attn(spec_ctx* c, const spec_model_shape& s, const Layout& L, const ch
     GemmArgs g{};
     g.A = w.h; g.lda = d; g.W = W(L.wqkv); g.C = w.qkv; g.ldc = qkv_rows; g.M = T; g.N = qkv_rows; g.K = d;
     // bf16 MFMA path with 128-wide heads: rotation, q store and KV append happen in the projection's
-    // epilogue (no f32 qkv round trip); otherwise projection to f32, then the rope/append kernel
-    const bool fused_rope = dt == SPEC_BF16 && !(c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS) && s.head_dim == 128 &&
-                            d % 64 == 0;
-    if (fused_rope) {
+    // epilogue (no f32 qkv round trip) unless the row count asks for tiles narrower than a pair of heads;
+    // otherwise projection to f32, then the rope/append kernel.  The two bf16 ways give the same bits.
+    const bool mfma_rope = dt == SPEC_BF16 && !(c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS) && s.head_dim == 128 &&
+                           d % 64 == 0;
+    if (mfma_rope && qkv_unfused_pays(T, qkv_rows, d)) {
+        g.epilogue = EPI_STORE_F32;
+        { ProfScope ps(c, SPEC_PROF_QKV, st); HIPCHK(c, gemm(c, g, dt, st)); }
+        { ProfScope ps(c, SPEC_PROF_ROPE, st);
+          HIPCHK(c, launch_rope_kv_bf16(w.qkv, r.cs, r.row_pos, page_table, w.q, kv_layer, geom, T, r.n_new,
+                                        s.n_q_heads, st)); }
+    } else if (mfma_rope) {
         g.epilogue = EPI_ROPE_KV;
         g.C = w.q; g.ldc = qkv_rows;       // unused by the epilogue; kept valid for the launcher's checks
         g.rope.cs = r.cs; g.rope.row_pos = r.row_pos; g.rope.page_table = page_table; g.rope.q_out = w.q;

@@ -4,13 +4,14 @@
 //     matrices, silu(gate) * up, bf16 store).
 //
 // Design (64-wide wavefronts, CDNA4):
-//   * workgroup = 4 wavefronts in a 2x2 grid; each wavefront owns a (16*MI) x (32*WN_T) block of
+//   * workgroup = 4 wavefronts in a 2x2 grid; each wavefront owns a (16*MI) x (16*NI) block of
 //     16x16 v_mfma_f32_16x16x32_bf16 tiles held in accumulator registers (measured on MI355X with
 //     register-only operands: 2.41 PFLOP/s for this instruction, 2.04 for the 32x32x16 form).  The
 //     weight fragment is the MFMA's A operand, so a lane ends up with four consecutive output
 //     columns of one row and the epilogue stores 16 (f32) or 8 (bf16) bytes at a time;
 //   * operands go global -> LDS with global_load_lds_dwordx4 (no VGPR staging), 64-wide K slabs, the
-//     weights three slabs deep and the activations two (three where 160 KB allow).  A slab is two phases
+//     weights three slabs deep and the activations two (three where 160 KB allow) for 256-column tiles, as
+//     deep as 160 KB allow (up to 16 slabs) for narrower ones.  A slab is two phases
 //     (its two k-steps) with one barrier between them; the fragments of a k-step are read one phase
 //     ahead; every LDS read and every direct-to-LDS load stands alone in front of one MFMA (a
 //     compile-time list of micro-operations dealt over the MFMA slots), the loads issued from inline
@@ -31,6 +32,10 @@
 //     lockstep, so the weight slab one of them pulls from HBM is an L2 hit for the others (measured on
 //     the MoE gate/up GEMM: with a full-tiles-plus-remainder split the short remainder tiles drift
 //     ahead and the weights are fetched 2.7 times; with equal tiles 1.2 times);
+//   * tile width: 256 columns, or 128, 64 or 32 where wider tiles would leave compute units idle (see
+//     choose_tiles); the weights carry the non-temporal hint where no second row tile reads them (8x7B-shaped gate/up
+//     product, 40 rows: 308 -> 279 us, 6.74 TB/s; a streaming read of the same buffers: 6.2 TB/s
+//     plain, 7.05 with the hint);
 //   * tile order: group (expert), then bands of four row tiles, then column tile, then row tile
 //     within the band; the linear workgroup id is remapped so that each XCD (id % 8) walks one
 //     contiguous range of that order: the ~32 workgroups an XCD runs at a time form a block of about
@@ -41,6 +46,11 @@
 #include <utility>
 
 #include "common.h"
+
+// This file is compiled once for the launcher (SV_GEMM_PART 0) and once for each kernel (1..13).
+#ifndef SV_GEMM_PART
+#define SV_GEMM_PART 0
+#endif
 
 // the direct-to-LDS loads below set M0 themselves and say so in their clobber list; clang notes that M0
 // is a reserved register
@@ -75,16 +85,27 @@ __host__ __device__ inline void split_rows(int r, int max_rows, int& nt, int& rt
     rt = nt > 0 ? (((r + nt - 1) / nt + 15) & ~15) : 0;
 }
 
-// One output tile with (32*MI) x (64*WN_T) accumulators: rows [row_begin, row_end) of the (gathered)
+// LDS stages of a tile of 32*mi rows and 32*ni columns (64-wide slabs, 128 B a row).  256 columns (products
+// bound by the matrix cores): three stages of both operands where the 160 KB of a compute unit allow it, else two of
+// the activations.  Narrower tiles are for products whose columns would not occupy the chip otherwise, bound
+// by the weight bytes a unit has in flight: as many stages as fit, up to 16.
+constexpr int MAX_STAGES = 16;
+constexpr int lds_stages(int mi, int ni) { return 160 * 1024 / ((32 * mi + 32 * ni) * 128); }
+constexpr int weight_stages(int mi, int ni) {
+    return ni == 8 || lds_stages(mi, ni) < 3 ? 3 : lds_stages(mi, ni) < MAX_STAGES ? lds_stages(mi, ni) : MAX_STAGES;
+}
+constexpr int act_stages(int mi, int ni) { return lds_stages(mi, ni) < 3 ? 2 : weight_stages(mi, ni); }
+
+// One output tile with (32*MI) x (32*NI) accumulators: rows [row_begin, row_end) of the (gathered)
 // A (row_end - row_begin <= 32*MI), output columns from n0 on, weights of `group`.
-template <int MI, int WN_T, bool SWIGLU>
+template <int MI, int NI, int EPI, bool NT>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row_begin, int row_end, int n0,
                                           int group) {
-    constexpr int BM = 32 * MI, BN = 64 * WN_T;
+    constexpr bool SWIGLU = EPI == EPI_SWIGLU_T;
+    constexpr int BM = 32 * MI, BN = 32 * NI;
     constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128;
-    // LDS: activation stages, then three weight stages; the activations are three deep as well where
-    // 160 KB allow it (tiles of up to 160 rows at 256 columns, every tile at 128 columns)
-    constexpr int AST = 3 * (A_BYTES + B_BYTES) <= 160 * 1024 ? 3 : 2;
+    // LDS: activation stages, then weight stages
+    constexpr int BST = weight_stages(MI, NI), AST = act_stages(MI, NI);
     constexpr int B_BASE = AST * A_BYTES;
     constexpr int A_INST = BM / 32, B_INST = BN / 32; // direct-to-LDS loads per wavefront per slab
     const int tid = threadIdx.x, lane = tid & 63;
@@ -149,10 +170,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
     auto issue_b = [&](int q, int kt, int bst) {     // load q of weight slab kt into B stage bst
         const uint32_t dst = lds0 + B_BASE + bst * B_BYTES + (wu * B_INST + q) * 1024;
         const char* base = Wb + (int64_t)kt * 128;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(dst), "v"(b_o[q]), "s"(base) : "memory", "m0");
+        if constexpr (NT) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" :: "s"(dst), "v"(b_o[q]), "s"(base) : "memory", "m0");
+        else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(dst), "v"(b_o[q]), "s"(base) : "memory", "m0");
     };
 
-    constexpr int NI = 2 * WN_T;              // 16x16 tiles per wavefront: MI rows x NI columns
     f32x4_t acc[MI][NI];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -164,8 +185,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
     // fragment read offsets: row (lane & 15) of each 16-row tile, chunk (4*kk + lane/16) ^ key(row)
     const int frag_row = lane & 15, kquart = lane >> 4, sw = (frag_row >> 1) & 7;
     const int a_off = (wm * 16 * MI + frag_row) * 128;
-    const int b_off = (wn * 32 * WN_T + frag_row) * 128;
+    const int b_off = (wn * 16 * NI + frag_row) * 128;
 
+    const int KT = a.K / 64;
     constexpr int NL = A_INST + B_INST;      // slab loads per wavefront
     constexpr int NM = MI * NI;              // MFMAs of one k-step
     constexpr int NR = MI + NI;              // fragment reads of one k-step
@@ -177,17 +199,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
     // k-step issued as a group cost ~110 cycles of MFMA time each, 10 % per group).  Every phase therefore
     // issues its memory instructions ONE per MFMA slot, alternating fragment reads and loads:
     //   phase 0 of slab kt multiplies k-step 0 (fragments read during phase 1 of slab kt-1), reads the
-    //     k-step-1 fragments of slab kt and issues the weight loads of slab kt+2;
+    //     k-step-1 fragments of slab kt and issues the weight loads of slab kt+BST-1;
     //   then the wavefront waits for its own loads of slab kt+1 (vmcnt) and for its fragment reads, and
     //     all wavefronts meet: slab kt has been read by everyone, slab kt+1 has landed;
     //   phase 1 multiplies k-step 1, reads the k-step-0 fragments of slab kt+1 and issues the activation
     //     loads of slab kt+AST into the stage slab kt just left.
     // No MFMA waits for a read issued right in front of it, and the barrier comes when a wavefront's
     // reads are long complete.
-    const int KT = a.K / 64;
     bf16x8_t af[2][MI], bfr[2][NI];
-    auto stage_a = [&](int kt) { return smem + (AST == 3 ? kt % 3 : kt & 1) * A_BYTES; };
-    auto stage_b = [&](int kt) { return smem + B_BASE + (kt % 3) * B_BYTES; };
+    auto stage_a = [&](int kt) { return smem + (kt % AST) * A_BYTES; };
+    auto stage_b = [&](int kt) { return smem + B_BASE + (kt % BST) * B_BYTES; };
     // fragment read r of k-step kk of a slab: the weight fragments first (the first row of MFMAs needs all
     // of them), then the activation fragments in row order
     auto read_frag = [&](const char* As, const char* Bs, int kk, int r) {
@@ -200,13 +221,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
         __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
     };
     using I0 = std::integral_constant<int, 0>;
-    // loads that may stay pending at the barrier of slab kt: those issued for slab kt+2
-    using IB = std::integral_constant<int, AST == 3 ? NL : B_INST>;
-    using IPRO = std::integral_constant<int, (AST - 1) * A_INST>;
+    // loads that may stay pending at the barrier of slab kt: those issued behind the last load of slab kt+1
+    // (its weights with equal stages, its activations with two activation stages)
+    using IB = std::integral_constant<int, AST == BST ? (BST - 2) * NL : B_INST>;
+    using IPRO = std::integral_constant<int, (AST - 1) * A_INST + (BST - 3) * B_INST>;
+    static_assert(IB::value < 64 && IPRO::value < 64, "vmcnt counts up to 63");
 
-    // prologue: weights of slabs 0 and 1, then (their source rows have arrived) activations of slabs
-    // 0..AST-1.  Loads land in issue order: at the first barrier only activations of later slabs may be
-    // pending.
+    // prologue: weights of slabs 0 and 1, then (their source rows have arrived) activations of slabs 0 and
+    // 1, then weights and activations of each further slab and the activations of slab AST-1.  Loads land in
+    // issue order: at the first barrier everything behind the activations of slab 0 may be pending.
 #pragma unroll
     for (int q = 0; q < B_INST; ++q) issue_b(q, 0, 0);
     if (KT > 1) {
@@ -224,15 +247,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
     }
 #pragma unroll
     for (int q = 0; q < A_INST; ++q) issue_a(q, 0, 0);
-    if (KT > 1) {
 #pragma unroll
-        for (int q = 0; q < A_INST; ++q) issue_a(q, 1, 1);
-        if (AST == 3 && KT > 2) {
+    for (int t = 1; t < AST; ++t) {
+        if (KT > t) {
+            if (t >= 2 && t < BST - 1) {
 #pragma unroll
-            for (int q = 0; q < A_INST; ++q) issue_a(q, 2, 2);
+                for (int q = 0; q < B_INST; ++q) issue_b(q, t, t);
+            }
+#pragma unroll
+            for (int q = 0; q < A_INST; ++q) issue_a(q, t, t);
         }
     }
-    if (KT > 1 && (KT > 2 || AST == 2)) wait_vm(IPRO{}); else wait_vm(I0{});
+    if (KT >= AST) wait_vm(IPRO{}); else wait_vm(I0{});
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma unroll
@@ -288,20 +314,20 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
     using CA = std::integral_constant<int, A_INST>;
     using CB = std::integral_constant<int, B_INST>;
 
-    // one slab; MORE2: slab kt+2 exists (its weights are issued in phase 0), MOREA: slab kt+AST exists (its
-    // activations are issued in phase 1), NEXT: slab kt+1 exists
+    // one slab; MORE2: slab kt+BST-1 exists (its weights are issued in phase 0), MOREA: slab kt+AST exists
+    // (its activations are issued in phase 1), NEXT: slab kt+1 exists
     auto body = [&](int kt, auto more2_c, auto morea_c, auto next_c) {
         constexpr bool MORE2 = decltype(more2_c)::value, MOREA = decltype(morea_c)::value, NEXT = decltype(next_c)::value;
-        const int bst2 = (kt + 2) % 3;
+        const int bst2 = (kt + BST - 1) % BST;
         const char* As0 = stage_a(kt); const char* Bs0 = stage_b(kt);
         auto no_m0 = [](auto, auto) {};
         phase(C0{}, CNR{}, std::integral_constant<int, MORE2 ? B_INST : 0>{},
               [&](auto r_c) { read_frag(As0, Bs0, 1, decltype(r_c)::value); },
-              [&](auto q_c) { issue_b(decltype(q_c)::value, kt + 2, bst2); }, no_m0);
+              [&](auto q_c) { issue_b(decltype(q_c)::value, kt + BST - 1, bst2); }, no_m0);
         if (MORE2) wait_vm(IB{}); else wait_vm(I0{});
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        const int ast2 = AST == 3 ? (kt + AST) % 3 : (kt + AST) & 1;
+        const int ast2 = kt % AST;
         const char* As1 = stage_a(kt + 1); const char* Bs1 = stage_b(kt + 1);
         phase(C1{}, std::integral_constant<int, NEXT ? NR : 0>{}, std::integral_constant<int, MOREA ? A_INST : 0>{},
               [&](auto r_c) { read_frag(As1, Bs1, 0, decltype(r_c)::value); },
@@ -315,25 +341,25 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
     // wavefront issues between two MFMAs takes issue time from them (about 4 cycles each, measured: a slab
     // of 96 MFMAs with 132 other instructions took 1536 + 4 x 132 cycles), so the instruction count of the
     // loop is what separates it from the MFMA rate.
-    constexpr int PER = AST == 3 ? 3 : 6;
+    constexpr int PER = AST == BST ? BST : 6;
     typedef const __attribute__((address_space(3))) char* lds_cptr;
-    lds_cptr a_rd[AST][2], b_rd[3][2];
+    lds_cptr a_rd[AST][2], b_rd[BST][2];
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
         const int coff = ((4 * kk + kquart) ^ sw) << 4;
 #pragma unroll
         for (int st = 0; st < AST; ++st) a_rd[st][kk] = (lds_cptr)smem + st * A_BYTES + a_off + coff;
 #pragma unroll
-        for (int st = 0; st < 3; ++st) b_rd[st][kk] = (lds_cptr)smem + B_BASE + st * B_BYTES + b_off + coff;
+        for (int st = 0; st < BST; ++st) b_rd[st][kk] = (lds_cptr)smem + B_BASE + st * B_BYTES + b_off + coff;
     }
     const uint32_t a_ld0 = lds0 + wu * A_INST * 1024, b_ld0 = lds0 + B_BASE + wu * B_INST * 1024;
     auto body_s = [&](auto s_c, int kt) {
         constexpr int S = decltype(s_c)::value;
-        constexpr int SA0 = AST == 3 ? S % 3 : S & 1, SB0 = S % 3;                       // stages of slab kt
-        constexpr int SA1 = AST == 3 ? (S + 1) % 3 : (S + 1) & 1, SB1 = (S + 1) % 3;       // of slab kt+1
-        constexpr int SB2 = (S + 2) % 3, SA2 = AST == 3 ? (S + AST) % 3 : (S + AST) & 1;   // where the loads go
+        constexpr int SA0 = S % AST, SB0 = S % BST;                    // stages of slab kt
+        constexpr int SA1 = (S + 1) % AST, SB1 = (S + 1) % BST;        // of slab kt+1
+        constexpr int SB2 = (S + BST - 1) % BST, SA2 = S % AST;        // where the loads go
         typedef const __attribute__((address_space(3))) bf16x8_t* lds_frag;
-        const char* wbase = Wb + (int64_t)(kt + 2) * 128;
+        const char* wbase = Wb + (int64_t)(kt + BST - 1) * 128;
         const char* abase = Ab + (int64_t)(kt + AST) * 128;
         phase(C0{}, CNR{}, CB{},
               [&](auto r_c) {
@@ -345,7 +371,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
                   // (locals: operands of an assembly statement do not make a generic lambda capture a variable)
                   const uint32_t off = b_o[decltype(q_c)::value];
                   const char* base = wbase;
-                  asm volatile("global_load_lds_dwordx4 %0, %1" :: "v"(off), "s"(base) : "memory");
+                  if constexpr (NT) asm volatile("global_load_lds_dwordx4 %0, %1 nt" :: "v"(off), "s"(base) : "memory");
+                  else asm volatile("global_load_lds_dwordx4 %0, %1" :: "v"(off), "s"(base) : "memory");
               },
               [&](auto q_c, auto nop_c) {
                   constexpr int off = SB2 * B_BYTES + decltype(q_c)::value * 1024;
@@ -377,15 +404,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
     using T_ = std::true_type;
     using F_ = std::false_type;
     int kt = 0;
-    // whole periods while the three slabs behind them still load everything (kt stays a multiple of PER)
-    for (; kt + PER + 2 < KT; kt += PER) static_for<PER>([&](auto s_c) { body_s(s_c, kt + decltype(s_c)::value); });
-    for (; kt + 3 < KT; ++kt) body(kt, T_{}, T_{}, T_{});
-    // the last three slabs (fewer if the product is that short)
-    if (kt + 2 < KT) {                       // slab KT-3: weights of the last slab; its activations only if two stages
-        if (AST == 2) body(kt, T_{}, T_{}, T_{}); else body(kt, T_{}, F_{}, T_{});
-        ++kt;
-    }
-    if (kt + 1 < KT) { body(kt, F_{}, F_{}, T_{}); ++kt; }
+    // whole periods while the slabs behind them still load everything (kt stays a multiple of PER)
+    constexpr int AHEAD = AST == BST ? BST : 2;          // slab kt+AHEAD is the last one slab kt issues loads for
+    for (; kt + PER - 1 + AHEAD < KT; kt += PER) static_for<PER>([&](auto s_c) { body_s(s_c, kt + decltype(s_c)::value); });
+    for (; kt + AHEAD < KT; ++kt) body(kt, T_{}, T_{}, T_{});
+    // the last slabs: the weights of the last one are still to come if the stages are equal, then nothing is
+    if (AST == BST && kt + BST - 1 < KT) { body(kt, T_{}, F_{}, T_{}); ++kt; }
+    for (; kt + 1 < KT; ++kt) body(kt, F_{}, F_{}, T_{});
     if (kt < KT) body(kt, F_{}, F_{}, F_{});
     // the last MFMAs must have left the pipe before the accumulators are read (the compiler cannot see the
     // producers inside the assembly statements)
@@ -412,85 +437,125 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
                     *(bf16x4_t*)((bf16*)a.C + (int64_t)row * a.ldc + col) = __builtin_convertvector(p, bf16x4_t);
             }
         }
+    } else if constexpr (EPI == EPI_STORE_F32) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            const int row = row_begin + wm * 16 * MI + i * 16 + row_in;
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                const int col = n0 + wn * 16 * NI + j * 16 + cq;
+                if (row < row_end && col < a.N) *(f32x4_t*)((float*)a.C + (int64_t)row * a.ldc + col) = acc[i][j];
+            }
+        }
+    } else if constexpr (EPI == EPI_ADD_F32) {
+        // the old values of row i+1 are on their way while row i is added and stored (an element at a time,
+        // every load waited behind the store before it; 2304 rows, 4096 x 4096: 81 -> 78 us)
+        f32x4_t old[2][NI];
+        auto at = [&](int i, int j) -> float* {       // clamped: masked at the store
+            const int row = row_begin + wm * 16 * MI + i * 16 + row_in, col = n0 + wn * 16 * NI + j * 16 + cq;
+            return (float*)a.C + (int64_t)(row < row_end ? row : row_end - 1) * a.ldc + (col < a.N ? col : a.N - 4);
+        };
+        auto load_old = [&](int i) {
+#pragma unroll
+            for (int j = 0; j < NI; ++j) old[i & 1][j] = *(const f32x4_t*)at(i, j);
+        };
+        load_old(0);
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            if (i + 1 < MI) load_old(i + 1);
+            const int row = row_begin + wm * 16 * MI + i * 16 + row_in;
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+                if (row < row_end && n0 + wn * 16 * NI + j * 16 + cq < a.N) *(f32x4_t*)at(i, j) = old[i & 1][j] + acc[i][j];
+        }
     } else {
-        auto store_all = [&](auto kind) {
-            constexpr int KIND = decltype(kind)::value;
+        static_assert(EPI == EPI_ROPE_KV && NI == 8, "a wavefront's 128 columns are one head");
+        // QKV projection: this wavefront's 128 columns are one head (BN = 256, head_dim 128); the
+        // rotation partner of dim j*16 + c is dim (j + 4)*16 + c, i.e. tile j + 4 of the same lane
+        const RopeKvArgs& rp = a.rope;
+        const int head = (n0 + wn * 128) >> 7;                 // wave-uniform
+        const int Hq = rp.n_q_heads, Hkv = rp.geom.n_kv_heads;
+        if (head >= Hq + 2 * Hkv) return;
+        const bool is_q = head < Hq, is_k = !is_q && head < Hq + Hkv;
+        // Where each row's 128 values of the head go: the q buffer, or the row's slot of a KV page.  All rows'
+        // positions are requested at once, then all page-table entries, and the cos/sin of a row
+        // while the row before it is rotated: one row after the other, each row's loads
+        // depend on each other and nothing covers them (2304 rows, 6144 x 4096: 116 -> 109 us).
+        auto row_of = [&](int i) { return row_begin + wm * 16 * MI + i * 16 + row_in; };
+        auto clamped = [&](int i) { const int r = row_of(i); return r < row_end ? r : row_end - 1; };
+        int pos[MI], pg[MI];
+        if (!is_q) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i) pos[i] = rp.row_pos[clamped(i)];
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
-                const int row = row_begin + wm * 16 * MI + i * 16 + row_in;
+                const int lp = pos[i] / rp.geom.page_tokens;      // (a negative position gives an entry that is not used)
+                const bool ok = pos[i] >= 0 && lp < rp.geom.pages_per_seq;
+                pg[i] = rp.page_table[(clamped(i) / rp.n_new) * rp.geom.pages_per_seq + (ok ? lp : 0)];
+                if (!ok || row_of(i) >= row_end) pos[i] = -1;
+            }
+        }
+        f32x4_t cs[2][8];                    // (cos, sin) of the row's pairs j*16 + cq + 0..3, j = 0..3
+        auto load_cs = [&](int i) {
+            const float2* cp = rp.cs + (int64_t)clamped(i) * 64 + cq;
 #pragma unroll
-                for (int j = 0; j < NI; ++j) {
-                    const int col = n0 + wn * 32 * WN_T + j * 16 + cq;
-                    if (row >= row_end || col >= a.N) continue;
-                    const int64_t o = (int64_t)row * a.ldc + col;
-                    if constexpr (KIND == EPI_STORE_F32) *(f32x4_t*)((float*)a.C + o) = acc[i][j];
-                    else if constexpr (KIND == EPI_ADD_F32) {
-                        f32x4_t* d = (f32x4_t*)((float*)a.C + o);
-                        *d = *d + acc[i][j];
-                    } else *(bf16x4_t*)((bf16*)a.C + o) = __builtin_convertvector(acc[i][j], bf16x4_t);
-                }
+            for (int j = 0; j < 4; ++j) {
+                cs[i & 1][2 * j] = *(const f32x4_t*)(cp + j * 16);
+                cs[i & 1][2 * j + 1] = *(const f32x4_t*)(cp + j * 16 + 2);
             }
         };
-        if (a.epilogue == EPI_ROPE_KV) {
-            // QKV projection: this wavefront's 128 columns are one head (BN = 256, head_dim 128); the
-            // rotation partner of dim j*16 + c is dim (j + 4)*16 + c, i.e. tile j + 4 of the same lane
-            if constexpr (WN_T == 4) {
-                const RopeKvArgs& rp = a.rope;
-                const int head = (n0 + wn * 128) >> 7;                 // wave-uniform
-                const int Hq = rp.n_q_heads, Hkv = rp.geom.n_kv_heads;
+        bf16* kvp = (bf16*)rp.kv_layer;
+        if (is_q || is_k) {
+            load_cs(0);
 #pragma unroll
-                for (int i = 0; i < MI; ++i) {
-                    const int row = row_begin + wm * 16 * MI + i * 16 + row_in;
-                    if (row >= row_end || head >= Hq + 2 * Hkv) continue;
-                    // where this row's 128 values of the head go: the q buffer, or the row's slot of a KV page
-                    // (one pair of 16-column tiles at a time, so that few values are live at once)
-                    const bool is_q = head < Hq, is_k = !is_q && head < Hq + Hkv;
-                    bf16* dst = nullptr;
-                    bf16* kvp = (bf16*)rp.kv_layer;
-                    int64_t page = 0;
-                    int slot = 0, kvh = 0;
-                    if (is_q) {
-                        dst = (bf16*)rp.q_out + ((int64_t)row * Hq + head) * 128;
-                    } else {
-                        const int pos = rp.row_pos[row];
-                        if (pos < 0) continue;
-                        const int lp = pos / rp.geom.page_tokens;
-                        if (lp >= rp.geom.pages_per_seq) continue;
-                        page = rp.page_table[(row / rp.n_new) * rp.geom.pages_per_seq + lp];
-                        slot = pos % rp.geom.page_tokens;
-                        if (is_k) dst = kvp + rp.geom.k_off(page, head - Hq, slot);
-                        else kvh = head - Hq - Hkv;
+            for (int i = 0; i < MI; ++i) {
+                if (i + 1 < MI) load_cs(i + 1);
+                bf16* dst;
+                if (is_q) dst = (bf16*)rp.q_out + ((int64_t)row_of(i) * Hq + head) * 128;
+                else dst = kvp + rp.geom.k_off(pg[i], head - Hq, pos[i] < 0 ? 0 : pos[i] % rp.geom.page_tokens);
+                const bool on = is_q ? row_of(i) < row_end : pos[i] >= 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    f32x4_t lo = acc[i][j], hi = acc[i][j + 4];
+                    const f32x4_t c01 = cs[i & 1][2 * j], c23 = cs[i & 1][2 * j + 1];
+                    const float cs_c[4] = {c01[0], c01[2], c23[0], c23[2]};
+                    const float cs_s[4] = {c01[1], c01[3], c23[1], c23[3]};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float x0 = lo[r], x1 = hi[r];
+                        lo[r] = x0 * cs_c[r] - x1 * cs_s[r];
+                        hi[r] = x1 * cs_c[r] + x0 * cs_s[r];
                     }
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        f32x4_t lo = acc[i][j], hi = acc[i][j + 4];
-                        if (is_q || is_k) {
-                            const float2* cp = rp.cs + (int64_t)row * 64 + j * 16 + cq;
-                            const f32x4_t c01 = *(const f32x4_t*)cp, c23 = *(const f32x4_t*)(cp + 2);
-                            const float cs_c[4] = {c01[0], c01[2], c23[0], c23[2]};
-                            const float cs_s[4] = {c01[1], c01[3], c23[1], c23[3]};
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                const float x0 = lo[r], x1 = hi[r];
-                                lo[r] = x0 * cs_c[r] - x1 * cs_s[r];
-                                hi[r] = x1 * cs_c[r] + x0 * cs_s[r];
-                            }
-                            *(bf16x4_t*)(dst + j * 16 + cq) = __builtin_convertvector(lo, bf16x4_t);
-                            *(bf16x4_t*)(dst + 64 + j * 16 + cq) = __builtin_convertvector(hi, bf16x4_t);
-                        } else {
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                kvp[rp.geom.v_off(page, kvh, slot, j * 16 + cq + r)] = f32_to_bf16(lo[r]);
-                                kvp[rp.geom.v_off(page, kvh, slot, 64 + j * 16 + cq + r)] = f32_to_bf16(hi[r]);
-                            }
-                        }
+                    if (on) {
+                        *(bf16x4_t*)(dst + j * 16 + cq) = __builtin_convertvector(lo, bf16x4_t);
+                        *(bf16x4_t*)(dst + 64 + j * 16 + cq) = __builtin_convertvector(hi, bf16x4_t);
                     }
                 }
             }
-        } else if (a.epilogue == EPI_STORE_F32) store_all(std::integral_constant<int, EPI_STORE_F32>{});
-        else if (a.epilogue == EPI_ADD_F32) store_all(std::integral_constant<int, EPI_ADD_F32>{});
-        else store_all(std::integral_constant<int, EPI_STORE_T>{});
+        } else {
+            const int kvh = head - Hq - Hkv;
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                if (pos[i] < 0) continue;
+                const int slot = pos[i] % rp.geom.page_tokens;
+                bf16* dst = kvp + rp.geom.v_off(pg[i], kvh, slot, cq);
+                const int dim = rp.geom.sub_tokens();               // elements between a value's dims
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) dst[(j * 16 + r) * dim] = f32_to_bf16(acc[i][j][r]);
+            }
+        }
     }
+}
+
+// gemm_tile for a tile height known at run time (mi 32-row units, at most MAX_MI)
+template <int MAX_MI, int MI, int NI, int EPI, bool NT>
+__device__ __forceinline__ void run_tile(int mi, const GemmArgs& a, char* smem, int row_begin, int row_end, int n0, int group) {
+    if constexpr (MI < MAX_MI) {
+        if (mi > MI) return run_tile<MAX_MI, MI + 1, NI, EPI, NT>(mi, a, smem, row_begin, row_end, n0, group);
+    }
+    gemm_tile<MI, NI, EPI, NT>(a, smem, row_begin, row_end, n0, group);
 }
 
 // position `local` of a group's nt x tiles_n tiles, ordered band of BAND row tiles, then column tile,
@@ -504,15 +569,12 @@ __device__ inline void band_order(int local, int nt, int tiles_n, int& tile_m, i
     tile_m = first + in_band % bm;
 }
 
-// dynamic LDS a launch needs: the largest of activation stages + three weight stages over the tile heights
-// (the same stage rule as in gemm_tile)
-template <int BN>
+// dynamic LDS a launch needs: the most that a tile of any height takes
+template <int NI>
 constexpr int gemm_lds_bytes() {
     int need = 0;
     for (int mi = 1; mi <= 8; ++mi) {
-        const int a_bytes = 32 * mi * 128, b_bytes = BN * 128;
-        const int ast = 3 * (a_bytes + b_bytes) <= 160 * 1024 ? 3 : 2;
-        const int n = ast * a_bytes + 3 * b_bytes;
+        const int n = (act_stages(mi, NI) * 32 * mi + weight_stages(mi, NI) * 32 * NI) * 128;
         need = n > need ? n : need;
     }
     return need;
@@ -520,12 +582,12 @@ constexpr int gemm_lds_bytes() {
 
 constexpr int MAX_GROUPS_FAST = 63;   // group offsets are fetched by one load (lane g holds offset g)
 constexpr int CUS_PER_XCD = 32;
+enum { HALVES_NONE = 0, HALVES_ROWS = 1, HALVES_COLS = 2 };   // how the tiles of a sparse last round are cut
 
-template <int WN_T, bool SWIGLU>
+template <int NI, int EPI, bool NT>
 __global__ void __launch_bounds__(256, 1)
-gemm_bf16_mfma_kernel(GemmArgs a, int max_rows, int tiles_n) {
-    constexpr int BN = 64 * WN_T;
-    constexpr int N_OUT = SWIGLU ? BN / 2 : BN;       // output columns per workgroup
+gemm_bf16_mfma_kernel(GemmArgs a, int max_rows, int tiles_n, int halves) {
+    constexpr int N_OUT = EPI == EPI_SWIGLU_T ? 16 * NI : 32 * NI;       // output columns per workgroup
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
     // ---- which tile.  Workgroup id x runs on XCD x % 8, and each XCD takes one contiguous range of the
@@ -584,7 +646,7 @@ gemm_bf16_mfma_kernel(GemmArgs a, int max_rows, int tiles_n) {
     // whose eighth of the total work its midpoint falls.
     const int xcd = (int)(blockIdx.x & 7);
     int per_xcd = (total + 7) >> 3, my_start = xcd * per_xcd;
-    if (ng > 0) {
+    if (ng > 0 && total > 8 * CUS_PER_XCD) {     // (at most one tile per compute unit: equal counts)
         auto start_of = [&](int x) -> int {              // first tile of XCD x's range
             if (x >= 8) return total;
             const long long t8 = (long long)x * total_work;                  // 8 x the work in front of the range
@@ -603,7 +665,7 @@ gemm_bf16_mfma_kernel(GemmArgs a, int max_rows, int tiles_n) {
         per_xcd = start_of(xcd + 1) - my_start;
     }
     const int rem = per_xcd % CUS_PER_XCD;
-    const int n_split = (per_xcd > CUS_PER_XCD && rem > 0 && rem <= CUS_PER_XCD / 2) ? rem : 0;
+    const int n_split = (halves && per_xcd > CUS_PER_XCD && rem > 0 && rem <= CUS_PER_XCD / 2) ? rem : 0;
     const int wg_per_xcd = (int)(gridDim.x >> 3);
     for (int slot = (int)(blockIdx.x >> 3); slot < per_xcd + n_split; slot += wg_per_xcd) {
     int t = slot, half = -1;
@@ -631,46 +693,45 @@ gemm_bf16_mfma_kernel(GemmArgs a, int max_rows, int tiles_n) {
         row_begin = tile_m * rt;
         row_end = row_begin + rt < a.M ? row_begin + rt : a.M;
     }
-    if (half >= 0) {                // a row half of a tile of the last round (halves of a multiple of 16 rows)
+    const bool col_half = NI == 8 && NT && half >= 0 && halves == HALVES_COLS;
+    if (half >= 0 && !col_half) {   // a row half of a tile of the last round (halves of a multiple of 16 rows)
         const int mid = row_begin + ((((row_end - row_begin + 1) >> 1) + 15) & ~15);
         if (half == 0) row_end = mid < row_end ? mid : row_end;
         else row_begin = mid;
     }
     const int rows = row_end - row_begin;
     if (rows <= 0) continue;        // rounding the tile height up to 16 can leave a last tile (or half) empty
-    const int n0 = tile_n * N_OUT;
-    switch ((rows + 31) >> 5) {
-        case 1: gemm_tile<1, WN_T, SWIGLU>(a, smem, row_begin, row_end, n0, group); break;
-        case 2: gemm_tile<2, WN_T, SWIGLU>(a, smem, row_begin, row_end, n0, group); break;
-        case 3: gemm_tile<3, WN_T, SWIGLU>(a, smem, row_begin, row_end, n0, group); break;
-        case 4: gemm_tile<4, WN_T, SWIGLU>(a, smem, row_begin, row_end, n0, group); break;
-        case 5: gemm_tile<5, WN_T, SWIGLU>(a, smem, row_begin, row_end, n0, group); break;
-        case 6: gemm_tile<6, WN_T, SWIGLU>(a, smem, row_begin, row_end, n0, group); break;
-        case 7: gemm_tile<7, WN_T, SWIGLU>(a, smem, row_begin, row_end, n0, group); break;
-        default: gemm_tile<8, WN_T, SWIGLU>(a, smem, row_begin, row_end, n0, group); break;
+    const int n0 = tile_n * N_OUT + (col_half && half == 1 ? N_OUT / 2 : 0);
+    if (n0 >= a.N) continue;        // the second column half of a tile at the edge
+    const int mi = (rows + 31) >> 5;
+    if constexpr (NI == 8 && NT && EPI != EPI_ROPE_KV) {
+        if (col_half) { run_tile<4, 1, NI / 2, EPI, NT>(mi, a, smem, row_begin, row_end, n0, group); continue; }
     }
+    run_tile<8, 1, NI, EPI, NT>(mi, a, smem, row_begin, row_end, n0, group);
     // (no barrier between tiles: behind the last barrier of a tile no wavefront reads LDS any more, so the
     // next tile's first loads may overwrite the stages at once)
     }
 }
 
-template <int WN_T, bool SWIGLU>
+}  // namespace
+
+template <int NI, int EPI, bool NT>
 hipError_t launch_cfg(const GemmArgs& a, int max_rows, hipStream_t st) {
-    constexpr int BN = 64 * WN_T;
-    constexpr int N_OUT = SWIGLU ? BN / 2 : BN;
-    // what the tallest need of any tile height is: gemm_tile keeps three activation stages where three of
-    // each operand fit into 160 KB and two otherwise (with 128-column tiles every height has three: 144 KB
-    // at 256 rows, which a size computed for two stages does not cover)
-    constexpr int SMEM = gemm_lds_bytes<BN>();
+    constexpr int N_OUT = EPI == EPI_SWIGLU_T ? 16 * NI : 32 * NI;
+    constexpr int SMEM = gemm_lds_bytes<NI>();
     static_assert(SMEM <= 160 * 1024, "LDS of a compute unit");
     static bool attr_set = false;
-    auto kern = gemm_bf16_mfma_kernel<WN_T, SWIGLU>;
+    auto kern = gemm_bf16_mfma_kernel<NI, EPI, NT>;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const int tiles_n = (a.N + N_OUT - 1) / N_OUT;
+    // The tiles of a last round that would leave half the units idle are cut in two: by rows where the product
+    // is bound by the matrix cores, by columns where one row tile reads the weights (each half reads half of them;
+    // 8 experts, 80 rows each, gate/up product: 330 -> 320 us)
+    const int halves = NI == 8 && NT && max_rows <= 128 && EPI != EPI_ROPE_KV ? HALVES_COLS : max_rows > 128 || NI == 8 ? HALVES_ROWS : HALVES_NONE;
     int tiles_m;
     if (a.group_offsets) {
         // every group rounds its tile count up, so at most n_groups more row tiles than rows / max_rows
@@ -681,11 +742,161 @@ hipError_t launch_cfg(const GemmArgs& a, int max_rows, hipStream_t st) {
     }
     // one workgroup per compute unit (the LDS of a unit holds one), fewer if there are fewer tiles
     const int per_xcd = std::min((tiles_m * tiles_n + 7) / 8, CUS_PER_XCD);
-    hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(256), SMEM, st, a, max_rows, tiles_n);
+    hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(256), SMEM, st, a, max_rows, tiles_n, halves);
     return hipGetLastError();
+}
+#define SV_GEMM_INSTANCE(...) template hipError_t launch_cfg<__VA_ARGS__>(const GemmArgs&, int, hipStream_t);
+#if SV_GEMM_PART == 1
+SV_GEMM_INSTANCE(8, EPI_SWIGLU_T, false)
+#elif SV_GEMM_PART == 2
+SV_GEMM_INSTANCE(8, EPI_SWIGLU_T, true)
+#elif SV_GEMM_PART == 3
+SV_GEMM_INSTANCE(8, EPI_STORE_F32, false)
+#elif SV_GEMM_PART == 4
+SV_GEMM_INSTANCE(8, EPI_STORE_F32, true)
+#elif SV_GEMM_PART == 5
+SV_GEMM_INSTANCE(8, EPI_ADD_F32, false)
+#elif SV_GEMM_PART == 6
+SV_GEMM_INSTANCE(8, EPI_ADD_F32, true)
+#elif SV_GEMM_PART == 7
+SV_GEMM_INSTANCE(8, EPI_ROPE_KV, false)
+#elif SV_GEMM_PART == 8
+SV_GEMM_INSTANCE(8, EPI_ROPE_KV, true)
+#elif SV_GEMM_PART == 9
+SV_GEMM_INSTANCE(4, EPI_SWIGLU_T, false)
+SV_GEMM_INSTANCE(4, EPI_SWIGLU_T, true)
+#elif SV_GEMM_PART == 10
+SV_GEMM_INSTANCE(4, EPI_STORE_F32, false)
+SV_GEMM_INSTANCE(4, EPI_STORE_F32, true)
+#elif SV_GEMM_PART == 11
+SV_GEMM_INSTANCE(4, EPI_ADD_F32, false)
+SV_GEMM_INSTANCE(4, EPI_ADD_F32, true)
+#elif SV_GEMM_PART == 12
+SV_GEMM_INSTANCE(2, EPI_STORE_F32, false)
+SV_GEMM_INSTANCE(2, EPI_STORE_F32, true)
+SV_GEMM_INSTANCE(2, EPI_ADD_F32, false)
+SV_GEMM_INSTANCE(2, EPI_ADD_F32, true)
+#elif SV_GEMM_PART == 13
+SV_GEMM_INSTANCE(1, EPI_STORE_F32, false)
+SV_GEMM_INSTANCE(1, EPI_STORE_F32, true)
+SV_GEMM_INSTANCE(1, EPI_ADD_F32, false)
+SV_GEMM_INSTANCE(1, EPI_ADD_F32, true)
+#else
+#undef SV_GEMM_INSTANCE
+#define SV_GEMM_INSTANCE(...) extern template hipError_t launch_cfg<__VA_ARGS__>(const GemmArgs&, int, hipStream_t);
+SV_GEMM_INSTANCE(8, EPI_SWIGLU_T, false)
+SV_GEMM_INSTANCE(8, EPI_SWIGLU_T, true)
+SV_GEMM_INSTANCE(8, EPI_STORE_F32, false)
+SV_GEMM_INSTANCE(8, EPI_STORE_F32, true)
+SV_GEMM_INSTANCE(8, EPI_ADD_F32, false)
+SV_GEMM_INSTANCE(8, EPI_ADD_F32, true)
+SV_GEMM_INSTANCE(8, EPI_ROPE_KV, false)
+SV_GEMM_INSTANCE(8, EPI_ROPE_KV, true)
+SV_GEMM_INSTANCE(4, EPI_SWIGLU_T, false)
+SV_GEMM_INSTANCE(4, EPI_SWIGLU_T, true)
+SV_GEMM_INSTANCE(4, EPI_STORE_F32, false)
+SV_GEMM_INSTANCE(4, EPI_STORE_F32, true)
+SV_GEMM_INSTANCE(4, EPI_ADD_F32, false)
+SV_GEMM_INSTANCE(4, EPI_ADD_F32, true)
+SV_GEMM_INSTANCE(2, EPI_STORE_F32, false)
+SV_GEMM_INSTANCE(2, EPI_STORE_F32, true)
+SV_GEMM_INSTANCE(2, EPI_ADD_F32, false)
+SV_GEMM_INSTANCE(2, EPI_ADD_F32, true)
+SV_GEMM_INSTANCE(1, EPI_STORE_F32, false)
+SV_GEMM_INSTANCE(1, EPI_STORE_F32, true)
+SV_GEMM_INSTANCE(1, EPI_ADD_F32, false)
+SV_GEMM_INSTANCE(1, EPI_ADD_F32, true)
+
+namespace {
+
+// rows that one weight matrix meets (grouped problems are judged by their average group, whose size lives on the
+// device: 4 % slack for imbalance)
+int expected_rows(const GemmArgs& a) {
+    if (!a.group_offsets) return a.M;
+    const int groups = a.n_groups > 0 ? a.n_groups : 1;
+    return a.m_expected > 0 ? (int)((int64_t)a.m_expected * 26 / 25) + 1 : (int)((int64_t)a.m_upper * 26 / (25 * groups)) + 1;
+}
+
+struct TileChoice { int ni = 8, max_rows = 256; double cost = 0.0; };
+
+// Time (microseconds) of a product cut into tiles of at most max_rows rows and 32*ni columns.  A compute unit
+// takes a 64-wide slab of (mi + ni) x 32 operand rows at about 53 GB/s (0.076 us per 32 rows, measured
+// over tiles of (1, 1) to (8, 8)) or at the rate of its matrix instructions (32 cycles per mi x ni); a tile costs 3 us around
+// its slabs; a last round that fills at most half the units is cut in halves (256 columns); and the weights come from HBM
+// at 6.5 TB/s at best.  The second term of the result keeps the cheaper of two tilings that both wait for HBM.
+double tile_cost(const GemmArgs& a, int ni, int max_rows) {
+    const bool sw = a.epilogue == EPI_SWIGLU_T;
+    const int groups = a.group_offsets ? (a.n_groups > 0 ? a.n_groups : 1) : 1, cols = sw ? 16 * ni : 32 * ni;
+    int nt, rt;
+    split_rows(expected_rows(a), max_rows, nt, rt);
+    const int mi = (rt + 31) / 32, slabs = a.K / 64;
+    const int64_t jobs = (int64_t)groups * nt * ((a.N + cols - 1) / cols);
+    double slab = std::max(0.076 * (mi + ni) + 0.02, 0.0168 * mi * ni);
+    if (nt > 1) slab *= 1.05;              // (the row tiles of one weight slab do not all find it in L2)
+    const int64_t full = jobs / 256, rem = jobs % 256;
+    const double rounds = full + (rem == 0 ? 0.0 : ni == 8 && full > 0 && rem <= 128 ? 0.6 : 1.0);
+    const double t = rounds * (slabs * slab + 3.0);
+    const double hbm = (double)groups * (sw ? 2 : 1) * a.N * a.K * 2.0 / 6.5e6;
+    return std::max(t, hbm) + 0.2 * t;
+}
+
+// 256-column tiles: the height whose tile count fills the 256 compute units best.  The cost of a tile is
+// its accumulator height in 32-row units plus about three units for the column operand and the
+// per-slab overheads (fitted to measurements of the projection shapes).  Each group is then cut into
+// equal tiles of at most that height on the device.
+TileChoice choose_wide(const GemmArgs& a) {
+    const bool sw = a.epilogue == EPI_SWIGLU_T;
+    const int tiles_n = (a.N + (sw ? 127 : 255)) / (sw ? 128 : 256), r = expected_rows(a);
+    const int groups = a.group_offsets ? (a.n_groups > 0 ? a.n_groups : 1) : 1;
+    TileChoice t;
+    double best = 0;
+    for (int cand = 256; cand >= 96; cand -= 32) {
+        int nt, rt;
+        split_rows(r, cand, nt, rt);
+        const int64_t jobs = (int64_t)groups * nt * tiles_n;
+        const double cost = (double)((jobs + 255) / 256) * ((rt + 31) / 32 + 3);
+        if (best == 0 || cost < best - 1e-9) { best = cost; t.max_rows = cand; }
+    }
+    if (r <= 128) t.max_rows = 128;      // one row tile (see HALVES_COLS)
+    t.cost = tile_cost(a, 8, t.max_rows);
+    return t;
+}
+
+// The tiles of a product.  Every output's sum runs over the contraction in the same order whatever the tiles, so the choice
+// changes no bit of the result.  Narrow tiles give a product of few rows or few columns more tiles
+// than 256-column ones, hence more compute units that pull weights (us; 4096 x 4096 and 6144 x 4096 weights):
+//   rows        5          32         64         128        320        896
+//   256 cols    43 / 42    46 / 47    50 / 51    46 / 50    47 / 51    50 / 53
+//   chosen      11 / 12    14 / 14    14 / 19    17 / 24    25 / 33    39 / 51
+TileChoice choose_tiles(const GemmArgs& a) {
+    TileChoice best = choose_wide(a);
+    for (int ni = 4; ni >= (a.epilogue == EPI_SWIGLU_T ? 4 : 1); ni /= 2)
+        for (int rows = 256; rows >= 32; rows -= 32) {
+            const double c = tile_cost(a, ni, rows);
+            if (c < 0.97 * best.cost) best = TileChoice{ni, rows, c};
+        }
+    return best;
 }
 
 }  // namespace
+
+// the kernel for tiles of 32*ni columns (ni 8, 4, 2, 1 as the epilogue has them); nt: no weight is read by two
+// row tiles
+template <int EPI, int NI>
+hipError_t launch_ni(const GemmArgs& a, int ni, int max_rows, bool nt, hipStream_t st) {
+    if constexpr (NI > (EPI == EPI_SWIGLU_T ? 4 : EPI == EPI_ROPE_KV ? 8 : 1)) {
+        if (ni < NI) return launch_ni<EPI, NI / 2>(a, ni, max_rows, nt, st);
+    }
+    return nt ? launch_cfg<NI, EPI, true>(a, max_rows, st) : launch_cfg<NI, EPI, false>(a, max_rows, st);
+}
+hipError_t launch_gemm_tiles(const GemmArgs& a, int ni, int max_rows, bool nt, hipStream_t st) {
+    switch (a.epilogue) {
+        case EPI_SWIGLU_T: return launch_ni<EPI_SWIGLU_T, 8>(a, ni, max_rows, nt, st);
+        case EPI_ADD_F32: return launch_ni<EPI_ADD_F32, 8>(a, ni, max_rows, nt, st);
+        case EPI_ROPE_KV: return launch_ni<EPI_ROPE_KV, 8>(a, ni, max_rows, nt, st);
+        default: return launch_ni<EPI_STORE_F32, 8>(a, ni, max_rows, nt, st);
+    }
+}
 
 hipError_t launch_gemm_mfma_bf16(const GemmArgs& a, hipStream_t st) {
     const int rows = a.group_offsets ? a.m_upper : a.M;
@@ -694,7 +905,7 @@ hipError_t launch_gemm_mfma_bf16(const GemmArgs& a, hipStream_t st) {
     // take 4-element vector stores; anything else (never the case for the supported model shapes)
     // takes the plain kernel
     if (a.K % 64 != 0 || a.lda % 8 != 0 || ((uintptr_t)a.A & 15) || ((uintptr_t)a.W & 15) || a.N % 4 != 0 ||
-        a.ldc % 4 != 0 || ((uintptr_t)a.C & 15) || (a.epilogue == EPI_SWIGLU_T && ((uintptr_t)a.W3 & 15)))
+        a.ldc % 4 != 0 || ((uintptr_t)a.C & 15) || a.epilogue == EPI_STORE_T || (a.epilogue == EPI_SWIGLU_T && ((uintptr_t)a.W3 & 15)))
         return a.epilogue == EPI_ROPE_KV ? hipErrorInvalidValue : launch_gemm_simple(a, SPEC_BF16, st);
     const bool sw = a.epilogue == EPI_SWIGLU_T;
     // operand rows are addressed as a 64-bit base per slab plus a 32-bit byte offset per lane: the rows a
@@ -709,41 +920,21 @@ hipError_t launch_gemm_mfma_bf16(const GemmArgs& a, hipStream_t st) {
     }
     if (a.epilogue == EPI_ROPE_KV && (a.group_offsets || a.rope.geom.head_dim != 128 || a.N % 128 != 0))
         return hipErrorInvalidValue;
-    // Tile height: the one whose tile count fills the 256 compute units best.  The cost of a tile is
-    // its accumulator height in 32-row units plus about three units for the column operand and the
-    // per-slab overheads (fitted to measurements of the projection shapes).  Grouped problems are
-    // judged by their average group (the group sizes live on the device; 4 % slack for imbalance) and
-    // each group is then cut into equal tiles of at most that height on the device.
-    int max_rows = 256;
-    {
-        const int tiles_n = (a.N + (sw ? 127 : 255)) / (sw ? 128 : 256);
-        const int groups = a.group_offsets ? (a.n_groups > 0 ? a.n_groups : 1) : 1;
-        const int r = !a.group_offsets ? rows
-                      : a.m_expected > 0 ? (int)((int64_t)a.m_expected * 26 / 25) + 1
-                                         : (int)((int64_t)rows * 26 / (25 * groups)) + 1;
-        double best = 0;
-        for (int cand = 256; cand >= 96; cand -= 32) {
-            int nt, rt;
-            split_rows(r, cand, nt, rt);
-            const int jobs = groups * nt * tiles_n;
-            const double cost = (double)((jobs + 255) / 256) * ((rt + 31) / 32 + 3);
-            if (best == 0 || cost < best - 1e-9) { best = cost; max_rows = cand; }
-        }
-    }
-    int wn_t = 4;
-    {
-        // a launch that gives at most half the compute units a 256-column tile (one expert of a small batch,
-        // a short projection) is bound by how many units pull weights from HBM: halve the tile width
-        int nt, rt;
-        split_rows(a.group_offsets ? (a.m_expected > 0 ? a.m_expected : rows / (a.n_groups > 0 ? a.n_groups : 1)) : rows,
-                   max_rows, nt, rt);
-        const int64_t tiles = (int64_t)(a.group_offsets ? a.n_groups : 1) * nt * ((a.N + (sw ? 127 : 255)) / (sw ? 128 : 256));
-        if (tiles <= 128 && a.epilogue != EPI_ROPE_KV) wn_t = 2;
-    }
-    if (a.force_max_rows > 0) max_rows = a.force_max_rows;
-    if (a.force_wn_t == 2 || a.force_wn_t == 4) wn_t = a.force_wn_t;
-    if (wn_t == 4) return sw ? launch_cfg<4, true>(a, max_rows, st) : launch_cfg<4, false>(a, max_rows, st);
-    return sw ? launch_cfg<2, true>(a, max_rows, st) : launch_cfg<2, false>(a, max_rows, st);
+    TileChoice t = choose_tiles(a);
+    if (a.force_max_rows > 0) { t.max_rows = a.force_max_rows; t.ni = 2 * a.force_wn_t; }
+    if (a.epilogue == EPI_ROPE_KV) t = choose_wide(a);
+    return launch_gemm_tiles(a, t.ni, t.max_rows, expected_rows(a) <= t.max_rows, st);
 }
 
+// Whether a QKV projection of M rows runs faster as narrow tiles into an f32 buffer and a rotary/append kernel of
+// its own than with 256-column tiles and the fused epilogue: the buffer is written and read once and the kernel
+// takes about 6 us.  64 rows, 6144 x 4096: 51 us fused, 19 + 6 apart; 896 rows, 8192 x 6144: 105 fused, 82 + 21.
+bool qkv_unfused_pays(int M, int N, int K) {
+    GemmArgs a{};
+    a.M = M; a.N = N; a.K = K; a.epilogue = EPI_STORE_F32;
+    const TileChoice t = choose_tiles(a), w = choose_wide(a);
+    return t.ni < 8 && t.cost + 6.0 + 2.0 * M * N * 4.0 / 4.0e6 < w.cost;
+}
+
+#endif
 }  // namespace sv

@@ -7,6 +7,9 @@
 
 namespace sv {
 
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
+
 #define DISPATCH_DTYPE(dtype, ...)                                     \
     do {                                                               \
         if ((dtype) == SPEC_F32) { using T = float; __VA_ARGS__; }     \
@@ -256,6 +259,62 @@ hipError_t launch_rope_kv(const float* qkv, const float2* cs, const int32_t* row
     DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(rope_kv_kernel<T>, dim3(T_), dim3(256), 0, st, qkv, cs,
                                              row_pos, page_table, (T*)q_out, (T*)kv_layer, geom, n_new,
                                              n_q_heads));
+    return hipGetLastError();
+}
+
+// The same for a bf16 model of head_dim 128, 16-byte accesses: 16 lanes take one head of a row (dims
+// 4 l .. 4 l + 3 and their rotation partners 64 above), a workgroup 16 heads.  Rotation and rounding are
+// written as in the projection's fused epilogue: both ways give the same bits. 
+__global__ void __launch_bounds__(256)
+rope_kv_bf16_kernel(const float* __restrict__ qkv, const float2* __restrict__ cs, const int32_t* __restrict__ row_pos,
+                        const int32_t* __restrict__ page_table, bf16* __restrict__ q_out, bf16* __restrict__ kv_layer,
+                        KvGeom geom, int n_new, int n_q_heads) {
+    const int t = blockIdx.x, hd = blockIdx.y * 16 + (threadIdx.x >> 4), i = (threadIdx.x & 15) * 4;
+    const int Hkv = geom.n_kv_heads, n_heads = n_q_heads + 2 * Hkv;
+    if (hd >= n_heads) return;
+    const int pos = row_pos[t];
+    const float* src = qkv + ((int64_t)t * n_heads + hd) * 128 + i;
+    f32x4_t lo = *(const f32x4_t*)src, hi = *(const f32x4_t*)(src + 64);
+    const bool is_q = hd < n_q_heads, is_k = !is_q && hd < n_q_heads + Hkv;
+    if (is_q || is_k) {
+        const float4 c01 = *(const float4*)(cs + (int64_t)t * 64 + i), c23 = *(const float4*)(cs + (int64_t)t * 64 + i + 2);
+        const float c[4] = {c01.x, c01.z, c23.x, c23.z}, sn[4] = {c01.y, c01.w, c23.y, c23.w};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float x0 = lo[r], x1 = hi[r];
+            lo[r] = x0 * c[r] - x1 * sn[r];
+            hi[r] = x1 * c[r] + x0 * sn[r];
+        }
+    }
+    const bf16x4_t l4 = __builtin_convertvector(lo, bf16x4_t), h4 = __builtin_convertvector(hi, bf16x4_t);
+    bf16* dst;
+    if (is_q) dst = q_out + ((int64_t)t * n_q_heads + hd) * 128 + i;
+    else {
+        if (pos < 0) return;
+        const int lp = pos / geom.page_tokens, slot = pos % geom.page_tokens;
+        if (lp >= geom.pages_per_seq) return;
+        const int64_t page = page_table[(t / n_new) * geom.pages_per_seq + lp];
+        if (!is_k) {
+            const int kvh = hd - n_q_heads - Hkv;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                *(__bf16*)(kv_layer + geom.v_off(page, kvh, slot, i + r)) = l4[r];
+                *(__bf16*)(kv_layer + geom.v_off(page, kvh, slot, 64 + i + r)) = h4[r];
+            }
+            return;
+        }
+        dst = kv_layer + geom.k_off(page, hd - n_q_heads, slot) + i;
+    }
+    *(bf16x4_t*)dst = l4;
+    *(bf16x4_t*)(dst + 64) = h4;
+}
+hipError_t launch_rope_kv_bf16(const float* qkv, const float2* cs, const int32_t* row_pos, const int32_t* page_table,
+                                   void* q_out, void* kv_layer, KvGeom geom, int T_, int n_new, int n_q_heads, hipStream_t st) {
+    if (T_ <= 0) return hipSuccess;
+    if (geom.head_dim != 128) return hipErrorInvalidValue;
+    const int n_heads = n_q_heads + 2 * geom.n_kv_heads;
+    hipLaunchKernelGGL(rope_kv_bf16_kernel, dim3(T_, (n_heads + 15) / 16), dim3(256), 0, st, qkv, cs, row_pos, page_table,
+                       (bf16*)q_out, (bf16*)kv_layer, geom, n_new, n_q_heads);
     return hipGetLastError();
 }
 

@@ -64,6 +64,30 @@ def test_gemm_bf16_mfma_every_tile_variant(tile_rows, tile_cols):
     assert np.abs(got - ref).max() < 2e-4 * np.sqrt(K) * 0.05, np.abs(got - ref).max()
 
 
+# products whose own tiles are narrower than 256 columns (32, 64 and 128 columns; one row tile and several; a
+# ragged last row and column tile; as many slabs as stages, fewer, more) and, the last two, 256-column tiles
+@pytest.mark.parametrize("M,N,K", [(1, 4096, 64), (5, 4096, 1024), (33, 6144, 512), (33, 4100, 1088), (64, 2048, 2048),
+                                   (100, 4096, 320), (128, 6144, 1152), (230, 4096, 960), (320, 6144, 256),
+                                   (513, 4096, 448), (900, 8192, 128), (2304, 4096, 128), (40, 65536, 64)])
+def test_gemm_bf16_tile_choice_changes_no_bit(M, N, K):
+    """Every output is one sum over K in ascending order whatever the tiles: the launcher's choice and forced
+    256-column tiles agree bit for bit (and the forced ones are checked against float64 above)."""
+    import torch
+    import paper_2505_10259_amd as P
+    from gpu_common import dev
+    A, W = dev(_rand_bf16((M, K), 5)), dev(_rand_bf16((N, K), 6, std=0.05))
+    C = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    D = torch.zeros_like(C)
+    P.spec_gemm(A, W, C, M, N, K, P.SPEC_BF16)
+    P.spec_debug_gemm(A, W, D, M, N, K, 256, 256)
+    torch.cuda.synchronize()
+    assert torch.equal(C, D)
+    rows = slice(0, min(M, 64))
+    ref = A.view(torch.bfloat16)[rows].double() @ W.view(torch.bfloat16).double().t()
+    # f32 sums of K products: error below K * 2^-24 of the sum of magnitudes, far less for random signs
+    assert ((C[rows].double() - ref).abs().max() < 2e-4 * np.sqrt(K) * 0.05).item()
+
+
 def test_gemm_f32_plain():
     import torch
     import paper_2505_10259_amd as P
