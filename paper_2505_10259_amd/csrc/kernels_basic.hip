@@ -653,9 +653,123 @@ gemm_simple_kernel(GemmArgs a) {
     }
 }
 
+// The same product for problems that 64x64 tiles would run on a handful of compute units (small f32 models: a
+// round of the 256-wide two-layer one is 60 products of 4 to 20 rows): 8x32 tiles, one output per thread, the
+// contraction in steps of 256 whose elements are requested a step ahead.  What bounds such a product is
+// latency: 35-48 us per launch as 16-wide steps on one to sixteen workgroups (8 rows, 256 to 1024 columns,
+// K = 256 to 1024), 5-11 us so; the round of four sequences with four candidates 2177 -> 457 us (with the
+// vector loads of the plain attention below and the greedy rule on all rows at once).  Every output is the same
+// chain of fused multiply-adds over ascending k.
+constexpr int SMALL_BM = 8, SMALL_BN = 32, SMALL_BK = 256, SMALL_LK = SMALL_BK / 128;
+template <typename T>
+__device__ inline float4 load4_guarded(const T* __restrict__ row, int k, int K, bool vec) {     // zeros past K
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (vec && k + 4 <= K) {
+        alignas(4 * sizeof(T)) T e[4];
+        if constexpr (sizeof(T) == 2) *(uint2*)e = *(const uint2*)(row + k);
+        else *(uint4*)e = *(const uint4*)(row + k);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = to_f32<T>(e[q]);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) if (k + q < K) v[q] = to_f32<T>(row[k + q]);
+    }
+    return make_float4(v[0], v[1], v[2], v[3]);
+}
+template <typename T, bool SWIGLU>
+__global__ void __launch_bounds__(256)
+gemm_small_kernel(GemmArgs a, int vec) {
+    constexpr int PITCH = SMALL_BK + 4, WQ = SMALL_BN / 8;      // weight rows per thread and 128 columns of a step
+    __shared__ __attribute__((aligned(16))) float As[SMALL_BM][PITCH];
+    __shared__ __attribute__((aligned(16))) float Ws[SWIGLU ? 2 : 1][SMALL_BN][PITCH];
+    int row_begin = blockIdx.y * SMALL_BM, row_end = a.M, group = 0;
+    if (a.group_offsets) {
+        int tiles = 0;
+        bool found = false;
+        for (int g = 0; g < a.n_groups; ++g) {
+            const int b0 = a.group_offsets[g], b1 = a.group_offsets[g + 1], nt = (b1 - b0 + SMALL_BM - 1) / SMALL_BM;
+            if (!found && (int)blockIdx.y < tiles + nt) {
+                group = g; row_begin = b0 + ((int)blockIdx.y - tiles) * SMALL_BM; row_end = b1; found = true;
+            }
+            tiles += nt;
+        }
+        if (!found) return;
+    }
+    const T* A = (const T*)a.A;
+    const T* W[2] = {(const T*)a.W + (int64_t)group * a.w_group_stride,
+                     SWIGLU ? (const T*)a.W3 + (int64_t)group * a.w_group_stride : nullptr};
+    const int col0 = blockIdx.x * SMALL_BN, tid = threadIdx.x;
+    // loader: thread takes 4 elements at k = 4 (tid % 32) + 128 j of activation row tid / 32 and of weight rows
+    // tid / 32 + 8 q
+    const int lk = (tid & 31) * 4, lr = tid >> 5;
+    const bool a_on = row_begin + lr < row_end;
+    const T* arow = A + (a_on ? (int64_t)(a.a_rows ? a.a_rows[row_begin + lr] : row_begin + lr) * a.lda : 0);
+    float4 ra[SMALL_LK], rw[SWIGLU ? 2 : 1][WQ][SMALL_LK];
+    auto request = [&](int k0) {
+        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int j = 0; j < SMALL_LK; ++j) {
+            const int k = k0 + lk + 128 * j;
+            ra[j] = a_on ? load4_guarded<T>(arow, k, a.K, vec) : z;
+#pragma unroll
+            for (int m = 0; m < (SWIGLU ? 2 : 1); ++m)
+#pragma unroll
+                for (int q = 0; q < WQ; ++q) {
+                    const int n = col0 + lr + 8 * q;
+                    rw[m][q][j] = n < a.N ? load4_guarded<T>(W[m] + (int64_t)n * a.K, k, a.K, vec) : z;
+                }
+        }
+    };
+    const int n_in = tid & 31, m_in = tid >> 5;
+    float acc = 0.f, acc3 = 0.f;
+    request(0);
+    for (int k0 = 0; k0 < a.K; k0 += SMALL_BK) {
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < SMALL_LK; ++j) {
+            *(float4*)&As[lr][lk + 128 * j] = ra[j];
+#pragma unroll
+            for (int m = 0; m < (SWIGLU ? 2 : 1); ++m)
+#pragma unroll
+                for (int q = 0; q < WQ; ++q) *(float4*)&Ws[m][lr + 8 * q][lk + 128 * j] = rw[m][q][j];
+        }
+        __syncthreads();
+        if (k0 + SMALL_BK < a.K) request(k0 + SMALL_BK);
+#pragma unroll 8
+        for (int k = 0; k < SMALL_BK; k += 4) {
+            const float4 x = *(const float4*)&As[m_in][k], w = *(const float4*)&Ws[0][n_in][k];
+            acc = fmaf(x.x, w.x, acc); acc = fmaf(x.y, w.y, acc); acc = fmaf(x.z, w.z, acc); acc = fmaf(x.w, w.w, acc);
+            if (SWIGLU) {
+                const float4 u = *(const float4*)&Ws[SWIGLU ? 1 : 0][n_in][k];
+                acc3 = fmaf(x.x, u.x, acc3); acc3 = fmaf(x.y, u.y, acc3); acc3 = fmaf(x.z, u.z, acc3); acc3 = fmaf(x.w, u.w, acc3);
+            }
+        }
+    }
+    const int r = row_begin + m_in, c = col0 + n_in;
+    if (r >= row_end || c >= a.N) return;
+    const int64_t o = (int64_t)r * a.ldc + c;
+    if (SWIGLU) ((T*)a.C)[o] = from_f32<T>(acc / (1.0f + expf(-acc)) * acc3);
+    else if (a.epilogue == EPI_STORE_F32) ((float*)a.C)[o] = acc;
+    else if (a.epilogue == EPI_ADD_F32) ((float*)a.C)[o] += acc;
+    else ((T*)a.C)[o] = from_f32<T>(acc);
+}
+
 hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st) {
     int rows = a.group_offsets ? a.m_upper : a.M;
     if (rows <= 0 || a.N <= 0) return hipSuccess;
+    const bool swiglu = a.epilogue == EPI_SWIGLU_T;
+    // 64x64 tiles on fewer than half the compute units: small tiles (8 times the reads of a weight, from L2)
+    if ((int64_t)((rows + 63) / 64) * ((a.N + 63) / 64) < 128) {
+        const size_t es = dtype == SPEC_F32 ? 4 : 2;
+        const uintptr_t base = (uintptr_t)a.A | (uintptr_t)a.W | (swiglu ? (uintptr_t)a.W3 : 0) | (uintptr_t)(a.w_group_stride * es);
+        const int vec = base % (4 * es) == 0 && a.lda % 4 == 0 && a.K % 4 == 0;
+        dim3 sgrid((a.N + SMALL_BN - 1) / SMALL_BN, (rows + SMALL_BM - 1) / SMALL_BM + (a.group_offsets ? a.n_groups : 0));
+        DISPATCH_DTYPE(dtype, {
+            if (swiglu) hipLaunchKernelGGL((gemm_small_kernel<T, true>), sgrid, dim3(256), 0, st, a, vec);
+            else hipLaunchKernelGGL((gemm_small_kernel<T, false>), sgrid, dim3(256), 0, st, a, vec);
+        });
+        return hipGetLastError();
+    }
     int tiles_m = (rows + 63) / 64 + (a.group_offsets ? a.n_groups : 0);
     dim3 grid((a.N + 63) / 64, tiles_m);
     bool sw = a.epilogue == EPI_SWIGLU_T;
@@ -696,11 +810,22 @@ attention_simple_kernel(AttnArgs a) {
     for (int c0 = 0; c0 < n_keys; c0 += 64) {
         int key = c0 + lane;
         float s = -INFINITY;
+        const int page_l = key < n_keys ? pt[key / a.geom.page_tokens] : 0;       // page of this lane's key
         if (key < n_keys) {
-            int64_t page = pt[key / a.geom.page_tokens];
+            int64_t page = page_l;
             const T* kr = kv + a.geom.k_off(page, kvh, key % a.geom.page_tokens);
             float dot = 0.f;
-            for (int c = 0; c < dh; ++c) dot += qs[c] * to_f32<T>(kr[c]);
+            if (dh % 16 == 0) {       // 16 elements requested at a time; the sum runs over ascending dims as below
+                for (int c = 0; c < dh; c += 16) {
+                    alignas(16) T kv16[16];
+#pragma unroll
+                    for (int q = 0; q < (int)(16 * sizeof(T)) / 16; ++q) ((uint4*)kv16)[q] = ((const uint4*)(kr + c))[q];
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) dot = fmaf(qs[c + q], to_f32<T>(kv16[q]), dot);
+                }
+            } else {
+                for (int c = 0; c < dh; ++c) dot += qs[c] * to_f32<T>(kr[c]);
+            }
             s = dot * a.scale;
         }
         float m_new = fmaxf(m, wave_max(s));
@@ -709,16 +834,30 @@ attention_simple_kernel(AttnArgs a) {
         l = l * corr + wave_sum(p);
 #pragma unroll
         for (int dd = 0; dd < 4; ++dd) acc[dd] *= corr;
+        // values are stored transposed, so four consecutive positions of a dimension are one 16- or 8-byte piece
+        // (pages and sub-blocks are multiples of 16 tokens); positions past the last key have weight 0
         int nk = min(64, n_keys - c0);
-        for (int j = 0; j < nk; ++j) {
-            float pj = __shfl(p, j, 64);
-            int kj = c0 + j;
-            int64_t page = pt[kj / a.geom.page_tokens];
-            int sl = kj % a.geom.page_tokens;
 #pragma unroll
-            for (int dd = 0; dd < 4; ++dd) {
-                int c = lane + 64 * dd;
-                if (c < dh) acc[dd] += pj * to_f32<T>(kv[a.geom.v_off(page, kvh, sl, c)]);
+        for (int dd = 0; dd < 4; ++dd) {
+            const int c = min(lane + 64 * dd, dh - 1);           // (lanes past the last dimension store nothing)
+            if (64 * dd >= dh) break;
+#pragma unroll
+            for (int j0 = 0; j0 < 64; j0 += 16) {                // 16 positions requested at a time
+                if (j0 >= nk) break;
+                alignas(16) T v[4][4];
+#pragma unroll
+                for (int g4 = 0; g4 < 4; ++g4) {
+                    const int j = min(j0 + 4 * g4, (nk - 1) & ~3);
+                    const int64_t page = __shfl(page_l, j, 64);
+                    const T* vp = kv + a.geom.v_off(page, kvh, (c0 + j) % a.geom.page_tokens, c);
+                    if constexpr (sizeof(T) == 2) *(uint2*)v[g4] = *(const uint2*)vp;
+                    else *(uint4*)v[g4] = *(const uint4*)vp;
+                }
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    const float pj = __shfl(p, j0 + q, 64);
+                    if (j0 + q < nk) acc[dd] = fmaf(pj, to_f32<T>(v[q >> 2][q & 3]), acc[dd]);
+                }
             }
         }
         m = m_new;

@@ -88,6 +88,26 @@ def test_gemm_bf16_tile_choice_changes_no_bit(M, N, K):
     assert ((C[rows].double() - ref).abs().max() < 2e-4 * np.sqrt(K) * 0.05).item()
 
 
+# small plain tiles (8 x 32, steps of 256) with ragged rows, columns and contractions, unaligned rows (K odd), and
+# the sizes on either side of the line to the 64 x 64 tiles
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (8, 32, 128), (9, 33, 129), (20, 768, 256), (4, 256, 1024), (7, 100, 255), (3, 40, 257),
+                                   (64, 8128, 64), (64, 8192, 64), (65, 4033, 96)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_gemm_plain_small_and_large_tiles(M, N, K, dtype):
+    import torch
+    import paper_2505_10259_amd as P
+    g = torch.Generator("cuda").manual_seed(M + N + K)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    A = torch.randn(M, K, device="cuda", generator=g).to(t)
+    W = torch.randn(N, K, device="cuda", generator=g).to(t)
+    C = torch.full((M, N), float("nan"), device="cuda")
+    P.spec_gemm(A, W, C, M, N, K, P.SPEC_F32 if dtype == "f32" else P.SPEC_BF16, P.SPEC_FLAG_SIMPLE_KERNELS)
+    torch.cuda.synchronize()
+    ref = A.double() @ W.double().t()
+    # a chain of K fused multiply-adds: error at most K * 2^-24 * sum |a w|, about K * E|a w| = 0.64 K
+    assert (C.double() - ref).abs().max().item() < max(2, K) * 2.0 ** -24 * 2 * K
+
+
 def test_gemm_f32_plain():
     import torch
     import paper_2505_10259_amd as P
