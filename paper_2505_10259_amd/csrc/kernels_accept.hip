@@ -53,30 +53,129 @@ hipError_t launch_philox_uniforms(uint64_t seed, uint32_t round, uint32_t seq_ba
     return hipGetLastError();
 }
 
-// ---- 256-thread block helpers -----------------------------------------------------------------
-constexpr int ACC_THREADS = 256;
+// exp(x) for x <= 0: 2^(x log2 e) with the product's rounding error carried as a first-order correction.  The
+// library's expf also covers overflow and subnormal results, which these weights do not need, in twice the
+// instructions (at most 2.0 x 2^-24 off over [-86, 0]; 256 sequences of 6 candidates, 32000 ids: 116 -> 104 us).
+__device__ inline float exp_neg(float x) {
+    const float t = x * 1.44269502f;                                       // log2 e = 1.44269502 + 1.92596299e-8
+    const float r = __builtin_fmaf(x, 1.92596299e-8f, __builtin_fmaf(x, 1.44269502f, -t));
+    const float e = __builtin_amdgcn_exp2f(t);
+    return t < -150.f ? 0.f : __builtin_fmaf(e, r * 0.693147182f, e);      // (x = -inf: r is not a number)
+}
 
-__device__ inline float block_sum(float v, float* sh /*>=4*/) {
-    v = wave_sum(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return sh[0] + sh[1] + sh[2] + sh[3];
+// =================================================================================================
+// General path: any vocabulary size and row alignment.  One workgroup of 1024 threads per sequence; a row is read in
+// aligned 16-byte granules (elements outside the row count as -inf), several granules per thread in flight.
+// The maximum and the normaliser of the two rows of a candidate come from one pass (running maximum per thread), the
+// draw takes one pass for the sums of runs of 64 U granules and reads again only the run that holds the
+// crossing.  What bounds it is the exponentials of one compute unit per sequence: 24 sequences of 5 candidates,
+// 65537 ids, 1255 us as 256 threads with 4-byte loads and a pass per reduction, 137 so, 80 with the candidates
+// tested at once (accept_test_generic_kernel 25, draw 53).
+// =================================================================================================
+constexpr int WIDE_THREADS = 1024, WIDE_WAVES = WIDE_THREADS / 64, WIDE_RUNS = 1024;
+
+struct WideShared {
+    float red[2][WIDE_WAVES];
+    int redi[WIDE_WAVES];
+    float run[WIDE_RUNS];             // total of every run, then the sum in front of it
+    float wave_tot[WIDE_WAVES];
+    int pick, last, stop;
+};
+
+// a row of V floats at any alignment, as granules of four: granule g holds ids 4 g - off .. 4 g - off + 3
+struct WideRow {
+    const float* row;
+    int V, off, n;
+    __device__ WideRow(const float* r, int V_) : row(r), V(V_), off((int)(((uintptr_t)r >> 2) & 3)), n((V_ + off + 3) >> 2) {}
+    __device__ float4 load(int g) const {
+        const int id = 4 * g - off;
+        if (g < n && id >= 0 && id + 3 < V) return *(const float4*)(row + id);
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = g < n && id + j >= 0 && id + j < V ? row[id + j] : -INFINITY;
+        return make_float4(v[0], v[1], v[2], v[3]);
+    }
+};
+
+// running maximum and sum of exp((z - m) inv_tau) over what a thread has seen
+struct MaxSum {
+    float m = -INFINITY, s = 0.f;
+    __device__ void take(const float4 (&v)[4], float inv_tau) {
+        float mx = m;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) mx = fmaxf(fmaxf(fmaxf(mx, v[q].x), fmaxf(v[q].y, v[q].z)), v[q].w);
+        if (mx == -INFINITY) return;                       // nothing but padding or masked ids so far
+        if (mx > m) { s *= exp_neg((m - mx) * inv_tau); m = mx; }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            s += (exp_neg((v[q].x - m) * inv_tau) + exp_neg((v[q].y - m) * inv_tau)) +
+                 (exp_neg((v[q].z - m) * inv_tau) + exp_neg((v[q].w - m) * inv_tau));
+    }
+};
+
+// maximum and normaliser of one or two rows (b: may be the same row as a, then computed for nothing else)
+template <bool TWO>
+__device__ inline void wide_row_stats(const WideRow& a, const WideRow& b, float inv_tau, WideShared& sh, float* am, float* as,
+                                      float* bm, float* bs) {
+    constexpr int STEP = 4 * WIDE_THREADS;
+    const int n = TWO ? max(a.n, b.n) : a.n;
+    MaxSum x, y;
+    float4 va[2][4], vb[2][4];
+    auto request = [&](int buf, int g0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            va[buf][q] = a.load(g0 + q * WIDE_THREADS + (int)threadIdx.x);
+            if (TWO) vb[buf][q] = b.load(g0 + q * WIDE_THREADS + (int)threadIdx.x);
+        }
+    };
+    request(0, 0);
+    for (int g0 = 0; g0 < n; g0 += 2 * STEP) {              // the next four granules are requested ahead
+        if (g0 + STEP < n) request(1, g0 + STEP);
+        x.take(va[0], inv_tau);
+        if (TWO) y.take(vb[0], inv_tau);
+        if (g0 + STEP < n) {
+            if (g0 + 2 * STEP < n) request(0, g0 + 2 * STEP);
+            x.take(va[1], inv_tau);
+            if (TWO) y.take(vb[1], inv_tau);
+        }
+    }
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    auto reduce = [&](const MaxSum& t, int slot, float* mo, float* so) {
+        float m = wave_max(t.m);
+        __syncthreads();
+        if (lane == 0) sh.red[slot][wv] = m;
+        __syncthreads();
+        m = sh.red[slot][0];
+#pragma unroll
+        for (int w = 1; w < WIDE_WAVES; ++w) m = fmaxf(m, sh.red[slot][w]);
+        float v = wave_sum(t.m == -INFINITY ? 0.f : t.s * exp_neg((t.m - m) * inv_tau));
+        __syncthreads();
+        if (lane == 0) sh.red[slot][wv] = v;
+        __syncthreads();
+        v = 0.f;
+#pragma unroll
+        for (int w = 0; w < WIDE_WAVES; ++w) v += sh.red[slot][w];
+        *mo = m; *so = v;
+    };
+    reduce(x, 0, am, as);
+    if (TWO) reduce(y, 1, bm, bs);
 }
-__device__ inline float block_max(float v, float* sh) {
-    v = wave_max(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
-}
-// argmax with lowest-index tie-break
-__device__ inline int block_argmax(const float* __restrict__ z, int V, float* shv, int* shi) {
+
+// argmax, lowest id on ties
+__device__ inline int wide_argmax(const WideRow& a, WideShared& sh) {
     float bv = -INFINITY;
     int bi = 0x7fffffff;
-    for (int c = threadIdx.x; c < V; c += ACC_THREADS) {
-        float v = z[c];
-        if (v > bv) { bv = v; bi = c; }
+    for (int g0 = 0; g0 < a.n; g0 += 4 * WIDE_THREADS) {
+        float4 v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = a.load(g0 + q * WIDE_THREADS + (int)threadIdx.x);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int id = 4 * (g0 + q * WIDE_THREADS + (int)threadIdx.x) - a.off;
+            const float x[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) if (x[j] > bv) { bv = x[j]; bi = id + j; }
+        }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -85,102 +184,127 @@ __device__ inline int block_argmax(const float* __restrict__ z, int V, float* sh
         if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
     }
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) { shv[threadIdx.x >> 6] = bv; shi[threadIdx.x >> 6] = bi; }
+    if ((threadIdx.x & 63) == 0) { sh.red[0][threadIdx.x >> 6] = bv; sh.redi[threadIdx.x >> 6] = bi; }
     __syncthreads();
-    bv = shv[0]; bi = shi[0];
+    bv = sh.red[0][0]; bi = sh.redi[0];
 #pragma unroll
-    for (int w = 1; w < 4; ++w)
-        if (shv[w] > bv || (shv[w] == bv && shi[w] < bi)) { bv = shv[w]; bi = shi[w]; }
+    for (int w = 1; w < WIDE_WAVES; ++w)
+        if (sh.red[0][w] > bv || (sh.red[0][w] == bv && sh.redi[w] < bi)) { bv = sh.red[0][w]; bi = sh.redi[w]; }
     return bi;
 }
 
-// Smallest id whose running sum of w(id) (ascending ids) exceeds target; if rounding leaves none,
-// the largest id with positive weight.
+// Inverse CDF over non-negative weights: weight(g) gives the weights of granule g (ids 4 g - off + 0..3; 0 outside
+// the row).  The smallest id whose running sum (ascending ids) exceeds u * total; if rounding leaves none, the
+// largest id of positive weight.  *total_out: the total (0: no positive weight; result invalid).
 template <typename F>
-__device__ inline int block_inverse_cdf(F w, int V, float target, float* shf, int* shi) {
-    float run = 0.f;
-    int last_pos = -1;
-    int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int base = 0; base < V; base += ACC_THREADS * 4) {
-        int id0 = base + threadIdx.x * 4;
-        float x[4];
+__device__ inline int wide_inverse_cdf(F weight, int n, int off, float u, WideShared& sh, float* total_out) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int U = (n + 64 * WIDE_RUNS - 1) / (64 * WIDE_RUNS), runs = (n + 64 * U - 1) / (64 * U);
+    int last = -1;
+    auto sum4 = [](const float4& w) { return (w.x + w.y) + (w.z + w.w); };
+    auto see = [&](const float4& w, int g) {
+        if (w.x > 0.f) last = max(last, 4 * g - off);
+        if (w.y > 0.f) last = max(last, 4 * g - off + 1);
+        if (w.z > 0.f) last = max(last, 4 * g - off + 2);
+        if (w.w > 0.f) last = max(last, 4 * g - off + 3);
+    };
+    __syncthreads();
+    sh.run[threadIdx.x] = 0.f;
+    if (threadIdx.x == 0) { sh.pick = 0x7fffffff; sh.last = -1; }
+    __syncthreads();
+    for (int r0 = wv; r0 < runs; r0 += 4 * WIDE_WAVES) {             // four runs of a wavefront at a time
+        float t[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < U; ++i) {
+            float4 w[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            x[j] = id0 + j < V ? w(id0 + j) : 0.f;
-            if (x[j] > 0.f) last_pos = id0 + j;
-        }
-        float local = (x[0] + x[1]) + (x[2] + x[3]);
-        float incl = local;
+            for (int q = 0; q < 4; ++q) w[q] = weight(((r0 + q * WIDE_WAVES) * U + i) * 64 + lane);
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            float up = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += up;
+            for (int q = 0; q < 4; ++q) { t[q] += sum4(w[q]); see(w[q], ((r0 + q * WIDE_WAVES) * U + i) * 64 + lane); }
         }
-        __syncthreads();
-        if (lane == 63) shf[wv] = incl;
-        __syncthreads();
-        float wave_base = 0.f;
-        for (int q = 0; q < wv; ++q) wave_base += shf[q];
-        float seg_total = shf[0] + shf[1] + shf[2] + shf[3];
-        incl += wave_base;
-        bool over = run + incl > target;
-        // lowest thread over the target
-        unsigned long long bal = __ballot(over);
-        __syncthreads();
-        if (lane == 0) shi[wv] = bal ? (wv * 64 + (int)__ffsll((long long)bal) - 1) : 0x7fffffff;
-        __syncthreads();
-        int first = min(min(shi[0], shi[1]), min(shi[2], shi[3]));
-        if (first != 0x7fffffff) {
-            __syncthreads();
-            if ((int)threadIdx.x == first) {
-                float c = run + (incl - local);
-                int pick = -1, lastp = -1;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    c += x[j];
-                    if (x[j] > 0.f) lastp = id0 + j;
-                    if (pick < 0 && c > target && x[j] > 0.f) pick = id0 + j;
-                }
-                shi[4] = pick >= 0 ? pick : (lastp >= 0 ? lastp : id0);
-            }
-            __syncthreads();
-            return shi[4];
+        for (int q = 0; q < 4; ++q) {
+            const float v = wave_sum(t[q]);
+            if (lane == 0 && r0 + q * WIDE_WAVES < runs) sh.run[r0 + q * WIDE_WAVES] = v;
         }
-        run += seg_total;
     }
-    // no crossing found (target >= total after rounding): largest id of positive weight
+    if (last >= 0) atomicMax(&sh.last, last);
+    __syncthreads();
+    // exclusive prefix of the runs' totals, one per thread
+    const float mine = sh.run[threadIdx.x];
+    float incl = mine;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) last_pos = max(last_pos, __shfl_xor(last_pos, o, 64));
+    for (int o = 1; o < 64; o <<= 1) {
+        const float up = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += up;
+    }
+    if (lane == 63) sh.wave_tot[wv] = incl;
     __syncthreads();
-    if (lane == 0) shi[wv] = last_pos;
+    float before = 0.f, total = 0.f;
+#pragma unroll
+    for (int w = 0; w < WIDE_WAVES; ++w) { if (w < wv) before += sh.wave_tot[w]; total += sh.wave_tot[w]; }
+    const float target = u * total, slack = 1e-4f * total;
+    const float front = before + (incl - mine);
+    // the run that holds the crossing, and its neighbours within the rounding of these sums
+    const bool near = mine > 0.f && front <= target + slack && front + mine >= target - slack;
     __syncthreads();
-    int r = max(max(shi[0], shi[1]), max(shi[2], shi[3]));
-    return r < 0 ? 0 : r;
+    sh.run[threadIdx.x] = near ? front : -1.f;
+    __syncthreads();
+    int found = 0x7fffffff;
+    for (int r = wv; r < runs; r += WIDE_WAVES) {
+        float base = sh.run[r];
+        if (base < 0.f) continue;                        // (wave-uniform)
+        for (int i = 0; i < U; ++i) {
+            const int g = (r * U + i) * 64 + lane;
+            const float4 w = weight(g);
+            const float local = sum4(w);
+            float in = local;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const float up = __shfl_up(in, o, 64);
+                if (lane >= o) in += up;
+            }
+            float c = base + (in - local);
+            const float x[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                c += x[j];
+                if (x[j] > 0.f && c > target) found = min(found, 4 * g - off + j);
+            }
+            base += __shfl(in, 63, 64);
+        }
+    }
+    if (found != 0x7fffffff) atomicMin(&sh.pick, found);
+    __syncthreads();
+    *total_out = total;
+    return sh.pick != 0x7fffffff ? sh.pick : (sh.last >= 0 ? sh.last : 0);
+}
+// the softmax weights of granule g of a row (0 for -inf entries, i.e. outside the row)
+__device__ inline float4 wide_weights(const WideRow& r, int g, float m, float inv_tau, float inv_norm) {
+    const float4 z = r.load(g);
+    return make_float4(exp_neg((z.x - m) * inv_tau) * inv_norm, exp_neg((z.y - m) * inv_tau) * inv_norm,
+                       exp_neg((z.z - m) * inv_tau) * inv_norm, exp_neg((z.w - m) * inv_tau) * inv_norm);
 }
 
-// max and sum of exp((z - max) * inv_tau) of one row
-__device__ inline void block_row_stats(const float* __restrict__ z, int V, float inv_tau, float* sh,
-                                       float* out_max, float* out_sum) {
-    float m = -INFINITY;
-    for (int c = threadIdx.x; c < V; c += ACC_THREADS) m = fmaxf(m, z[c]);
-    m = block_max(m, sh);
-    float s = 0.f;
-    for (int c = threadIdx.x; c < V; c += ACC_THREADS) s += expf((z[c] - m) * inv_tau);
-    s = block_sum(s, sh);
-    *out_max = m; *out_sum = s;
+// the acceptance test of candidate i of sequence b (the rows' maxima and normalisers given): true = rejected
+__device__ inline bool rejects(const AcceptArgs& a, int b, int i, float pm, float ps, float qm, float qs) {
+    const int c = a.draft_tokens[b * a.k + i];
+    if (c < 0 || c >= a.V) return true;              // an id outside the vocabulary is a rejected candidate
+    const float pv = expf((a.p_logits[((int64_t)b * (a.k + 1) + i) * a.V + c] - pm) * a.inv_tau) / ps;
+    const float qv = expf((a.q_logits[((int64_t)b * a.k + i) * a.V + c] - qm) * a.inv_tau) / qs;
+    const float u = a.u_accept ? a.u_accept[b * a.k + i]
+                               : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)(i + 1), 1);
+    return !(u * qv < pv);
 }
 
-// ---- greedy accept, any vocabulary size: one 256-thread workgroup per sequence, early exit at the
-// first mismatch ---------------------------------------------------------------------------------
-__global__ void __launch_bounds__(ACC_THREADS)
+// greedy: early exit at the first mismatch
+__global__ void __launch_bounds__(WIDE_THREADS)
 accept_greedy_generic_kernel(AcceptArgs a) {
-    __shared__ float shv[4];
-    __shared__ int shi[4];
-    int b = blockIdx.x;
+    __shared__ WideShared sh;
+    const int b = blockIdx.x;
     const float* P = a.p_logits + (int64_t)b * (a.k + 1) * a.V;
     int n = 0, am;
     while (true) {
-        am = block_argmax(P + (int64_t)n * a.V, a.V, shv, shi);
+        am = wide_argmax(WideRow(P + (int64_t)n * a.V, a.V), sh);
         if (n < a.k && a.draft_tokens[b * a.k + n] == am) ++n; else break;
     }
     if (threadIdx.x == 0) {
@@ -189,65 +313,55 @@ accept_greedy_generic_kernel(AcceptArgs a) {
     }
 }
 
-// ---- stochastic accept, any vocabulary size (rows re-read for every reduction) ------------------
-__global__ void __launch_bounds__(ACC_THREADS)
-accept_sample_generic_kernel(AcceptArgs a) {
-    __shared__ float shf[4];
-    __shared__ int shi[5];
-    __shared__ int sh_stop;
-    int b = blockIdx.x, k = a.k, V = a.V;
+__global__ void __launch_bounds__(WIDE_THREADS)
+accept_sample_generic_kernel(AcceptArgs a, int tested) {
+    __shared__ WideShared sh;
+    const int b = blockIdx.x, k = a.k, V = a.V;
     const float* P = a.p_logits + (int64_t)b * (k + 1) * V;
     const float* Q = a.q_logits + (int64_t)b * k * V;
-    float it = a.inv_tau;
-    int n = 0;
+    const float it = a.inv_tau;
+    int n = tested ? a.n_accepted[b] : 0;      // tested: candidates were tested by accept_test kernels
     float pm = 0.f, ps = 1.f, qm = 0.f, qs = 1.f;
     // candidates are tested in order; each test needs the softmax normalisers of two rows
     while (true) {
-        block_row_stats(P + (int64_t)n * V, V, it, shf, &pm, &ps);
-        if (n == k) break;
-        block_row_stats(Q + (int64_t)n * V, V, it, shf, &qm, &qs);
-        if (threadIdx.x == 0) {
-            int c = a.draft_tokens[b * k + n];
-            if (c < 0 || c >= V) sh_stop = 1;       // an id outside the vocabulary is a rejected candidate
-            else {
-                float pv = expf((P[(int64_t)n * V + c] - pm) * it) / ps;
-                float qv = expf((Q[(int64_t)n * V + c] - qm) * it) / qs;
-                float u = a.u_accept ? a.u_accept[b * k + n]
-                                     : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)(n + 1), 1);
-                sh_stop = !(u * qv < pv);
-            }
-        }
+        const WideRow p(P + (int64_t)n * V, V);
+        if (n == k) { wide_row_stats<false>(p, p, it, sh, &pm, &ps, nullptr, nullptr); break; }
+        wide_row_stats<true>(p, WideRow(Q + (int64_t)n * V, V), it, sh, &pm, &ps, &qm, &qs);
+        if (tested) break;
+        if (threadIdx.x == 0) sh.stop = rejects(a, b, n, pm, ps, qm, qs);
         __syncthreads();
-        int stop = sh_stop;
+        const int stop = sh.stop;
         __syncthreads();
         if (stop) break;
         ++n;
     }
-    const float* pr = P + (int64_t)n * V;
-    const float* qr = n < k ? Q + (int64_t)n * V : nullptr;
-    float ipn = 1.0f / ps, iqn = 1.0f / qs;
-    auto wres = [&](int id) -> float {
-        float pv = expf((pr[id] - pm) * it) * ipn;
-        if (!qr) return pv;
-        float qv = expf((qr[id] - qm) * it) * iqn;
-        return fmaxf(0.f, pv - qv);
+    const WideRow pr(P + (int64_t)n * V, V), qr(Q + (int64_t)(n < k ? n : 0) * V, V);
+    const float ipn = 1.0f / ps, iqn = 1.0f / qs;
+    const float u = a.u_resample ? a.u_resample[b * (k + 1) + n]
+                                 : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)n, 2);
+    // (granules of the two rows differ where their alignments do: the residual takes q element by element then)
+    auto wp = [&](int g) { return wide_weights(pr, g, pm, it, ipn); };
+    auto wres = [&](int g) {
+        float4 w = wide_weights(pr, g, pm, it, ipn), q;
+        if (pr.off == qr.off) q = wide_weights(qr, g, qm, it, iqn);
+        else {
+            float z[4];
+            const int id = 4 * g - pr.off;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool in = id + j >= 0 && id + j < V;
+                z[j] = in ? exp_neg((qr.row[in ? id + j : 0] - qm) * it) * iqn : 0.f;
+            }
+            q = make_float4(z[0], z[1], z[2], z[3]);
+        }
+        return make_float4(fmaxf(0.f, w.x - q.x), fmaxf(0.f, w.y - q.y), fmaxf(0.f, w.z - q.z), fmaxf(0.f, w.w - q.w));
     };
-    auto wp = [&](int id) -> float { return expf((pr[id] - pm) * it) * ipn; };
     float tot = 0.f;
-    for (int c = threadIdx.x; c < V; c += ACC_THREADS) tot += wres(c);
-    tot = block_sum(tot, shf);
-    float u = a.u_resample ? a.u_resample[b * (k + 1) + n]
-                           : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)n, 2);
-    int nxt;
-    if (tot > 0.f) nxt = block_inverse_cdf(wres, V, u * tot, shf, shi);
-    else {                                  // p == q everywhere: fall back to the target row
-        float tp = 0.f;
-        for (int c = threadIdx.x; c < V; c += ACC_THREADS) tp += wp(c);
-        tp = block_sum(tp, shf);
-        nxt = block_inverse_cdf(wp, V, u * tp, shf, shi);
-    }
+    int nxt = 0;
+    if (n < k) nxt = wide_inverse_cdf(wres, pr.n, pr.off, u, sh, &tot);
+    if (n == k || !(tot > 0.f)) nxt = wide_inverse_cdf(wp, pr.n, pr.off, u, sh, &tot);    // (p == q everywhere: the target row)
     if (threadIdx.x == 0) {
-        if (a.n_accepted) a.n_accepted[b] = n;
+        if (a.n_accepted && !tested) a.n_accepted[b] = n;
         if (a.next_token) a.next_token[b] = nxt;
     }
 }
@@ -308,8 +422,8 @@ __device__ inline void fast_row_stats(const float4 (&v)[FAST_SWEEPS], float inv_
     float sum = 0.f;
 #pragma unroll
     for (int s = 0; s < FAST_SWEEPS; ++s)
-        sum += (expf((v[s].x - m) * inv_tau) + expf((v[s].y - m) * inv_tau)) +
-               (expf((v[s].z - m) * inv_tau) + expf((v[s].w - m) * inv_tau));
+        sum += (exp_neg((v[s].x - m) * inv_tau) + exp_neg((v[s].y - m) * inv_tau)) +
+               (exp_neg((v[s].z - m) * inv_tau) + exp_neg((v[s].w - m) * inv_tau));
     *out_max = m;
     *out_sum = fast_block_sum(sum, sh);
 }
@@ -397,8 +511,8 @@ __device__ inline int fast_inverse_cdf(const float4 (&wt)[FAST_SWEEPS], float u,
     return sh.pick != 0x7fffffff ? sh.pick : (sh.last >= 0 ? sh.last : 0);
 }
 __device__ inline float4 fast_softmax_weights(const float4& z, float m, float inv_tau, float inv_norm) {
-    return make_float4(expf((z.x - m) * inv_tau) * inv_norm, expf((z.y - m) * inv_tau) * inv_norm,
-                       expf((z.z - m) * inv_tau) * inv_norm, expf((z.w - m) * inv_tau) * inv_norm);
+    return make_float4(exp_neg((z.x - m) * inv_tau) * inv_norm, exp_neg((z.y - m) * inv_tau) * inv_norm,
+                       exp_neg((z.z - m) * inv_tau) * inv_norm, exp_neg((z.w - m) * inv_tau) * inv_norm);
 }
 
 __global__ void __launch_bounds__(FAST_THREADS)
@@ -454,13 +568,13 @@ accept_greedy_rows_kernel(AcceptArgs a) {
 }
 
 __global__ void __launch_bounds__(FAST_THREADS)
-accept_sample_kernel(AcceptArgs a) {
+accept_sample_kernel(AcceptArgs a, int tested) {
     __shared__ FastShared sh;
     const int b = blockIdx.x, k = a.k, V = a.V;
     const float* P = a.p_logits + (int64_t)b * (k + 1) * V;
     const float* Q = a.q_logits + (int64_t)b * k * V;
     const float it = a.inv_tau;
-    int n = 0;
+    int n = tested ? a.n_accepted[b] : 0;      // tested: candidates were tested by accept_test kernels
     float pm = 0.f, ps = 1.f, qm = 0.f, qs = 1.f;
     float4 pz[FAST_SWEEPS], qz[FAST_SWEEPS];
     // candidates are tested in order; each test needs the softmax normalisers of two rows, which stay
@@ -471,17 +585,8 @@ accept_sample_kernel(AcceptArgs a) {
         fast_row_stats(pz, it, sh, &pm, &ps);
         if (n == k) break;
         fast_row_stats(qz, it, sh, &qm, &qs);
-        if (threadIdx.x == 0) {
-            int c = a.draft_tokens[b * k + n];
-            if (c < 0 || c >= V) sh.stop = 1;       // an id outside the vocabulary is a rejected candidate
-            else {
-                float pv = expf((P[(int64_t)n * V + c] - pm) * it) / ps;
-                float qv = expf((Q[(int64_t)n * V + c] - qm) * it) / qs;
-                float u = a.u_accept ? a.u_accept[b * k + n]
-                                     : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)(n + 1), 1);
-                sh.stop = !(u * qv < pv);
-            }
-        }
+        if (tested) break;
+        if (threadIdx.x == 0) sh.stop = rejects(a, b, n, pm, ps, qm, qs);
         __syncthreads();
         const int stop = sh.stop;
         __syncthreads();
@@ -509,9 +614,36 @@ accept_sample_kernel(AcceptArgs a) {
         nxt = fast_inverse_cdf(w, u, sh, &tot);
     }
     if (threadIdx.x == 0) {
-        if (a.n_accepted) a.n_accepted[b] = n;
+        if (a.n_accepted && !tested) a.n_accepted[b] = n;
         if (a.next_token) a.next_token[b] = nxt;
     }
+}
+
+// Few sequences: every candidate of every sequence is tested by a workgroup of its own (n_accepted[b] starts at k and
+// becomes the smallest rejected index), then one workgroup per sequence draws.  The tests of a sequence one after
+// the other keep a compute unit each for (kept + 1) times two rows while the others idle; with B k <= 256 tests
+// they all run at once.  The rows behind the first rejection are read for nothing, which larger batches
+// would pay for (256 sequences are bound by these bytes).
+__global__ void __launch_bounds__(FAST_THREADS)
+accept_test_kernel(AcceptArgs a) {
+    __shared__ FastShared sh;
+    const int b = blockIdx.x / a.k, i = blockIdx.x % a.k;
+    float4 pz[FAST_SWEEPS], qz[FAST_SWEEPS];
+    fast_load_row(a.p_logits + ((int64_t)b * (a.k + 1) + i) * a.V, a.V, pz);
+    fast_load_row(a.q_logits + ((int64_t)b * a.k + i) * a.V, a.V, qz);
+    float pm, ps, qm, qs;
+    fast_row_stats(pz, a.inv_tau, sh, &pm, &ps);
+    fast_row_stats(qz, a.inv_tau, sh, &qm, &qs);
+    if (threadIdx.x == 0 && rejects(a, b, i, pm, ps, qm, qs)) atomicMin(&a.n_accepted[b], i);
+}
+__global__ void __launch_bounds__(WIDE_THREADS)
+accept_test_generic_kernel(AcceptArgs a) {
+    __shared__ WideShared sh;
+    const int b = blockIdx.x / a.k, i = blockIdx.x % a.k;
+    float pm, ps, qm, qs;
+    wide_row_stats<true>(WideRow(a.p_logits + ((int64_t)b * (a.k + 1) + i) * a.V, a.V),
+                         WideRow(a.q_logits + ((int64_t)b * a.k + i) * a.V, a.V), a.inv_tau, sh, &pm, &ps, &qm, &qs);
+    if (threadIdx.x == 0 && rejects(a, b, i, pm, ps, qm, qs)) atomicMin(&a.n_accepted[b], i);
 }
 
 static inline bool fast_rows_ok(const float* base, int V) {
@@ -522,33 +654,39 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t st) {
     if (a.B <= 0) return hipSuccess;
     const bool fast = fast_rows_ok(a.p_logits, a.V) && (!a.q_logits || fast_rows_ok(a.q_logits, a.V));
     if (a.q_logits) {
-        if (fast) hipLaunchKernelGGL(accept_sample_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
-        else hipLaunchKernelGGL(accept_sample_generic_kernel, dim3(a.B), dim3(ACC_THREADS), 0, st, a);
+        const int tested = a.n_accepted && a.k >= 2 && a.B * a.k <= 256;
+        if (tested) {
+            hipError_t e = launch_fill_words(a.n_accepted, (size_t)a.B, (uint32_t)a.k, st);
+            if (e != hipSuccess) return e;
+            if (fast) hipLaunchKernelGGL(accept_test_kernel, dim3(a.B * a.k), dim3(FAST_THREADS), 0, st, a);
+            else hipLaunchKernelGGL(accept_test_generic_kernel, dim3(a.B * a.k), dim3(WIDE_THREADS), 0, st, a);
+        }
+        if (fast) hipLaunchKernelGGL(accept_sample_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a, tested);
+        else hipLaunchKernelGGL(accept_sample_generic_kernel, dim3(a.B), dim3(WIDE_THREADS), 0, st, a, tested);
     } else {
         if (a.V <= ROWS_MAX_V) hipLaunchKernelGGL(accept_greedy_rows_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
         else if (fast) hipLaunchKernelGGL(accept_greedy_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
-        else hipLaunchKernelGGL(accept_greedy_generic_kernel, dim3(a.B), dim3(ACC_THREADS), 0, st, a);
+        else hipLaunchKernelGGL(accept_greedy_generic_kernel, dim3(a.B), dim3(WIDE_THREADS), 0, st, a);
     }
     return hipGetLastError();
 }
 
 // ---- draft token pick ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(ACC_THREADS)
+__global__ void __launch_bounds__(WIDE_THREADS)
 draft_pick_generic_kernel(const float* __restrict__ z, int64_t ld, int V, int mode, float inv_tau, uint64_t seed,
                           uint32_t round, uint32_t seq_base, int step, int32_t* __restrict__ draft_tokens, int k) {
-    __shared__ float shf[4];
-    __shared__ int shi[5];
-    int b = blockIdx.x;
-    const float* row = z + (int64_t)b * ld;
+    __shared__ WideShared sh;
+    const int b = blockIdx.x;
+    const WideRow row(z + (int64_t)b * ld, V);
     int pick;
     if (mode == SPEC_GREEDY) {
-        pick = block_argmax(row, V, shf, shi);
+        pick = wide_argmax(row, sh);
     } else {
-        float m, s;
-        block_row_stats(row, V, inv_tau, shf, &m, &s);
-        auto w = [&](int id) -> float { return expf((row[id] - m) * inv_tau); };
-        float u = philox_uniform(seed, round, seq_base + b, (uint32_t)step, 0);
-        pick = block_inverse_cdf(w, V, u * s, shf, shi);
+        float m, s, tot;
+        wide_row_stats<false>(row, row, inv_tau, sh, &m, &s, nullptr, nullptr);
+        auto w = [&](int g) { return wide_weights(row, g, m, inv_tau, 1.0f); };
+        const float u = philox_uniform(seed, round, seq_base + b, (uint32_t)step, 0);
+        pick = wide_inverse_cdf(w, row.n, row.off, u, sh, &tot);
     }
     if (threadIdx.x == 0) draft_tokens[b * k + step - 1] = pick;
 }
@@ -581,7 +719,7 @@ hipError_t launch_draft_pick(const float* z, int64_t ld, int V, int B, int mode,
         hipLaunchKernelGGL(draft_pick_kernel, dim3(B), dim3(FAST_THREADS), 0, st, z, ld, V, mode, inv_tau, seed,
                            round, seq_base, step, draft_tokens, k);
     else
-        hipLaunchKernelGGL(draft_pick_generic_kernel, dim3(B), dim3(ACC_THREADS), 0, st, z, ld, V, mode, inv_tau,
+        hipLaunchKernelGGL(draft_pick_generic_kernel, dim3(B), dim3(WIDE_THREADS), 0, st, z, ld, V, mode, inv_tau,
                            seed, round, seq_base, step, draft_tokens, k);
     return hipGetLastError();
 }

@@ -167,3 +167,53 @@ def test_candidate_outside_the_vocabulary_is_rejected(V):
         torch.cuda.synchronize()
         assert n.cpu().tolist() == [1, 0, 2, 3]
         assert all(0 <= t < V for t in nx.cpu().tolist())
+
+
+# candidates tested one workgroup each (B k <= 256) and one after the other (more); rows at every alignment
+# (V mod 4 = 0..3), one id short of and past a run of the inverse-CDF search, runs of more than one granule per lane
+@pytest.mark.parametrize("B,k,V,tau", [(4, 2, 65537, 0.8), (4, 3, 300001, 0.8), (4, 2, 262142, 0.8), (4, 2, 262147, 1.0),
+                                       (100, 3, 512, 0.8), (90, 4, 1001, 0.8), (64, 4, 1003, 0.8), (5, 16, 4098, 0.8),
+                                       (260, 1, 64, 0.8), (4, 1, 3, 0.8), (4, 2, 1, 0.8)])
+def test_accept_sample_wide_rows_and_both_test_orders(B, k, V, tau):
+    import torch
+    import paper_2505_10259_amd as P
+    from gpu_common import dev
+    test_accept_sample_given_uniforms(B, k, V, tau)
+    # without n_accepted the candidates are tested in turn: same next tokens
+    p, q, d = _logits(B, k, V, seed=3 * B + V)
+    p, q, d = dev(p), dev(q), dev(d)
+    out = []
+    for n in (torch.full((B,), -1, dtype=torch.int32, device="cuda"), None):
+        nx = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+        P.spec_accept(p, q, d, None, None, tau, 5, 1, 0, B, k, V, n, nx)
+        torch.cuda.synchronize()
+        out.append(nx)
+    assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("V", [40001, 1002, 512])
+def test_accept_sample_masked_and_infinite_rows(V):
+    """Ids masked with -inf are never emitted; a target row with one finite id emits it; rows of -inf or with a
+    not-a-number still give an id of the vocabulary."""
+    import torch
+    import paper_2505_10259_amd as P
+    B, k = 6, 2
+    g = torch.Generator("cuda").manual_seed(V)
+    p = torch.randn(B, k + 1, V, device="cuda", generator=g)
+    q = torch.randn(B, k, V, device="cuda", generator=g)
+    keep = torch.arange(V, device="cuda") % 7 == 3
+    p[:, :, ~keep] = -float("inf")
+    p[1] = -float("inf"); p[1, :, V // 2] = 0.0
+    p[2] = -float("inf")
+    p[3, :, 5] = float("nan")
+    p[4, :, 3] = float("inf")
+    d = torch.full((B, k), 4, dtype=torch.int32, device="cuda")      # masked: rejected at once
+    for n in (torch.zeros(B, dtype=torch.int32, device="cuda"), None):
+        nx = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+        P.spec_accept(p, q, d, None, None, 0.8, 7, 1, 0, B, k, V, n, nx)
+        torch.cuda.synchronize()
+        t = nx.cpu().tolist()
+        assert all(0 <= x < V for x in t)
+        assert t[0] % 7 == 3 and t[5] % 7 == 3 and t[1] == V // 2
+        if n is not None:
+            assert n.cpu().tolist()[:2] == [0, 0] and n[5].item() == 0
