@@ -174,6 +174,8 @@ struct spec_ctx {
     // refuses with SPEC_ERR_STATE until the context is destroyed
     bool broken = false;
     std::vector<void*> allocs;            // everything to hipFree
+    void* prefill_ws = nullptr;           // workspace of short prefills, kept between calls (see spec_prefill)
+    size_t prefill_ws_bytes = 0;
     int device = 0;
     void* scratch_ptr = nullptr;          // this device's copy of the static scratch array
     std::string scratch_err;              // why its address could not be looked up, if it could not
@@ -422,18 +424,19 @@ inline void* kv_layer_ptr(void* pool, const KvGeom& g, int layer, size_t es) {
     return (char*)pool + (size_t)layer * (size_t)g.layer_elems() * es;
 }
 
+// layer_qkv: first norm, QKV projection, rotation, KV append (all that a prefill needs of its last layer);
+// layer_attn: that, attention and the output projection.
 // A layer is enqueued in three parts so that a streamed layer can take its weights piece by piece:
 // layer_front (attention block, post-attention norm, routing: the weights before the experts),
 // the expert products (all experts in two grouped launches, or one expert at a time) and the combine.
 //
 // `pending`: on entry, true if the previous layer left its MoE output uncombined in ws.y.
-int layer_attn(spec_ctx* c, const spec_model_shape& s, const Layout& L, const char* Wb, Workspace& w,
-               const RowSet& r, void* kv_layer, const KvGeom& geom, const int32_t* page_table,
-               bool* pending, hipStream_t st) {
+int layer_qkv(spec_ctx* c, const spec_model_shape& s, const Layout& L, const char* Wb, Workspace& w,
+              const RowSet& r, void* kv_layer, const KvGeom& geom, const int32_t* page_table,
+              bool* pending, hipStream_t st) {
     const int dt = s.dtype;
     const size_t es = esize(dt);
     const int d = s.d_model, T = r.T;
-    const int hd = s.n_q_heads * s.head_dim;
     const int qkv_rows = (s.n_q_heads + 2 * s.n_kv_heads) * s.head_dim;
     auto W = [&](int64_t off) { return (const void*)(Wb + off * es); };
 
@@ -448,7 +451,7 @@ int layer_attn(spec_ctx* c, const spec_model_shape& s, const Layout& L, const ch
     // otherwise projection to f32, then the rope/append kernel.  The two bf16 ways give the same bits.
     const bool mfma_rope = dt == SPEC_BF16 && !(c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS) && s.head_dim == 128 &&
                            d % 64 == 0;
-    if (mfma_rope && qkv_unfused_pays(T, qkv_rows, d)) {
+    if (mfma_rope && w.qkv && qkv_unfused_pays(T, qkv_rows, d)) {
         g.epilogue = EPI_STORE_F32;
         { ProfScope ps(c, SPEC_PROF_QKV, st); HIPCHK(c, gemm(c, g, dt, st)); }
         { ProfScope ps(c, SPEC_PROF_ROPE, st);
@@ -467,13 +470,23 @@ int layer_attn(spec_ctx* c, const spec_model_shape& s, const Layout& L, const ch
           HIPCHK(c, launch_rope_kv(w.qkv, r.cs, r.row_pos, page_table, w.q, kv_layer, geom, T, r.n_new,
                                    s.n_q_heads, dt, st)); }
     }
+    return SPEC_OK;
+}
+
+int layer_attn(spec_ctx* c, const spec_model_shape& s, const Layout& L, const char* Wb, Workspace& w,
+               const RowSet& r, void* kv_layer, const KvGeom& geom, const int32_t* page_table,
+               bool* pending, hipStream_t st) {
+    int rc = layer_qkv(c, s, L, Wb, w, r, kv_layer, geom, page_table, pending, st);
+    if (rc) return rc;
+    const int dt = s.dtype;
+    const int d = s.d_model, T = r.T, hd = s.n_q_heads * s.head_dim;
     AttnArgs a{};
     a.q = w.q; a.out = w.att; a.kv_layer = kv_layer; a.page_table = page_table; a.row_pos = r.row_pos;
     a.geom = geom; a.B = r.B; a.n_new = r.n_new; a.n_q_heads = s.n_q_heads;
     a.scale = 1.0f / sqrtf((float)s.head_dim);
     { ProfScope ps(c, SPEC_PROF_ATTN, st); HIPCHK(c, attention(c, a, dt, st)); }
-    g = GemmArgs{};
-    g.A = w.att; g.lda = hd; g.W = W(L.wo); g.C = r.x; g.ldc = d; g.M = T; g.N = d; g.K = hd;
+    GemmArgs g{};
+    g.A = w.att; g.lda = hd; g.W = Wb + L.wo * esize(dt); g.C = r.x; g.ldc = d; g.M = T; g.N = d; g.K = hd;
     g.epilogue = EPI_ADD_F32;
     { ProfScope ps(c, SPEC_PROF_OPROJ, st); HIPCHK(c, gemm(c, g, dt, st)); }
     return SPEC_OK;
@@ -804,6 +817,7 @@ void spec_destroy(spec_ctx* c) {
         if (c->sub[s].ev_committed) hipEventDestroy(c->sub[s].ev_committed);
     }
     for (void* p : c->allocs) hipFree(p);
+    if (c->prefill_ws) hipFree(c->prefill_ws);
     if (c->own_compute) hipStreamDestroy(c->s_compute);
     if (c->own_copy) hipStreamDestroy(c->s_copy);
     if (c->s_copy2) hipStreamDestroy(c->s_copy2);
@@ -1063,140 +1077,157 @@ int spec_prefill(spec_ctx* c, int sub, const int32_t* tokens, const int32_t* cu_
     for (int b = 0; b < B; ++b) pmax = std::max(pmax, cu_lens[b + 1] - cu_lens[b] - 1);
     const int Q = c->cfg.prefill_chunk;
     const int n_chunks = (pmax + Q - 1) / Q;
-    const int T = B * Q;
     if (n_chunks > 0) {
-        const int d = c->tgt.d_model, half = c->tgt.head_dim / 2;
-        float* xall = nullptr; int32_t* pos_all = nullptr; float2* cs_all = nullptr;
         hipStream_t st = c->s_compute;
-        HIPCHK(c, hipMalloc(&xall, (size_t)n_chunks * T * d * 4));
-        hipError_t e1 = hipMalloc(&pos_all, (size_t)n_chunks * T * 4);
-        hipError_t e2 = hipMalloc(&cs_all, (size_t)n_chunks * T * half * sizeof(float2));
-        // The attention block runs chunk by chunk (Q prompt positions of every sequence); the feed-forward
-        // part runs on groups of chunks so that an expert sees thousands of rows per launch.  A layer that
-        // streams piece by piece holds each piece for all groups before the next piece arrives, so what a
-        // group carries from the routing to its experts and on to the combine (normalised rows, routing,
-        // expert outputs) is then kept per group.
-        const int G = std::max(1, std::min(n_chunks, c->cfg.prefill_group_rows / T));
-        const int n_grp = (n_chunks + G - 1) / G;
-        std::vector<void*> temps;
         const int32_t* forced = sb.forced_ids;
         const int64_t forced_rows = sb.forced_rows;
         sb.forced_ids = nullptr;
-        auto cleanup = [&]() { hipFree(xall); hipFree(pos_all); hipFree(cs_all); for (void* p : temps) hipFree(p); };
-        // The prefill lays its rows out in its own order of the sequences: longest prompt first.  In chunk
-        // ch only the first n_act[ch] sequences still have prompt positions, so the attention part of a
-        // chunk (norm, QKV, attention, O-projection) runs on that prefix of the chunk's rows and skips the
-        // padding of finished prompts (the feed-forward part already leaves inactive rows out through the
-        // routing).  seq_of maps a row block to its sequence for the token gather, and the page table handed
-        // to the kernels is the context's with its rows in the same order.  (Forced routing, a test hook whose
-        // ids come in sequence order, keeps the sequences in their own order.)
+        if (forced && forced_rows < (int64_t)n_chunks * B * Q)
+            return fail(c, SPEC_ERR_ARG, "forced routing covers %lld rows per layer, the prefill has %lld", (long long)forced_rows,
+                        (long long)n_chunks * B * Q);
+        // The rows of a prefill are blocks of Q prompt positions of one sequence, ordered by position and, at equal
+        // position, longest prompt first; a sequence has blocks up to the end of its prompt only, so nothing but the
+        // rest of its last block is padding.  seq_of and pos0 say what a block carries, and the page table
+        // handed to the kernels has one row per block.  (Forced routing, a test hook whose ids come in
+        // (chunk, sequence) order, keeps every sequence in every chunk, in the sequences' own order.)
         std::vector<int32_t> order(B);
         for (int b = 0; b < B; ++b) order[b] = b;
         if (!forced)
             std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
                 return cu_lens[x + 1] - cu_lens[x] > cu_lens[y + 1] - cu_lens[y]; });
-        std::vector<int> n_act(n_chunks, 0);
+        const int pps = c->gt.pages_per_seq, Bm = c->cfg.batch_max;
+        std::vector<int32_t> tab;              // [blocks] sequence, [blocks] first position, [blocks][pps] pages
         for (int ch = 0; ch < n_chunks; ++ch)
             for (int v = 0; v < B; ++v)
-                if (cu_lens[order[v] + 1] - cu_lens[order[v]] - 1 > ch * Q) n_act[ch] = v + 1;
-        const int pps = c->gt.pages_per_seq, Bm = c->cfg.batch_max;
-        int32_t* seq_of = nullptr; int32_t* pt_v = nullptr;
-        {
-            std::vector<int32_t> tab((size_t)B * pps);
+                if (forced || cu_lens[order[v] + 1] - cu_lens[order[v]] - 1 > ch * Q) tab.push_back(order[v]);
+        const int n_blocks = (int)tab.size();
+        for (int ch = 0; ch < n_chunks; ++ch)
             for (int v = 0; v < B; ++v)
-                for (int p = 0; p < pps; ++p) tab[(size_t)v * pps + p] = p * Bm + order[v];
-            hipError_t e3 = hipMalloc(&seq_of, (size_t)B * 4);
-            if (e3 == hipSuccess) temps.push_back(seq_of);
-            hipError_t e4 = hipMalloc(&pt_v, tab.size() * 4);
-            if (e4 == hipSuccess) temps.push_back(pt_v);
-            if (e3 == hipSuccess && e4 == hipSuccess) {
-                e3 = hipMemcpy(seq_of, order.data(), (size_t)B * 4, hipMemcpyHostToDevice);
-                e4 = hipMemcpy(pt_v, tab.data(), tab.size() * 4, hipMemcpyHostToDevice);
+                if (forced || cu_lens[order[v] + 1] - cu_lens[order[v]] - 1 > ch * Q) tab.push_back(ch * Q);
+        for (int i = 0; i < n_blocks; ++i)
+            for (int p = 0; p < pps; ++p) tab.push_back(p * Bm + tab[i]);
+        const int64_t R = (int64_t)n_blocks * Q;
+        // A layer runs on groups of blocks in order: a group's keys and values are appended before its attention
+        // runs and those of earlier positions were appended with it or with an earlier group, so one launch of every
+        // kernel serves all chunks of a group, and an expert sees thousands of rows.  A layer that streams
+        // piece by piece holds each piece for all groups before the next piece arrives, so what a group
+        // carries from the routing to its experts and on to the combine (normalised rows, routing,
+        // expert outputs) is then kept per group.  (The operands of a product must stay below 4 GB.)
+        const int64_t widest = std::max({c->tgt.d_model, c->tgt.n_q_heads * c->tgt.head_dim,
+                                         c->has_draft ? c->drf.n_q_heads * c->drf.head_dim : 0});
+        const int64_t row_cap = std::min<int64_t>(std::max(c->cfg.prefill_group_rows, B * Q), (((int64_t)1 << 32) - 1) / (widest * 4));
+        const int Gb = (int)std::max<int64_t>(1, std::min<int64_t>(n_blocks, row_cap / Q));
+        const int n_grp = (n_blocks + Gb - 1) / Gb;
+        const size_t Rg = (size_t)Gb * Q;
+        // workspace: rows of the whole prefill, then what a group needs, of the model that needs more of it
+        auto al = [](size_t n) { return (n + 255) & ~(size_t)255; };
+        size_t off = 0;
+        auto take = [&](size_t bytes) { size_t o = off; off += al(bytes); return o; };
+        const int d = c->tgt.d_model;
+        const size_t o_x = take((size_t)R * d * 4), o_pos = take((size_t)R * 4), o_tok = take((size_t)R * 4);
+        const size_t o_cs = take((size_t)R * (c->tgt.head_dim / 2) * sizeof(float2)), o_tab = take(tab.size() * 4);
+        const size_t common = off;
+        auto piecewise_of = [&](bool is_draft) {
+            if (!is_draft) for (int l = 0; l < c->tgt.n_layers; ++l) if (!layer_is_whole(c, l)) return true;
+            return false;
+        };
+        // carves the group workspaces of a model out of `base` (nullptr: sizes only); returns the end
+        auto carve = [&](bool is_draft, char* base, std::vector<Workspace>* wg) {
+            const spec_model_shape& s = is_draft ? c->drf : c->tgt;
+            const size_t hd = (size_t)s.n_q_heads * s.head_dim, qkv_rows = (size_t)(s.n_q_heads + 2 * s.n_kv_heads) * s.head_dim;
+            const bool ffn = !s.attn_only, moe = s.n_experts > 0;
+            const size_t n_wg = piecewise_of(is_draft) ? n_grp : 1;
+            off = common;
+            Workspace w;
+            w.t_max = (int)Rg;
+            w.q = base + take(Rg * hd * c->es);
+            w.att = base + take(Rg * hd * c->es);
+            // f32 projections: the plain path, and groups of so few rows that the epilogue does not rotate
+            const int last_rows = (n_blocks - (n_grp - 1) * Gb) * Q;
+            const bool mfma = s.dtype == SPEC_BF16 && !(c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS) && s.head_dim == 128 && s.d_model % 64 == 0;
+            if (!mfma || qkv_unfused_pays((int)Rg, (int)qkv_rows, d) || qkv_unfused_pays(last_rows, (int)qkv_rows, d))
+                w.qkv = (float*)(base + take(Rg * qkv_rows * 4));
+            if (ffn) w.u = base + take((moe ? 2 : 1) * Rg * s.d_ff * c->es);
+            for (size_t i = 0; i < n_wg; ++i) {
+                Workspace x = w;
+                x.h = base + take(Rg * d * c->es);
+                if (moe) {
+                    x.y = (float*)(base + take(2 * Rg * d * 4));
+                    x.r_ids = (int32_t*)(base + take(Rg * 8));
+                    x.r_wts = (float*)(base + take(Rg * 8));
+                    x.perm = (int32_t*)(base + take(Rg * 8));
+                    x.slots = (int32_t*)(base + take(Rg * 8));
+                    x.offsets = (int32_t*)(base + take(64));
+                }
+                if (wg) wg->push_back(x);
             }
-            if (e3 != hipSuccess || e4 != hipSuccess) { cleanup(); return fail(c, SPEC_ERR_HIP, "prefill scratch allocation failed"); }
+            return off;
+        };
+        size_t need = carve(false, nullptr, nullptr);
+        if (c->has_draft) need = std::max(need, carve(true, nullptr, nullptr));
+        // Short prefills (a few requests) keep their workspace for the next call: allocating and freeing it took
+        // longer than some of their layers.  Larger ones give it back at the end.
+        constexpr size_t KEEP_BYTES = (size_t)256 << 20;
+        char* ws = nullptr;
+        void* temp = nullptr;
+        if (need > KEEP_BYTES) {
+            if (hipMalloc(&temp, need) != hipSuccess) { (void)hipGetLastError(); return fail(c, SPEC_ERR_HIP, "prefill scratch allocation failed"); }
+            ws = (char*)temp;
+        } else {
+            if (need > c->prefill_ws_bytes) {
+                if (c->prefill_ws) hipFree(c->prefill_ws);
+                c->prefill_ws = nullptr; c->prefill_ws_bytes = 0;
+                if (hipMalloc(&c->prefill_ws, need) != hipSuccess) {
+                    (void)hipGetLastError();
+                    c->prefill_ws = nullptr;
+                    return fail(c, SPEC_ERR_HIP, "prefill scratch allocation failed");
+                }
+                c->prefill_ws_bytes = need;
+            }
+            ws = (char*)c->prefill_ws;
         }
-        if (forced && forced_rows < (int64_t)n_chunks * T) {
-            cleanup();
-            return fail(c, SPEC_ERR_ARG, "forced routing covers %lld rows per layer, the prefill has %lld", (long long)forced_rows,
-                        (long long)n_chunks * T);
-        }
-        if (e1 != hipSuccess || e2 != hipSuccess) { cleanup(); return fail(c, SPEC_ERR_HIP, "prefill scratch allocation failed"); }
+        float* xall = (float*)(ws + o_x);
+        int32_t *pos_all = (int32_t*)(ws + o_pos), *tok_all = (int32_t*)(ws + o_tok), *tab_dev = (int32_t*)(ws + o_tab);
+        float2* cs_all = (float2*)(ws + o_cs);
+        const int32_t *seq_of = tab_dev, *pos0 = tab_dev + n_blocks, *pt_v = tab_dev + 2 * n_blocks;
         auto run_model = [&](bool is_draft) -> int {
             const spec_model_shape& s = is_draft ? c->drf : c->tgt;
             const Layout& L = is_draft ? c->dl : c->tl;
             const KvGeom& geom = is_draft ? c->gd : c->gt;
-            Workspace& w = is_draft ? c->wd : c->wv;
             const char* G_ = (const char*)(is_draft ? c->d_draft_globals : c->d_globals);
             const int hf = s.head_dim / 2;
             const bool ffn = !s.attn_only, moe = s.n_experts > 0;
-            bool piecewise = false;
-            if (!is_draft) for (int l = 0; l < s.n_layers; ++l) piecewise = piecewise || !layer_is_whole(c, l);
-            std::vector<Workspace> wg(piecewise ? n_grp : 1, w);
-            if (ffn) {
-                auto al = [](size_t n) { return (n + 255) & ~(size_t)255; };
-                const size_t Tg = (size_t)G * T;
-                const size_t b_h = al(Tg * d * c->es), b_y = moe ? al(2 * Tg * d * 4) : 0, b_t8 = moe ? al(Tg * 8) : 0,
-                             b_off = moe ? 256 : 0, b_u = al((moe ? 2 : 1) * Tg * s.d_ff * c->es);
-                const size_t per = b_h + b_y + 4 * b_t8 + b_off;
-                char* base = nullptr;
-                if (hipMalloc(&base, per * wg.size() + b_u) != hipSuccess)
-                    return fail(c, SPEC_ERR_HIP, "prefill scratch allocation failed");
-                temps.push_back(base);
-                for (size_t i = 0; i < wg.size(); ++i) {
-                    char* p = base + per * i;
-                    Workspace& x = wg[i];
-                    x.u = base + per * wg.size();
-                    x.h = p; p += b_h;
-                    if (moe) {
-                        x.y = (float*)p; p += b_y;
-                        x.r_ids = (int32_t*)p; p += b_t8;
-                        x.r_wts = (float*)p; p += b_t8;
-                        x.perm = (int32_t*)p; p += b_t8;
-                        x.slots = (int32_t*)p; p += b_t8;
-                        x.offsets = (int32_t*)p;
-                    }
-                }
-            }
-            for (int ch = 0; ch < n_chunks; ++ch) {
-                int32_t* rp = pos_all + (size_t)ch * T;
-                HIPCHK(c, launch_prefill_prep(sb.st.tokens, sb.st.len, seq_of, sb.st.tok_cap, B, ch * Q, Q, w.tok_in, rp, st));
-                HIPCHK(c, launch_embed(G_ + c->gl.emb * c->es, w.tok_in, xall + (size_t)ch * T * d, T, d, s.vocab, s.dtype, st));
-                HIPCHK(c, launch_rope_table(rp, cs_all + (size_t)ch * T * hf, T, hf, s.rope_theta, st));
-            }
+            std::vector<Workspace> wg;
+            carve(is_draft, ws, &wg);
+            HIPCHK(c, launch_prefill_prep(sb.st.tokens, sb.st.len, seq_of, pos0, sb.st.tok_cap, n_blocks, Q, tok_all, pos_all, st));
+            HIPCHK(c, launch_embed(G_ + c->gl.emb * c->es, tok_all, xall, (int)R, d, s.vocab, s.dtype, st));
+            HIPCHK(c, launch_rope_table(pos_all, cs_all, (int)R, hf, s.rope_theta, st));
             int cur_layer = 0;
-            auto rows_of = [&](int ch, int n_ch) {     // n_ch consecutive chunks as one row set
-                RowSet r{xall + (size_t)ch * T * d, pos_all + (size_t)ch * T, cs_all + (size_t)ch * T * hf, n_ch * T, Q, B};
-                if (forced && !is_draft) r.forced = forced + ((int64_t)cur_layer * forced_rows + (int64_t)ch * T) * 2;
+            auto group_rows = [&](int g) {
+                const int b0 = g * Gb, nb = std::min(Gb, n_blocks - b0);
+                RowSet r{xall + (size_t)b0 * Q * d, pos_all + (size_t)b0 * Q, cs_all + (size_t)b0 * Q * hf, nb * Q, Q, nb};
+                if (forced && !is_draft) r.forced = forced + ((int64_t)cur_layer * forced_rows + (int64_t)b0 * Q) * 2;
                 return r;
             };
-            auto attn_of_group = [&](int g, const char* Wb, void* kvl) -> int {
-                for (int ch = g * G; ch < std::min(n_chunks, (g + 1) * G); ++ch) {
-                    bool pending = false;
-                    RowSet ra = rows_of(ch, 1);
-                    ra.T = n_act[ch] * Q; ra.B = n_act[ch];          // the sequences that still have prompt positions
-                    if (ra.T == 0) continue;
-                    int r2 = layer_attn(c, s, L, Wb, w, ra, kvl, geom, pt_v, &pending, st);
-                    if (r2) return r2;
-                }
-                return SPEC_OK;
-            };
-            auto group_rows = [&](int g) { return rows_of(g * G, std::min(G, n_chunks - g * G)); };
+            auto pages = [&](int g) { return pt_v + (size_t)g * Gb * pps; };
             const int ne = std::max(1, s.n_experts);
+            bool pending = false;         // (one group: the experts' outputs are mixed in by the next layer's first norm)
             for (int l = 0; l < s.n_layers; ++l) {
                 const char* Wb;
                 int r2;
                 cur_layer = l;
                 void* kvl = kv_layer_ptr(is_draft ? sb.kv_d : sb.kv_t, geom, l, c->es);
+                // a prefill leaves nothing but keys and values: behind the last layer's, nothing is read again
+                const bool last = l == s.n_layers - 1;
                 if (is_draft || layer_is_whole(c, l)) {
                     if (is_draft) Wb = (const char*)c->d_draft_layers[l];
                     else if ((r2 = acquire_piece(c, l, 0, &Wb))) return r2;
                     for (int g = 0; g < n_grp; ++g) {
-                        if ((r2 = attn_of_group(g, Wb, kvl))) return r2;
-                        if (!ffn) continue;
                         const RowSet rg = group_rows(g);
-                        if ((r2 = layer_route(c, s, L, Wb, wg[0], rg, st))) return r2;
-                        if ((r2 = layer_experts(c, s, L, Wb + L.w1 * c->es, 0, ne, wg[0], rg, st))) return r2;
-                        if (moe && (r2 = layer_combine(c, s, wg[0], rg, st))) return r2;
+                        if (last) r2 = layer_qkv(c, s, L, Wb, wg[0], rg, kvl, geom, pages(g), &pending, st);
+                        else if (ffn) r2 = layer_body(c, s, L, Wb, wg[0], rg, kvl, geom, pages(g), &pending, n_grp == 1, st);
+                        else r2 = layer_attn(c, s, L, Wb, wg[0], rg, kvl, geom, pages(g), &pending, st);
+                        if (r2) return r2;
                     }
                     if (!is_draft && (r2 = release_piece(c, l, 0))) return r2;
                     continue;
@@ -1205,27 +1236,30 @@ int spec_prefill(spec_ctx* c, int sub, const int32_t* tokens, const int32_t* cu_
                 // through expert 0, expert 1, ...; the arithmetic of a row is that of the whole-layer order
                 if ((r2 = acquire_piece(c, l, 0, &Wb))) return r2;
                 for (int g = 0; g < n_grp; ++g) {
-                    if ((r2 = attn_of_group(g, Wb, kvl))) return r2;
-                    if ((r2 = layer_route(c, s, L, Wb, wg[g], group_rows(g), st))) return r2;
+                    if (last) r2 = layer_qkv(c, s, L, Wb, wg[g], group_rows(g), kvl, geom, pages(g), &pending, st);
+                    else r2 = layer_front(c, s, L, Wb, wg[g], group_rows(g), kvl, geom, pages(g), &pending, st);
+                    if (r2) return r2;
                 }
                 if ((r2 = release_piece(c, l, 0))) return r2;
                 for (int e = 0; e < ne; ++e) {
                     if ((r2 = acquire_piece(c, l, 1 + e, &Wb))) return r2;
-                    for (int g = 0; g < n_grp; ++g)
+                    for (int g = 0; g < n_grp && !last; ++g)
                         if ((r2 = layer_experts(c, s, L, Wb, e, 1, wg[g], group_rows(g), st))) return r2;
                     if ((r2 = release_piece(c, l, 1 + e))) return r2;
                 }
-                if (moe)
-                    for (int g = 0; g < n_grp; ++g)
-                        if ((r2 = layer_combine(c, s, wg[g], group_rows(g), st))) return r2;
+                if (!moe || last) continue;
+                if (n_grp == 1) { pending = true; continue; }
+                for (int g = 0; g < n_grp; ++g)
+                    if ((r2 = layer_combine(c, s, wg[g], group_rows(g), st))) return r2;
             }
             return SPEC_OK;
         };
-        rc = run_model(false);
+        hipError_t es_ = hipMemcpyAsync(tab_dev, tab.data(), tab.size() * 4, hipMemcpyHostToDevice, st);
+        rc = es_ == hipSuccess ? run_model(false) : fail(c, SPEC_ERR_HIP, "prefill failed: %s", hipGetErrorString(es_));
         if (rc && !c->items.empty() && c->uses_done % (int64_t)c->items.size() != 0) c->broken = true;   // stopped mid-pass
         if (!rc && c->has_draft) rc = run_model(true);
-        hipError_t es_ = hipStreamSynchronize(st);
-        cleanup();
+        es_ = hipStreamSynchronize(st);
+        if (temp) hipFree(temp);
         if (rc) return rc;
         if (es_ != hipSuccess) return fail(c, SPEC_ERR_HIP, "prefill failed: %s", hipGetErrorString(es_));
     }

@@ -334,3 +334,34 @@ def test_step_with_no_candidates_is_plain_decoding():
     same = sum(got[b] == list(out_o[b]) for b in range(6))
     print(f"plain decoding through spec_step(k=0): {same}/6 sequences equal to the oracle's")
     assert same >= 4
+
+
+@pytest.mark.parametrize("dtype,draft_attn_only", [("bf16", True), ("bf16", False), ("f32", False)])
+def test_prefill_groups_and_repeated_prefills_change_no_bit(dtype, draft_attn_only):
+    """The prefill runs on groups of row blocks (one group, one per block, and a ragged last one) and keeps its
+    workspace between calls: the first verify pass after it gives the same logits whatever the grouping and
+    whatever was prefilled before."""
+    import torch
+    import paper_2505_10259_amd as P
+    from gpu_common import host_model_pinned
+    shp = synth.mini_moe_shape(dtype=dtype, n_layers=3, head_dim=128 if dtype == "bf16" else 64)
+    hm = host_model_pinned(shp, seed=21, std=0.05)
+    dm = hm.draft_view(2, draft_attn_only)
+    a = synth.make_prompts(5, (1, 150), shp.vocab, seed=1)
+    b = synth.make_prompts(2, (3, 40), shp.vocab, seed=2)
+    k, new = 2, 4
+
+    def logits(sess, prompts):
+        P.spec_prefill(sess.ctx, 0, prompts, new)
+        P.spec_step(sess.ctx, k)
+        out = torch.empty(len(prompts), k + 1, shp.vocab, device="cuda")
+        P.spec_debug_logits(sess.ctx, 0, out)
+        return out
+
+    ref = {}
+    for group_rows in (0, 1, 320):
+        with P.Session(hm, dm, batch_max=5, k_max=k, ctx_max=160, prefill_group_rows=group_rows) as s:
+            got = [logits(s, p) for p in (a, b, a, b)]
+        for i, g in enumerate(got):
+            assert torch.isfinite(g).all()
+            assert torch.equal(g, ref.setdefault(i & 1, g)), (group_rows, i)
