@@ -610,9 +610,12 @@ gemm_bf16_mfma_kernel(GemmArgs a, int max_rows, int tiles_n, int halves) {
         // a tile of accumulator height MI (32-row units) costs about 4 MI + 5 (measured on the MoE gate/up
         // product: tiles of 7 units take 1.134 times as long as tiles of 6; the constant is the part of a
         // slab that does not grow with the height); the last row tile of a group may be lower than the rest
+        // Where one row tile reads the weights (NT) the stream of the weights bounds a tile and its height hardly counts
+        // (gate/up product, experts of 64 to 92 rows: 358 us with the first rule, 327 with this one).
         if (g_nt > 0) {
             const int last_rows = (g_b1 - g_b0) - (g_nt - 1) * g_rt;
-            g_cost = (g_nt - 1) * (4 * ((g_rt + 31) >> 5) + 5) + 4 * ((last_rows + 31) >> 5) + 5;
+            constexpr int PER_UNIT = NT ? 1 : 4, PER_TILE = NT ? 8 : 5;
+            g_cost = (g_nt - 1) * (PER_UNIT * ((g_rt + 31) >> 5) + PER_TILE) + PER_UNIT * ((last_rows + 31) >> 5) + PER_TILE;
         }
         const int mine_w = tiles_n * g_cost;
         for (int g = 0; g < ng; ++g) {
