@@ -142,9 +142,6 @@ struct AttnArgs {
 hipError_t launch_attention_simple(const AttnArgs& a, int dtype, hipStream_t st);
 hipError_t launch_attention_mfma_bf16(const AttnArgs& a, hipStream_t st);   // attn_mfma.hip
 
-hipError_t launch_embed(const void* emb, const int32_t* tok, float* x, int T, int d, int vocab,
-                        int dtype, hipStream_t st);
-hipError_t launch_cast_to_f32(const void* in, float* out, int64_t n, int dtype, hipStream_t st);
 hipError_t launch_fill_words(void* p, size_t n_words, uint32_t value, hipStream_t st);
 // x[t] += w[t,0]*y[slot[t,0]] + w[t,1]*y[slot[t,1]]  (if y), then h[t] = rmsnorm(x[t]) * g (if g)
 hipError_t launch_combine_norm(float* x, const float* y, const float* wts, const int32_t* slots,
@@ -156,8 +153,6 @@ bool norm_route_supported(int d, int E);
 // `row_pos` (nullable): rows with a negative position are inactive and get no experts (ids -1, weights 0)
 hipError_t launch_norm_route(const float* x, const void* g, void* h, const void* wr, int32_t* ids, float* wts,
                              int T, int d, int E, float eps, const int32_t* forced, const int32_t* row_pos, int dtype,
-                             hipStream_t st);
-hipError_t launch_rope_table(const int32_t* row_pos, float2* cs, int T, int half, float theta,
                              hipStream_t st);
 hipError_t launch_rope_kv(const float* qkv, const float2* cs, const int32_t* row_pos,
                           const int32_t* page_table, void* q_out, void* kv_layer, KvGeom geom,
@@ -183,13 +178,47 @@ struct SeqState {
     int32_t* max_new;    // [B]
     int tok_cap;
 };
-hipError_t launch_verify_prep(SeqState s, const int32_t* draft_tokens, int k, int32_t* tok_in,
-                              int32_t* row_pos, int B, hipStream_t st);
-hipError_t launch_draft_prep(SeqState s, const int32_t* draft_tokens, int k, int step,
-                             int32_t* tok_in, int32_t* row_pos, int B, hipStream_t st);
-// blocks of Q rows: positions pos0[v] .. pos0[v]+Q-1 of sequence seq_of[v]
-hipError_t launch_prefill_prep(const int32_t* tokens_dev, const int32_t* plen, const int32_t* seq_of, const int32_t* pos0,
-                               int tok_cap, int n_blocks, int Q, int32_t* tok_in, int32_t* row_pos, hipStream_t st);
+// Token and position of every row of a pass
+struct RowSource {
+    SeqState s;
+    int kind;                                   // ROWS_*
+    int embed;                                  // 1: the rows are embeddings of the tokens, 0: given by the caller
+    const int32_t* draft_tokens; int k, step;   // candidates [B, k]; step of a draft pass (1-based)
+    const int32_t* seq_of; const int32_t* pos0; int Q;   // prefill: blocks of Q rows
+    enum { ROWS_VERIFY, ROWS_DRAFT, ROWS_PREFILL };
+    __device__ void row(int t, int& pos, int& tok) const {
+        if (kind == ROWS_VERIFY) {
+            // rows of sequence b: [last committed token, candidate 1..k] at positions len-1 .. len-1+k
+            // (Section 2.2: all candidates are scored by the target in one forward pass)
+            const int b = t / (k + 1), i = t % (k + 1), len = s.len[b];
+            pos = len - 1 + i;
+            tok = !embed ? 0 : i == 0 ? s.tokens[(int64_t)b * s.tok_cap + len - 1] : draft_tokens[b * k + i - 1];
+        } else if (kind == ROWS_DRAFT) {
+            // Step 1 feeds TWO rows per sequence, the tokens at positions len-2 and len-1: after a round in which every
+            // candidate was kept the draft cache lacks position len-2, otherwise that entry is recomputed to the
+            // same value, so the cache always covers [0, len-1) before candidate 1 is produced.  Step i >= 2
+            // feeds candidate i-1 at position len-2+i.
+            if (step == 1) {
+                const int b = t >> 1, len = s.len[b], at = len - 2 + (t & 1);
+                pos = at >= 0 ? at : -1;
+                tok = at >= 0 ? s.tokens[(int64_t)b * s.tok_cap + at] : 0;
+            } else {
+                pos = s.len[t] - 2 + step;
+                tok = draft_tokens[t * k + step - 2];
+            }
+        } else {
+            // block v carries positions pos0[v] .. pos0[v]+Q-1 of sequence seq_of[v]; only positions before the last
+            // prompt token are active (the last token is fed by the first verify pass)
+            const int v = t / Q, b = seq_of[v], at = pos0[v] + t % Q;
+            const bool on = at < s.len[b] - 1;
+            pos = on ? at : -1;
+            tok = on ? s.tokens[(int64_t)b * s.tok_cap + at] : 0;
+        }
+    }
+};
+// rows: the embedding table, or the caller's rows (model dtype); fills x [T, d], row_pos [T] and cs [T, half]
+hipError_t launch_rows_prep(const RowSource& src, const void* rows, float* x, int32_t* row_pos, float2* cs, int T, int d,
+                            int vocab, int half, float theta, int dtype, hipStream_t st);
 hipError_t launch_commit(SeqState s, const int32_t* draft_tokens, int k, const int32_t* n_acc,
                          const int32_t* next_tok, int64_t* hist, int64_t* committed, int B,
                          hipStream_t st);

@@ -86,7 +86,7 @@ inline size_t esize(int dtype) { return dtype == SPEC_BF16 ? 2 : 4; }
 struct Workspace {
     int t_max = 0;
     float* x = nullptr; void* h = nullptr; float* qkv = nullptr; void* q = nullptr; void* att = nullptr;
-    float2* cs = nullptr; int32_t* tok_in = nullptr; int32_t* row_pos = nullptr;
+    float2* cs = nullptr; int32_t* row_pos = nullptr;
     int32_t* r_ids = nullptr; float* r_wts = nullptr; int32_t* offsets = nullptr; int32_t* perm = nullptr;
     int32_t* slots = nullptr; void* u = nullptr; float* y = nullptr;
 };
@@ -224,7 +224,6 @@ int alloc_workspace(spec_ctx* c, Workspace& w, const spec_model_shape& s, int t_
     if ((rc = dev_alloc(c, (char**)&w.q, t_max * hd * es))) return rc;
     if ((rc = dev_alloc(c, (char**)&w.att, t_max * hd * es))) return rc;
     if ((rc = dev_alloc(c, &w.cs, (size_t)t_max * (s.head_dim / 2) * sizeof(float2)))) return rc;
-    if ((rc = dev_alloc(c, &w.tok_in, (size_t)t_max * 4))) return rc;
     if ((rc = dev_alloc(c, &w.row_pos, (size_t)t_max * 4))) return rc;
     if (!s.attn_only) {
         int mult = s.n_experts > 0 ? 2 : 1;
@@ -1124,7 +1123,7 @@ int spec_prefill(spec_ctx* c, int sub, const int32_t* tokens, const int32_t* cu_
         size_t off = 0;
         auto take = [&](size_t bytes) { size_t o = off; off += al(bytes); return o; };
         const int d = c->tgt.d_model;
-        const size_t o_x = take((size_t)R * d * 4), o_pos = take((size_t)R * 4), o_tok = take((size_t)R * 4);
+        const size_t o_x = take((size_t)R * d * 4), o_pos = take((size_t)R * 4);
         const size_t o_cs = take((size_t)R * (c->tgt.head_dim / 2) * sizeof(float2)), o_tab = take(tab.size() * 4);
         const size_t common = off;
         auto piecewise_of = [&](bool is_draft) {
@@ -1187,7 +1186,7 @@ int spec_prefill(spec_ctx* c, int sub, const int32_t* tokens, const int32_t* cu_
             ws = (char*)c->prefill_ws;
         }
         float* xall = (float*)(ws + o_x);
-        int32_t *pos_all = (int32_t*)(ws + o_pos), *tok_all = (int32_t*)(ws + o_tok), *tab_dev = (int32_t*)(ws + o_tab);
+        int32_t *pos_all = (int32_t*)(ws + o_pos), *tab_dev = (int32_t*)(ws + o_tab);
         float2* cs_all = (float2*)(ws + o_cs);
         const int32_t *seq_of = tab_dev, *pos0 = tab_dev + n_blocks, *pt_v = tab_dev + 2 * n_blocks;
         auto run_model = [&](bool is_draft) -> int {
@@ -1199,9 +1198,9 @@ int spec_prefill(spec_ctx* c, int sub, const int32_t* tokens, const int32_t* cu_
             const bool ffn = !s.attn_only, moe = s.n_experts > 0;
             std::vector<Workspace> wg;
             carve(is_draft, ws, &wg);
-            HIPCHK(c, launch_prefill_prep(sb.st.tokens, sb.st.len, seq_of, pos0, sb.st.tok_cap, n_blocks, Q, tok_all, pos_all, st));
-            HIPCHK(c, launch_embed(G_ + c->gl.emb * c->es, tok_all, xall, (int)R, d, s.vocab, s.dtype, st));
-            HIPCHK(c, launch_rope_table(pos_all, cs_all, (int)R, hf, s.rope_theta, st));
+            RowSource src{};
+            src.s = sb.st; src.kind = RowSource::ROWS_PREFILL; src.embed = 1; src.seq_of = seq_of; src.pos0 = pos0; src.Q = Q;
+            HIPCHK(c, launch_rows_prep(src, G_ + c->gl.emb * c->es, xall, pos_all, cs_all, (int)R, d, s.vocab, hf, s.rope_theta, s.dtype, st));
             int cur_layer = 0;
             auto group_rows = [&](int g) {
                 const int b0 = g * Gb, nb = std::min(Gb, n_blocks - b0);
@@ -1315,9 +1314,9 @@ int spec_draft(spec_ctx* c, int sub, int k, int32_t* out_tokens) {
     c->prof_mask &= (1u << SPEC_PROF_DRAFT);
     for (int step = 1; step <= k; ++step) {
         int n_new = step == 1 ? 2 : 1, T = B * n_new;
-        HIPCHK(c, launch_draft_prep(sb.st, sb.draft_tokens, k, step, w.tok_in, w.row_pos, B, st));
-        HIPCHK(c, launch_embed(G + c->gl.emb * c->es, w.tok_in, w.x, T, d, V, s.dtype, st));
-        HIPCHK(c, launch_rope_table(w.row_pos, w.cs, T, half, s.rope_theta, st));
+        RowSource src{};
+        src.s = sb.st; src.kind = RowSource::ROWS_DRAFT; src.embed = 1; src.draft_tokens = sb.draft_tokens; src.k = k; src.step = step;
+        HIPCHK(c, launch_rows_prep(src, G + c->gl.emb * c->es, w.x, w.row_pos, w.cs, T, d, V, half, s.rope_theta, s.dtype, st));
         if ((rc = draft_layers(c, sb, w, T, n_new, true, st))) return rc;
         GemmArgs g{};
         g.A = (const char*)w.h + (size_t)(n_new - 1) * d * c->es; g.lda = (int64_t)n_new * d;
@@ -1356,9 +1355,9 @@ int spec_verify(spec_ctx* c, int sub, const int32_t* draft_tokens, int k, int32_
     const spec_model_shape& s = c->tgt;
     const char* G = (const char*)c->d_globals;
     const int B = sb.B, d = s.d_model, V = s.vocab, T = B * (k + 1);
-    HIPCHK(c, launch_verify_prep(sb.st, sb.draft_tokens, k, w.tok_in, w.row_pos, B, st));
-    HIPCHK(c, launch_embed(G + c->gl.emb * c->es, w.tok_in, w.x, T, d, V, s.dtype, st));
-    HIPCHK(c, launch_rope_table(w.row_pos, w.cs, T, s.head_dim / 2, s.rope_theta, st));
+    RowSource src{};
+    src.s = sb.st; src.kind = RowSource::ROWS_VERIFY; src.embed = 1; src.draft_tokens = sb.draft_tokens; src.k = k;
+    HIPCHK(c, launch_rows_prep(src, G + c->gl.emb * c->es, w.x, w.row_pos, w.cs, T, d, V, s.head_dim / 2, s.rope_theta, s.dtype, st));
     if ((rc = target_layers(c, sb, w, T, k + 1, true))) {
         if (!c->items.empty() && c->uses_done % (int64_t)c->items.size() != 0) c->broken = true;   // stopped mid-pass
         return rc;
@@ -1536,9 +1535,9 @@ static int layer_forward_impl(spec_ctx* c, int sub, int layer, const void* x_in,
     const spec_model_shape& s = c->tgt;
     hipStream_t st = c->s_compute;
     const int T = sb.B * n_new;
-    HIPCHK(c, launch_verify_prep(sb.st, sb.draft_tokens, n_new - 1, w.tok_in, w.row_pos, sb.B, st));
-    HIPCHK(c, launch_cast_to_f32(x_in, x_out, (int64_t)T * s.d_model, s.dtype, st));
-    HIPCHK(c, launch_rope_table(w.row_pos, w.cs, T, s.head_dim / 2, s.rope_theta, st));
+    RowSource src{};
+    src.s = sb.st; src.kind = RowSource::ROWS_VERIFY; src.k = n_new - 1;
+    HIPCHK(c, launch_rows_prep(src, x_in, x_out, w.row_pos, w.cs, T, s.d_model, s.vocab, s.head_dim / 2, s.rope_theta, s.dtype, st));
     RowSet r{x_out, w.row_pos, w.cs, T, n_new, sb.B};
     if (sb.forced_ids) {
         if (sb.forced_rows < T) return fail(c, SPEC_ERR_ARG, "forced routing covers %d rows per layer, the pass has %d", sb.forced_rows, T);
@@ -1591,7 +1590,6 @@ int spec_layer_forward_static(spec_ctx* c, int sub, int layer, const void* x_in,
     w.q = take(T * hd * es);
     w.att = take(T * hd * es);
     w.cs = (float2*)take(T * (s.head_dim / 2) * sizeof(float2));
-    w.tok_in = (int32_t*)take(T * 4);
     w.row_pos = (int32_t*)take(T * 4);
     const size_t mult = s.n_experts > 0 ? 2 : 1;
     w.u = take(mult * T * s.d_ff * es);

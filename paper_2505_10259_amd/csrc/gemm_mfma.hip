@@ -723,6 +723,8 @@ hipError_t launch_cfg(const GemmArgs& a, int max_rows, hipStream_t st) {
     constexpr int N_OUT = EPI == EPI_SWIGLU_T ? 16 * NI : 32 * NI;
     constexpr int SMEM = gemm_lds_bytes<NI>();
     static_assert(SMEM <= 160 * 1024, "LDS of a compute unit");
+    // column halves run tiles of half the width, with more stages, in the same launch
+    static_assert(NI < 8 || SMEM >= gemm_lds_bytes<(NI > 1 ? NI / 2 : 1)>(), "LDS of a column half");
     static bool attr_set = false;
     auto kern = gemm_bf16_mfma_kernel<NI, EPI, NT>;
     if (!attr_set) {

@@ -16,28 +16,6 @@ typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
         else { using T = bf16; __VA_ARGS__; }                          \
     } while (0)
 
-// ---------------------------------------------------------------------------------------------
-// embedding gather: x[t,:] = Emb[tok[t],:]
-// ---------------------------------------------------------------------------------------------
-template <typename T>
-__global__ void embed_kernel(const T* __restrict__ emb, const int32_t* __restrict__ tok,
-                             float* __restrict__ x, int d, int vocab) {
-    int t = blockIdx.x;
-    int id = tok[t];
-    id = id < 0 ? 0 : (id >= vocab ? vocab - 1 : id);
-    const T* src = emb + (int64_t)id * d;
-    float* dst = x + (int64_t)t * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) dst[c] = to_f32<T>(src[c]);
-}
-
-hipError_t launch_embed(const void* emb, const int32_t* tok, float* x, int T_, int d, int vocab,
-                        int dtype, hipStream_t st) {
-    if (T_ <= 0) return hipSuccess;
-    DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(embed_kernel<T>, dim3(T_), dim3(256), 0, st,
-                                             (const T*)emb, tok, x, d, vocab));
-    return hipGetLastError();
-}
-
 // fill n 32-bit words with one value (grid-stride; used to clear or poison buffers on a stream without
 // a memset node, which must stay out of captured graphs)
 __global__ void fill_words_kernel(uint32_t* __restrict__ p, size_t n, uint32_t v) {
@@ -50,28 +28,48 @@ hipError_t launch_fill_words(void* p, size_t n_words, uint32_t v, hipStream_t st
     return hipGetLastError();
 }
 
-// 8 elements per thread (one 16-byte load of bf16 / two of f32, two 16-byte stores); the tail and
-// unaligned buffers go element by element
+// ---------------------------------------------------------------------------------------------
+// The rows of a pass in one kernel, a workgroup per row: which token at which position (RowSource), its residual
+// stream x[t] = Emb[token] (or the caller's row t), and its rotary table cs[t] (positions are the same for every
+// layer of a pass), computed in double so that large positions lose nothing.  As three launches
+// (tokens and positions, gather, table) this was 13 to 20 us of every pass and draft step, all of it launch and
+// latency; 32768 rows of 4096 were gathered by 2-byte loads at 3.4 TB/s.
+// ---------------------------------------------------------------------------------------------
 template <typename T>
-__global__ void cast_kernel(const T* __restrict__ in, float* __restrict__ out, int64_t n, int vec) {
-    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 8;
-    if (i >= n) return;
-    if (vec && i + 8 <= n) {
-        T v[8];
-        if (sizeof(T) == 2) *(uint4*)v = *(const uint4*)(in + i);
-        else { *(uint4*)v = *(const uint4*)(in + i); *(uint4*)(v + 4) = *(const uint4*)(in + i + 4); }
-        *(float4*)(out + i) = make_float4(to_f32<T>(v[0]), to_f32<T>(v[1]), to_f32<T>(v[2]), to_f32<T>(v[3]));
-        *(float4*)(out + i + 4) = make_float4(to_f32<T>(v[4]), to_f32<T>(v[5]), to_f32<T>(v[6]), to_f32<T>(v[7]));
+__global__ void __launch_bounds__(256)
+rows_prep_kernel(RowSource src, const T* __restrict__ rows, float* __restrict__ x, int32_t* __restrict__ row_pos,
+                 float2* __restrict__ cs, int d, int vocab, int half, double theta, int vec) {
+    const int t = blockIdx.x, tid = threadIdx.x;
+    int pos, tok;
+    src.row(t, pos, tok);
+    if (tid == 0) row_pos[t] = pos;
+    const T* from = rows + (int64_t)(src.embed ? (tok < 0 ? 0 : (tok >= vocab ? vocab - 1 : tok)) : t) * d;
+    float* to = x + (int64_t)t * d;
+    if (vec) {
+        for (int c = tid * 8; c < d; c += 256 * 8) {
+            alignas(16) T v[8];
+            *(uint4*)v = *(const uint4*)(from + c);
+            if constexpr (sizeof(T) == 4) *(uint4*)(v + 4) = *(const uint4*)(from + c + 4);
+            *(float4*)(to + c) = make_float4(to_f32<T>(v[0]), to_f32<T>(v[1]), to_f32<T>(v[2]), to_f32<T>(v[3]));
+            *(float4*)(to + c + 4) = make_float4(to_f32<T>(v[4]), to_f32<T>(v[5]), to_f32<T>(v[6]), to_f32<T>(v[7]));
+        }
     } else {
-        for (int64_t j = i; j < n && j < i + 8; ++j) out[j] = to_f32<T>(in[j]);
+        for (int c = tid; c < d; c += 256) to[c] = to_f32<T>(from[c]);
+    }
+    for (int i = tid; i < half; i += 256) {
+        double inv = pow(theta, -(double)i / (double)half);      // theta^(-2i/dh)
+        double a = (double)pos * inv;
+        double s, c;
+        sincos(a, &s, &c);
+        cs[(int64_t)t * half + i] = make_float2((float)c, (float)s);
     }
 }
-hipError_t launch_cast_to_f32(const void* in, float* out, int64_t n, int dtype, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    const int vec = (((uintptr_t)in | (uintptr_t)out) & 15) == 0;
-    const int64_t threads = (n + 7) / 8;
-    DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(cast_kernel<T>, dim3((unsigned)((threads + 255) / 256)),
-                                             dim3(256), 0, st, (const T*)in, out, n, vec));
+hipError_t launch_rows_prep(const RowSource& src, const void* rows, float* x, int32_t* row_pos, float2* cs, int T_, int d,
+                            int vocab, int half, float theta, int dtype, hipStream_t st) {
+    if (T_ <= 0) return hipSuccess;
+    const int vec = d % 8 == 0 && (((uintptr_t)rows | (uintptr_t)x) & 15) == 0;
+    DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(rows_prep_kernel<T>, dim3(T_), dim3(256), 0, st, src, (const T*)rows, x, row_pos,
+                                             cs, d, vocab, half, (double)theta, vec));
     return hipGetLastError();
 }
 
@@ -188,30 +186,8 @@ hipError_t launch_combine_norm(float* x, const float* y, const float* wts, const
 }
 
 // ---------------------------------------------------------------------------------------------
-// RoPE: cos/sin table per row (positions are the same for every layer of a pass), computed in
-// double so that large positions lose nothing; then rotate q,k (pair (i, i+dh/2)) and append
-// k,v to the sequence's KV pages.
+// RoPE: rotate q,k (pair (i, i+dh/2)) with the rows' table and append k,v to the sequence's KV pages.
 // ---------------------------------------------------------------------------------------------
-__global__ void rope_table_kernel(const int32_t* __restrict__ row_pos, float2* __restrict__ cs,
-                                  int T_, int half, double theta) {
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= T_ * half) return;
-    int t = idx / half, i = idx % half;
-    double inv = pow(theta, -(double)i / (double)half);      // theta^(-2i/dh)
-    double a = (double)row_pos[t] * inv;
-    double s, c;
-    sincos(a, &s, &c);
-    cs[idx] = make_float2((float)c, (float)s);
-}
-hipError_t launch_rope_table(const int32_t* row_pos, float2* cs, int T_, int half, float theta,
-                             hipStream_t st) {
-    int n = T_ * half;
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, row_pos, cs, T_, half,
-                       (double)theta);
-    return hipGetLastError();
-}
-
 template <typename T>
 __global__ void rope_kv_kernel(const float* __restrict__ qkv, const float2* __restrict__ cs,
                                const int32_t* __restrict__ row_pos,
@@ -359,16 +335,21 @@ hipError_t launch_kv_import(const void* k_ctx, const void* v_ctx, void* kv_layer
 // all: ids -1 and weights 0, so that the sort leaves it out of every expert's rows.
 __device__ inline void pick_top2(const float* lg, int E, const int32_t* forced, bool active, int32_t* ids, float* wts) {
     if (!active) { ids[0] = -1; ids[1] = -1; wts[0] = 0.f; wts[1] = 0.f; return; }
-    int i0 = 0;
-    for (int e = 1; e < E; ++e) if (lg[e] > lg[i0]) i0 = e;
-    int i1 = i0 == 0 ? 1 : 0;
-    for (int e = 0; e < E; ++e) if (e != i0 && lg[e] > lg[i1]) i1 = e;
+    // (every index a compile-time constant: a lookup lg[i0] would put the logits into scratch memory)
+    int i0 = 0, i1 = -1;
+    float l0 = lg[0], l1 = 0.f;
+#pragma unroll
+    for (int e = 1; e < 8; ++e) if (e < E && lg[e] > l0) { i0 = e; l0 = lg[e]; }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) if (e < E && e != i0 && (i1 < 0 || lg[e] > l1)) { i1 = e; l1 = lg[e]; }
     if (forced) {
         const int f0 = forced[0], f1 = forced[1];
-        if (f0 >= 0 && f0 < E && f1 >= 0 && f1 < E && f0 != f1) { i0 = f0; i1 = f1; }
+        if (f0 >= 0 && f0 < E && f1 >= 0 && f1 < E && f0 != f1) {
+            i0 = f0; i1 = f1;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { if (e == i0) l0 = lg[e]; if (e == i1) l1 = lg[e]; }
+        }
     }
-    float l0 = lg[0], l1 = lg[0];
-    for (int e = 0; e < E; ++e) { if (e == i0) l0 = lg[e]; if (e == i1) l1 = lg[e]; }
     const float w0 = 1.0f / (1.0f + expf(l1 - l0));
     ids[0] = i0; ids[1] = i1;
     wts[0] = w0; wts[1] = 1.0f - w0;
@@ -507,52 +488,67 @@ hipError_t launch_norm_route(const float* x, const void* g, void* h, const void*
 
 // Stable counting sort of the 2T (token, choice) pairs by expert id, one 1024-thread workgroup.  Pairs
 // of rows without experts (id < 0: inactive rows) are left out: offsets[E] is the number of routed pairs.
+// Every wavefront takes a contiguous range of the pairs, 64 at a time: a ballot per expert counts them, and in a second
+// pass ranks them (lane order is pair order, so the sort is stable).  A scan of per-thread counts over LDS took
+// 7.4 us for 640 pairs and 75 us for 65536 (a thread's pairs were neighbours in memory).
 __global__ void __launch_bounds__(1024)
 moe_sort_kernel(const int32_t* __restrict__ ids, int32_t* __restrict__ offsets,
                 int32_t* __restrict__ perm, int32_t* __restrict__ slots, int n_pairs, int E) {
-    __shared__ int cnt[8][1024];
-    __shared__ int base[9];
-    int tid = threadIdx.x;
-    int chunk = (n_pairs + 1023) / 1024;
-    int p0 = tid * chunk, p1 = min(p0 + chunk, n_pairs);
-    int local[8];
+    __shared__ int cnt[16][8];          // pairs of expert e in wavefront w's range, then its first row
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int seg = ((n_pairs + 1023) / 1024) * 64, p0 = w * seg, p1 = min(p0 + seg, n_pairs);
+    int run[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) local[e] = 0;
-    for (int p = p0; p < p1; ++p) {
-        int e = ids[p];
+    for (int q = 0; q < 8; ++q) run[q] = 0;
+#pragma unroll 4
+    for (int p = p0; p < p1; p += 64) {
+        const int e = p + lane < p1 ? ids[p + lane] : -1;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) local[q] += (q == e);
+        for (int q = 0; q < 8; ++q) run[q] += __popcll(__ballot(e == q));
     }
+    if (lane == 0) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) cnt[e][tid] = local[e];
-    __syncthreads();
-    // inclusive Hillis-Steele scan of each expert's per-thread counts
-    for (int off = 1; off < 1024; off <<= 1) {
-        int v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = tid >= off ? cnt[e][tid - off] : 0;
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < 8; ++e) cnt[e][tid] += v[e];
-        __syncthreads();
-    }
-    if (tid == 0) {
-        int run = 0;
-        for (int e = 0; e < E; ++e) { base[e] = run; offsets[e] = run; run += cnt[e][1023]; }
-        base[E] = run; offsets[E] = run;
+        for (int q = 0; q < 8; ++q) cnt[w][q] = run[q];
     }
     __syncthreads();
-    int start[8];
+    if (w == 0) {                       // lane q (and its copies): exclusive sums over the experts, then over the wavefronts
+        const int q = lane & 7;
+        int c[16], total = 0;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) start[e] = (e < E ? base[e] : 0) + cnt[e][tid] - local[e];
-    for (int p = p0; p < p1; ++p) {
-        int e = ids[p];
-        if (e < 0) { slots[p] = 0; continue; }
+        for (int v = 0; v < 16; ++v) { c[v] = cnt[v][q]; total += c[v]; }
+        int incl = total;
+#pragma unroll
+        for (int o = 1; o < 8; o <<= 1) {
+            const int up = __shfl_up(incl, o, 8);
+            if (q >= o) incl += up;
+        }
+        int base = incl - total;
+        if (lane < 8) {
+            if (q < E) offsets[q] = base;
+            if (q == E - 1) offsets[E] = incl;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { cnt[v][q] = base; base += c[v]; }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) run[q] = cnt[w][q];
+    const unsigned long long before = (1ull << lane) - 1;
+#pragma unroll 2
+    for (int p = p0; p < p1; p += 64) {
+        const bool in = p + lane < p1;
+        const int e = in ? ids[p + lane] : -1;
         int row = 0;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) if (q == e) { row = start[q]; start[q] += 1; }
-        perm[row] = p >> 1;
-        slots[p] = row;
+        for (int q = 0; q < 8; ++q) {
+            const unsigned long long m = __ballot(e == q);
+            if (e == q) row = run[q] + __popcll(m & before);
+            run[q] += __popcll(m);
+        }
+        if (in) {
+            if (e >= 0) perm[row] = (p + lane) >> 1;
+            slots[p + lane] = row;
+        }
     }
 }
 hipError_t launch_moe_sort(const int32_t* ids, int32_t* offsets, int32_t* perm, int32_t* slots, int T_,

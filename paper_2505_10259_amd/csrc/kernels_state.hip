@@ -1,78 +1,8 @@
-// Sequence-state kernels: they build the token / position rows of each pass from the committed
-// tokens kept in HBM and commit accepted tokens, so that the host never has to read results back
-// inside the draft/verify loop.
+// Sequence-state kernel: accepted tokens are committed to the sequences kept in HBM (the rows of each pass are built
+// from them in rows_prep_kernel), so that the host never has to read results back inside the draft/verify loop.
 #include "common.h"
 
 namespace sv {
-
-// Verify rows of sequence b: [last committed token, candidate 1..k] at positions len-1 .. len-1+k
-// (Section 2.2: all candidates are scored by the target in one forward pass).
-__global__ void verify_prep_kernel(SeqState s, const int32_t* __restrict__ d, int k,
-                                   int32_t* __restrict__ tok_in, int32_t* __restrict__ row_pos, int B) {
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= B * (k + 1)) return;
-    int b = idx / (k + 1), i = idx % (k + 1);
-    int len = s.len[b];
-    tok_in[idx] = i == 0 ? s.tokens[(int64_t)b * s.tok_cap + len - 1] : d[b * k + i - 1];
-    row_pos[idx] = len - 1 + i;
-}
-hipError_t launch_verify_prep(SeqState s, const int32_t* draft_tokens, int k, int32_t* tok_in,
-                              int32_t* row_pos, int B, hipStream_t st) {
-    int n = B * (k + 1);
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(verify_prep_kernel, dim3((n + 255) / 256), dim3(256), 0, st, s, draft_tokens, k,
-                       tok_in, row_pos, B);
-    return hipGetLastError();
-}
-
-// Draft rows.  Step 1 feeds TWO rows per sequence, the tokens at positions len-2 and len-1: after a
-// round in which every candidate was kept the draft cache lacks position len-2, otherwise that entry
-// is recomputed to the same value, so the cache always covers [0, len-1) before candidate 1 is
-// produced.  Step i >= 2 feeds candidate i-1 at position len-2+i.
-__global__ void draft_prep_kernel(SeqState s, const int32_t* __restrict__ d, int k, int step,
-                                  int32_t* __restrict__ tok_in, int32_t* __restrict__ row_pos, int B) {
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    int len = s.len[b];
-    const int32_t* toks = s.tokens + (int64_t)b * s.tok_cap;
-    if (step == 1) {
-        tok_in[2 * b] = len >= 2 ? toks[len - 2] : 0;
-        row_pos[2 * b] = len >= 2 ? len - 2 : -1;
-        tok_in[2 * b + 1] = toks[len - 1];
-        row_pos[2 * b + 1] = len - 1;
-    } else {
-        tok_in[b] = d[b * k + step - 2];
-        row_pos[b] = len - 2 + step;
-    }
-}
-hipError_t launch_draft_prep(SeqState s, const int32_t* draft_tokens, int k, int step, int32_t* tok_in,
-                             int32_t* row_pos, int B, hipStream_t st) {
-    if (B <= 0) return hipSuccess;
-    hipLaunchKernelGGL(draft_prep_kernel, dim3((B + 255) / 256), dim3(256), 0, st, s, draft_tokens, k, step,
-                       tok_in, row_pos, B);
-    return hipGetLastError();
-}
-
-// Prefill rows: block v carries positions pos0[v] .. pos0[v]+Q-1 of sequence seq_of[v]; only positions before
-// the last prompt token are active (the last token is fed by the first verify pass).
-__global__ void prefill_prep_kernel(const int32_t* __restrict__ tokens, const int32_t* __restrict__ plen,
-                                    const int32_t* __restrict__ seq_of, const int32_t* __restrict__ pos0, int tok_cap,
-                                    int n_rows, int Q, int32_t* __restrict__ tok_in, int32_t* __restrict__ row_pos) {
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n_rows) return;
-    int v = idx / Q, b = seq_of[v], pos = pos0[v] + idx % Q;
-    bool on = pos < plen[b] - 1;
-    tok_in[idx] = on ? tokens[(int64_t)b * tok_cap + pos] : 0;
-    row_pos[idx] = on ? pos : -1;
-}
-hipError_t launch_prefill_prep(const int32_t* tokens_dev, const int32_t* plen, const int32_t* seq_of, const int32_t* pos0,
-                               int tok_cap, int n_blocks, int Q, int32_t* tok_in, int32_t* row_pos, hipStream_t st) {
-    int n = n_blocks * Q;
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(prefill_prep_kernel, dim3((n + 255) / 256), dim3(256), 0, st, tokens_dev, plen, seq_of, pos0,
-                       tok_cap, n, Q, tok_in, row_pos);
-    return hipGetLastError();
-}
 
 // Commit: append candidates 1..n and the target's token, clipped to the sequence's remaining quota
 // (a round emits between 1 and k+1 tokens, Appendix A.1 "Generated Tokens").  The KV caches need no
