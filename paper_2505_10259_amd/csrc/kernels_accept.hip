@@ -53,15 +53,9 @@ hipError_t launch_philox_uniforms(uint64_t seed, uint32_t round, uint32_t seq_ba
     return hipGetLastError();
 }
 
-// exp(x) for x <= 0: 2^(x log2 e) with the product's rounding error carried as a first-order correction.  The
-// library's expf also covers overflow and subnormal results, which these weights do not need, in twice the
-// instructions (at most 2.0 x 2^-24 off over [-86, 0]; 256 sequences of 6 candidates, 32000 ids: 116 -> 104 us).
-__device__ inline float exp_neg(float x) {
-    const float t = x * 1.44269502f;                                       // log2 e = 1.44269502 + 1.92596299e-8
-    const float r = __builtin_fmaf(x, 1.92596299e-8f, __builtin_fmaf(x, 1.44269502f, -t));
-    const float e = __builtin_amdgcn_exp2f(t);
-    return t < -150.f ? 0.f : __builtin_fmaf(e, r * 0.693147182f, e);      // (x = -inf: r is not a number)
-}
+// Softmax weights use the library's expf throughout.  One exp2 instruction on the rounded product x log2 e (its rounding
+// error added to first order) was 10 % faster for 256 sequences of 6 candidates over 32000 ids, 105 against 117 us, but up to
+// 2.3 x 2^-24 off where expf is 1.4, and it loses weights below 2^-126.
 
 // =================================================================================================
 // General path: any vocabulary size and row alignment.  One workgroup of 1024 threads per sequence; a row is read in
@@ -69,8 +63,8 @@ __device__ inline float exp_neg(float x) {
 // The maximum and the normaliser of the two rows of a candidate come from one pass (running maximum per thread), the
 // draw takes one pass for the sums of runs of 64 U granules and reads again only the run that holds the
 // crossing.  What bounds it is the exponentials of one compute unit per sequence: 24 sequences of 5 candidates,
-// 65537 ids, 1255 us as 256 threads with 4-byte loads and a pass per reduction, 137 so, 80 with the candidates
-// tested at once (accept_test_generic_kernel 25, draw 53).
+// 65537 ids, 1255 us as 256 threads with 4-byte loads and a pass per reduction, 93 so with the candidates
+// tested at once.
 // =================================================================================================
 constexpr int WIDE_THREADS = 1024, WIDE_WAVES = WIDE_THREADS / 64, WIDE_RUNS = 1024;
 
@@ -105,11 +99,11 @@ struct MaxSum {
 #pragma unroll
         for (int q = 0; q < 4; ++q) mx = fmaxf(fmaxf(fmaxf(mx, v[q].x), fmaxf(v[q].y, v[q].z)), v[q].w);
         if (mx == -INFINITY) return;                       // nothing but padding or masked ids so far
-        if (mx > m) { s *= exp_neg((m - mx) * inv_tau); m = mx; }
+        if (mx > m) { s *= expf((m - mx) * inv_tau); m = mx; }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            s += (exp_neg((v[q].x - m) * inv_tau) + exp_neg((v[q].y - m) * inv_tau)) +
-                 (exp_neg((v[q].z - m) * inv_tau) + exp_neg((v[q].w - m) * inv_tau));
+            s += (expf((v[q].x - m) * inv_tau) + expf((v[q].y - m) * inv_tau)) +
+                 (expf((v[q].z - m) * inv_tau) + expf((v[q].w - m) * inv_tau));
     }
 };
 
@@ -148,7 +142,7 @@ __device__ inline void wide_row_stats(const WideRow& a, const WideRow& b, float 
         m = sh.red[slot][0];
 #pragma unroll
         for (int w = 1; w < WIDE_WAVES; ++w) m = fmaxf(m, sh.red[slot][w]);
-        float v = wave_sum(t.m == -INFINITY ? 0.f : t.s * exp_neg((t.m - m) * inv_tau));
+        float v = wave_sum(t.m == -INFINITY ? 0.f : t.s * expf((t.m - m) * inv_tau));
         __syncthreads();
         if (lane == 0) sh.red[slot][wv] = v;
         __syncthreads();
@@ -281,8 +275,8 @@ __device__ inline int wide_inverse_cdf(F weight, int n, int off, float u, WideSh
 // the softmax weights of granule g of a row (0 for -inf entries, i.e. outside the row)
 __device__ inline float4 wide_weights(const WideRow& r, int g, float m, float inv_tau, float inv_norm) {
     const float4 z = r.load(g);
-    return make_float4(exp_neg((z.x - m) * inv_tau) * inv_norm, exp_neg((z.y - m) * inv_tau) * inv_norm,
-                       exp_neg((z.z - m) * inv_tau) * inv_norm, exp_neg((z.w - m) * inv_tau) * inv_norm);
+    return make_float4(expf((z.x - m) * inv_tau) * inv_norm, expf((z.y - m) * inv_tau) * inv_norm,
+                       expf((z.z - m) * inv_tau) * inv_norm, expf((z.w - m) * inv_tau) * inv_norm);
 }
 
 // the acceptance test of candidate i of sequence b (the rows' maxima and normalisers given): true = rejected
@@ -350,7 +344,7 @@ accept_sample_generic_kernel(AcceptArgs a, int tested) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const bool in = id + j >= 0 && id + j < V;
-                z[j] = in ? exp_neg((qr.row[in ? id + j : 0] - qm) * it) * iqn : 0.f;
+                z[j] = in ? expf((qr.row[in ? id + j : 0] - qm) * it) * iqn : 0.f;
             }
             q = make_float4(z[0], z[1], z[2], z[3]);
         }
@@ -422,8 +416,8 @@ __device__ inline void fast_row_stats(const float4 (&v)[FAST_SWEEPS], float inv_
     float sum = 0.f;
 #pragma unroll
     for (int s = 0; s < FAST_SWEEPS; ++s)
-        sum += (exp_neg((v[s].x - m) * inv_tau) + exp_neg((v[s].y - m) * inv_tau)) +
-               (exp_neg((v[s].z - m) * inv_tau) + exp_neg((v[s].w - m) * inv_tau));
+        sum += (expf((v[s].x - m) * inv_tau) + expf((v[s].y - m) * inv_tau)) +
+               (expf((v[s].z - m) * inv_tau) + expf((v[s].w - m) * inv_tau));
     *out_max = m;
     *out_sum = fast_block_sum(sum, sh);
 }
@@ -511,8 +505,8 @@ __device__ inline int fast_inverse_cdf(const float4 (&wt)[FAST_SWEEPS], float u,
     return sh.pick != 0x7fffffff ? sh.pick : (sh.last >= 0 ? sh.last : 0);
 }
 __device__ inline float4 fast_softmax_weights(const float4& z, float m, float inv_tau, float inv_norm) {
-    return make_float4(exp_neg((z.x - m) * inv_tau) * inv_norm, exp_neg((z.y - m) * inv_tau) * inv_norm,
-                       exp_neg((z.z - m) * inv_tau) * inv_norm, exp_neg((z.w - m) * inv_tau) * inv_norm);
+    return make_float4(expf((z.x - m) * inv_tau) * inv_norm, expf((z.y - m) * inv_tau) * inv_norm,
+                       expf((z.z - m) * inv_tau) * inv_norm, expf((z.w - m) * inv_tau) * inv_norm);
 }
 
 __global__ void __launch_bounds__(FAST_THREADS)

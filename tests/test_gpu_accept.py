@@ -217,3 +217,36 @@ def test_accept_sample_masked_and_infinite_rows(V):
         assert t[0] % 7 == 3 and t[5] % 7 == 3 and t[1] == V // 2
         if n is not None:
             assert n.cpu().tolist()[:2] == [0, 0] and n[5].item() == 0
+
+
+# register-resident kernel (8) and general ones (5, 40001)
+@pytest.mark.parametrize("V,B", [(8, 16384), (5, 16384), (40001, 512)])
+def test_weights_have_the_error_of_the_library_exponential(V, B):
+    """A bonus row [x, 0, -inf, ...] draws id 0 exactly while u < exp(x): for x < -17.4 the normaliser and the total are 1
+    in f32, so bisecting u over the floats gives the kernel's exp(x) to the bit.  Bound: 1 ulp, the documented error of
+    expf (a rounded product x log2 e in front of exp2 alone is off by up to 2.3), subnormal results included."""
+    import torch
+    import paper_2505_10259_amd as P
+    inf = float("inf")
+    x = torch.linspace(-103.0, -17.5, B, dtype=torch.float64).float()
+    p = torch.full((B, 2, V), -inf, device="cuda")
+    p[:, 0, 1] = 0.0                             # the candidate, token 1, is certain on both sides: kept
+    q = p[:, :1].contiguous()
+    p[:, 1, 0], p[:, 1, 1] = x.cuda(), 0.0
+    d = torch.ones(B, 1, dtype=torch.int32, device="cuda")
+    ua = torch.full((B, 1), 0.5, device="cuda")
+    lo = torch.zeros(B, dtype=torch.int32, device="cuda")                     # bits of the largest u that draws id 0
+    hi = torch.full((B,), 0x34000000, dtype=torch.int32, device="cuda")       # (2^-23: id 1)
+    nx = torch.empty(B, dtype=torch.int32, device="cuda")
+    for _ in range(31):
+        mid = lo + (hi - lo) // 2
+        ur = mid.view(torch.float32).reshape(B, 1).repeat(1, 2).contiguous()
+        P.spec_accept(p, q, d, ua, ur, 1.0, 0, 0, 0, B, 1, V, None, nx)
+        torch.cuda.synchronize()
+        assert ((nx == 0) | (nx == 1)).all()
+        lo, hi = torch.where(nx == 0, mid, lo), torch.where(nx == 0, hi, mid)
+    got = hi.cpu().view(torch.float32).double()  # exp(x) is the first float that u does not stay below
+    ref = x.double().exp()
+    ulp = torch.exp2(ref.log2().floor().clamp(min=-126) - 23)
+    err = (got - ref).abs() / ulp
+    assert err.max().item() <= 1.0, (err.max().item(), x[err.argmax()].item())
