@@ -98,12 +98,13 @@ struct MaxSum {
         float mx = m;
 #pragma unroll
         for (int q = 0; q < 4; ++q) mx = fmaxf(fmaxf(fmaxf(mx, v[q].x), fmaxf(v[q].y, v[q].z)), v[q].w);
-        if (mx == -INFINITY) return;                       // nothing but padding or masked ids so far
         if (mx > m) { s *= expf((m - mx) * inv_tau); m = mx; }
+        // (nothing but -inf and not-a-numbers so far: the former add nothing, one of the latter makes the sum one)
+        const float at = m == -INFINITY ? 0.f : m;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            s += (expf((v[q].x - m) * inv_tau) + expf((v[q].y - m) * inv_tau)) +
-                 (expf((v[q].z - m) * inv_tau) + expf((v[q].w - m) * inv_tau));
+            s += (expf((v[q].x - at) * inv_tau) + expf((v[q].y - at) * inv_tau)) +
+                 (expf((v[q].z - at) * inv_tau) + expf((v[q].w - at) * inv_tau));
     }
 };
 
@@ -142,7 +143,7 @@ __device__ inline void wide_row_stats(const WideRow& a, const WideRow& b, float 
         m = sh.red[slot][0];
 #pragma unroll
         for (int w = 1; w < WIDE_WAVES; ++w) m = fmaxf(m, sh.red[slot][w]);
-        float v = wave_sum(t.m == -INFINITY ? 0.f : t.s * expf((t.m - m) * inv_tau));
+        float v = wave_sum(t.m == -INFINITY ? t.s : t.s * expf((t.m - m) * inv_tau));
         __syncthreads();
         if (lane == 0) sh.red[slot][wv] = v;
         __syncthreads();

@@ -250,3 +250,38 @@ def test_weights_have_the_error_of_the_library_exponential(V, B):
     ulp = torch.exp2(ref.log2().floor().clamp(min=-126) - 23)
     err = (got - ref).abs() / ulp
     assert err.max().item() <= 1.0, (err.max().item(), x[err.argmax()].item())
+
+
+# every value that one thread of the general kernel holds of the row is not a number: a granule of four where a
+# thread takes one (4001), ten granules 4096 ids apart (40001)
+@pytest.mark.parametrize("V", [1001, 4001, 40001, 4096])
+@pytest.mark.parametrize("side", ["p", "q"])
+def test_not_a_number_anywhere_in_a_row_rejects(V, side):
+    """A row with a not-a-number has no normaliser: whatever the candidate's own value, it is not kept."""
+    import torch
+    import paper_2505_10259_amd as P
+    B, k = 8, 1
+    g = torch.Generator("cuda").manual_seed(V)
+    p = torch.randn(B, k + 1, V, device="cuda", generator=g)
+    q = p[:, :k].clone().contiguous()
+    p[:, 0, 7], q[:, 0, 7] = 30.0, 30.0          # certain on both sides: kept but for the not-a-numbers
+    d = torch.full((B, k), 7, dtype=torch.int32, device="cuda")
+    ua = torch.full((B, k), 0.5, device="cuda")
+    ur = torch.full((B, k + 1), 0.5, device="cuda")
+
+    def kept():
+        n = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+        nx = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+        P.spec_accept(p, q, d, ua, ur, 0.8, 0, 0, 0, B, k, V, n, nx)
+        torch.cuda.synchronize()
+        assert all(0 <= t < V for t in nx.cpu().tolist())
+        return n.cpu().tolist()
+
+    assert kept() == [1] * B
+    t = p if side == "p" else q
+    for b in range(1, B):
+        row = t[b, 0]
+        off = (row.data_ptr() // 4) % 4          # granules lie at 16-byte boundaries
+        for first in range(64 - off, V - 3, 4096):
+            row[first:first + 4] = float("nan")
+    assert kept() == [1] + [0] * (B - 1)
