@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <deque>
+#include <limits>
 #include <string>
 #include <vector>
 
@@ -82,6 +83,8 @@ GlobalLayout make_global_layout(const spec_model_shape& s) {
     return G;
 }
 inline size_t esize(int dtype) { return dtype == SPEC_BF16 ? 2 : 4; }
+// never 0 (infinite temperature): masked ids and the kernels' padding are -inf, and -inf * 0 is not a number
+inline float inverse_temperature(float t) { return std::max(1.0f / t, std::numeric_limits<float>::denorm_min()); }
 
 struct Workspace {
     int t_max = 0;
@@ -1326,7 +1329,7 @@ int spec_draft(spec_ctx* c, int sub, int k, int32_t* out_tokens) {
         else { z = sb.draft_logits; ld = V; }
         g.C = z; g.ldc = ld;
         HIPCHK(c, gemm(c, g, s.dtype, st));
-        HIPCHK(c, launch_draft_pick(z, ld, V, B, c->cfg.mode, 1.0f / (sample ? c->cfg.temperature : 1.0f),
+        HIPCHK(c, launch_draft_pick(z, ld, V, B, c->cfg.mode, inverse_temperature(sample ? c->cfg.temperature : 1.0f),
                                     c->cfg.seed, sb.round, sb.seq_base, step, sb.draft_tokens, k, st));
     }
     if (out_tokens) HIPCHK(c, hipMemcpyAsync(out_tokens, sb.draft_tokens, (size_t)B * k * 4, hipMemcpyDeviceToDevice, st));
@@ -1368,7 +1371,7 @@ int spec_verify(spec_ctx* c, int sub, const int32_t* draft_tokens, int k, int32_
     { ProfScope ps(c, SPEC_PROF_HEAD, st); HIPCHK(c, gemm(c, g, s.dtype, st)); }
     AcceptArgs a{};
     a.p_logits = sb.logits; a.q_logits = sample ? sb.q_logits : nullptr; a.draft_tokens = sb.draft_tokens;
-    a.inv_tau = 1.0f / (sample ? c->cfg.temperature : 1.0f);
+    a.inv_tau = inverse_temperature(sample ? c->cfg.temperature : 1.0f);
     a.seed = c->cfg.seed; a.round = sb.round; a.seq_base = sb.seq_base;
     a.B = B; a.k = k; a.V = V; a.n_accepted = sb.n_acc; a.next_token = sb.next_tok;
     { ProfScope ps(c, SPEC_PROF_ACCEPT, st); HIPCHK(c, launch_accept(a, st)); }
@@ -1623,7 +1626,7 @@ int spec_accept(const float* p_logits, const float* q_logits, const int32_t* dra
     if ((u_accept == nullptr) != (u_resample == nullptr)) return fail(nullptr, SPEC_ERR_ARG, "spec_accept: give both uniform arrays or neither");
     AcceptArgs a{};
     a.p_logits = p_logits; a.q_logits = q_logits; a.draft_tokens = draft_tokens; a.u_accept = u_accept;
-    a.u_resample = u_resample; a.inv_tau = q_logits ? 1.0f / temperature : 1.0f; a.seed = seed; a.round = round;
+    a.u_resample = u_resample; a.inv_tau = q_logits ? inverse_temperature(temperature) : 1.0f; a.seed = seed; a.round = round;
     a.seq_base = seq_base; a.B = B; a.k = k; a.V = V; a.n_accepted = n_accepted; a.next_token = next_token;
     HIPCHK(nullptr, launch_accept(a, (hipStream_t)stream));
     return SPEC_OK;

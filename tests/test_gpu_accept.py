@@ -285,3 +285,24 @@ def test_not_a_number_anywhere_in_a_row_rejects(V, side):
         for first in range(64 - off, V - 3, 4096):
             row[first:first + 4] = float("nan")
     assert kept() == [1] + [0] * (B - 1)
+
+
+@pytest.mark.parametrize("V", [512, 1001, 4001, 32000, 40001])
+def test_infinite_temperature_is_uniform(V):
+    """1 / temperature = 0: every id is as likely as the next, on the rows' padding as little as before."""
+    import torch
+    import paper_2505_10259_amd as P
+    B, k = 33, 2
+    g = torch.Generator("cuda").manual_seed(V)
+    p = torch.randn(B, k + 1, V, device="cuda", generator=g) * 5
+    q = torch.randn(B, k, V, device="cuda", generator=g) * 5
+    d = torch.randint(0, V, (B, k), device="cuda", generator=g, dtype=torch.int32)
+    ids = torch.linspace(0, V - 1, B).long()
+    ua = torch.full((B, k), 0.99, device="cuda")
+    ur = ((ids + 0.5) / V).float().cuda().reshape(B, 1).repeat(1, k + 1).contiguous()
+    n = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    nx = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    P.spec_accept(p, q, d, ua, ur, float("inf"), 0, 0, 0, B, k, V, n, nx)
+    torch.cuda.synchronize()
+    assert n.cpu().tolist() == [k] * B
+    assert nx.cpu().tolist() == ids.tolist()
