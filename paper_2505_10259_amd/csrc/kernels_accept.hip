@@ -58,7 +58,7 @@ hipError_t launch_philox_uniforms(uint64_t seed, uint32_t round, uint32_t seq_ba
 // 2.3 x 2^-24 off where expf is 1.4, and it loses weights below 2^-126.
 
 // =================================================================================================
-// General path: any vocabulary size and row alignment.  One workgroup of 1024 threads per sequence; a row is read in
+// General path: long rows of any vocabulary size and alignment.  One workgroup of 1024 threads per sequence; a row is read in
 // aligned 16-byte granules (elements outside the row count as -inf), several granules per thread in flight.
 // The maximum and the normaliser of the two rows of a candidate come from one pass (running maximum per thread), the
 // draw takes one pass for the sums of runs of 64 U granules and reads again only the run that holds the
@@ -362,6 +362,181 @@ accept_sample_generic_kernel(AcceptArgs a, int tested) {
 }
 
 // =================================================================================================
+// Short rows of any vocabulary size and alignment: one workgroup of 256 threads per sequence, an element per thread and
+// load, a pass over the row (in L1) per reduction.  Bound by the latency of its few steps, which four wavefronts
+// go through faster than the sixteen of the general path: 16 sequences, 4 candidates, us per call as this and as
+// the general path, first candidate rejected / all kept: 1001 ids 9 / 20 and 17 / 33, 2001 ids 14 / 30 and 18 / 36, 3001 ids
+// 18 / 40 and 19 / 40, 4097 ids 24 / 51 and 21 / 44.
+// =================================================================================================
+constexpr int NARROW_THREADS = 256, NARROW_MAX_V = 3072;
+
+__device__ inline float narrow_sum(float v, float* sh /*>=4*/) {
+    v = wave_sum(v);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return sh[0] + sh[1] + sh[2] + sh[3];
+}
+__device__ inline float narrow_max(float v, float* sh) {
+    v = wave_max(v);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
+}
+// argmax with lowest-index tie-break
+__device__ inline int narrow_argmax(const float* __restrict__ z, int V, float* shv, int* shi) {
+    float bv = -INFINITY;
+    int bi = 0x7fffffff;
+    for (int c = threadIdx.x; c < V; c += NARROW_THREADS) {
+        float v = z[c];
+        if (v > bv) { bv = v; bi = c; }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        float ov = __shfl_xor(bv, o, 64);
+        int oi = __shfl_xor(bi, o, 64);
+        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) { shv[threadIdx.x >> 6] = bv; shi[threadIdx.x >> 6] = bi; }
+    __syncthreads();
+    bv = shv[0]; bi = shi[0];
+#pragma unroll
+    for (int w = 1; w < 4; ++w)
+        if (shv[w] > bv || (shv[w] == bv && shi[w] < bi)) { bv = shv[w]; bi = shi[w]; }
+    return bi;
+}
+
+// Smallest id whose running sum of w(id) (ascending ids) exceeds target; if rounding leaves none,
+// the largest id with positive weight.
+template <typename F>
+__device__ inline int narrow_inverse_cdf(F w, int V, float target, float* shf, int* shi) {
+    float run = 0.f;
+    int last_pos = -1;
+    int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    for (int base = 0; base < V; base += NARROW_THREADS * 4) {
+        int id0 = base + threadIdx.x * 4;
+        float x[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            x[j] = id0 + j < V ? w(id0 + j) : 0.f;
+            if (x[j] > 0.f) last_pos = id0 + j;
+        }
+        float local = (x[0] + x[1]) + (x[2] + x[3]);
+        float incl = local;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            float up = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += up;
+        }
+        __syncthreads();
+        if (lane == 63) shf[wv] = incl;
+        __syncthreads();
+        float wave_base = 0.f;
+        for (int q = 0; q < wv; ++q) wave_base += shf[q];
+        float seg_total = shf[0] + shf[1] + shf[2] + shf[3];
+        incl += wave_base;
+        bool over = run + incl > target;
+        // lowest thread over the target
+        unsigned long long bal = __ballot(over);
+        __syncthreads();
+        if (lane == 0) shi[wv] = bal ? (wv * 64 + (int)__ffsll((long long)bal) - 1) : 0x7fffffff;
+        __syncthreads();
+        int first = min(min(shi[0], shi[1]), min(shi[2], shi[3]));
+        if (first != 0x7fffffff) {
+            __syncthreads();
+            if ((int)threadIdx.x == first) {
+                float c = run + (incl - local);
+                int pick = -1, lastp = -1;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    c += x[j];
+                    if (x[j] > 0.f) lastp = id0 + j;
+                    if (pick < 0 && c > target && x[j] > 0.f) pick = id0 + j;
+                }
+                shi[4] = pick >= 0 ? pick : (lastp >= 0 ? lastp : id0);
+            }
+            __syncthreads();
+            return shi[4];
+        }
+        run += seg_total;
+    }
+    // no crossing found (target >= total after rounding): largest id of positive weight
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) last_pos = max(last_pos, __shfl_xor(last_pos, o, 64));
+    __syncthreads();
+    if (lane == 0) shi[wv] = last_pos;
+    __syncthreads();
+    int r = max(max(shi[0], shi[1]), max(shi[2], shi[3]));
+    return r < 0 ? 0 : r;
+}
+
+// max and sum of exp((z - max) * inv_tau) of one row
+__device__ inline void narrow_row_stats(const float* __restrict__ z, int V, float inv_tau, float* sh,
+                                       float* out_max, float* out_sum) {
+    float m = -INFINITY;
+    for (int c = threadIdx.x; c < V; c += NARROW_THREADS) m = fmaxf(m, z[c]);
+    m = narrow_max(m, sh);
+    float s = 0.f;
+    for (int c = threadIdx.x; c < V; c += NARROW_THREADS) s += expf((z[c] - m) * inv_tau);
+    s = narrow_sum(s, sh);
+    *out_max = m; *out_sum = s;
+}
+
+__global__ void __launch_bounds__(NARROW_THREADS)
+accept_sample_narrow_kernel(AcceptArgs a) {
+    __shared__ float shf[4];
+    __shared__ int shi[5];
+    __shared__ int sh_stop;
+    int b = blockIdx.x, k = a.k, V = a.V;
+    const float* P = a.p_logits + (int64_t)b * (k + 1) * V;
+    const float* Q = a.q_logits + (int64_t)b * k * V;
+    float it = a.inv_tau;
+    int n = 0;
+    float pm = 0.f, ps = 1.f, qm = 0.f, qs = 1.f;
+    // candidates are tested in order; each test needs the softmax normalisers of two rows
+    while (true) {
+        narrow_row_stats(P + (int64_t)n * V, V, it, shf, &pm, &ps);
+        if (n == k) break;
+        narrow_row_stats(Q + (int64_t)n * V, V, it, shf, &qm, &qs);
+        if (threadIdx.x == 0) sh_stop = rejects(a, b, n, pm, ps, qm, qs);
+        __syncthreads();
+        int stop = sh_stop;
+        __syncthreads();
+        if (stop) break;
+        ++n;
+    }
+    const float* pr = P + (int64_t)n * V;
+    const float* qr = n < k ? Q + (int64_t)n * V : nullptr;
+    float ipn = 1.0f / ps, iqn = 1.0f / qs;
+    auto wres = [&](int id) -> float {
+        float pv = expf((pr[id] - pm) * it) * ipn;
+        if (!qr) return pv;
+        float qv = expf((qr[id] - qm) * it) * iqn;
+        return fmaxf(0.f, pv - qv);
+    };
+    auto wp = [&](int id) -> float { return expf((pr[id] - pm) * it) * ipn; };
+    float tot = 0.f;
+    for (int c = threadIdx.x; c < V; c += NARROW_THREADS) tot += wres(c);
+    tot = narrow_sum(tot, shf);
+    float u = a.u_resample ? a.u_resample[b * (k + 1) + n]
+                           : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)n, 2);
+    int nxt;
+    if (tot > 0.f) nxt = narrow_inverse_cdf(wres, V, u * tot, shf, shi);
+    else {                                  // p == q everywhere: fall back to the target row
+        float tp = 0.f;
+        for (int c = threadIdx.x; c < V; c += NARROW_THREADS) tp += wp(c);
+        tp = narrow_sum(tp, shf);
+        nxt = narrow_inverse_cdf(wp, V, u * tp, shf, shi);
+    }
+    if (threadIdx.x == 0) {
+        if (a.n_accepted) a.n_accepted[b] = n;
+        if (a.next_token) a.next_token[b] = nxt;
+    }
+}
+
+// =================================================================================================
 // Fast path: vocabularies of up to 32768 ids (a multiple of 4, rows 16-byte aligned).  One workgroup
 // of 1024 threads per sequence; a logits row is loaded once, 32 values per thread as 8 float4 (thread
 // t of sweep s holds ids 4096 s + 4 t .. + 3, so running sums stay in ascending id order), and every
@@ -649,7 +824,13 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t st) {
     if (a.B <= 0) return hipSuccess;
     const bool fast = fast_rows_ok(a.p_logits, a.V) && (!a.q_logits || fast_rows_ok(a.q_logits, a.V));
     if (a.q_logits) {
-        const int tested = a.n_accepted && a.k >= 2 && a.B * a.k <= 256;
+        // Testing at once costs two launches more, about 14 us, and saves a candidate's time for every one that the sequence
+        // which keeps most has kept.  For the short rows of the kernel below that is only V / 430 us a candidate, and one to
+        // three sequences keep few: 16 sequences, first candidate rejected / all kept, in turn against at once: 2001
+        // ids, 4 candidates 14 / 30 against 27 / 23; 3001 ids, 6 candidates 18 / 54 against 31 / 26; 4097 ids, 4
+        // candidates 21 / 44 against 32 / 27.
+        const bool pays = fast || a.V > 2 * NARROW_MAX_V || (a.B >= 4 && (int64_t)a.k * a.V >= 4 * NARROW_MAX_V);
+        const int tested = a.n_accepted && a.k >= 2 && a.B * a.k <= 256 && pays;
         if (tested) {
             hipError_t e = launch_fill_words(a.n_accepted, (size_t)a.B, (uint32_t)a.k, st);
             if (e != hipSuccess) return e;
@@ -657,6 +838,7 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t st) {
             else hipLaunchKernelGGL(accept_test_generic_kernel, dim3(a.B * a.k), dim3(WIDE_THREADS), 0, st, a);
         }
         if (fast) hipLaunchKernelGGL(accept_sample_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a, tested);
+        else if (!tested && a.V <= NARROW_MAX_V) hipLaunchKernelGGL(accept_sample_narrow_kernel, dim3(a.B), dim3(NARROW_THREADS), 0, st, a);
         else hipLaunchKernelGGL(accept_sample_generic_kernel, dim3(a.B), dim3(WIDE_THREADS), 0, st, a, tested);
     } else {
         if (a.V <= ROWS_MAX_V) hipLaunchKernelGGL(accept_greedy_rows_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
@@ -682,6 +864,25 @@ draft_pick_generic_kernel(const float* __restrict__ z, int64_t ld, int V, int mo
         auto w = [&](int g) { return wide_weights(row, g, m, inv_tau, 1.0f); };
         const float u = philox_uniform(seed, round, seq_base + b, (uint32_t)step, 0);
         pick = wide_inverse_cdf(w, row.n, row.off, u, sh, &tot);
+    }
+    if (threadIdx.x == 0) draft_tokens[b * k + step - 1] = pick;
+}
+__global__ void __launch_bounds__(NARROW_THREADS)
+draft_pick_narrow_kernel(const float* __restrict__ z, int64_t ld, int V, int mode, float inv_tau, uint64_t seed,
+                          uint32_t round, uint32_t seq_base, int step, int32_t* __restrict__ draft_tokens, int k) {
+    __shared__ float shf[4];
+    __shared__ int shi[5];
+    int b = blockIdx.x;
+    const float* row = z + (int64_t)b * ld;
+    int pick;
+    if (mode == SPEC_GREEDY) {
+        pick = narrow_argmax(row, V, shf, shi);
+    } else {
+        float m, s;
+        narrow_row_stats(row, V, inv_tau, shf, &m, &s);
+        auto w = [&](int id) -> float { return expf((row[id] - m) * inv_tau); };
+        float u = philox_uniform(seed, round, seq_base + b, (uint32_t)step, 0);
+        pick = narrow_inverse_cdf(w, V, u * s, shf, shi);
     }
     if (threadIdx.x == 0) draft_tokens[b * k + step - 1] = pick;
 }
@@ -712,6 +913,9 @@ hipError_t launch_draft_pick(const float* z, int64_t ld, int V, int B, int mode,
     if (B <= 0) return hipSuccess;
     if (fast_rows_ok(z, V) && ld % 4 == 0)
         hipLaunchKernelGGL(draft_pick_kernel, dim3(B), dim3(FAST_THREADS), 0, st, z, ld, V, mode, inv_tau, seed,
+                           round, seq_base, step, draft_tokens, k);
+    else if (V <= NARROW_MAX_V)
+        hipLaunchKernelGGL(draft_pick_narrow_kernel, dim3(B), dim3(NARROW_THREADS), 0, st, z, ld, V, mode, inv_tau, seed,
                            round, seq_base, step, draft_tokens, k);
     else
         hipLaunchKernelGGL(draft_pick_generic_kernel, dim3(B), dim3(WIDE_THREADS), 0, st, z, ld, V, mode, inv_tau,

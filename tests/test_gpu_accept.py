@@ -169,11 +169,14 @@ def test_candidate_outside_the_vocabulary_is_rejected(V):
         assert all(0 <= t < V for t in nx.cpu().tolist())
 
 
-# candidates tested one workgroup each (B k <= 256) and one after the other (more); rows at every alignment
+# candidates tested one workgroup each and one after the other, on either side of the lines between the two and between
+# the kernels for short and long rows; rows at every alignment
 # (V mod 4 = 0..3), one id short of and past a run of the inverse-CDF search, runs of more than one granule per lane
 @pytest.mark.parametrize("B,k,V,tau", [(4, 2, 65537, 0.8), (4, 3, 300001, 0.8), (4, 2, 262142, 0.8), (4, 2, 262147, 1.0),
                                        (100, 3, 512, 0.8), (90, 4, 1001, 0.8), (64, 4, 1003, 0.8), (5, 16, 4098, 0.8),
-                                       (260, 1, 64, 0.8), (4, 1, 3, 0.8), (4, 2, 1, 0.8)])
+                                       (260, 1, 64, 0.8), (4, 1, 3, 0.8), (4, 2, 1, 0.8), (5, 2, 3071, 0.8), (5, 2, 3073, 0.8),
+                                       (5, 6, 2047, 0.8), (5, 6, 2049, 0.8), (3, 6, 6143, 0.8), (3, 6, 6145, 0.8),
+                                       (200, 4, 1021, 0.8)])
 def test_accept_sample_wide_rows_and_both_test_orders(B, k, V, tau):
     import torch
     import paper_2505_10259_amd as P
