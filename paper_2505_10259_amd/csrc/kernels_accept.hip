@@ -790,10 +790,14 @@ accept_sample_kernel(AcceptArgs a, int tested) {
 }
 
 // Few sequences: every candidate of every sequence is tested by a workgroup of its own (n_accepted[b] starts at k and
-// becomes the smallest rejected index), then one workgroup per sequence draws.  The tests of a sequence one after
-// the other keep a compute unit each for (kept + 1) times two rows while the others idle; with B k <= 256 tests
-// they all run at once.  The rows behind the first rejection are read for nothing, which larger batches
-// would pay for (256 sequences are bound by these bytes).
+// becomes the smallest rejected index), then one workgroup per sequence draws (and takes the statistics of the two rows
+// of its draw again).  In turn a sequence takes a + n b us when it keeps n candidates, and the call as long as the sequence
+// that keeps most; at once it takes the same whatever is kept, two launches and the rows behind the first
+// rejection included.  16 sequences, us, 512 / 32000 ids by the register kernel: in turn 23 + 7.3 n / 27 + 8.4 n, at once
+// 37 / 41, with every candidate kept 30 / 34 (one row to draw from); 64 sequences of 4 candidates, 32000 ids, 27 + 9.7 n against
+// 49 and 42.  So at once from three candidates on, where a sequence among the batch usually keeps two or more
+// (break-even at an acceptance of 0.2 with 16 sequences, 0.4 with 4, 0.6 with one); a call whose draft is always wrong
+// takes up to 1.7 times as long.  With B k <= 256 tests they all run at once; 128 sequences of 2 candidates gain nothing.
 __global__ void __launch_bounds__(FAST_THREADS)
 accept_test_kernel(AcceptArgs a) {
     __shared__ FastShared sh;
@@ -830,7 +834,7 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t st) {
         // ids, 4 candidates 14 / 30 against 27 / 23; 3001 ids, 6 candidates 18 / 54 against 31 / 26; 4097 ids, 4
         // candidates 21 / 44 against 32 / 27.
         const bool pays = fast || a.V > 2 * NARROW_MAX_V || (a.B >= 4 && (int64_t)a.k * a.V >= 4 * NARROW_MAX_V);
-        const int tested = a.n_accepted && a.k >= 2 && a.B * a.k <= 256 && pays;
+        const int tested = a.n_accepted && a.k >= 3 && a.B <= 256 / a.k && pays;
         if (tested) {
             hipError_t e = launch_fill_words(a.n_accepted, (size_t)a.B, (uint32_t)a.k, st);
             if (e != hipSuccess) return e;

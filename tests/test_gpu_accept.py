@@ -175,7 +175,7 @@ def test_candidate_outside_the_vocabulary_is_rejected(V):
 @pytest.mark.parametrize("B,k,V,tau", [(4, 2, 65537, 0.8), (4, 3, 300001, 0.8), (4, 2, 262142, 0.8), (4, 2, 262147, 1.0),
                                        (100, 3, 512, 0.8), (90, 4, 1001, 0.8), (64, 4, 1003, 0.8), (5, 16, 4098, 0.8),
                                        (260, 1, 64, 0.8), (4, 1, 3, 0.8), (4, 2, 1, 0.8), (5, 2, 3071, 0.8), (5, 2, 3073, 0.8),
-                                       (5, 6, 2047, 0.8), (5, 6, 2049, 0.8), (3, 6, 6143, 0.8), (3, 6, 6145, 0.8),
+                                       (5, 6, 2047, 0.8), (5, 6, 2049, 0.8), (3, 6, 6143, 0.8), (3, 6, 6145, 0.8), (4, 3, 262147, 1.0),
                                        (200, 4, 1021, 0.8)])
 def test_accept_sample_wide_rows_and_both_test_orders(B, k, V, tau):
     import torch
