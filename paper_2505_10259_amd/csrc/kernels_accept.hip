@@ -704,8 +704,12 @@ accept_greedy_kernel(AcceptArgs a) {
 }
 
 // Small vocabularies: all k + 1 rows at once, a wavefront per row (a row after the other, each behind a
-// workgroup reduction, five rows of 512 ids took 16 us).
+// workgroup reduction, costs 1.3 us a row and more: 16 sequences, 4 candidates, 1001 ids, 3.1 us where the first differs and
+// 8.3 where all agree, 3.4 and 3.7 so).  Not where the rows behind the first mismatch are too many bytes to read for
+// nothing and the register kernel takes the vocabulary: 256 sequences, 4096 ids, first mismatch at once, 8 candidates
+// (38 MB) 7.5 us against 5.1, 16 (71 MB) 14.8 against 5.0.
 constexpr int ROWS_MAX_V = 4096;
+constexpr int64_t ROWS_MAX_IDS = 8 << 20;
 __global__ void __launch_bounds__(FAST_THREADS)
 accept_greedy_rows_kernel(AcceptArgs a) {
     __shared__ int am[17];
@@ -845,7 +849,8 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t st) {
         else if (!tested && a.V <= NARROW_MAX_V) hipLaunchKernelGGL(accept_sample_narrow_kernel, dim3(a.B), dim3(NARROW_THREADS), 0, st, a);
         else hipLaunchKernelGGL(accept_sample_generic_kernel, dim3(a.B), dim3(WIDE_THREADS), 0, st, a, tested);
     } else {
-        if (a.V <= ROWS_MAX_V) hipLaunchKernelGGL(accept_greedy_rows_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
+        const bool rows = a.V <= ROWS_MAX_V && (!fast || (int64_t)a.B * (a.k + 1) * a.V <= ROWS_MAX_IDS);
+        if (rows) hipLaunchKernelGGL(accept_greedy_rows_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
         else if (fast) hipLaunchKernelGGL(accept_greedy_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
         else hipLaunchKernelGGL(accept_greedy_generic_kernel, dim3(a.B), dim3(WIDE_THREADS), 0, st, a);
     }

@@ -22,7 +22,8 @@ def _logits(B, k, V, seed, agree=0.6):
 # vocabularies of up to 32768 ids that are a multiple of 4 take the register-resident kernels (each row
 # read once); 33 and 40000 take the general ones
 @pytest.mark.parametrize("B,k,V", [(7, 4, 512), (3, 8, 32000), (1, 1, 33), (5, 0, 100), (64, 6, 32768),
-                                   (4, 3, 40000), (3, 2, 12), (5, 16, 32768), (3, 16, 1001), (300, 2, 256)])
+                                   (4, 3, 40000), (3, 2, 12), (5, 16, 32768), (3, 16, 1001), (300, 2, 256),
+                                   (300, 6, 4096), (300, 6, 4095)])
 def test_accept_greedy(B, k, V):
     import torch
     import paper_2505_10259_amd as P
