@@ -87,7 +87,7 @@ inline size_t esize(int dtype) { return dtype == SPEC_BF16 ? 2 : 4; }
 inline float inverse_temperature(float t) { return std::max(1.0f / t, std::numeric_limits<float>::denorm_min()); }
 
 struct Workspace {
-    int t_max = 0;
+    int t_max = 0;            // rows of the routing arrays
     float* x = nullptr; void* h = nullptr; float* qkv = nullptr; void* q = nullptr; void* att = nullptr;
     float2* cs = nullptr; int32_t* row_pos = nullptr;
     int32_t* r_ids = nullptr; float* r_wts = nullptr; int32_t* offsets = nullptr; int32_t* perm = nullptr;
@@ -215,11 +215,12 @@ int dev_alloc(spec_ctx* c, P** out, size_t bytes) {
     return SPEC_OK;
 }
 
-int alloc_workspace(spec_ctx* c, Workspace& w, const spec_model_shape& s, int t_max) {
+// t_route: rows of the routing arrays, which spec_debug_routing reads (at least t_max)
+int alloc_workspace(spec_ctx* c, Workspace& w, const spec_model_shape& s, int t_max, int t_route) {
     size_t es = esize(s.dtype);
     int64_t d = s.d_model, hd = (int64_t)s.n_q_heads * s.head_dim;
     int64_t qkv_rows = (int64_t)(s.n_q_heads + 2 * s.n_kv_heads) * s.head_dim;
-    w.t_max = t_max;
+    w.t_max = t_route;
     int rc;
     if ((rc = dev_alloc(c, &w.x, t_max * d * 4))) return rc;
     if ((rc = dev_alloc(c, (char**)&w.h, t_max * d * es))) return rc;
@@ -232,8 +233,8 @@ int alloc_workspace(spec_ctx* c, Workspace& w, const spec_model_shape& s, int t_
         int mult = s.n_experts > 0 ? 2 : 1;
         if ((rc = dev_alloc(c, (char**)&w.u, (size_t)mult * t_max * s.d_ff * es))) return rc;
         if (s.n_experts > 0) {
-            if ((rc = dev_alloc(c, &w.r_ids, (size_t)t_max * 8))) return rc;
-            if ((rc = dev_alloc(c, &w.r_wts, (size_t)t_max * 8))) return rc;
+            if ((rc = dev_alloc(c, &w.r_ids, (size_t)t_route * 8))) return rc;
+            if ((rc = dev_alloc(c, &w.r_wts, (size_t)t_route * 8))) return rc;
             if ((rc = dev_alloc(c, &w.offsets, 64))) return rc;
             if ((rc = dev_alloc(c, &w.perm, (size_t)t_max * 8))) return rc;
             if ((rc = dev_alloc(c, &w.slots, (size_t)t_max * 8))) return rc;
@@ -622,7 +623,7 @@ int target_layer(spec_ctx* c, int l, Workspace& w, const RowSet& r, void* kv_lay
 }
 
 
-// target pass over rows already embedded in w.x (tok_in/row_pos/cs set); leaves normalised final
+// target pass over rows already embedded in w.x (row_pos/cs set); leaves normalised final
 // state in w.h when want_head
 int target_layers(spec_ctx* c, Sub& sb, Workspace& w, int T, int n_new, bool want_final_norm) {
     RowSet r{w.x, w.row_pos, w.cs, T, n_new, sb.B};
@@ -978,10 +979,10 @@ static int init_impl(spec_ctx* c, const spec_host_weights* tw, const spec_host_w
         HIPCHK(c, hipEventCreateWithFlags(&sb.ev_committed, hipEventDisableTiming));
         sb.seq_base = (uint32_t)(s * Bm);
     }
-    int chunk = cfg.prefill_chunk;
-    int t_max = Bm * std::max(km + 1, chunk);
-    if ((rc = alloc_workspace(c, c->wv, t, t_max))) return rc;
-    if (c->has_draft && (rc = alloc_workspace(c, c->wd, c->drf, Bm * std::max(2, chunk)))) return rc;
+    // rows of a verify pass and of a draft step (two rows per sequence in its first one); a prefill has its own workspace.
+    // (spec_debug_routing takes row counts of up to a prefill chunk of every sequence.)
+    if ((rc = alloc_workspace(c, c->wv, t, Bm * (km + 1), Bm * std::max(km + 1, cfg.prefill_chunk)))) return rc;
+    if (c->has_draft && (rc = alloc_workspace(c, c->wd, c->drf, Bm * 2, Bm * 2))) return rc;
     if ((rc = dev_alloc(c, &c->d_hist, 18 * 8))) return rc;
     HIPCHK(c, hipMemset(c->d_hist, 0, 18 * 8));
     HIPCHK(c, hipDeviceSynchronize());
@@ -1141,7 +1142,6 @@ int spec_prefill(spec_ctx* c, int sub, const int32_t* tokens, const int32_t* cu_
             const size_t n_wg = piecewise_of(is_draft) ? n_grp : 1;
             off = common;
             Workspace w;
-            w.t_max = (int)Rg;
             w.q = base + take(Rg * hd * c->es);
             w.att = base + take(Rg * hd * c->es);
             // f32 projections: the plain path, and groups of so few rows that the epilogue does not rotate
@@ -1587,7 +1587,6 @@ int spec_layer_forward_static(spec_ctx* c, int sub, int layer, const void* x_in,
     size_t off = 0;
     auto take = [&](size_t bytes) { char* p = base + off; off += (bytes + 255) & ~(size_t)255; return p; };
     Workspace w;
-    w.t_max = (int)T;
     w.h = take(T * d * es);
     w.qkv = (float*)take(T * qkv_rows * 4);
     w.q = take(T * hd * es);

@@ -365,3 +365,21 @@ def test_prefill_groups_and_repeated_prefills_change_no_bit(dtype, draft_attn_on
         for i, g in enumerate(got):
             assert torch.isfinite(g).all()
             assert torch.equal(g, ref.setdefault(i & 1, g)), (group_rows, i)
+
+
+def test_context_holds_the_rows_of_verify_passes_only():
+    """The context's activation workspace serves verify passes and draft steps; prompt positions per prefill block do
+    not enlarge it (a prefill has a workspace of its own)."""
+    import torch
+    import paper_2505_10259_amd as P
+    from gpu_common import host_model_pinned
+    shp = synth.mini_moe_shape(d_model=1024, d_ff=2048, n_experts=2)
+    hm = host_model_pinned(shp, seed=5)
+    held = []
+    for chunk in (1, 64, 1):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        with P.Session(hm, hm.draft_view(1, False), batch_max=256, k_max=2, ctx_max=64, prefill_chunk=chunk):
+            held.append(before - torch.cuda.mem_get_info()[0])
+    # (the routing arrays keep a chunk's rows: 256 KB; allocations come in steps of 2 MB)
+    assert held[1] - min(held[0], held[2]) <= 8 << 20, held
