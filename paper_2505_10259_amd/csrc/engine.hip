@@ -1142,6 +1142,8 @@ int spec_prefill(spec_ctx* c, int sub, const int32_t* tokens, const int32_t* cu_
             const size_t n_wg = piecewise_of(is_draft) ? n_grp : 1;
             off = common;
             Workspace w;
+            // (what the attention part of a group holds and the experts' intermediate are never alive together)
+            const size_t shared = off;
             w.q = base + take(Rg * hd * c->es);
             w.att = base + take(Rg * hd * c->es);
             // f32 projections: the plain path, and groups of so few rows that the epilogue does not rotate
@@ -1149,7 +1151,10 @@ int spec_prefill(spec_ctx* c, int sub, const int32_t* tokens, const int32_t* cu_
             const bool mfma = s.dtype == SPEC_BF16 && !(c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS) && s.head_dim == 128 && s.d_model % 64 == 0;
             if (!mfma || qkv_unfused_pays((int)Rg, (int)qkv_rows, d) || qkv_unfused_pays(last_rows, (int)qkv_rows, d))
                 w.qkv = (float*)(base + take(Rg * qkv_rows * 4));
+            const size_t attn_end = off;
+            off = shared;
             if (ffn) w.u = base + take((moe ? 2 : 1) * Rg * s.d_ff * c->es);
+            off = std::max(off, attn_end);
             for (size_t i = 0; i < n_wg; ++i) {
                 Workspace x = w;
                 x.h = base + take(Rg * d * c->es);

@@ -383,3 +383,27 @@ def test_context_holds_the_rows_of_verify_passes_only():
             held.append(before - torch.cuda.mem_get_info()[0])
     # (the routing arrays keep a chunk's rows: 256 KB; allocations come in steps of 2 MB)
     assert held[1] - min(held[0], held[2]) <= 8 << 20, held
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_prefill_workspace_is_no_larger_than_its_rows_need(dtype):
+    """The workspace of a short prefill, which stays with the context: residual stream, positions, rotary table and page
+    rows, and per row of a group normalised state, expert outputs and routing plus the larger of attention part and experts'
+    intermediate."""
+    import torch
+    import paper_2505_10259_amd as P
+    from gpu_common import host_model_pinned
+    shp = synth.mini_moe_shape(dtype=dtype, d_model=1024, n_q_heads=8, n_kv_heads=2, d_ff=2048, n_experts=2)
+    hm = host_model_pinned(shp, seed=5)
+    B, L, Q, ctx = 8, 257, 64, 320
+    with P.Session(hm, None, batch_max=B, k_max=2, ctx_max=ctx, prefill_chunk=Q) as s:
+        P.spec_prefill(s.ctx, 0, synth.make_prompts(1, (3, 3), shp.vocab, seed=1), 4)     # (kernels are loaded)
+        before = torch.cuda.mem_get_info()[0]
+        P.spec_prefill(s.ctx, 0, synth.make_prompts(B, (L, L), shp.vocab, seed=1), 4)
+        held = before - torch.cuda.mem_get_info()[0]
+    es, d, hd = 2 if dtype == "bf16" else 4, shp.d_model, shp.n_q_heads * shp.head_dim
+    rows, pages = B * (L - 1), (ctx + 2) // 64 + 1
+    qkv = 4 * (hd + 2 * shp.n_kv_heads * shp.head_dim)
+    per_row = 4 * d + 4 + 8 * (shp.head_dim // 2) + (pages + 2) * 4 // Q + 1 + es * d + 8 * d + 32 + \
+        max(2 * es * hd + qkv, 2 * es * shp.d_ff)
+    assert held <= rows * per_row + (4 << 20), (held, rows * per_row)
