@@ -1115,10 +1115,14 @@ int spec_prefill(spec_ctx* c, int sub, const int32_t* tokens, const int32_t* cu_
         // kernel serves all chunks of a group, and an expert sees thousands of rows.  A layer that streams
         // piece by piece holds each piece for all groups before the next piece arrives, so what a group
         // carries from the routing to its experts and on to the combine (normalised rows, routing,
-        // expert outputs) is then kept per group.  (The operands of a product must stay below 4 GB.)
-        const int64_t widest = std::max({c->tgt.d_model, c->tgt.n_q_heads * c->tgt.head_dim,
-                                         c->has_draft ? c->drf.n_q_heads * c->drf.head_dim : 0});
-        const int64_t row_cap = std::min<int64_t>(std::max(c->cfg.prefill_group_rows, B * Q), (((int64_t)1 << 32) - 1) / (widest * 4));
+        // expert outputs) is then kept per group.  (The activations of a product must stay below 4 GB, which 32 bits
+        // address: the normalised rows gathered for two experts each, the attention output, the experts' intermediate.)
+        auto widest = [](const spec_model_shape& m) -> int64_t {
+            const int mult = m.n_experts > 0 ? 2 : 1;
+            return std::max<int64_t>({mult * m.d_model, m.n_q_heads * m.head_dim, m.attn_only ? 0 : (int64_t)mult * m.d_ff});
+        };
+        const int64_t row_bytes = std::max(widest(c->tgt), c->has_draft ? widest(c->drf) : 0) * (int64_t)c->es;
+        const int64_t row_cap = std::min<int64_t>(std::max(c->cfg.prefill_group_rows, B * Q), (((int64_t)1 << 32) - 1) / row_bytes);
         const int Gb = (int)std::max<int64_t>(1, std::min<int64_t>(n_blocks, row_cap / Q));
         const int n_grp = (n_blocks + Gb - 1) / Gb;
         const size_t Rg = (size_t)Gb * Q;

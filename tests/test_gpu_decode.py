@@ -407,3 +407,24 @@ def test_prefill_workspace_is_no_larger_than_its_rows_need(dtype):
     per_row = 4 * d + 4 + 8 * (shp.head_dim // 2) + (pages + 2) * 4 // Q + 1 + es * d + 8 * d + 32 + \
         max(2 * es * hd + qkv, 2 * es * shp.d_ff)
     assert held <= rows * per_row + (4 << 20), (held, rows * per_row)
+
+
+def test_prefill_groups_stay_below_4_gb_of_activations():
+    """17408 rows whose experts' intermediate (two experts a row, 65536 wide, bf16) would be 4.6 GB as one group: the
+    down product stays on the matrix cores, so a prefill of small groups gives the same bits."""
+    import torch
+    import paper_2505_10259_amd as P
+    from gpu_common import host_model_pinned
+    shp = synth.mini_moe_shape(d_model=128, n_q_heads=1, n_kv_heads=1, d_ff=65536, n_experts=2, vocab=256)
+    hm = host_model_pinned(shp, seed=4, std=0.05)
+    B, L = 17, 1025
+    prompts = synth.make_prompts(B, (L, L), shp.vocab, seed=6)
+    ref = None
+    for group_rows in (1024, 1 << 20):
+        with P.Session(hm, None, batch_max=B, k_max=1, ctx_max=L + 4, prefill_group_rows=group_rows) as s:
+            P.spec_prefill(s.ctx, 0, prompts, 3)
+            P.spec_verify(s.ctx, 0, torch.ones(B, 1, dtype=torch.int32, device="cuda"), 1)
+            out = torch.empty(B, 2, shp.vocab, device="cuda")
+            P.spec_debug_logits(s.ctx, 0, out)
+        ref = out if ref is None else ref
+        assert torch.isfinite(out).all() and torch.equal(out, ref)
