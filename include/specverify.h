@@ -127,7 +127,9 @@ typedef struct {
     void* draft_stream;
     int32_t n_piece_slots;           /* piece staging: slots in the ring, 2..16 (0 = default, 3) */
     int32_t prefill_group_rows;      /* prefill: rows (row blocks x prefill_chunk) that run through a layer as one
-                                        set of launches (0 = default, 32768; temporary HBM grows with it) */
+                                        set of launches, at least one block (0 = default, 32768; fewer where
+                                        the activations of a product would reach 4 GB; temporary HBM grows
+                                        with it) */
 } spec_runtime_cfg;
 
 typedef struct {

@@ -1122,7 +1122,7 @@ int spec_prefill(spec_ctx* c, int sub, const int32_t* tokens, const int32_t* cu_
             return std::max<int64_t>({mult * m.d_model, m.n_q_heads * m.head_dim, m.attn_only ? 0 : (int64_t)mult * m.d_ff});
         };
         const int64_t row_bytes = std::max(widest(c->tgt), c->has_draft ? widest(c->drf) : 0) * (int64_t)c->es;
-        const int64_t row_cap = std::min<int64_t>(std::max(c->cfg.prefill_group_rows, B * Q), (((int64_t)1 << 32) - 1) / row_bytes);
+        const int64_t row_cap = std::min<int64_t>(c->cfg.prefill_group_rows, (((int64_t)1 << 32) - 1) / row_bytes);
         const int Gb = (int)std::max<int64_t>(1, std::min<int64_t>(n_blocks, row_cap / Q));
         const int n_grp = (n_blocks + Gb - 1) / Gb;
         const size_t Rg = (size_t)Gb * Q;

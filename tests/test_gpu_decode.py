@@ -359,8 +359,16 @@ def test_prefill_groups_and_repeated_prefills_change_no_bit(dtype, draft_attn_on
         return out
 
     ref = {}
+    Q = 64 if dtype == "bf16" else 16
+    blocks = sum((len(p) - 1 + Q - 1) // Q for p in a)
     for group_rows in (0, 1, 320):
-        with P.Session(hm, dm, batch_max=5, k_max=k, ctx_max=160, prefill_group_rows=group_rows) as s:
+        with P.Session(hm, dm, batch_max=5, k_max=k, ctx_max=160, prefill_group_rows=group_rows, prefill_chunk=Q) as s:
+            # a QKV projection per group and layer of the target and of the draft
+            P.spec_profile_enable(s.ctx, ["qkv"])
+            P.spec_prefill(s.ctx, 0, a, new)
+            groups = -(-blocks // max(1, min(blocks, (group_rows or 32768) // Q)))
+            assert P.spec_profile_read(s.ctx)["qkv"]["launches"] == groups * (3 + 2), (group_rows, blocks)
+            P.spec_profile_enable(s.ctx, [])
             got = [logits(s, p) for p in (a, b, a, b)]
         for i, g in enumerate(got):
             assert torch.isfinite(g).all()
@@ -407,6 +415,32 @@ def test_prefill_workspace_is_no_larger_than_its_rows_need(dtype):
     per_row = 4 * d + 4 + 8 * (shp.head_dim // 2) + (pages + 2) * 4 // Q + 1 + es * d + 8 * d + 32 + \
         max(2 * es * hd + qkv, 2 * es * shp.d_ff)
     assert held <= rows * per_row + (4 << 20), (held, rows * per_row)
+
+
+def test_prefill_on_either_side_of_the_projection_with_its_own_rotary_kernel():
+    """A QKV projection rotates and appends in its epilogue or, for few rows, leaves that to a kernel of its own
+    (1536 columns, K = 1024: up to 960 rows); both give the same bits, whichever takes which part of a prefill."""
+    import torch
+    import paper_2505_10259_amd as P
+    from gpu_common import host_model_pinned
+    shp = synth.mini_moe_shape(d_model=1024, n_q_heads=8, n_kv_heads=2)
+    hm = host_model_pinned(shp, seed=9, std=0.05)
+    prompts = synth.make_prompts(6, (215, 250), shp.vocab, seed=3)
+    k, new, n_layers = 2, 4, shp.n_layers
+    ref = None
+    # 24 blocks: one group that rotates in the epilogue; three of 512 rows that do not; one of each
+    for group_rows, apart in ((0, 0), (512, 3), (1024, 1)):
+        with P.Session(hm, None, batch_max=6, k_max=k, ctx_max=260, prefill_group_rows=group_rows) as s:
+            P.spec_profile_enable(s.ctx, ["rope"])
+            P.spec_prefill(s.ctx, 0, prompts, new)
+            assert P.spec_profile_read(s.ctx)["rope"]["launches"] == apart * n_layers
+            P.spec_profile_enable(s.ctx, [])
+            P.spec_verify(s.ctx, 0, torch.ones(6, k, dtype=torch.int32, device="cuda"), k)
+            out = torch.empty(6, k + 1, shp.vocab, device="cuda")
+            P.spec_debug_logits(s.ctx, 0, out)
+        assert torch.isfinite(out).all()
+        ref = out if ref is None else ref
+        assert torch.equal(out, ref), group_rows
 
 
 def test_prefill_groups_stay_below_4_gb_of_activations():
