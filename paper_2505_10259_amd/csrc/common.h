@@ -91,9 +91,8 @@ struct KvGeom {
 enum GemmEpilogue {
     EPI_STORE_F32 = 0,   // C float = acc
     EPI_ADD_F32 = 1,     // C float += acc           (residual accumulate; one writer per element)
-    EPI_STORE_T = 2,     // C (model dtype) = acc
-    EPI_SWIGLU_T = 3,    // C (model dtype)[M, N] = silu(A W^T) * (A W3^T)   (W3 = second weight)
-    EPI_ROPE_KV = 4      // QKV projection (bf16 MFMA kernel, head_dim 128 only): columns are
+    EPI_SWIGLU_T = 2,    // C (model dtype)[M, N] = silu(A W^T) * (A W3^T)   (W3 = second weight)
+    EPI_ROPE_KV = 3      // QKV projection (bf16 MFMA kernel, head_dim 128 only): columns are
                          // [q heads | k heads | v heads]; q and k are rotated (pair (i, i + 64)) with the
                          // row's cos/sin table, q goes to rope.q_out, k and v to the row's KV page slot
 };

@@ -1,6 +1,6 @@
 // bf16 MFMA GEMM for gfx950:  C[M,N] (+)= A[M,K] * W[N,K]^T, f32 accumulate, with
 //   - optional row gather on A and row grouping with per-group weights (top-2 MoE grouped GEMM),
-//   - fused epilogues: f32 store, f32 residual accumulate, bf16 store, SwiGLU (two weight
+//   - fused epilogues: f32 store, f32 residual accumulate, rotary + KV append (QKV), SwiGLU (two weight
 //     matrices, silu(gate) * up, bf16 store).
 //
 // Design (64-wide wavefronts, CDNA4):
@@ -910,7 +910,7 @@ hipError_t launch_gemm_mfma_bf16(const GemmArgs& a, hipStream_t st) {
     // take 4-element vector stores; anything else (never the case for the supported model shapes)
     // takes the plain kernel
     if (a.K % 64 != 0 || a.lda % 8 != 0 || ((uintptr_t)a.A & 15) || ((uintptr_t)a.W & 15) || a.N % 4 != 0 ||
-        a.ldc % 4 != 0 || ((uintptr_t)a.C & 15) || a.epilogue == EPI_STORE_T || (a.epilogue == EPI_SWIGLU_T && ((uintptr_t)a.W3 & 15)))
+        a.ldc % 4 != 0 || ((uintptr_t)a.C & 15) || (a.epilogue == EPI_SWIGLU_T && ((uintptr_t)a.W3 & 15)))
         return a.epilogue == EPI_ROPE_KV ? hipErrorInvalidValue : launch_gemm_simple(a, SPEC_BF16, st);
     const bool sw = a.epilogue == EPI_SWIGLU_T;
     // operand rows are addressed as a 64-bit base per slab plus a 32-bit byte offset per lane: the rows a

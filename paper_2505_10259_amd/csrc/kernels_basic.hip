@@ -240,7 +240,7 @@ hipError_t launch_rope_kv(const float* qkv, const float2* cs, const int32_t* row
 
 // The same for a bf16 model of head_dim 128, 16-byte accesses: 16 lanes take one head of a row (dims
 // 4 l .. 4 l + 3 and their rotation partners 64 above), a workgroup 16 heads.  Rotation and rounding are
-// written as in the projection's fused epilogue: both ways give the same bits. 
+// written as in the projection's fused epilogue: both ways give the same bits.
 __global__ void __launch_bounds__(256)
 rope_kv_bf16_kernel(const float* __restrict__ qkv, const float2* __restrict__ cs, const int32_t* __restrict__ row_pos,
                         const int32_t* __restrict__ page_table, bf16* __restrict__ q_out, bf16* __restrict__ kv_layer,
@@ -642,9 +642,8 @@ gemm_simple_kernel(GemmArgs a) {
             if (SWIGLU) {
                 float s = v / (1.0f + expf(-v));
                 ((T*)a.C)[o] = from_f32<T>(s * acc3[i][j]);
-            } else if (a.epilogue == EPI_STORE_F32) ((float*)a.C)[o] = v;
-            else if (a.epilogue == EPI_ADD_F32) ((float*)a.C)[o] += v;
-            else ((T*)a.C)[o] = from_f32<T>(v);
+            } else if (a.epilogue == EPI_ADD_F32) ((float*)a.C)[o] += v;
+            else ((float*)a.C)[o] = v;
         }
     }
 }
@@ -745,9 +744,8 @@ gemm_small_kernel(GemmArgs a, int vec) {
     if (r >= row_end || c >= a.N) return;
     const int64_t o = (int64_t)r * a.ldc + c;
     if (SWIGLU) ((T*)a.C)[o] = from_f32<T>(acc / (1.0f + expf(-acc)) * acc3);
-    else if (a.epilogue == EPI_STORE_F32) ((float*)a.C)[o] = acc;
     else if (a.epilogue == EPI_ADD_F32) ((float*)a.C)[o] += acc;
-    else ((T*)a.C)[o] = from_f32<T>(acc);
+    else ((float*)a.C)[o] = acc;
 }
 
 hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st) {
