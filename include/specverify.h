@@ -331,6 +331,15 @@ int spec_gemm(const void* A_dev, const void* W_dev, float* C_dev, int M, int N, 
  * of 64, N not a multiple of 4, ...) fall to the plain kernel as in spec_gemm.  Errors: SPEC_ERR_ARG. */
 int spec_debug_gemm(const void* A_dev, const void* W_dev, float* C_dev, int M, int N, int K, int tile_rows,
                     int tile_cols, void* stream);
+/* Tests only: the same kernel with the epilogues and the grouping of a layer's products.  `epilogue`: C float = A W^T,
+ * C float += A W^T, or C bf16 = silu(A W^T) * (A W3^T) (W3 below 2 GB above W, NULL otherwise).  group_offsets_dev
+ * (NULL: one matrix, n_groups 0): device int32 [n_groups + 1], ascending from 0 to at most M; rows [offsets[g], offsets[g+1]) take
+ * the weights W + g * N * K (and W3 alike), 1 <= n_groups <= 8.  tile_rows as above, tile_cols: weight
+ * columns per tile, 256, 128, 64 or 32 (SwiGLU 256 or 128); both 0: the launcher's choice.  Errors: SPEC_ERR_ARG. */
+enum { SPEC_GEMM_STORE = 0, SPEC_GEMM_ADD = 1, SPEC_GEMM_SWIGLU = 2 };
+int spec_debug_gemm_epilogue(const void* A_dev, const void* W_dev, const void* W3_dev, void* C_dev,
+                             const int32_t* group_offsets_dev, int n_groups, int M, int N, int K, int epilogue,
+                             int tile_rows, int tile_cols, void* stream);
 /* Measures host->HBM copy bandwidth of pinned memory: copies `bytes` from a pinned buffer `reps`
  * times with hipMemcpyAsync and returns GB/s (1e9) in *gbps — the denominator of the link
  * fraction (the paper's planner likewise profiles the CPU-GPU channel first, Section 3). */

@@ -17,6 +17,7 @@ SPEC_OK = 0
 SPEC_ERR_ARG, SPEC_ERR_SHAPE, SPEC_ERR_BUDGET, SPEC_ERR_CAPACITY, SPEC_ERR_HIP, SPEC_ERR_STATE = -1, -2, -3, -4, -5, -6
 SPEC_F32, SPEC_BF16 = 0, 1
 SPEC_GREEDY, SPEC_SAMPLE = 0, 1
+SPEC_GEMM_STORE, SPEC_GEMM_ADD, SPEC_GEMM_SWIGLU = 0, 1, 2
 SPEC_FLAG_NO_OVERLAP, SPEC_FLAG_SIMPLE_KERNELS, SPEC_FLAG_POISON_RELEASED, SPEC_FLAG_PIN_ATTENTION = 1, 2, 4, 8
 
 EXPORTS = [
@@ -27,7 +28,7 @@ EXPORTS = [
     "spec_debug_draft_logits", "spec_accept", "spec_philox_uniforms", "spec_layer_forward",
     "spec_debug_routing", "spec_gemm", "spec_debug_gemm", "spec_measure_link", "spec_profile_enable", "spec_profile_read",
     "spec_plan_paraspec", "spec_plan_evaluate", "spec_plan_placement", "spec_debug_force_routing",
-    "spec_layer_forward_static",
+    "spec_layer_forward_static", "spec_debug_gemm_epilogue",
 ]
 PROF_CLASSES = ["norm", "qkv", "rope", "attn", "oproj", "route", "moe1", "moe2", "head", "accept", "draft"]
 
@@ -131,6 +132,7 @@ def _load() -> C.CDLL:
         "spec_debug_routing": (i32, [vp, i32, vp, vp, i32]),
         "spec_gemm": (i32, [vp, vp, vp, i32, i32, i32, i32, i32, vp]),
         "spec_debug_gemm": (i32, [vp, vp, vp, i32, i32, i32, i32, i32, vp]),
+        "spec_debug_gemm_epilogue": (i32, [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, vp]),
         "spec_measure_link": (i32, [C.c_size_t, i32, P(C.c_double)]),
         "spec_profile_enable": (i32, [vp, u32]),
         "spec_profile_read": (i32, [vp, P(C.c_double), P(i64), i32]),
@@ -356,6 +358,12 @@ def spec_gemm(A_dev, W_dev, C_dev, M, N, K, dtype, flags=0, stream=None) -> None
 
 def spec_debug_gemm(A_dev, W_dev, C_dev, M, N, K, tile_rows, tile_cols, stream=None) -> None:
     _check(lib.spec_debug_gemm(_ptr(A_dev), _ptr(W_dev), _ptr(C_dev), M, N, K, tile_rows, tile_cols, stream))
+
+
+def spec_debug_gemm_epilogue(A_dev, W_dev, W3_dev, C_dev, group_offsets_dev, n_groups, M, N, K, epilogue, tile_rows, tile_cols,
+                             stream=None) -> None:
+    _check(lib.spec_debug_gemm_epilogue(_ptr(A_dev), _ptr(W_dev), _ptr(W3_dev), _ptr(C_dev), _ptr(group_offsets_dev), n_groups,
+                                        M, N, K, epilogue, tile_rows, tile_cols, stream))
 
 
 def spec_measure_link(nbytes: int, reps: int = 4) -> float:

@@ -1664,7 +1664,24 @@ int spec_debug_gemm(const void* A, const void* W, float* C, int M, int N, int K,
         return fail(nullptr, SPEC_ERR_ARG, "spec_debug_gemm: bad arguments");
     GemmArgs g{};
     g.A = A; g.lda = K; g.W = W; g.C = C; g.ldc = N; g.M = M; g.N = N; g.K = K; g.epilogue = EPI_STORE_F32;
-    g.force_max_rows = tile_rows; g.force_wn_t = tile_cols / 64;
+    g.force_max_rows = tile_rows; g.force_cols = tile_cols;
+    HIPCHK(nullptr, launch_gemm_mfma_bf16(g, (hipStream_t)stream));
+    return SPEC_OK;
+}
+
+int spec_debug_gemm_epilogue(const void* A, const void* W, const void* W3, void* C, const int32_t* group_offsets, int n_groups,
+                             int M, int N, int K, int epilogue, int tile_rows, int tile_cols, void* stream) {
+    const bool sw = epilogue == SPEC_GEMM_SWIGLU;
+    if (!A || !W || !C || M <= 0 || N <= 0 || K <= 0 || (epilogue != SPEC_GEMM_STORE && epilogue != SPEC_GEMM_ADD && !sw) ||
+        sw != (W3 != nullptr) || (group_offsets ? n_groups < 1 || n_groups > 8 : n_groups != 0) || (tile_rows == 0) != (tile_cols == 0) ||
+        tile_rows < 0 || tile_rows > 256 || tile_rows % 32 != 0 ||
+        (tile_cols && tile_cols != 256 && tile_cols != 128 && (sw || (tile_cols != 64 && tile_cols != 32))))
+        return fail(nullptr, SPEC_ERR_ARG, "spec_debug_gemm_epilogue: bad arguments");
+    GemmArgs g{};
+    g.A = A; g.lda = K; g.W = W; g.W3 = W3; g.C = C; g.ldc = N; g.M = M; g.N = N; g.K = K;
+    g.epilogue = sw ? EPI_SWIGLU_T : epilogue == SPEC_GEMM_ADD ? EPI_ADD_F32 : EPI_STORE_F32;
+    g.group_offsets = group_offsets; g.n_groups = n_groups; g.w_group_stride = (int64_t)N * K; g.m_upper = M;
+    g.force_max_rows = tile_rows; g.force_cols = tile_cols;
     HIPCHK(nullptr, launch_gemm_mfma_bf16(g, (hipStream_t)stream));
     return SPEC_OK;
 }

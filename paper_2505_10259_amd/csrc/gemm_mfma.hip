@@ -926,7 +926,7 @@ hipError_t launch_gemm_mfma_bf16(const GemmArgs& a, hipStream_t st) {
     if (a.epilogue == EPI_ROPE_KV && (a.group_offsets || a.rope.geom.head_dim != 128 || a.N % 128 != 0))
         return hipErrorInvalidValue;
     TileChoice t = choose_tiles(a);
-    if (a.force_max_rows > 0) { t.max_rows = a.force_max_rows; t.ni = 2 * a.force_wn_t; }
+    if (a.force_max_rows > 0) { t.max_rows = a.force_max_rows; t.ni = a.force_cols / 32; }
     if (a.epilogue == EPI_ROPE_KV) t = choose_wide(a);
     return launch_gemm_tiles(a, t.ni, t.max_rows, expected_rows(a) <= t.max_rows, st);
 }

@@ -88,6 +88,72 @@ def test_gemm_bf16_tile_choice_changes_no_bit(M, N, K):
     assert ((C[rows].double() - ref).abs().max() < 2e-4 * np.sqrt(K) * 0.05).item()
 
 
+# heights of one, three, five and eight 32-row units; contractions of one slab, two, one short of a tile's LDS stages, as
+# many, one more, and two rounds of them and one
+@pytest.mark.parametrize("tile_rows", [32, 96, 160, 256])
+@pytest.mark.parametrize("epilogue,tile_cols", [("add", 32), ("add", 64), ("add", 128), ("store", 32), ("store", 64), ("store", 128),
+                                                ("swiglu", 128)])
+def test_gemm_narrow_tiles_with_every_epilogue_change_no_bit(tile_rows, epilogue, tile_cols):
+    """Narrow tiles at ragged rows and columns against 256-column tiles, bit for bit, and those against float64."""
+    import torch
+    import paper_2505_10259_amd as P
+    epi = {"store": P.SPEC_GEMM_STORE, "add": P.SPEC_GEMM_ADD, "swiglu": P.SPEC_GEMM_SWIGLU}[epilogue]
+    g = torch.Generator("cuda").manual_seed(tile_rows + tile_cols)
+    mi, ni = tile_rows // 32, tile_cols // 32
+    stages = min(16, max(3, 160 * 1024 // ((32 * mi + 32 * ni) * 128)))
+    for slabs in sorted({1, 2, stages - 1, stages, stages + 1, 2 * stages + 1}):
+        M, N, K = 2 * tile_rows + 17, 2 * 256 + tile_cols // 2 + 12, 64 * slabs
+        A = torch.randn(M, K, device="cuda", generator=g).bfloat16()
+        W = (torch.randn(2, N, K, device="cuda", generator=g) * 0.05).bfloat16()
+        W3 = W[1] if epilogue == "swiglu" else None
+        out = []
+        for rows, cols in ((tile_rows, tile_cols), (256, 256)):
+            C = torch.full((M, N), 0.25, device="cuda", dtype=torch.bfloat16 if epilogue == "swiglu" else torch.float32)
+            P.spec_debug_gemm_epilogue(A, W[0], W3, C, None, 0, M, N, K, epi, rows, cols)
+            torch.cuda.synchronize()
+            out.append(C)
+        assert torch.equal(out[0], out[1]), slabs
+        x = A.double() @ W[0].double().t()
+        if epilogue == "swiglu":
+            x = torch.nn.functional.silu(x) * (A.double() @ W[1].double().t())
+            assert ((out[1].double() - x).abs() <= 2.0 ** -8 * x.abs() + 2e-4 * np.sqrt(K)).all()       # one bf16 rounding
+        else:
+            x = x + (0.25 if epilogue == "add" else 0.0)
+            # f32 sums of K products: error below K * 2^-24 of the sum of magnitudes, far less for random signs
+            assert (out[1].double() - x).abs().max().item() < 2e-4 * np.sqrt(K) * 0.05 + 2.0 ** -22
+
+
+# 36 column tiles for each of the groups that have rows: an XCD's list is longer than its 32 units by a few tiles, which are cut
+# into column halves where one row tile reads the weights; the last column tile is ragged on either side of its middle
+@pytest.mark.parametrize("epilogue", ["store", "add", "swiglu"])
+@pytest.mark.parametrize("short_by", [32, 160])
+@pytest.mark.parametrize("sizes", [(80, 80, 80, 80, 80, 80, 80, 80), (5, 128, 0, 97, 64, 17, 33, 96)])
+def test_gemm_column_halves_change_no_bit(epilogue, short_by, sizes):
+    """Groups of at most 128 rows (some without any) in one launch against every group by itself."""
+    import torch
+    import paper_2505_10259_amd as P
+    epi = {"store": P.SPEC_GEMM_STORE, "add": P.SPEC_GEMM_ADD, "swiglu": P.SPEC_GEMM_SWIGLU}[epilogue]
+    g = torch.Generator("cuda").manual_seed(short_by)
+    live = sum(1 for n in sizes if n)
+    cols = 128 if epilogue == "swiglu" else 256                # outputs per tile
+    N = -(-36 * 8 // live) * cols - (short_by // 2 if epilogue == "swiglu" else short_by)
+    M, K, G = sum(sizes), 192, len(sizes)
+    A = torch.randn(M, K, device="cuda", generator=g).bfloat16()
+    W = (torch.randn(2, G, N, K, device="cuda", generator=g) * 0.05).bfloat16()
+    W3 = W[1] if epilogue == "swiglu" else None
+    off = torch.tensor([0] + list(np.cumsum(sizes)), dtype=torch.int32, device="cuda")
+    C = torch.full((M, N), 0.25, device="cuda", dtype=torch.bfloat16 if epilogue == "swiglu" else torch.float32)
+    D = C.clone()
+    P.spec_debug_gemm_epilogue(A, W[0], W3, C, off, G, M, N, K, epi, 128, 256)
+    b = 0
+    for i, n in enumerate(sizes):
+        if n:
+            P.spec_debug_gemm_epilogue(A[b:b + n], W[0, i], W[1, i] if W3 is not None else None, D[b:b + n], None, 0, n, N, K, epi, 256, 256)
+        b += n
+    torch.cuda.synchronize()
+    assert torch.equal(C, D)
+
+
 # small plain tiles (8 x 32, steps of 256) with ragged rows, columns and contractions, unaligned rows (K odd), and
 # the sizes on either side of the line to the 64 x 64 tiles
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (8, 32, 128), (9, 33, 129), (20, 768, 256), (4, 256, 1024), (7, 100, 255), (3, 40, 257),
