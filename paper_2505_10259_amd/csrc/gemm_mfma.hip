@@ -862,7 +862,10 @@ TileChoice choose_wide(const GemmArgs& a) {
         const double cost = (double)((jobs + 255) / 256) * ((rt + 31) / 32 + 3);
         if (best == 0 || cost < best - 1e-9) { best = cost; t.max_rows = cand; }
     }
-    if (r <= 128) t.max_rows = 128;      // one row tile (see HALVES_COLS)
+    // One row tile of at most 128 rows (see HALVES_COLS).  The groups of a routed product differ: with r their average and 4 %,
+    // the largest of eight passes 128 rows often where r does, and each one that does adds a round of tiles (8x22B shape,
+    // 495 rows, r = 128: gate/up and down 730 + 398 us with this limit, 639 + 356 with the one found above).
+    if (r <= (a.group_offsets ? 112 : 128)) t.max_rows = 128;
     t.cost = tile_cost(a, 8, t.max_rows);
     return t;
 }

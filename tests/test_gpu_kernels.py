@@ -127,9 +127,11 @@ def test_gemm_narrow_tiles_with_every_epilogue_change_no_bit(tile_rows, epilogue
 # into column halves where one row tile reads the weights; the last column tile is ragged on either side of its middle
 @pytest.mark.parametrize("epilogue", ["store", "add", "swiglu"])
 @pytest.mark.parametrize("short_by", [32, 160])
-@pytest.mark.parametrize("sizes", [(80, 80, 80, 80, 80, 80, 80, 80), (5, 128, 0, 97, 64, 17, 33, 96)])
+@pytest.mark.parametrize("sizes", [(80, 80, 80, 80, 80, 80, 80, 80), (5, 128, 0, 97, 64, 17, 33, 96),
+                                   (131, 110, 128, 97, 125, 140, 118, 127)])
 def test_gemm_column_halves_change_no_bit(epilogue, short_by, sizes):
-    """Groups of at most 128 rows (some without any) in one launch against every group by itself."""
+    """Groups of at most 128 rows (some without any) in one launch against every group by itself; groups on either side of
+    128 rows as the launcher cuts them."""
     import torch
     import paper_2505_10259_amd as P
     epi = {"store": P.SPEC_GEMM_STORE, "add": P.SPEC_GEMM_ADD, "swiglu": P.SPEC_GEMM_SWIGLU}[epilogue]
@@ -144,7 +146,8 @@ def test_gemm_column_halves_change_no_bit(epilogue, short_by, sizes):
     off = torch.tensor([0] + list(np.cumsum(sizes)), dtype=torch.int32, device="cuda")
     C = torch.full((M, N), 0.25, device="cuda", dtype=torch.bfloat16 if epilogue == "swiglu" else torch.float32)
     D = C.clone()
-    P.spec_debug_gemm_epilogue(A, W[0], W3, C, off, G, M, N, K, epi, 128, 256)
+    forced = (128, 256) if max(sizes) <= 128 else (0, 0)
+    P.spec_debug_gemm_epilogue(A, W[0], W3, C, off, G, M, N, K, epi, *forced)
     b = 0
     for i, n in enumerate(sizes):
         if n:
