@@ -1176,8 +1176,10 @@ int spec_prefill(spec_ctx* c, int sub, const int32_t* tokens, const int32_t* cu_
         };
         size_t need = carve(false, nullptr, nullptr);
         if (c->has_draft) need = std::max(need, carve(true, nullptr, nullptr));
-        // Short prefills (a few requests) keep their workspace for the next call: allocating and freeing it took
-        // longer than some of their layers.  Larger ones give it back at the end.
+        // Short prefills (a few requests) keep their workspace for the next call, larger ones give it back at the end.
+        // hipMalloc and hipFree together take 25 us up to 64 MB, 250 us from 128 MB to 1 GB and 520 us at 2 to 4 GB: the
+        // 256 MB of 2300 rows of the 8x7B shape take 250 us, a tenth of a 4-layer prefill of 333 rows and 0.4 % of a
+        // 32-layer one of 2300.
         constexpr size_t KEEP_BYTES = (size_t)256 << 20;
         char* ws = nullptr;
         void* temp = nullptr;

@@ -888,8 +888,14 @@ TileChoice choose_tiles(const GemmArgs& a) {
 
 }  // namespace
 
-// the kernel for tiles of 32*ni columns (ni 8, 4, 2, 1 as the epilogue has them); nt: no weight is read by two
-// row tiles
+// The kernel for tiles of 32*ni columns (ni 8, 4, 2, 1 as the epilogue has them); nt: no weight is read by two
+// row tiles of the expected height.  The hint is for weights that come from HBM, as those of a target or draft beyond the
+// 256 MB of last-level cache do: up to 32 rows, 100 to 200 MB of weights, 21 to 40 us with it and 24 to 44 without.  A
+// single matrix of 100 to 250 MB used over and over by itself would stay in that cache without it (16384 x 4096 weights,
+// 5 rows: 27 against 23 us; below 64 MB no difference).  Routing that gives an expert more rows than expected, so that
+// two row tiles stream its weights with the hint, does not undo the gain: 320 rows, us per layer with routing uniform /
+// every second row on one expert / all rows on one, 8x7B shape 676 / 783 / 768 before the hint and the narrow tiles,
+// 604 / 653 / 745 now; 8x22B shape 1124 / 1310 / 1352 and 978 / 1034 / 1089.
 template <int EPI, int NI>
 hipError_t launch_ni(const GemmArgs& a, int ni, int max_rows, bool nt, hipStream_t st) {
     if constexpr (NI > (EPI == EPI_SWIGLU_T ? 4 : EPI == EPI_ROPE_KV ? 8 : 1)) {
