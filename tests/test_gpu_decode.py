@@ -414,7 +414,7 @@ def test_prefill_workspace_is_no_larger_than_its_rows_need(dtype):
     qkv = 4 * (hd + 2 * shp.n_kv_heads * shp.head_dim)
     per_row = 4 * d + 4 + 8 * (shp.head_dim // 2) + (pages + 2) * 4 // Q + 1 + es * d + 8 * d + 32 + \
         max(2 * es * hd + qkv, 2 * es * shp.d_ff)
-    assert held <= rows * per_row + (4 << 20), (held, rows * per_row)
+    assert held <= rows * per_row + (8 << 20), (held, rows * per_row)      # (allocations come in steps of 2 MB; apart: 17 and 29 MB more)
 
 
 def test_prefill_on_either_side_of_the_projection_with_its_own_rotary_kernel():
