@@ -340,6 +340,14 @@ enum { SPEC_GEMM_STORE = 0, SPEC_GEMM_ADD = 1, SPEC_GEMM_SWIGLU = 2 };
 int spec_debug_gemm_epilogue(const void* A_dev, const void* W_dev, const void* W3_dev, void* C_dev,
                              const int32_t* group_offsets_dev, int n_groups, int M, int N, int K, int epilogue,
                              int tile_rows, int tile_cols, void* stream);
+/* For tests: turns a bf16 matrix [N, K] in HBM, in place, from rows into the panels that resident weights are kept as, and
+ * returns the rows of a panel (1: a matrix of these sizes stays as rows). */
+int spec_debug_weight_panels(void* W_dev, int64_t N, int64_t K, void* stream);
+/* spec_debug_gemm_epilogue with the launcher's tiles on weights that spec_debug_weight_panels has turned; plain != 0: the
+ * plain kernel. */
+int spec_debug_gemm_panels(const void* A_dev, const void* W_dev, const void* W3_dev, void* C_dev,
+                           const int32_t* group_offsets_dev, int n_groups, int M, int N, int K, int epilogue, int plain,
+                           void* stream);
 /* Measures host->HBM copy bandwidth of pinned memory: copies `bytes` from a pinned buffer `reps`
  * times with hipMemcpyAsync and returns GB/s (1e9) in *gbps — the denominator of the link
  * fraction (the paper's planner likewise profiles the CPU-GPU channel first, Section 3). */

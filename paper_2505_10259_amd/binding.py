@@ -28,7 +28,7 @@ EXPORTS = [
     "spec_debug_draft_logits", "spec_accept", "spec_philox_uniforms", "spec_layer_forward",
     "spec_debug_routing", "spec_gemm", "spec_debug_gemm", "spec_measure_link", "spec_profile_enable", "spec_profile_read",
     "spec_plan_paraspec", "spec_plan_evaluate", "spec_plan_placement", "spec_debug_force_routing",
-    "spec_layer_forward_static", "spec_debug_gemm_epilogue",
+    "spec_layer_forward_static", "spec_debug_gemm_epilogue", "spec_debug_weight_panels", "spec_debug_gemm_panels",
 ]
 PROF_CLASSES = ["norm", "qkv", "rope", "attn", "oproj", "route", "moe1", "moe2", "head", "accept", "draft"]
 
@@ -133,6 +133,8 @@ def _load() -> C.CDLL:
         "spec_gemm": (i32, [vp, vp, vp, i32, i32, i32, i32, i32, vp]),
         "spec_debug_gemm": (i32, [vp, vp, vp, i32, i32, i32, i32, i32, vp]),
         "spec_debug_gemm_epilogue": (i32, [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, vp]),
+        "spec_debug_weight_panels": (i32, [vp, i64, i64, vp]),
+        "spec_debug_gemm_panels": (i32, [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, vp]),
         "spec_measure_link": (i32, [C.c_size_t, i32, P(C.c_double)]),
         "spec_profile_enable": (i32, [vp, u32]),
         "spec_profile_read": (i32, [vp, P(C.c_double), P(i64), i32]),
@@ -364,6 +366,15 @@ def spec_debug_gemm_epilogue(A_dev, W_dev, W3_dev, C_dev, group_offsets_dev, n_g
                              stream=None) -> None:
     _check(lib.spec_debug_gemm_epilogue(_ptr(A_dev), _ptr(W_dev), _ptr(W3_dev), _ptr(C_dev), _ptr(group_offsets_dev), n_groups,
                                         M, N, K, epilogue, tile_rows, tile_cols, stream))
+
+
+def spec_debug_weight_panels(W_dev, N, K, stream=None) -> int:
+    return _check(lib.spec_debug_weight_panels(_ptr(W_dev), N, K, stream))
+
+
+def spec_debug_gemm_panels(A_dev, W_dev, W3_dev, C_dev, group_offsets_dev, n_groups, M, N, K, epilogue, plain=0, stream=None) -> None:
+    _check(lib.spec_debug_gemm_panels(_ptr(A_dev), _ptr(W_dev), _ptr(W3_dev), _ptr(C_dev), _ptr(group_offsets_dev), n_groups,
+                                      M, N, K, epilogue, plain, stream))
 
 
 def spec_measure_link(nbytes: int, reps: int = 4) -> float:

@@ -117,12 +117,36 @@ struct GemmArgs {
     const int32_t* group_offsets;   // nullable
     int n_groups;
     int64_t w_group_stride;         // elements between consecutive groups' W (and W3)
+    int w_panel;                    // log2 of the rows of a weight panel (see weight_panel_log2); 0: plain rows
     int m_upper;                    // grouped: upper bound on total rows (grid sizing)
     int m_expected;                 // grouped: expected rows per group if known (tile-height choice), else 0
     RopeKvArgs rope;                // EPI_ROPE_KV only
     int force_max_rows, force_cols; // tests: tile height limit (multiple of 32, <= 256) and weight columns per tile (256, 128, 64 or 32,
                                     // SwiGLU 256 or 128); 0 = the launcher's choice
 };
+
+// ---- weight panels ---------------------------------------------------------------------------
+// Resident bf16 matrices [N, K] are kept as panels of R = 2^log2 rows, each panel cut into slabs of 64 columns:
+// [N/R][K/64][R][64].  A panel covers the same bytes as its rows, so the layout inside a blob does not move.  The GEMM's
+// slab loads then take R x 128 B runs of HBM where plain rows give 128 B pieces a row pitch apart.  Panels of 8 are one 1 KB load
+// of a wavefront; measured on grouped products with real blobs, us as plain rows / panels of 4 / of 8 / of 16 / of 32:
+//   gate/up  K = 4096   80 rows an expert 328 / 293 / 303 / 325 / 322    224 rows 418 / 380 / 404 / 426 / 420
+//            K = 6144   20 rows 484 / 486 / 466 / 479 / 482              224 rows 728 / 690 / 675 / 698 / 690
+//   down     K = 14336  20 rows 155 / 141 / 138 / 138 / 140              80 rows 175 / 159 / 156 / 157 / 158
+//            K = 16384  20 rows 305 / 270 / 263 / 260 / 263              224 rows 380 / 346 / 353 / 355 / 359
+// so panels of 4 up to K = 4096 and of 8 above.  (Rotating the slabs of a panel by its position gave nothing.)
+constexpr int PANEL_MAX_K = 16384;     // a panel is turned in the registers of one workgroup
+__host__ __device__ inline int weight_panel_log2(int64_t N, int64_t K) {
+    if (K % 64 != 0 || K > PANEL_MAX_K || N % 8 != 0) return 0;
+    return K <= 4096 ? 2 : 3;
+}
+// element (n, k) of a matrix of row length K
+__host__ __device__ inline int64_t weight_elem(int64_t n, int64_t k, int64_t K, int log2) {
+    if (log2 == 0) return n * K + k;
+    return ((n >> log2) * (K >> 6) + (k >> 6) << (log2 + 6)) + ((n & ((1 << log2) - 1)) << 6) + (k & 63);
+}
+// rows -> panels, in place (bf16; 16-byte aligned; log2 from weight_panel_log2, not 0)
+hipError_t launch_weight_panels(void* W, int64_t N, int64_t K, int log2, hipStream_t st);
 
 // launchers (kernels_*.hip) -------------------------------------------------------------------
 hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st);

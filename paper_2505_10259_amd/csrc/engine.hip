@@ -95,6 +95,14 @@ struct Workspace {
 };
 
 struct Piece { size_t off, bytes; };               // byte range of a layer blob
+// Weights in HBM: a blob (or a part of one), and whether its matrices are panels (see common.h).  Resident ones of a bf16
+// context with MFMA kernels are, pieces in a staging slot lie there as they crossed the link.
+struct Weights {
+    const char* p = nullptr;
+    bool panels = false;
+    const void* at(int64_t elems, size_t es) const { return p + elems * (int64_t)es; }
+    int panel(int64_t N, int64_t K) const { return panels ? weight_panel_log2(N, K) : 0; }
+};
 struct Item { int layer, piece; bool last; };      // `last`: last streamed piece of its layer
 
 struct Sub {
@@ -146,6 +154,7 @@ struct spec_ctx {
     std::vector<hipEvent_t> ev_ready, ev_free;
     int64_t copies_issued = 0, uses_done = 0;
     size_t blob_bytes = 0;
+    bool panels = false;                  // resident matrices are kept as panels
     void* d_globals = nullptr;
     // draft weights
     std::vector<void*> d_draft_layers;
@@ -369,8 +378,8 @@ int prefetch(spec_ctx* c) {
 
 // HBM address of piece `piece` of `layer` for the kernels enqueued next on the compute stream: the
 // pinned copy, or the staging slot once its copy has landed (the compute stream waits, not the host)
-int acquire_piece(spec_ctx* c, int layer, int piece, const char** base) {
-    if (c->piece_ptr[layer][piece]) { *base = (const char*)c->piece_ptr[layer][piece]; return SPEC_OK; }
+int acquire_piece(spec_ctx* c, int layer, int piece, Weights* base) {
+    if (c->piece_ptr[layer][piece]) { *base = Weights{(const char*)c->piece_ptr[layer][piece], c->panels}; return SPEC_OK; }
     const int ns = (int)c->ring.size();
     const int64_t j = c->uses_done;
     const Item& expect = c->items[(size_t)(j % (int64_t)c->items.size())];
@@ -393,7 +402,7 @@ int acquire_piece(spec_ctx* c, int layer, int piece, const char** base) {
     }
     const int slot = (int)(j % ns);
     HIPCHK(c, hipStreamWaitEvent(c->s_compute, c->ev_ready[slot], 0));
-    *base = (const char*)c->ring[slot];
+    *base = Weights{(const char*)c->ring[slot], false};
     return SPEC_OK;
 }
 
@@ -434,14 +443,14 @@ inline void* kv_layer_ptr(void* pool, const KvGeom& g, int layer, size_t es) {
 // the expert products (all experts in two grouped launches, or one expert at a time) and the combine.
 //
 // `pending`: on entry, true if the previous layer left its MoE output uncombined in ws.y.
-int layer_qkv(spec_ctx* c, const spec_model_shape& s, const Layout& L, const char* Wb, Workspace& w,
+int layer_qkv(spec_ctx* c, const spec_model_shape& s, const Layout& L, const Weights& Wb, Workspace& w,
               const RowSet& r, void* kv_layer, const KvGeom& geom, const int32_t* page_table,
               bool* pending, hipStream_t st) {
     const int dt = s.dtype;
     const size_t es = esize(dt);
     const int d = s.d_model, T = r.T;
     const int qkv_rows = (s.n_q_heads + 2 * s.n_kv_heads) * s.head_dim;
-    auto W = [&](int64_t off) { return (const void*)(Wb + off * es); };
+    auto W = [&](int64_t off) { return Wb.at(off, es); };
 
     { ProfScope ps(c, SPEC_PROF_NORM, st);
       HIPCHK(c, launch_combine_norm(r.x, *pending ? w.y : nullptr, w.r_wts, w.slots, W(L.g1), w.h, T, d,
@@ -449,6 +458,7 @@ int layer_qkv(spec_ctx* c, const spec_model_shape& s, const Layout& L, const cha
     *pending = false;
     GemmArgs g{};
     g.A = w.h; g.lda = d; g.W = W(L.wqkv); g.C = w.qkv; g.ldc = qkv_rows; g.M = T; g.N = qkv_rows; g.K = d;
+    g.w_panel = Wb.panel(qkv_rows, d);
     // bf16 MFMA path with 128-wide heads: rotation, q store and KV append happen in the projection's
     // epilogue (no f32 qkv round trip) unless the row count asks for tiles narrower than a pair of heads;
     // otherwise projection to f32, then the rope/append kernel.  The two bf16 ways give the same bits.
@@ -476,7 +486,7 @@ int layer_qkv(spec_ctx* c, const spec_model_shape& s, const Layout& L, const cha
     return SPEC_OK;
 }
 
-int layer_attn(spec_ctx* c, const spec_model_shape& s, const Layout& L, const char* Wb, Workspace& w,
+int layer_attn(spec_ctx* c, const spec_model_shape& s, const Layout& L, const Weights& Wb, Workspace& w,
                const RowSet& r, void* kv_layer, const KvGeom& geom, const int32_t* page_table,
                bool* pending, hipStream_t st) {
     int rc = layer_qkv(c, s, L, Wb, w, r, kv_layer, geom, page_table, pending, st);
@@ -489,20 +499,20 @@ int layer_attn(spec_ctx* c, const spec_model_shape& s, const Layout& L, const ch
     a.scale = 1.0f / sqrtf((float)s.head_dim);
     { ProfScope ps(c, SPEC_PROF_ATTN, st); HIPCHK(c, attention(c, a, dt, st)); }
     GemmArgs g{};
-    g.A = w.att; g.lda = hd; g.W = Wb + L.wo * esize(dt); g.C = r.x; g.ldc = d; g.M = T; g.N = d; g.K = hd;
-    g.epilogue = EPI_ADD_F32;
+    g.A = w.att; g.lda = hd; g.W = Wb.at(L.wo, esize(dt)); g.C = r.x; g.ldc = d; g.M = T; g.N = d; g.K = hd;
+    g.epilogue = EPI_ADD_F32; g.w_panel = Wb.panel(d, hd);
     { ProfScope ps(c, SPEC_PROF_OPROJ, st); HIPCHK(c, gemm(c, g, dt, st)); }
     return SPEC_OK;
 }
 
 // post-attention norm of rows r.x into w.h and, for MoE layers, routing and the expert-sorted row order
-int layer_route(spec_ctx* c, const spec_model_shape& s, const Layout& L, const char* Wb, Workspace& w,
+int layer_route(spec_ctx* c, const spec_model_shape& s, const Layout& L, const Weights& Wb, Workspace& w,
                 const RowSet& r, hipStream_t st) {
     if (s.attn_only) return SPEC_OK;
     const int dt = s.dtype;
     const size_t es = esize(dt);
     const int d = s.d_model, T = r.T;
-    auto W = [&](int64_t off) { return (const void*)(Wb + off * es); };
+    auto W = [&](int64_t off) { return Wb.at(off, es); };
     // post-attention norm; for MoE layers the router logits are taken in the same kernel while the
     // normalised row is still in registers (the plain-kernel mode keeps the two-kernel form)
     const bool fused_route = s.n_experts > 0 && !(c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS) &&
@@ -520,7 +530,7 @@ int layer_route(spec_ctx* c, const spec_model_shape& s, const Layout& L, const c
     return SPEC_OK;
 }
 
-int layer_front(spec_ctx* c, const spec_model_shape& s, const Layout& L, const char* Wb, Workspace& w,
+int layer_front(spec_ctx* c, const spec_model_shape& s, const Layout& L, const Weights& Wb, Workspace& w,
                 const RowSet& r, void* kv_layer, const KvGeom& geom, const int32_t* page_table,
                 bool* pending, hipStream_t st) {
     int rc = layer_attn(c, s, L, Wb, w, r, kv_layer, geom, page_table, pending, st);
@@ -531,34 +541,35 @@ int layer_front(spec_ctx* c, const spec_model_shape& s, const Layout& L, const c
 // gate, up, down of one expert are contiguous); n_exp experts starting there are applied, each to its
 // own rows of the expert-sorted order, so any split into launches gives the same result.  A dense FFN
 // (n_experts == 0) is the single "expert" 0 and adds straight into the residual stream.
-int layer_experts(spec_ctx* c, const spec_model_shape& s, const Layout& L, const char* We, int first, int n_exp,
+int layer_experts(spec_ctx* c, const spec_model_shape& s, const Layout& L, const Weights& We, int first, int n_exp,
                   Workspace& w, const RowSet& r, hipStream_t st) {
     const int dt = s.dtype;
     const size_t es = esize(dt);
     const int d = s.d_model, T = r.T;
-    const void* W1 = We;
-    const void* W3 = We + (L.w3 - L.w1) * es;
-    const void* W2 = We + (L.w2 - L.w1) * es;
+    const void* W1 = We.p;
+    const void* W3 = We.at(L.w3 - L.w1, es);
+    const void* W2 = We.at(L.w2 - L.w1, es);
+    const int up_panel = We.panel(s.d_ff, d), down_panel = We.panel(d, s.d_ff);
     GemmArgs g{};
     if (s.n_experts > 0) {
         g.A = w.h; g.lda = d; g.a_rows = w.perm; g.W = W1; g.W3 = W3; g.C = w.u; g.ldc = s.d_ff;
-        g.M = 2 * T; g.N = s.d_ff; g.K = d; g.epilogue = EPI_SWIGLU_T;
+        g.M = 2 * T; g.N = s.d_ff; g.K = d; g.epilogue = EPI_SWIGLU_T; g.w_panel = up_panel;
         g.group_offsets = w.offsets + first; g.n_groups = n_exp; g.w_group_stride = L.expert_stride;
         g.m_upper = 2 * T; g.m_expected = std::max(1, 2 * T / s.n_experts);
         { ProfScope ps(c, SPEC_PROF_MOE1, st); HIPCHK(c, gemm(c, g, dt, st)); }
         g = GemmArgs{};
         g.A = w.u; g.lda = s.d_ff; g.W = W2; g.C = w.y; g.ldc = d; g.M = 2 * T; g.N = d; g.K = s.d_ff;
-        g.epilogue = EPI_STORE_F32;
+        g.epilogue = EPI_STORE_F32; g.w_panel = down_panel;
         g.group_offsets = w.offsets + first; g.n_groups = n_exp; g.w_group_stride = L.expert_stride;
         g.m_upper = 2 * T; g.m_expected = std::max(1, 2 * T / s.n_experts);
         { ProfScope ps(c, SPEC_PROF_MOE2, st); HIPCHK(c, gemm(c, g, dt, st)); }
     } else {
         g.A = w.h; g.lda = d; g.W = W1; g.W3 = W3; g.C = w.u; g.ldc = s.d_ff; g.M = T; g.N = s.d_ff;
-        g.K = d; g.epilogue = EPI_SWIGLU_T;
+        g.K = d; g.epilogue = EPI_SWIGLU_T; g.w_panel = up_panel;
         { ProfScope ps(c, SPEC_PROF_MOE1, st); HIPCHK(c, gemm(c, g, dt, st)); }
         g = GemmArgs{};
         g.A = w.u; g.lda = s.d_ff; g.W = W2; g.C = r.x; g.ldc = d; g.M = T; g.N = d; g.K = s.d_ff;
-        g.epilogue = EPI_ADD_F32;
+        g.epilogue = EPI_ADD_F32; g.w_panel = down_panel;
         { ProfScope ps(c, SPEC_PROF_MOE2, st); HIPCHK(c, gemm(c, g, dt, st)); }
     }
     return SPEC_OK;
@@ -574,12 +585,12 @@ int layer_combine(spec_ctx* c, const spec_model_shape& s, Workspace& w, const Ro
 
 // whole layer from one contiguous blob.  On exit *pending is true if the MoE output is left
 // uncombined in ws.y (defer == true); with defer == false the combine is applied before returning.
-int layer_body(spec_ctx* c, const spec_model_shape& s, const Layout& L, const char* Wb, Workspace& w,
+int layer_body(spec_ctx* c, const spec_model_shape& s, const Layout& L, const Weights& Wb, Workspace& w,
                const RowSet& r, void* kv_layer, const KvGeom& geom, const int32_t* page_table,
                bool* pending, bool defer, hipStream_t st) {
     int rc = layer_front(c, s, L, Wb, w, r, kv_layer, geom, page_table, pending, st);
     if (rc || s.attn_only) return rc;
-    if ((rc = layer_experts(c, s, L, Wb + L.w1 * esize(s.dtype), 0, std::max(1, s.n_experts), w, r, st))) return rc;
+    if ((rc = layer_experts(c, s, L, Weights{Wb.p + L.w1 * esize(s.dtype), Wb.panels}, 0, std::max(1, s.n_experts), w, r, st))) return rc;
     if (s.n_experts > 0) {
         *pending = true;
         if (!defer) {
@@ -596,7 +607,7 @@ int target_layer(spec_ctx* c, int l, Workspace& w, const RowSet& r, void* kv_lay
                  bool* pending, bool defer) {
     const spec_model_shape& s = c->tgt;
     hipStream_t st = c->s_compute;
-    const char* Wb;
+    Weights Wb;
     int rc;
     if (layer_is_whole(c, l)) {
         if ((rc = acquire_piece(c, l, 0, &Wb))) return rc;
@@ -649,7 +660,7 @@ int draft_layers(spec_ctx* c, Sub& sb, Workspace& w, int T, int n_new, bool want
     RowSet r{w.x, w.row_pos, w.cs, T, n_new, sb.B};
     bool pending = false;
     for (int l = 0; l < c->drf.n_layers; ++l) {
-        int rc = layer_body(c, c->drf, c->dl, (const char*)c->d_draft_layers[l], w, r,
+        int rc = layer_body(c, c->drf, c->dl, Weights{(const char*)c->d_draft_layers[l], c->panels}, w, r,
                             kv_layer_ptr(sb.kv_d, c->gd, l, c->es), c->gd, sb.page_table, &pending, true, st);
         if (rc) return rc;
     }
@@ -828,6 +839,34 @@ void spec_destroy(spec_ctx* c) {
     delete c;
 }
 
+// Turns the matrices of a resident copy into panels: the part in front of the experts, one expert, the LM head
+static int panels_of(spec_ctx* c, char* base, int64_t off, int64_t N, int64_t K) {
+    const int log2 = weight_panel_log2(N, K);
+    if (log2) HIPCHK(c, launch_weight_panels(base + off * (int64_t)c->es, N, K, log2, nullptr));
+    return SPEC_OK;
+}
+static int front_to_panels(spec_ctx* c, char* blob, const spec_model_shape& s, const Layout& L) {
+    if (!c->panels) return SPEC_OK;
+    const int64_t hd = (int64_t)s.n_q_heads * s.head_dim, qkv_rows = hd + 2 * (int64_t)s.n_kv_heads * s.head_dim;
+    int rc = panels_of(c, blob, L.wqkv, qkv_rows, s.d_model);
+    return rc ? rc : panels_of(c, blob, L.wo, s.d_model, hd);
+}
+static int expert_to_panels(spec_ctx* c, char* expert, const spec_model_shape& s, const Layout& L) {
+    if (!c->panels) return SPEC_OK;
+    int rc = panels_of(c, expert, 0, s.d_ff, s.d_model);
+    if (!rc) rc = panels_of(c, expert, L.w3 - L.w1, s.d_ff, s.d_model);
+    return rc ? rc : panels_of(c, expert, L.w2 - L.w1, s.d_model, s.d_ff);
+}
+static int layer_to_panels(spec_ctx* c, char* blob, const spec_model_shape& s, const Layout& L) {
+    int rc = front_to_panels(c, blob, s, L);
+    for (int e = 0; !rc && !s.attn_only && e < std::max(1, s.n_experts); ++e)
+        rc = expert_to_panels(c, blob + (L.w1 + e * L.expert_stride) * (int64_t)c->es, s, L);
+    return rc;
+}
+static int head_to_panels(spec_ctx* c, char* globals) {
+    return c->panels ? panels_of(c, globals, c->gl.head, c->tgt.vocab, c->tgt.d_model) : SPEC_OK;
+}
+
 static int init_impl(spec_ctx* c, const spec_host_weights* tw, const spec_host_weights* dw) {
     const spec_model_shape& t = c->tgt;
     const spec_runtime_cfg& cfg = c->cfg;
@@ -847,6 +886,7 @@ static int init_impl(spec_ctx* c, const spec_host_weights* tw, const spec_host_w
     c->gl = make_global_layout(t);
     c->blob_bytes = (size_t)c->tl.total * c->es;
     if (c->has_draft) c->dl = make_layout(c->drf);
+    c->panels = t.dtype == SPEC_BF16 && !(cfg.flags & SPEC_FLAG_SIMPLE_KERNELS);
 
     auto mk_stream = [&](void* given, hipStream_t* s, bool* own) -> int {
         if (given) { *s = (hipStream_t)given; *own = false; return SPEC_OK; }
@@ -878,6 +918,7 @@ static int init_impl(spec_ctx* c, const spec_host_weights* tw, const spec_host_w
             char* p;
             if ((rc = dev_alloc(c, &p, c->blob_bytes))) return rc;
             HIPCHK(c, hipMemcpy(p, c->host_layers[l], c->blob_bytes, hipMemcpyHostToDevice));
+            if ((rc = layer_to_panels(c, p, t, c->tl))) return rc;
             c->resident[l] = p;
             for (int q = 0; q < np; ++q) c->piece_ptr[l][q] = p + c->pieces[q].off;
             continue;
@@ -888,6 +929,7 @@ static int init_impl(spec_ctx* c, const spec_host_weights* tw, const spec_host_w
                 if ((rc = dev_alloc(c, &p, c->pieces[q].bytes))) return rc;
                 HIPCHK(c, hipMemcpy(p, (const char*)c->host_layers[l] + c->pieces[q].off, c->pieces[q].bytes,
                                     hipMemcpyHostToDevice));
+                if ((rc = q == 0 ? front_to_panels(c, p, t, c->tl) : expert_to_panels(c, p, t, c->tl))) return rc;
                 c->piece_ptr[l][q] = p;
             } else {
                 if (!c->items.empty() && c->items.back().layer == l) c->items.back().last = false;
@@ -916,6 +958,7 @@ static int init_impl(spec_ctx* c, const spec_host_weights* tw, const spec_host_w
         size_t gb = (size_t)c->gl.total * c->es;
         if ((rc = dev_alloc(c, &p, gb))) return rc;
         HIPCHK(c, hipMemcpy(p, tw->global_blob, gb, hipMemcpyHostToDevice));
+        if ((rc = head_to_panels(c, p))) return rc;
         c->d_globals = p;
     }
     if (c->has_draft) {
@@ -925,6 +968,7 @@ static int init_impl(spec_ctx* c, const spec_host_weights* tw, const spec_host_w
             char* p;
             if ((rc = dev_alloc(c, &p, lb))) return rc;
             HIPCHK(c, hipMemcpy(p, dw->layer_blobs[l], lb, hipMemcpyHostToDevice));
+            if ((rc = layer_to_panels(c, p, c->drf, c->dl))) return rc;
             c->d_draft_layers.push_back(p);
         }
         if (dw->global_blob == tw->global_blob) { c->d_draft_globals = c->d_globals; c->draft_globals_shared = true; }
@@ -933,6 +977,7 @@ static int init_impl(spec_ctx* c, const spec_host_weights* tw, const spec_host_w
             size_t gb = (size_t)c->gl.total * c->es;
             if ((rc = dev_alloc(c, &p, gb))) return rc;
             HIPCHK(c, hipMemcpy(p, dw->global_blob, gb, hipMemcpyHostToDevice));
+            if ((rc = head_to_panels(c, p))) return rc;
             c->d_draft_globals = p;
             c->hbm_weight_bytes += (int64_t)gb;
         }
@@ -1226,14 +1271,14 @@ int spec_prefill(spec_ctx* c, int sub, const int32_t* tokens, const int32_t* cu_
             const int ne = std::max(1, s.n_experts);
             bool pending = false;         // (one group: the experts' outputs are mixed in by the next layer's first norm)
             for (int l = 0; l < s.n_layers; ++l) {
-                const char* Wb;
+                Weights Wb;
                 int r2;
                 cur_layer = l;
                 void* kvl = kv_layer_ptr(is_draft ? sb.kv_d : sb.kv_t, geom, l, c->es);
                 // a prefill leaves nothing but keys and values: behind the last layer's, nothing is read again
                 const bool last = l == s.n_layers - 1;
                 if (is_draft || layer_is_whole(c, l)) {
-                    if (is_draft) Wb = (const char*)c->d_draft_layers[l];
+                    if (is_draft) Wb = Weights{(const char*)c->d_draft_layers[l], c->panels};
                     else if ((r2 = acquire_piece(c, l, 0, &Wb))) return r2;
                     for (int g = 0; g < n_grp; ++g) {
                         const RowSet rg = group_rows(g);
@@ -1335,6 +1380,7 @@ int spec_draft(spec_ctx* c, int sub, int k, int32_t* out_tokens) {
         GemmArgs g{};
         g.A = (const char*)w.h + (size_t)(n_new - 1) * d * c->es; g.lda = (int64_t)n_new * d;
         g.W = G + c->gl.head * c->es; g.M = B; g.N = V; g.K = d; g.epilogue = EPI_STORE_F32;
+        g.w_panel = c->panels ? weight_panel_log2(V, d) : 0;
         float* z; int64_t ld;
         if (sample) { z = sb.q_logits + (size_t)(step - 1) * V; ld = (int64_t)k * V; }
         else { z = sb.draft_logits; ld = V; }
@@ -1378,7 +1424,7 @@ int spec_verify(spec_ctx* c, int sub, const int32_t* draft_tokens, int k, int32_
     }
     GemmArgs g{};
     g.A = w.h; g.lda = d; g.W = G + c->gl.head * c->es; g.C = sb.logits; g.ldc = V; g.M = T; g.N = V; g.K = d;
-    g.epilogue = EPI_STORE_F32;
+    g.epilogue = EPI_STORE_F32; g.w_panel = c->panels ? weight_panel_log2(V, d) : 0;
     { ProfScope ps(c, SPEC_PROF_HEAD, st); HIPCHK(c, gemm(c, g, s.dtype, st)); }
     AcceptArgs a{};
     a.p_logits = sb.logits; a.q_logits = sample ? sb.q_logits : nullptr; a.draft_tokens = sb.draft_tokens;
@@ -1559,7 +1605,7 @@ static int layer_forward_impl(spec_ctx* c, int sub, int layer, const void* x_in,
         sb.forced_ids = nullptr;
     }
     bool pending = false;
-    return layer_body(c, s, c->tl, (const char*)c->resident[layer], w, r, kv_layer_ptr(sb.kv_t, c->gt, layer, c->es),
+    return layer_body(c, s, c->tl, Weights{(const char*)c->resident[layer], c->panels}, w, r, kv_layer_ptr(sb.kv_t, c->gt, layer, c->es),
                       c->gt, sb.page_table, &pending, false, st);
 }
 
@@ -1685,6 +1731,28 @@ int spec_debug_gemm_epilogue(const void* A, const void* W, const void* W3, void*
     g.group_offsets = group_offsets; g.n_groups = n_groups; g.w_group_stride = (int64_t)N * K; g.m_upper = M;
     g.force_max_rows = tile_rows; g.force_cols = tile_cols;
     HIPCHK(nullptr, launch_gemm_mfma_bf16(g, (hipStream_t)stream));
+    return SPEC_OK;
+}
+
+int spec_debug_weight_panels(void* W, int64_t N, int64_t K, void* stream) {
+    if (!W || N <= 0 || K <= 0) return fail(nullptr, SPEC_ERR_ARG, "spec_debug_weight_panels: bad arguments");
+    const int log2 = weight_panel_log2(N, K);
+    if (log2) HIPCHK(nullptr, launch_weight_panels(W, N, K, log2, (hipStream_t)stream));
+    return 1 << log2;
+}
+
+int spec_debug_gemm_panels(const void* A, const void* W, const void* W3, void* C, const int32_t* group_offsets, int n_groups,
+                           int M, int N, int K, int epilogue, int plain, void* stream) {
+    const bool sw = epilogue == SPEC_GEMM_SWIGLU;
+    if (!A || !W || !C || M <= 0 || N <= 0 || K <= 0 || (epilogue != SPEC_GEMM_STORE && epilogue != SPEC_GEMM_ADD && !sw) ||
+        sw != (W3 != nullptr) || (group_offsets ? n_groups < 1 || n_groups > 8 : n_groups != 0))
+        return fail(nullptr, SPEC_ERR_ARG, "spec_debug_gemm_panels: bad arguments");
+    GemmArgs g{};
+    g.A = A; g.lda = K; g.W = W; g.W3 = W3; g.C = C; g.ldc = N; g.M = M; g.N = N; g.K = K;
+    g.epilogue = sw ? EPI_SWIGLU_T : epilogue == SPEC_GEMM_ADD ? EPI_ADD_F32 : EPI_STORE_F32;
+    g.group_offsets = group_offsets; g.n_groups = n_groups; g.w_group_stride = (int64_t)N * K; g.m_upper = M;
+    g.w_panel = weight_panel_log2(N, K);
+    HIPCHK(nullptr, plain ? launch_gemm_simple(g, SPEC_BF16, (hipStream_t)stream) : launch_gemm_mfma_bf16(g, (hipStream_t)stream));
     return SPEC_OK;
 }
 

@@ -36,6 +36,7 @@
 //     choose_tiles); the weights carry the non-temporal hint where no second row tile reads them (8x7B-shaped gate/up
 //     product, 40 rows: 308 -> 279 us, 6.74 TB/s; a streaming read of the same buffers: 6.2 TB/s
 //     plain, 7.05 with the hint);
+//   * resident weights are panels of 4 or 8 rows (see common.h): a load then takes runs of 512 B or 1 KB of HBM;
 //   * tile order: group (expert), then bands of four row tiles, then column tile, then row tile
 //     within the band; the linear workgroup id is remapped so that each XCD (id % 8) walks one
 //     contiguous range of that order: the ~32 workgroups an XCD runs at a time form a block of about
@@ -138,6 +139,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
             asm volatile("global_load_dword %0, %1, off" : "=v"(srow[j]) : "v"(src) : "memory");
         }
     }
+    const int w_slab = 7 + a.w_panel;                // log2 of the bytes from a row's slab to its next one
     const uint32_t w3_delta = SWIGLU ? (uint32_t)(W3b - Wb) : 0u;      // launcher: 0 < W3 - W < 2^31
 #pragma unroll
     for (int j = 0; j < B_INST; ++j) {
@@ -154,7 +156,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
             n = n0 + tr;
         }
         n = n < a.N ? n : a.N - 1;
-        b_o[j] = (uint32_t)(((int64_t)n * a.K + gchunk_of(w * B_INST + j) * 8) * 2) + extra;
+        b_o[j] = (uint32_t)((weight_elem(n, 0, a.K, a.w_panel) + gchunk_of(w * B_INST + j) * 8) * 2) + extra;
     }
 
     // Direct-to-LDS loads are issued from inline assembly (the compiler's wait-count pass would make every
@@ -169,7 +171,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
     };
     auto issue_b = [&](int q, int kt, int bst) {     // load q of weight slab kt into B stage bst
         const uint32_t dst = lds0 + B_BASE + bst * B_BYTES + (wu * B_INST + q) * 1024;
-        const char* base = Wb + (int64_t)kt * 128;
+        const char* base = Wb + ((int64_t)kt << w_slab);
         if constexpr (NT) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" :: "s"(dst), "v"(b_o[q]), "s"(base) : "memory", "m0");
         else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(dst), "v"(b_o[q]), "s"(base) : "memory", "m0");
     };
@@ -359,7 +361,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
         constexpr int SA1 = (S + 1) % AST, SB1 = (S + 1) % BST;        // of slab kt+1
         constexpr int SB2 = (S + BST - 1) % BST, SA2 = S % AST;        // where the loads go
         typedef const __attribute__((address_space(3))) bf16x8_t* lds_frag;
-        const char* wbase = Wb + (int64_t)(kt + BST - 1) * 128;
+        const char* wbase = Wb + ((int64_t)(kt + BST - 1) << w_slab);
         const char* abase = Ab + (int64_t)(kt + AST) * 128;
         phase(C0{}, CNR{}, CB{},
               [&](auto r_c) {

@@ -561,7 +561,7 @@ hipError_t launch_moe_sort(const int32_t* ids, int32_t* offsets, int32_t* perm, 
 // Plain tiled GEMM (any dtype, any size): 64x64 output tile, 256 threads, 4x4 outputs each.
 // Used for f32 models; bf16 models use the MFMA kernels.
 // ---------------------------------------------------------------------------------------------
-template <typename T, bool SWIGLU>
+template <typename T, bool SWIGLU, bool PANELS>
 __global__ void __launch_bounds__(256)
 gemm_simple_kernel(GemmArgs a) {
     constexpr int BM = 64, BN = 64, BK = 16;
@@ -608,8 +608,8 @@ gemm_simple_kernel(GemmArgs a) {
             int kk = k0 + lk + q;
             As[lk + q][lr] = (asrc >= 0 && kk < a.K) ? to_f32<T>(A[asrc * a.lda + kk]) : 0.f;
             bool wv = wrow < a.N && kk < a.K;
-            Ws[lk + q][lr] = wv ? to_f32<T>(W[(int64_t)wrow * a.K + kk]) : 0.f;
-            if (SWIGLU) W3s[lk + q][lr] = wv ? to_f32<T>(W3[(int64_t)wrow * a.K + kk]) : 0.f;
+            Ws[lk + q][lr] = wv ? to_f32<T>(W[weight_elem(wrow, kk, a.K, PANELS ? a.w_panel : 0)]) : 0.f;
+            if (SWIGLU) W3s[lk + q][lr] = wv ? to_f32<T>(W3[weight_elem(wrow, kk, a.K, PANELS ? a.w_panel : 0)]) : 0.f;
         }
         __syncthreads();
 #pragma unroll
@@ -753,7 +753,7 @@ hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st) {
     if (rows <= 0 || a.N <= 0) return hipSuccess;
     const bool swiglu = a.epilogue == EPI_SWIGLU_T;
     // 64x64 tiles on fewer than half the compute units: small tiles (8 times the reads of a weight, from L2)
-    if ((int64_t)((rows + 63) / 64) * ((a.N + 63) / 64) < 128) {
+    if (!a.w_panel && (int64_t)((rows + 63) / 64) * ((a.N + 63) / 64) < 128) {
         const size_t es = dtype == SPEC_F32 ? 4 : 2;
         const uintptr_t base = (uintptr_t)a.A | (uintptr_t)a.W | (swiglu ? (uintptr_t)a.W3 : 0) | (uintptr_t)(a.w_group_stride * es);
         const int vec = base % (4 * es) == 0 && a.lda % 4 == 0 && a.K % 4 == 0;
@@ -768,9 +768,43 @@ hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st) {
     dim3 grid((a.N + 63) / 64, tiles_m);
     bool sw = a.epilogue == EPI_SWIGLU_T;
     DISPATCH_DTYPE(dtype, {
-        if (sw) hipLaunchKernelGGL((gemm_simple_kernel<T, true>), grid, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((gemm_simple_kernel<T, false>), grid, dim3(256), 0, st, a);
+        if (a.w_panel) {
+            if constexpr (sizeof(T) == 2) {
+                if (sw) hipLaunchKernelGGL((gemm_simple_kernel<T, true, true>), grid, dim3(256), 0, st, a);
+                else hipLaunchKernelGGL((gemm_simple_kernel<T, false, true>), grid, dim3(256), 0, st, a);
+            } else return hipErrorInvalidValue;
+        } else if (sw) hipLaunchKernelGGL((gemm_simple_kernel<T, true, false>), grid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((gemm_simple_kernel<T, false, false>), grid, dim3(256), 0, st, a);
     });
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------------------
+// Rows -> panels of a weight matrix, in place (see common.h): one workgroup holds a panel, at most 256 KB, in registers
+// between its reads and its writes.
+// ---------------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(1024)
+weight_panels_kernel(uint4* __restrict__ W, int K, int log2) {
+    constexpr int CHUNKS = 8 * PANEL_MAX_K / 8 / 1024;
+    const int n = (K >> 3) << log2;                      // 16-byte chunks of a panel
+    uint4* panel = W + (int64_t)blockIdx.x * n;
+    uint4 v[CHUNKS];
+#pragma unroll
+    for (int q = 0; q < CHUNKS; ++q) {
+        const int i = q * 1024 + (int)threadIdx.x;       // chunk i % 8 of row (i / 8) % R of slab i / (8 R)
+        if (i < n) v[q] = panel[((i >> 3) & ((1 << log2) - 1)) * (K >> 3) + ((i >> (3 + log2)) << 3) + (i & 7)];
+    }
+    __syncthreads();                                     // (every read of the panel has landed before the first write)
+#pragma unroll
+    for (int q = 0; q < CHUNKS; ++q) {
+        const int i = q * 1024 + (int)threadIdx.x;
+        if (i < n) panel[i] = v[q];
+    }
+}
+hipError_t launch_weight_panels(void* W, int64_t N, int64_t K, int log2, hipStream_t st) {
+    if (N <= 0) return hipSuccess;
+    if (log2 <= 0 || log2 != weight_panel_log2(N, K) || ((uintptr_t)W & 15)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(weight_panels_kernel, dim3((unsigned)(N >> log2)), dim3(1024), 0, st, (uint4*)W, (int)K, log2);
     return hipGetLastError();
 }
 

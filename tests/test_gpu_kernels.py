@@ -157,6 +157,51 @@ def test_gemm_column_halves_change_no_bit(epilogue, short_by, sizes):
     assert torch.equal(C, D)
 
 
+# panels of 4 rows (K up to 4096) and of 8, one to two hundred slabs, ragged column tiles; sizes that stay as rows
+@pytest.mark.parametrize("epilogue", ["store", "add", "swiglu"])
+@pytest.mark.parametrize("N,K,rows", [(8, 64, 4), (264, 1024, 4), (520, 4096, 4), (136, 4160, 8), (40, 16384, 8), (36, 256, 1),
+                                      (64, 16448, 1)])
+def test_gemm_weight_panels_change_no_bit(epilogue, N, K, rows):
+    """Weights turned into panels: the matrix itself against the layout written out, and the products against those of the rows."""
+    import torch
+    import paper_2505_10259_amd as P
+    G, sizes = 3, [5, 0, 70]
+    epi = {"store": P.SPEC_GEMM_STORE, "add": P.SPEC_GEMM_ADD, "swiglu": P.SPEC_GEMM_SWIGLU}[epilogue]
+    g = torch.Generator("cuda").manual_seed(N + K)
+    W = (torch.randn(2, G, N, K, device="cuda", generator=g) * 0.05).bfloat16()
+    A = torch.randn(sum(sizes), K, device="cuda", generator=g).bfloat16()
+    off = torch.tensor(np.cumsum([0] + sizes), dtype=torch.int32, device="cuda")
+    V = W.clone()
+    for i in range(2):
+        for e in range(G):
+            assert P.spec_debug_weight_panels(V[i, e], N, K) == rows
+    torch.cuda.synchronize()
+    if rows > 1:
+        assert torch.equal(V.reshape(2, G, N // rows, K // 64, rows, 64), W.reshape(2, G, N // rows, rows, K // 64, 64).transpose(4, 3))
+    else:
+        assert torch.equal(V, W)
+
+    def call(groups, plain, panels):
+        C = torch.full((len(A), N), 0.25, device="cuda", dtype=torch.bfloat16 if epilogue == "swiglu" else torch.float32)
+        w = V if panels else W
+        w = w if groups else w[:, 2]
+        args = (A, w[0], w[1] if epilogue == "swiglu" else None, C, off if groups else None, G if groups else 0, len(A), N, K, epi)
+        if panels:
+            P.spec_debug_gemm_panels(*args, plain)
+        else:
+            P.spec_debug_gemm_epilogue(*args, 0, 0)
+        torch.cuda.synchronize()
+        return C
+
+    for groups in (False, True):
+        rows_out = call(groups, 0, False)
+        assert torch.equal(call(groups, 0, True), rows_out)
+        plain = call(groups, 1, True).float()
+        # the plain kernel sums in another order: K products of about 0.05 each way, and one bf16 rounding of a SwiGLU result
+        tol = 2e-5 * np.sqrt(K) + (2.0 ** -7 * rows_out.float().abs() if epilogue == "swiglu" else 0.0)
+        assert ((plain - rows_out.float()).abs() <= tol).all()
+
+
 # small plain tiles (8 x 32, steps of 256) with ragged rows, columns and contractions, unaligned rows (K odd), and
 # the sizes on either side of the line to the 64 x 64 tiles
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (8, 32, 128), (9, 33, 129), (20, 768, 256), (4, 256, 1024), (7, 100, 255), (3, 40, 257),
