@@ -143,7 +143,7 @@ __host__ __device__ inline int weight_panel_log2(int64_t N, int64_t K) {
 // element (n, k) of a matrix of row length K
 __host__ __device__ inline int64_t weight_elem(int64_t n, int64_t k, int64_t K, int log2) {
     if (log2 == 0) return n * K + k;
-    return ((n >> log2) * (K >> 6) + (k >> 6) << (log2 + 6)) + ((n & ((1 << log2) - 1)) << 6) + (k & 63);
+    return (((n >> log2) * (K >> 6) + (k >> 6)) << (log2 + 6)) + ((n & ((1 << log2) - 1)) << 6) + (k & 63);
 }
 // rows -> panels, in place (bf16; 16-byte aligned; log2 from weight_panel_log2, not 0)
 hipError_t launch_weight_panels(void* W, int64_t N, int64_t K, int log2, hipStream_t st);

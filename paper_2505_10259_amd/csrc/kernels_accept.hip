@@ -63,9 +63,9 @@ hipError_t launch_philox_uniforms(uint64_t seed, uint32_t round, uint32_t seq_ba
 // aligned 16-byte granules (elements outside the row count as -inf), several granules per thread in flight.
 // The maximum and the normaliser of the two rows of a candidate come from one pass (running maximum per thread), the
 // draw takes one pass for the sums of runs of 64 U granules and reads again only the run that holds the
-// crossing.  What bounds it is the exponentials of one compute unit per sequence: 24 sequences of 5 candidates,
-// 65537 ids, 1255 us as 256 threads with 4-byte loads and a pass per reduction, 93 so with the candidates
-// tested at once (accept_test_generic_kernel 30, draw 61).  The normaliser's error is 1.0 x 2^-24 on average (256 threads: 3.7).
+// crossing.  What bounds it is the exponentials of one compute unit per row pair: 24 sequences of 5 candidates,
+// 65537 ids, 1255 us as 256 threads with 4-byte loads and a pass per reduction, 93 as a launch of tests and one of draws, 66 with
+// the draw in the workgroup that rejects (accept_ahead_generic_kernel).  The normaliser's error is 1.0 x 2^-24 on average (256 threads: 3.7).
 // =================================================================================================
 constexpr int WIDE_THREADS = 1024, WIDE_WAVES = WIDE_THREADS / 64, WIDE_RUNS = 1024;
 
@@ -309,30 +309,11 @@ accept_greedy_generic_kernel(AcceptArgs a) {
     }
 }
 
-__global__ void __launch_bounds__(WIDE_THREADS)
-accept_sample_generic_kernel(AcceptArgs a, int tested) {
-    __shared__ WideShared sh;
-    const int b = blockIdx.x, k = a.k, V = a.V;
-    const float* P = a.p_logits + (int64_t)b * (k + 1) * V;
-    const float* Q = a.q_logits + (int64_t)b * k * V;
-    const float it = a.inv_tau;
-    int n = tested ? a.n_accepted[b] : 0;      // tested: candidates were tested by accept_test kernels
-    float pm = 0.f, ps = 1.f, qm = 0.f, qs = 1.f;
-    // candidates are tested in order; each test needs the softmax normalisers of two rows
-    while (true) {
-        const WideRow p(P + (int64_t)n * V, V);
-        if (n == k) { wide_row_stats<false>(p, p, it, sh, &pm, &ps, nullptr, nullptr); break; }
-        wide_row_stats<true>(p, WideRow(Q + (int64_t)n * V, V), it, sh, &pm, &ps, &qm, &qs);
-        if (tested) break;
-        if (threadIdx.x == 0) sh.stop = rejects(a, b, n, pm, ps, qm, qs);
-        __syncthreads();
-        const int stop = sh.stop;
-        __syncthreads();
-        if (stop) break;
-        ++n;
-    }
-    const WideRow pr(P + (int64_t)n * V, V), qr(Q + (int64_t)(n < k ? n : 0) * V, V);
-    const float ipn = 1.0f / ps, iqn = 1.0f / qs;
+// the draw behind n kept candidates, from the residual of the two rows or (n == k) from the target's row
+__device__ inline int wide_draw(const AcceptArgs& a, int b, int n, const WideRow& pr, const WideRow& qr, float pm, float ps,
+                                float qm, float qs, WideShared& sh) {
+    const int k = a.k, V = a.V;
+    const float it = a.inv_tau, ipn = 1.0f / ps, iqn = 1.0f / qs;
     const float u = a.u_resample ? a.u_resample[b * (k + 1) + n]
                                  : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)n, 2);
     // (granules of the two rows differ where their alignments do: the residual takes q element by element then)
@@ -356,8 +337,33 @@ accept_sample_generic_kernel(AcceptArgs a, int tested) {
     int nxt = 0;
     if (n < k) nxt = wide_inverse_cdf(wres, pr.n, pr.off, u, sh, &tot);
     if (n == k || !(tot > 0.f)) nxt = wide_inverse_cdf(wp, pr.n, pr.off, u, sh, &tot);    // (p == q everywhere: the target row)
+    return nxt;
+}
+
+__global__ void __launch_bounds__(WIDE_THREADS)
+accept_sample_generic_kernel(AcceptArgs a) {
+    __shared__ WideShared sh;
+    const int b = blockIdx.x, k = a.k, V = a.V;
+    const float* P = a.p_logits + (int64_t)b * (k + 1) * V;
+    const float* Q = a.q_logits + (int64_t)b * k * V;
+    const float it = a.inv_tau;
+    int n = 0;
+    float pm = 0.f, ps = 1.f, qm = 0.f, qs = 1.f;
+    // candidates are tested in order; each test needs the softmax normalisers of two rows
+    while (true) {
+        const WideRow p(P + (int64_t)n * V, V);
+        if (n == k) { wide_row_stats<false>(p, p, it, sh, &pm, &ps, nullptr, nullptr); break; }
+        wide_row_stats<true>(p, WideRow(Q + (int64_t)n * V, V), it, sh, &pm, &ps, &qm, &qs);
+        if (threadIdx.x == 0) sh.stop = rejects(a, b, n, pm, ps, qm, qs);
+        __syncthreads();
+        const int stop = sh.stop;
+        __syncthreads();
+        if (stop) break;
+        ++n;
+    }
+    const int nxt = wide_draw(a, b, n, WideRow(P + (int64_t)n * V, V), WideRow(Q + (int64_t)(n < k ? n : 0) * V, V), pm, ps, qm, qs, sh);
     if (threadIdx.x == 0) {
-        if (a.n_accepted && !tested) a.n_accepted[b] = n;
+        if (a.n_accepted) a.n_accepted[b] = n;
         if (a.next_token) a.next_token[b] = nxt;
     }
 }
@@ -543,9 +549,9 @@ accept_sample_narrow_kernel(AcceptArgs a) {
 // t of sweep s holds ids 4096 s + 4 t .. + 3, so running sums stay in ascending id order), and every
 // reduction of that row (max, normaliser, residual total, inverse CDF) runs on the registers.  Candidates
 // tested in turn, with early exit at the first rejected one, read each row they need exactly once: (2 n + 2) rows of V
-// floats per sequence when n are kept (2 k + 1 when all are).  Candidates tested at once (accept_test_kernel) read all 2 k
-// rows, and the draw its two again.  In turn a call is bound by the dependent chain of the sequence that keeps most, about
-// 8 us a candidate at 32000 ids, not by bytes (256 sequences of 6 candidates: 117 us, 2.2 TB/s).
+// floats per sequence when n are kept (2 k + 1 when all are).  In turn a call is bound by the dependent chain of the sequence
+// that keeps most, about 8 us a candidate at 32000 ids, not by bytes (256 sequences of 6 candidates: 117 us, 2.2 TB/s); with
+// fewer sequences the candidates are tested at once (accept_ahead_kernel).
 // =================================================================================================
 constexpr int FAST_THREADS = 1024, FAST_WAVES = FAST_THREADS / 64, FAST_SWEEPS = 8;
 constexpr int FAST_MAX_V = FAST_THREADS * 4 * FAST_SWEEPS;
@@ -585,18 +591,23 @@ __device__ inline float fast_block_max(float v, FastShared& sh) {
     for (int w = 1; w < FAST_WAVES; ++w) t = fmaxf(t, sh.red[w]);
     return t;
 }
-// max and sum of exp((z - max) * inv_tau) of a row held in registers (padding is -inf: adds 0)
-__device__ inline void fast_row_stats(const float4 (&v)[FAST_SWEEPS], float inv_tau, FastShared& sh, float* out_max,
-                                      float* out_sum) {
+// max and sum of exp((z - max) * inv_tau) of a row held in registers (padding is -inf: adds 0).  KEEP: the row becomes those
+// exponentials, which a draw that follows needs again (not where candidates are tested in turn: most tests are not
+// followed by one, and writing them back costs 2 % of a call of 256 sequences)
+template <bool KEEP>
+__device__ inline void fast_row_stats(float4 (&v)[FAST_SWEEPS], float inv_tau, FastShared& sh, float* out_max, float* out_sum) {
     float m = -INFINITY;
 #pragma unroll
     for (int s = 0; s < FAST_SWEEPS; ++s) m = fmaxf(fmaxf(fmaxf(m, v[s].x), fmaxf(v[s].y, v[s].z)), v[s].w);
     m = fast_block_max(m, sh);
     float sum = 0.f;
 #pragma unroll
-    for (int s = 0; s < FAST_SWEEPS; ++s)
-        sum += (expf((v[s].x - m) * inv_tau) + expf((v[s].y - m) * inv_tau)) +
-               (expf((v[s].z - m) * inv_tau) + expf((v[s].w - m) * inv_tau));
+    for (int s = 0; s < FAST_SWEEPS; ++s) {
+        const float4 e = make_float4(expf((v[s].x - m) * inv_tau), expf((v[s].y - m) * inv_tau), expf((v[s].z - m) * inv_tau),
+                                     expf((v[s].w - m) * inv_tau));
+        if (KEEP) v[s] = e;
+        sum += (e.x + e.y) + (e.z + e.w);
+    }
     *out_max = m;
     *out_sum = fast_block_sum(sum, sh);
 }
@@ -687,6 +698,35 @@ __device__ inline float4 fast_softmax_weights(const float4& z, float m, float in
     return make_float4(expf((z.x - m) * inv_tau) * inv_norm, expf((z.y - m) * inv_tau) * inv_norm,
                        expf((z.z - m) * inv_tau) * inv_norm, expf((z.w - m) * inv_tau) * inv_norm);
 }
+__device__ inline float4 fast_scaled(const float4& e, float f) { return make_float4(e.x * f, e.y * f, e.z * f, e.w * f); }
+
+// The draw behind n kept candidates: from the residual of the rows p and q (n < k) or from p, with the rows' maxima and
+// normalisers; KEPT: the rows are their exponentials already
+template <bool KEPT>
+__device__ inline int fast_draw(const AcceptArgs& a, int b, int n, const float4 (&p)[FAST_SWEEPS], const float4 (&q)[FAST_SWEEPS],
+                                float pm, float ps, float qm, float qs, FastShared& sh) {
+    const float it = a.inv_tau, ipn = 1.0f / ps, iqn = 1.0f / qs;
+    auto weights = [&](const float4& v, float m, float inv) { return KEPT ? fast_scaled(v, inv) : fast_softmax_weights(v, m, it, inv); };
+    float4 w[FAST_SWEEPS];
+#pragma unroll
+    for (int s = 0; s < FAST_SWEEPS; ++s) {
+        w[s] = weights(p[s], pm, ipn);
+        if (n < a.k) {
+            const float4 x = weights(q[s], qm, iqn);
+            w[s] = make_float4(fmaxf(0.f, w[s].x - x.x), fmaxf(0.f, w[s].y - x.y), fmaxf(0.f, w[s].z - x.z), fmaxf(0.f, w[s].w - x.w));
+        }
+    }
+    const float u = a.u_resample ? a.u_resample[b * (a.k + 1) + n]
+                                 : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)n, 2);
+    float tot;
+    int nxt = fast_inverse_cdf(w, u, sh, &tot);
+    if (!(tot > 0.f)) {                     // p == q everywhere: fall back to the target row
+#pragma unroll
+        for (int s = 0; s < FAST_SWEEPS; ++s) w[s] = weights(p[s], pm, ipn);
+        nxt = fast_inverse_cdf(w, u, sh, &tot);
+    }
+    return nxt;
+}
 
 __global__ void __launch_bounds__(FAST_THREADS)
 accept_greedy_kernel(AcceptArgs a) {
@@ -745,13 +785,13 @@ accept_greedy_rows_kernel(AcceptArgs a) {
 }
 
 __global__ void __launch_bounds__(FAST_THREADS)
-accept_sample_kernel(AcceptArgs a, int tested) {
+accept_sample_kernel(AcceptArgs a) {
     __shared__ FastShared sh;
     const int b = blockIdx.x, k = a.k, V = a.V;
     const float* P = a.p_logits + (int64_t)b * (k + 1) * V;
     const float* Q = a.q_logits + (int64_t)b * k * V;
     const float it = a.inv_tau;
-    int n = tested ? a.n_accepted[b] : 0;      // tested: candidates were tested by accept_test kernels
+    int n = 0;
     float pm = 0.f, ps = 1.f, qm = 0.f, qs = 1.f;
     float4 pz[FAST_SWEEPS], qz[FAST_SWEEPS];
     // candidates are tested in order; each test needs the softmax normalisers of two rows, which stay
@@ -759,10 +799,9 @@ accept_sample_kernel(AcceptArgs a, int tested) {
     while (true) {
         fast_load_row(P + (int64_t)n * V, V, pz);
         if (n < k) fast_load_row(Q + (int64_t)n * V, V, qz);
-        fast_row_stats(pz, it, sh, &pm, &ps);
+        fast_row_stats<false>(pz, it, sh, &pm, &ps);
         if (n == k) break;
-        fast_row_stats(qz, it, sh, &qm, &qs);
-        if (tested) break;
+        fast_row_stats<false>(qz, it, sh, &qm, &qs);
         if (threadIdx.x == 0) sh.stop = rejects(a, b, n, pm, ps, qm, qs);
         __syncthreads();
         const int stop = sh.stop;
@@ -770,61 +809,103 @@ accept_sample_kernel(AcceptArgs a, int tested) {
         if (stop) break;
         ++n;
     }
-    const float ipn = 1.0f / ps, iqn = 1.0f / qs;
-    float4 w[FAST_SWEEPS];
-#pragma unroll
-    for (int s = 0; s < FAST_SWEEPS; ++s) {
-        w[s] = fast_softmax_weights(pz[s], pm, it, ipn);
-        if (n < k) {
-            const float4 q = fast_softmax_weights(qz[s], qm, it, iqn);
-            w[s] = make_float4(fmaxf(0.f, w[s].x - q.x), fmaxf(0.f, w[s].y - q.y), fmaxf(0.f, w[s].z - q.z),
-                               fmaxf(0.f, w[s].w - q.w));
-        }
-    }
-    const float u = a.u_resample ? a.u_resample[b * (k + 1) + n]
-                                 : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)n, 2);
-    float tot;
-    int nxt = fast_inverse_cdf(w, u, sh, &tot);
-    if (!(tot > 0.f)) {                     // p == q everywhere: fall back to the target row
-#pragma unroll
-        for (int s = 0; s < FAST_SWEEPS; ++s) w[s] = fast_softmax_weights(pz[s], pm, it, ipn);
-        nxt = fast_inverse_cdf(w, u, sh, &tot);
-    }
+    const int nxt = fast_draw<false>(a, b, n, pz, qz, pm, ps, qm, qs, sh);
     if (threadIdx.x == 0) {
-        if (a.n_accepted && !tested) a.n_accepted[b] = n;
+        if (a.n_accepted) a.n_accepted[b] = n;
         if (a.next_token) a.next_token[b] = nxt;
     }
 }
 
-// Few sequences: every candidate of every sequence is tested by a workgroup of its own (n_accepted[b] starts at k and
-// becomes the smallest rejected index), then one workgroup per sequence draws (and takes the statistics of the two rows
-// of its draw again).  In turn a sequence takes a + n b us when it keeps n candidates, and the call as long as the sequence
-// that keeps most; at once it takes the same whatever is kept, two launches and the rows behind the first
-// rejection included.  16 sequences, us, 512 / 32000 ids by the register kernel: in turn 23 + 7.3 n / 27 + 8.4 n, at once
-// 37 / 41, with every candidate kept 30 / 34 (one row to draw from); 64 sequences of 4 candidates, 32000 ids, 27 + 9.7 n against
-// 49 and 42.  So at once from three candidates on, where a sequence among the batch usually keeps two or more
-// (break-even at an acceptance of 0.2 with 16 sequences, 0.4 with 4, 0.6 with one); a call whose draft is always wrong
-// takes up to 1.7 times as long.  With B k <= 256 tests they all run at once; 128 sequences of 2 candidates gain nothing.
+// All candidates at once: a workgroup for each of the k + 1 rows of a sequence tests its candidate and, where it is rejected (or
+// the row is the one behind the last candidate), draws the sequence's next token.  The outputs serve as the meeting
+// point: next_token[b] holds the smallest (row << 27 | token) of those that would draw, announced without a token before
+// the draw, n_accepted[b] counts the workgroups that are through, and the last one turns both into the results.  Nobody waits.
+// A workgroup leaves as soon as it sees a rejection in front of it; those of the first candidates start first, so with more
+// workgroups than the chip holds few rows are read for nothing.
+//
+// us per call, in turn / at once (32000 ids; candidates of which the given number is kept on average):
+//   sequences, candidates        1, 4     16, 1    16, 4    64, 4    64, 8    100, 4   160, 4   256, 6
+//   about half kept              42 / 24  30 / 27  66 / 29  69 / 46  127 / 70  77 / 59  80 / 88  117 / 161
+//   nearly all                   65 / 21  30 / 23  66 / 29  75 / 46  131 / 70  78 / 57  83 / 93  128 / 175
+//   nearly none                  27 / 27  29 / 28  36 / 30  45 / 39   50 / 42  53 / 47  59 / 75   70 / 99
+// 65537 ids (general path): 16 sequences of 4 140 / 68, 64 of 8 287 / 138, 100 of 4 168 / 125, 160 of 4 173 / 166.
+// What bounds it is the exponentials of one compute unit: 4.2 us a row of 32000 ids (17 instructions each), and as much for a
+// row's bytes where all units load.  (Two workgroups per unit in half the registers spill and are slower; so is a next row
+// requested into LDS while the draft's is summed.)
+constexpr int AHEAD_MAX_B = 100;
+constexpr int PICK_BITS = 27;
+constexpr uint32_t PICK_NO_TOKEN = (1u << PICK_BITS) - 1;
+__global__ void accept_begin_kernel(AcceptArgs a) {
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b < a.B) { a.n_accepted[b] = 0; a.next_token[b] = -1; }
+}
+// (one thread) whether a candidate in front of row i of sequence b is known to be rejected
+__device__ inline bool rejected_before(const AcceptArgs& a, int b, int i) {
+    return (int)(__hip_atomic_load((uint32_t*)a.next_token + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> PICK_BITS) < i;
+}
+__device__ inline void offer_pick(const AcceptArgs& a, int b, int i, uint32_t token) {
+    __hip_atomic_fetch_min((uint32_t*)a.next_token + b, ((uint32_t)i << PICK_BITS) | token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// (one thread) this workgroup is through; the last of the sequence writes the results
+__device__ inline void report(const AcceptArgs& a, int b) {
+    if (__hip_atomic_fetch_add(a.n_accepted + b, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != a.k) return;
+    const uint32_t v = __hip_atomic_load((uint32_t*)a.next_token + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    a.n_accepted[b] = (int)(v >> PICK_BITS);
+    a.next_token[b] = (int)(v & PICK_NO_TOKEN);
+}
 __global__ void __launch_bounds__(FAST_THREADS)
-accept_test_kernel(AcceptArgs a) {
+accept_ahead_kernel(AcceptArgs a) {
     __shared__ FastShared sh;
-    const int b = blockIdx.x / a.k, i = blockIdx.x % a.k;
-    float4 pz[FAST_SWEEPS], qz[FAST_SWEEPS];
-    fast_load_row(a.p_logits + ((int64_t)b * (a.k + 1) + i) * a.V, a.V, pz);
-    fast_load_row(a.q_logits + ((int64_t)b * a.k + i) * a.V, a.V, qz);
-    float pm, ps, qm, qs;
-    fast_row_stats(pz, a.inv_tau, sh, &pm, &ps);
-    fast_row_stats(qz, a.inv_tau, sh, &qm, &qs);
-    if (threadIdx.x == 0 && rejects(a, b, i, pm, ps, qm, qs)) atomicMin(&a.n_accepted[b], i);
+    const int b = blockIdx.x % a.B, i = blockIdx.x / a.B, k = a.k, V = a.V;
+    if (threadIdx.x == 0) sh.stop = rejected_before(a, b, i);
+    __syncthreads();
+    bool go = !sh.stop;
+    if (go) {
+        float4 pz[FAST_SWEEPS], qz[FAST_SWEEPS];
+        float pm, ps, qm = 0.f, qs = 1.f;
+        fast_load_row(a.p_logits + ((int64_t)b * (k + 1) + i) * V, V, pz);
+        if (i < k) fast_load_row(a.q_logits + ((int64_t)b * k + i) * V, V, qz);
+        fast_row_stats<true>(pz, a.inv_tau, sh, &pm, &ps);
+        if (i < k) fast_row_stats<true>(qz, a.inv_tau, sh, &qm, &qs);
+        if (threadIdx.x == 0) {
+            const bool draws = (i == k || rejects(a, b, i, pm, ps, qm, qs)) && !rejected_before(a, b, i);
+            if (draws) offer_pick(a, b, i, PICK_NO_TOKEN);
+            sh.stop = !draws;
+        }
+        __syncthreads();
+        go = !sh.stop;
+        if (go) {
+            const int nxt = fast_draw<true>(a, b, i, pz, qz, pm, ps, qm, qs, sh);
+            if (threadIdx.x == 0) offer_pick(a, b, i, (uint32_t)nxt);
+        }
+    }
+    if (threadIdx.x == 0) report(a, b);
 }
 __global__ void __launch_bounds__(WIDE_THREADS)
-accept_test_generic_kernel(AcceptArgs a) {
+accept_ahead_generic_kernel(AcceptArgs a) {
     __shared__ WideShared sh;
-    const int b = blockIdx.x / a.k, i = blockIdx.x % a.k;
-    float pm, ps, qm, qs;
-    wide_row_stats<true>(WideRow(a.p_logits + ((int64_t)b * (a.k + 1) + i) * a.V, a.V),
-                         WideRow(a.q_logits + ((int64_t)b * a.k + i) * a.V, a.V), a.inv_tau, sh, &pm, &ps, &qm, &qs);
-    if (threadIdx.x == 0 && rejects(a, b, i, pm, ps, qm, qs)) atomicMin(&a.n_accepted[b], i);
+    const int b = blockIdx.x % a.B, i = blockIdx.x / a.B, k = a.k, V = a.V;
+    if (threadIdx.x == 0) sh.stop = rejected_before(a, b, i);
+    __syncthreads();
+    bool go = !sh.stop;
+    if (go) {
+        const WideRow p(a.p_logits + ((int64_t)b * (k + 1) + i) * V, V), q(a.q_logits + ((int64_t)b * k + (i < k ? i : 0)) * V, V);
+        float pm, ps, qm = 0.f, qs = 1.f;
+        if (i < k) wide_row_stats<true>(p, q, a.inv_tau, sh, &pm, &ps, &qm, &qs);
+        else wide_row_stats<false>(p, p, a.inv_tau, sh, &pm, &ps, nullptr, nullptr);
+        if (threadIdx.x == 0) {
+            const bool draws = (i == k || rejects(a, b, i, pm, ps, qm, qs)) && !rejected_before(a, b, i);
+            if (draws) offer_pick(a, b, i, PICK_NO_TOKEN);
+            sh.stop = !draws;
+        }
+        __syncthreads();
+        go = !sh.stop;
+        if (go) {
+            const int nxt = wide_draw(a, b, i, p, q, pm, ps, qm, qs, sh);
+            if (threadIdx.x == 0) offer_pick(a, b, i, (uint32_t)nxt);
+        }
+    }
+    if (threadIdx.x == 0) report(a, b);
 }
 
 static inline bool fast_rows_ok(const float* base, int V) {
@@ -835,22 +916,23 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t st) {
     if (a.B <= 0) return hipSuccess;
     const bool fast = fast_rows_ok(a.p_logits, a.V) && (!a.q_logits || fast_rows_ok(a.q_logits, a.V));
     if (a.q_logits) {
-        // Testing at once costs two launches more, about 14 us, and saves a candidate's time for every one that the sequence
-        // which keeps most has kept.  For the short rows of the kernel below that is only V / 430 us a candidate, and one to
-        // three sequences keep few: 16 sequences, first candidate rejected / all kept, in turn against at once: 2001
-        // ids, 4 candidates 14 / 30 against 27 / 23; 3001 ids, 6 candidates 18 / 54 against 31 / 26; 4097 ids, 4
-        // candidates 21 / 44 against 32 / 27.
-        const bool pays = fast || a.V > 2 * NARROW_MAX_V || (a.B >= 4 && (int64_t)a.k * a.V >= 4 * NARROW_MAX_V);
-        const int tested = a.n_accepted && a.k >= 3 && a.B <= 256 / a.k && pays;
-        if (tested) {
-            hipError_t e = launch_fill_words(a.n_accepted, (size_t)a.B, (uint32_t)a.k, st);
-            if (e != hipSuccess) return e;
-            if (fast) hipLaunchKernelGGL(accept_test_kernel, dim3(a.B * a.k), dim3(FAST_THREADS), 0, st, a);
-            else hipLaunchKernelGGL(accept_test_generic_kernel, dim3(a.B * a.k), dim3(WIDE_THREADS), 0, st, a);
-        }
-        if (fast) hipLaunchKernelGGL(accept_sample_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a, tested);
-        else if (!tested && a.V <= NARROW_MAX_V) hipLaunchKernelGGL(accept_sample_narrow_kernel, dim3(a.B), dim3(NARROW_THREADS), 0, st, a);
-        else hipLaunchKernelGGL(accept_sample_generic_kernel, dim3(a.B), dim3(WIDE_THREADS), 0, st, a, tested);
+        // Candidates at once or in turn (accept_ahead_kernel has the figures).  At once a sequence takes one test and one draw, but
+        // the rows behind its first rejection are read as well and a workgroup holds a compute unit: from about 100
+        // sequences on, whose first candidates alone come near to filling the chip, in turn is faster again.  Rows off the register
+        // path: one candidate is tested in turn (65537 ids, 16 sequences: 63 us, at once 65), and so are short rows, whose test
+        // costs only V / 430 us, unless there are several candidates and sequences.
+        const bool short_rows = a.V <= 2 * NARROW_MAX_V;
+        const bool pays = fast               ? a.B <= AHEAD_MAX_B
+                          : a.V <= NARROW_MAX_V ? a.k >= 3 && a.B >= 4 && a.B <= 256 / a.k && (int64_t)a.k * a.V >= 4 * NARROW_MAX_V
+                                             : a.B <= AHEAD_MAX_B && a.k >= 2 && (!short_rows || (a.B >= 4 && (int64_t)a.k * a.V >= 4 * NARROW_MAX_V));
+        const bool ahead = pays && a.n_accepted && a.next_token && a.V < (int)PICK_NO_TOKEN;
+        if (ahead) {
+            hipLaunchKernelGGL(accept_begin_kernel, dim3((a.B + 255) / 256), dim3(256), 0, st, a);
+            if (fast) hipLaunchKernelGGL(accept_ahead_kernel, dim3(a.B * (a.k + 1)), dim3(FAST_THREADS), 0, st, a);
+            else hipLaunchKernelGGL(accept_ahead_generic_kernel, dim3(a.B * (a.k + 1)), dim3(WIDE_THREADS), 0, st, a);
+        } else if (fast) hipLaunchKernelGGL(accept_sample_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
+        else if (a.V <= NARROW_MAX_V) hipLaunchKernelGGL(accept_sample_narrow_kernel, dim3(a.B), dim3(NARROW_THREADS), 0, st, a);
+        else hipLaunchKernelGGL(accept_sample_generic_kernel, dim3(a.B), dim3(WIDE_THREADS), 0, st, a);
     } else {
         const bool rows = a.V <= ROWS_MAX_V && (!fast || (int64_t)a.B * (a.k + 1) * a.V <= ROWS_MAX_IDS);
         if (rows) hipLaunchKernelGGL(accept_greedy_rows_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
@@ -911,9 +993,7 @@ draft_pick_kernel(const float* __restrict__ z, int64_t ld, int V, int mode, floa
         pick = fast_argmax(row, sh);
     } else {
         float m, s, tot;
-        fast_row_stats(row, inv_tau, sh, &m, &s);
-#pragma unroll
-        for (int q = 0; q < FAST_SWEEPS; ++q) row[q] = fast_softmax_weights(row[q], m, inv_tau, 1.0f);
+        fast_row_stats<true>(row, inv_tau, sh, &m, &s);        // (the row is its exponentials now)
         const float u = philox_uniform(seed, round, seq_base + b, (uint32_t)step, 0);
         pick = fast_inverse_cdf(row, u, sh, &tot);
     }

@@ -177,7 +177,8 @@ def test_candidate_outside_the_vocabulary_is_rejected(V):
                                        (100, 3, 512, 0.8), (90, 4, 1001, 0.8), (64, 4, 1003, 0.8), (5, 16, 4098, 0.8),
                                        (260, 1, 64, 0.8), (4, 1, 3, 0.8), (4, 2, 1, 0.8), (5, 2, 3071, 0.8), (5, 2, 3073, 0.8),
                                        (5, 6, 2047, 0.8), (5, 6, 2049, 0.8), (3, 6, 6143, 0.8), (3, 6, 6145, 0.8), (4, 3, 262147, 1.0),
-                                       (200, 4, 1021, 0.8)])
+                                       (200, 4, 1021, 0.8), (100, 1, 512, 0.8), (101, 1, 512, 0.8), (100, 2, 8190, 0.8),
+                                       (101, 2, 8190, 0.8), (4, 16, 32000, 0.8), (3, 1, 8191, 0.8)])
 def test_accept_sample_wide_rows_and_both_test_orders(B, k, V, tau):
     import torch
     import paper_2505_10259_amd as P
@@ -193,6 +194,36 @@ def test_accept_sample_wide_rows_and_both_test_orders(B, k, V, tau):
         torch.cuda.synchronize()
         out.append(nx)
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("V", [512, 40001])
+def test_accept_at_once_under_capture(V):
+    """The outputs are the meeting point of the workgroups of a sequence: every replay starts it afresh, whatever they hold."""
+    import torch
+    import paper_2505_10259_amd as P
+    from gpu_common import dev
+    B, k = 7, 4
+    p, q, d = (dev(x) for x in _logits(B, k, V, seed=0))
+    n = torch.zeros(B, dtype=torch.int32, device="cuda")
+    nx = torch.zeros_like(n)
+    n1, nx1 = torch.zeros_like(n), torch.zeros_like(n)
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        P.spec_accept(p, q, d, None, None, 0.8, 5, 1, 0, B, k, V, n, nx, torch.cuda.current_stream().cuda_stream)
+    for seed in range(4):
+        for t, x in zip((p, q, d), _logits(B, k, V, seed=seed)):
+            t.copy_(dev(x))
+        n.fill_(12345)
+        nx.fill_(seed - 2)
+        P.spec_accept(p, q, d, None, None, 0.8, 5, 1, 0, B, k, V, None, nx1)          # in turn
+        P.spec_accept(p, q, d, None, None, 0.8, 5, 1, 0, B, k, V, n1, nx1)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(n, n1) and torch.equal(nx, nx1)
+        assert 0 <= n.min().item() and n.max().item() <= k
 
 
 @pytest.mark.parametrize("V", [40001, 1002, 512])
