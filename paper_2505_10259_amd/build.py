@@ -13,7 +13,7 @@ SO = os.path.join(HERE, "libspecverify.so")
 # (source, object, flags): the GEMM's kernels are compiled one per object, which is most of the build's time
 SOURCES = [(f + ".hip", f + ".o", []) for f in ("engine", "kernels_basic", "kernels_state", "kernels_accept", "gemm_mfma",
                                                 "attn_mfma", "planner")]
-SOURCES += [("gemm_mfma.hip", "gemm_mfma_%d.o" % i, ["-DSV_GEMM_PART=%d" % i]) for i in range(1, 14)]
+SOURCES += [("gemm_mfma.hip", "gemm_mfma_%d.o" % i, ["-DSV_GEMM_PART=%d" % i]) for i in range(1, 15)]
 # packed-fp32 instruction forms are disabled on purpose (they have produced wrong results on this
 # hardware pool); hipcc's host pass prints a harmless "unknown feature" warning for the flag.
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",

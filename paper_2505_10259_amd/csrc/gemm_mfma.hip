@@ -48,7 +48,7 @@
 
 #include "common.h"
 
-// This file is compiled once for the launcher (SV_GEMM_PART 0) and once for each kernel (1..13).
+// This file is compiled once for the launcher (SV_GEMM_PART 0) and once for each kernel (1..14).
 #ifndef SV_GEMM_PART
 #define SV_GEMM_PART 0
 #endif
@@ -152,6 +152,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
             bool up = within >= BN / 4;
             n = n0 + wcol * (BN / 4) + (up ? within - BN / 4 : within);
             extra = up ? w3_delta : 0u;
+        } else if (EPI == EPI_ROPE_KV && NI < 8) {
+            // a wavefront column block = [first halves of its rotary pairs | second halves], 8 NI pairs of one head
+            const int wcol = tr / (16 * NI), within = tr % (16 * NI);
+            n = (n0 & ~127) + ((n0 & 127) >> 1) + wcol * 8 * NI + within + (within >= 8 * NI ? 64 - 8 * NI : 0);
         } else {
             n = n0 + tr;
         }
@@ -471,15 +475,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
                 if (row < row_end && n0 + wn * 16 * NI + j * 16 + cq < a.N) *(f32x4_t*)at(i, j) = old[i & 1][j] + acc[i][j];
         }
     } else {
-        static_assert(EPI == EPI_ROPE_KV && NI == 8, "a wavefront's 128 columns are one head");
-        // QKV projection: this wavefront's 128 columns are one head (BN = 256, head_dim 128); the
-        // rotation partner of dim j*16 + c is dim (j + 4)*16 + c, i.e. tile j + 4 of the same lane
+        static_assert(EPI == EPI_ROPE_KV, "the last epilogue");
+        // QKV projection (head_dim 128): this wavefront's columns are 8 NI rotary pairs of one head, pair base p0.  The partner
+        // of a column of tile j is the same lane's in tile j + NI/2; with one tile, the lane's 32 further on.
+        constexpr int NP = NI > 1 ? NI / 2 : 1;                // tiles that a lane's first halves are in
         const RopeKvArgs& rp = a.rope;
-        const int head = (n0 + wn * 128) >> 7;                 // wave-uniform
+        const int head = NI == 8 ? (n0 + wn * 128) >> 7 : n0 >> 7;                       // wave-uniform
+        const int p0 = NI == 8 ? 0 : ((n0 & 127) >> 1) + wn * 8 * NI;
+        const int pc = p0 + (NI > 1 ? cq : cq & 7);            // this lane's pairs of tile j: pc + 16 j + 0..3
         const int Hq = rp.n_q_heads, Hkv = rp.geom.n_kv_heads;
         if (head >= Hq + 2 * Hkv) return;
         const bool is_q = head < Hq, is_k = !is_q && head < Hq + Hkv;
-        // Where each row's 128 values of the head go: the q buffer, or the row's slot of a KV page.  All rows'
+        // Where each row's values of the head go: the q buffer, or the row's slot of a KV page.  All rows'
         // positions are requested at once, then all page-table entries, and the cos/sin of a row
         // while the row before it is rotated: one row after the other, each row's loads
         // depend on each other and nothing covers them (2304 rows, 6144 x 4096: 116 -> 109 us).
@@ -497,16 +504,17 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
                 if (!ok || row_of(i) >= row_end) pos[i] = -1;
             }
         }
-        f32x4_t cs[2][8];                    // (cos, sin) of the row's pairs j*16 + cq + 0..3, j = 0..3
+        f32x4_t cs[2][2 * NP];               // (cos, sin) of the row's pairs pc + 16 j + 0..3
         auto load_cs = [&](int i) {
-            const float2* cp = rp.cs + (int64_t)clamped(i) * 64 + cq;
+            const float2* cp = rp.cs + (int64_t)clamped(i) * 64 + pc;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
+            for (int j = 0; j < NP; ++j) {
                 cs[i & 1][2 * j] = *(const f32x4_t*)(cp + j * 16);
                 cs[i & 1][2 * j + 1] = *(const f32x4_t*)(cp + j * 16 + 2);
             }
         };
         bf16* kvp = (bf16*)rp.kv_layer;
+        const int hi_half = cq >> 3;         // NI == 1: this lane holds the second halves of its pairs
         if (is_q || is_k) {
             load_cs(0);
 #pragma unroll
@@ -517,8 +525,17 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
                 else dst = kvp + rp.geom.k_off(pg[i], head - Hq, pos[i] < 0 ? 0 : pos[i] % rp.geom.page_tokens);
                 const bool on = is_q ? row_of(i) < row_end : pos[i] >= 0;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    f32x4_t lo = acc[i][j], hi = acc[i][j + 4];
+                for (int j = 0; j < NP; ++j) {
+                    f32x4_t lo = acc[i][j], hi;
+                    if constexpr (NI > 1) hi = acc[i][j + NP];
+                    else {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const float other = __shfl_xor(acc[i][j][r], 32, WAVE);
+                            hi[r] = hi_half ? acc[i][j][r] : other;
+                            lo[r] = hi_half ? other : acc[i][j][r];
+                        }
+                    }
                     const f32x4_t c01 = cs[i & 1][2 * j], c23 = cs[i & 1][2 * j + 1];
                     const float cs_c[4] = {c01[0], c01[2], c23[0], c23[2]};
                     const float cs_s[4] = {c01[1], c01[3], c23[1], c23[3]};
@@ -529,8 +546,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
                         hi[r] = x1 * cs_c[r] + x0 * cs_s[r];
                     }
                     if (on) {
-                        *(bf16x4_t*)(dst + j * 16 + cq) = __builtin_convertvector(lo, bf16x4_t);
-                        *(bf16x4_t*)(dst + 64 + j * 16 + cq) = __builtin_convertvector(hi, bf16x4_t);
+                        if (NI > 1 || !hi_half) *(bf16x4_t*)(dst + pc + j * 16) = __builtin_convertvector(lo, bf16x4_t);
+                        if (NI > 1 || hi_half) *(bf16x4_t*)(dst + 64 + pc + j * 16) = __builtin_convertvector(hi, bf16x4_t);
                     }
                 }
             }
@@ -540,12 +557,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, char* smem, int row
             for (int i = 0; i < MI; ++i) {
                 if (pos[i] < 0) continue;
                 const int slot = pos[i] % rp.geom.page_tokens;
-                bf16* dst = kvp + rp.geom.v_off(pg[i], kvh, slot, cq);
+                bf16* dst = kvp + rp.geom.v_off(pg[i], kvh, slot, pc + (NI > 1 ? 0 : 64 * hi_half));
                 const int dim = rp.geom.sub_tokens();               // elements between a value's dims
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
+                for (int j = 0; j < NI; ++j)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) dst[(j * 16 + r) * dim] = f32_to_bf16(acc[i][j][r]);
+                    for (int r = 0; r < 4; ++r)
+                        dst[((j % NP) * 16 + (j / NP) * 64 + r) * dim] = f32_to_bf16(acc[i][j][r]);
             }
         }
     }
@@ -788,6 +806,13 @@ SV_GEMM_INSTANCE(1, EPI_STORE_F32, false)
 SV_GEMM_INSTANCE(1, EPI_STORE_F32, true)
 SV_GEMM_INSTANCE(1, EPI_ADD_F32, false)
 SV_GEMM_INSTANCE(1, EPI_ADD_F32, true)
+#elif SV_GEMM_PART == 14
+SV_GEMM_INSTANCE(4, EPI_ROPE_KV, false)
+SV_GEMM_INSTANCE(4, EPI_ROPE_KV, true)
+SV_GEMM_INSTANCE(2, EPI_ROPE_KV, false)
+SV_GEMM_INSTANCE(2, EPI_ROPE_KV, true)
+SV_GEMM_INSTANCE(1, EPI_ROPE_KV, false)
+SV_GEMM_INSTANCE(1, EPI_ROPE_KV, true)
 #else
 #undef SV_GEMM_INSTANCE
 #define SV_GEMM_INSTANCE(...) extern template hipError_t launch_cfg<__VA_ARGS__>(const GemmArgs&, int, hipStream_t);
@@ -813,6 +838,12 @@ SV_GEMM_INSTANCE(1, EPI_STORE_F32, false)
 SV_GEMM_INSTANCE(1, EPI_STORE_F32, true)
 SV_GEMM_INSTANCE(1, EPI_ADD_F32, false)
 SV_GEMM_INSTANCE(1, EPI_ADD_F32, true)
+SV_GEMM_INSTANCE(4, EPI_ROPE_KV, false)
+SV_GEMM_INSTANCE(4, EPI_ROPE_KV, true)
+SV_GEMM_INSTANCE(2, EPI_ROPE_KV, false)
+SV_GEMM_INSTANCE(2, EPI_ROPE_KV, true)
+SV_GEMM_INSTANCE(1, EPI_ROPE_KV, false)
+SV_GEMM_INSTANCE(1, EPI_ROPE_KV, true)
 
 namespace {
 
@@ -900,7 +931,7 @@ TileChoice choose_tiles(const GemmArgs& a) {
 // 604 / 653 / 745 now; 8x22B shape 1124 / 1310 / 1352 and 978 / 1034 / 1089.
 template <int EPI, int NI>
 hipError_t launch_ni(const GemmArgs& a, int ni, int max_rows, bool nt, hipStream_t st) {
-    if constexpr (NI > (EPI == EPI_SWIGLU_T ? 4 : EPI == EPI_ROPE_KV ? 8 : 1)) {
+    if constexpr (NI > (EPI == EPI_SWIGLU_T ? 4 : 1)) {
         if (ni < NI) return launch_ni<EPI, NI / 2>(a, ni, max_rows, nt, st);
     }
     return nt ? launch_cfg<NI, EPI, true>(a, max_rows, st) : launch_cfg<NI, EPI, false>(a, max_rows, st);
@@ -938,14 +969,17 @@ hipError_t launch_gemm_mfma_bf16(const GemmArgs& a, hipStream_t st) {
         return hipErrorInvalidValue;
     TileChoice t = choose_tiles(a);
     if (a.force_max_rows > 0) { t.max_rows = a.force_max_rows; t.ni = a.force_cols / 32; }
-    if (a.epilogue == EPI_ROPE_KV) t = choose_wide(a);
     return launch_gemm_tiles(a, t.ni, t.max_rows, expected_rows(a) <= t.max_rows, st);
 }
 
-// Whether a QKV projection of M rows runs faster as narrow tiles into an f32 buffer and a rotary/append kernel of
-// its own than with 256-column tiles and the fused epilogue: the buffer is written and read once and the kernel
-// takes about 6 us.  64 rows, 6144 x 4096: 51 us fused, 19 + 6 apart; 896 rows, 8192 x 6144: 105 fused, 82 + 21.
+// Whether a QKV projection of M rows is made as narrow tiles into an f32 buffer, with a rotary/append kernel behind it (6 us and
+// a round trip of the buffer).  Narrow tiles rotate themselves, which is faster at every size measured, us as buffer and kernel / in
+// the epilogue, K = 4096, 6144 columns: layer of 512 rows 644 / 637, 768 rows 726 / 722, prefill of 520 rows (8 layers) 3641 / 3570, of
+// 333 rows 3200 / 3130, round of 32 sequences (28 layers of 32 to 224 rows) 3918 / 3841.  Projections of fewer columns than a
+// launch of 128-column tiles can spread over half the units, with rows enough that the buffer's kernel spreads better, were
+// not measured and keep the cost model's choice.
 bool qkv_unfused_pays(int M, int N, int K) {
+    if (M <= 448 || N >= 4096) return false;
     GemmArgs a{};
     a.M = M; a.N = N; a.K = K; a.epilogue = EPI_STORE_F32;
     const TileChoice t = choose_tiles(a), w = choose_wide(a);

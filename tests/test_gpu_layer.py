@@ -93,6 +93,21 @@ def test_small_layer_matches_oracle(B, n_new, ctx, page_tokens, flags):
     print(f"layer B={B} n_new={n_new} ctx={ctx}: max diff {diff[ok].max():.2e} on {ok.sum()}/{ok.size} rows")
 
 
+def test_layer_rows_have_the_same_bits_whatever_the_projection_tiles():
+    """The rows of a call choose the QKV projection's tiles (32, 64, 128 or 256 columns, each with its own deal of rotary pairs
+    to lanes); a sequence's output has the same bits in all of them."""
+    from gpu_common import host_model_pinned
+    shp = synth.mini_moe_shape(dtype="bf16", n_layers=1, d_model=1024, n_q_heads=24, n_kv_heads=4)
+    hm = host_model_pinned(shp, seed=3, std=0.05)
+    B, n_new, ctx = 400, 5, 33
+    x, kc, vc = synth.make_layer_inputs(shp, B, n_new, ctx, seed=4)
+    ref, _ = _run_gpu(hm, x, kc, vc, B, n_new, ctx)
+    assert np.isfinite(ref).all()
+    for n in (1, 7, 20, 64, 103, 260):        # tiles of 32, 32, 64, 64, 128 and 128 columns; the 400 of 256
+        got, _ = _run_gpu(hm, x[:n * n_new], kc[:n], vc[:n], n, n_new, ctx)
+        assert np.array_equal(got, ref[:n * n_new]), n
+
+
 @pytest.mark.parametrize("B,n_new", [(3, 16), (4, 9)])      # 32 query rows (one column tile) / 36 (two)
 def test_layer_when_the_softmax_reference_has_to_move(B, n_new):
     """Keys whose scores grow by far more than the kernel's lazy-reference slack from one key tile of a
