@@ -92,16 +92,16 @@ enum GemmEpilogue {
     EPI_STORE_F32 = 0,   // C float = acc
     EPI_ADD_F32 = 1,     // C float += acc           (residual accumulate; one writer per element)
     EPI_SWIGLU_T = 2,    // C (model dtype)[M, N] = silu(A W^T) * (A W3^T)   (W3 = second weight)
-    EPI_ROPE_KV = 3      // QKV projection (bf16 MFMA kernel, head_dim 128 only): columns are
-                         // [q heads | k heads | v heads]; q and k are rotated (pair (i, i + 64)) with the
+    EPI_ROPE_KV = 3      // QKV projection (bf16 MFMA kernel with head_dim 128, small f32 products): columns are
+                         // [q heads | k heads | v heads]; q and k are rotated (pair (i, i + head_dim/2)) with the
                          // row's cos/sin table, q goes to rope.q_out, k and v to the row's KV page slot
 };
 
 struct RopeKvArgs {               // EPI_ROPE_KV: what rope_kv_kernel takes, minus the f32 qkv buffer
-    const float2* cs;             // [M, 64] (cos, sin) per row
+    const float2* cs;             // [M, head_dim / 2] (cos, sin) per row
     const int32_t* row_pos;       // [M] absolute position of each row (< 0: row inactive)
     const int32_t* page_table;    // [B, pages_per_seq]
-    void* q_out;                  // [M, n_q_heads * 128] model dtype
+    void* q_out;                  // [M, n_q_heads * head_dim] model dtype
     void* kv_layer;               // KV pool of this layer
     KvGeom geom;
     int n_new, n_q_heads;
@@ -121,6 +121,8 @@ struct GemmArgs {
     int m_upper;                    // grouped: upper bound on total rows (grid sizing)
     int m_expected;                 // grouped: expected rows per group if known (tile-height choice), else 0
     RopeKvArgs rope;                // EPI_ROPE_KV only
+    const void* norm_g;             // nullable (small f32 products): A holds f32 rows x, the product takes rmsnorm(x) * norm_g
+    float norm_eps;
     int force_max_rows, force_cols; // tests: tile height limit (multiple of 32, <= 256) and weight columns per tile (256, 128, 64 or 32,
                                     // SwiGLU 256 or 128); 0 = the launcher's choice
 };
@@ -152,6 +154,8 @@ hipError_t launch_weight_panels(void* W, int64_t N, int64_t K, int log2, hipStre
 hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st);
 hipError_t launch_gemm_mfma_bf16(const GemmArgs& a, hipStream_t st);   // gemm_mfma.hip
 bool qkv_unfused_pays(int M, int N, int K);
+// whether an f32 product of this size takes the small tiles, which can normalise their rows (norm_g) and rotate (EPI_ROPE_KV)
+bool gemm_small_fuses(int M, int N, int K, int dtype);
 
 struct AttnArgs {
     const void* q;            // [T, Hq*dh] model dtype

@@ -432,6 +432,11 @@ struct RowSet {
     const int32_t* forced = nullptr;   // [T, 2] expert ids forced on these rows in this layer, or null
 };
 
+// small f32 products normalise their rows and rotate themselves (the plain-kernel mode keeps the separate kernels)
+inline bool small_fuses(const spec_ctx* c, int M, int N, int K, int dtype) {
+    return !(c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS) && gemm_small_fuses(M, N, K, dtype);
+}
+
 inline void* kv_layer_ptr(void* pool, const KvGeom& g, int layer, size_t es) {
     return (char*)pool + (size_t)layer * (size_t)g.layer_elems() * es;
 }
@@ -452,16 +457,19 @@ int layer_qkv(spec_ctx* c, const spec_model_shape& s, const Layout& L, const Wei
     const int qkv_rows = (s.n_q_heads + 2 * s.n_kv_heads) * s.head_dim;
     auto W = [&](int64_t off) { return Wb.at(off, es); };
 
-    { ProfScope ps(c, SPEC_PROF_NORM, st);
-      HIPCHK(c, launch_combine_norm(r.x, *pending ? w.y : nullptr, w.r_wts, w.slots, W(L.g1), w.h, T, d,
-                                    s.rms_eps, dt, st)); }
+    const bool small = small_fuses(c, T, qkv_rows, d, dt), norm_in = small && !*pending;
+    if (!norm_in) {
+        ProfScope ps(c, SPEC_PROF_NORM, st);
+        HIPCHK(c, launch_combine_norm(r.x, *pending ? w.y : nullptr, w.r_wts, w.slots, W(L.g1), w.h, T, d,
+                                      s.rms_eps, dt, st));
+    }
     *pending = false;
     GemmArgs g{};
     g.A = w.h; g.lda = d; g.W = W(L.wqkv); g.C = w.qkv; g.ldc = qkv_rows; g.M = T; g.N = qkv_rows; g.K = d;
     g.w_panel = Wb.panel(qkv_rows, d);
     // bf16 MFMA path with 128-wide heads: rotation, q store and KV append happen in the projection's
-    // epilogue (no f32 qkv round trip) unless the row count asks for tiles narrower than a pair of heads;
-    // otherwise projection to f32, then the rope/append kernel.  The two bf16 ways give the same bits.
+    // epilogue (no f32 qkv round trip) except where qkv_unfused_pays, and so they do in small f32 products; otherwise
+    // projection to f32, then the rope/append kernel.  The two bf16 ways give the same bits.
     const bool mfma_rope = dt == SPEC_BF16 && !(c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS) && s.head_dim == 128 &&
                            d % 64 == 0;
     if (mfma_rope && w.qkv && qkv_unfused_pays(T, qkv_rows, d)) {
@@ -470,8 +478,9 @@ int layer_qkv(spec_ctx* c, const spec_model_shape& s, const Layout& L, const Wei
         { ProfScope ps(c, SPEC_PROF_ROPE, st);
           HIPCHK(c, launch_rope_kv_bf16(w.qkv, r.cs, r.row_pos, page_table, w.q, kv_layer, geom, T, r.n_new,
                                         s.n_q_heads, st)); }
-    } else if (mfma_rope) {
+    } else if (mfma_rope || small) {
         g.epilogue = EPI_ROPE_KV;
+        if (norm_in) { g.A = r.x; g.norm_g = W(L.g1); g.norm_eps = s.rms_eps; }
         g.C = w.q; g.ldc = qkv_rows;       // unused by the epilogue; kept valid for the launcher's checks
         g.rope.cs = r.cs; g.rope.row_pos = r.row_pos; g.rope.page_table = page_table; g.rope.q_out = w.q;
         g.rope.kv_layer = kv_layer; g.rope.geom = geom; g.rope.n_new = r.n_new; g.rope.n_q_heads = s.n_q_heads;
@@ -541,8 +550,9 @@ int layer_front(spec_ctx* c, const spec_model_shape& s, const Layout& L, const W
 // gate, up, down of one expert are contiguous); n_exp experts starting there are applied, each to its
 // own rows of the expert-sorted order, so any split into launches gives the same result.  A dense FFN
 // (n_experts == 0) is the single "expert" 0 and adds straight into the residual stream.
+// With `norm_g` (dense FFN, small f32 products) the gate/up product takes the residual stream and normalises it itself.
 int layer_experts(spec_ctx* c, const spec_model_shape& s, const Layout& L, const Weights& We, int first, int n_exp,
-                  Workspace& w, const RowSet& r, hipStream_t st) {
+                  Workspace& w, const RowSet& r, hipStream_t st, const void* norm_g = nullptr) {
     const int dt = s.dtype;
     const size_t es = esize(dt);
     const int d = s.d_model, T = r.T;
@@ -566,6 +576,7 @@ int layer_experts(spec_ctx* c, const spec_model_shape& s, const Layout& L, const
     } else {
         g.A = w.h; g.lda = d; g.W = W1; g.W3 = W3; g.C = w.u; g.ldc = s.d_ff; g.M = T; g.N = s.d_ff;
         g.K = d; g.epilogue = EPI_SWIGLU_T; g.w_panel = up_panel;
+        if (norm_g) { g.A = r.x; g.norm_g = norm_g; g.norm_eps = s.rms_eps; }
         { ProfScope ps(c, SPEC_PROF_MOE1, st); HIPCHK(c, gemm(c, g, dt, st)); }
         g = GemmArgs{};
         g.A = w.u; g.lda = s.d_ff; g.W = W2; g.C = r.x; g.ldc = d; g.M = T; g.N = d; g.K = s.d_ff;
@@ -588,9 +599,13 @@ int layer_combine(spec_ctx* c, const spec_model_shape& s, Workspace& w, const Ro
 int layer_body(spec_ctx* c, const spec_model_shape& s, const Layout& L, const Weights& Wb, Workspace& w,
                const RowSet& r, void* kv_layer, const KvGeom& geom, const int32_t* page_table,
                bool* pending, bool defer, hipStream_t st) {
-    int rc = layer_front(c, s, L, Wb, w, r, kv_layer, geom, page_table, pending, st);
+    // (the whole blob is there: a streamed FFN has lost its norm's weights with the piece in front of it)
+    const bool norm_in = !s.attn_only && s.n_experts == 0 && small_fuses(c, r.T, s.d_ff, s.d_model, s.dtype);
+    int rc = norm_in ? layer_attn(c, s, L, Wb, w, r, kv_layer, geom, page_table, pending, st)
+                     : layer_front(c, s, L, Wb, w, r, kv_layer, geom, page_table, pending, st);
     if (rc || s.attn_only) return rc;
-    if ((rc = layer_experts(c, s, L, Weights{Wb.p + L.w1 * esize(s.dtype), Wb.panels}, 0, std::max(1, s.n_experts), w, r, st))) return rc;
+    if ((rc = layer_experts(c, s, L, Weights{Wb.p + L.w1 * esize(s.dtype), Wb.panels}, 0, std::max(1, s.n_experts), w, r, st,
+                            norm_in ? Wb.at(L.g2, esize(s.dtype)) : nullptr))) return rc;
     if (s.n_experts > 0) {
         *pending = true;
         if (!defer) {
@@ -633,6 +648,11 @@ int target_layer(spec_ctx* c, int l, Workspace& w, const RowSet& r, void* kv_lay
     return SPEC_OK;
 }
 
+
+// whether an LM head of M rows takes the residual stream and the final norm with it (no expert outputs left to mix in)
+bool head_norm_in(const spec_ctx* c, const spec_model_shape& s, int M) {
+    return (s.attn_only || s.n_experts == 0) && small_fuses(c, M, s.vocab, s.d_model, s.dtype);
+}
 
 // target pass over rows already embedded in w.x (row_pos/cs set); leaves normalised final
 // state in w.h when want_head
@@ -1195,7 +1215,7 @@ int spec_prefill(spec_ctx* c, int sub, const int32_t* tokens, const int32_t* cu_
             const size_t shared = off;
             w.q = base + take(Rg * hd * c->es);
             w.att = base + take(Rg * hd * c->es);
-            // f32 projections: the plain path, and groups of so few rows that the epilogue does not rotate
+            // f32 projections: the plain path, and groups for which qkv_unfused_pays
             const int last_rows = (n_blocks - (n_grp - 1) * Gb) * Q;
             const bool mfma = s.dtype == SPEC_BF16 && !(c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS) && s.head_dim == 128 && s.d_model % 64 == 0;
             if (!mfma || qkv_unfused_pays((int)Rg, (int)qkv_rows, d) || qkv_unfused_pays(last_rows, (int)qkv_rows, d))
@@ -1361,7 +1381,7 @@ int spec_draft(spec_ctx* c, int sub, int k, int32_t* out_tokens) {
     const spec_model_shape& s = c->drf;
     const char* G = (const char*)c->d_draft_globals;
     const int B = sb.B, d = s.d_model, V = s.vocab, half = s.head_dim / 2;
-    const bool sample = c->cfg.mode == SPEC_SAMPLE;
+    const bool sample = c->cfg.mode == SPEC_SAMPLE, norm_in = head_norm_in(c, s, B);
     HIPCHK(c, hipStreamWaitEvent(st, sb.ev_committed, 0));
     ProfScope ps_draft(c, SPEC_PROF_DRAFT, st);
     // the draft pass is timed as one class: its kernels' own classes are masked until this call returns,
@@ -1376,9 +1396,10 @@ int spec_draft(spec_ctx* c, int sub, int k, int32_t* out_tokens) {
         RowSource src{};
         src.s = sb.st; src.kind = RowSource::ROWS_DRAFT; src.embed = 1; src.draft_tokens = sb.draft_tokens; src.k = k; src.step = step;
         HIPCHK(c, launch_rows_prep(src, G + c->gl.emb * c->es, w.x, w.row_pos, w.cs, T, d, V, half, s.rope_theta, s.dtype, st));
-        if ((rc = draft_layers(c, sb, w, T, n_new, true, st))) return rc;
+        if ((rc = draft_layers(c, sb, w, T, n_new, !norm_in, st))) return rc;
         GemmArgs g{};
         g.A = (const char*)w.h + (size_t)(n_new - 1) * d * c->es; g.lda = (int64_t)n_new * d;
+        if (norm_in) { g.A = w.x + (size_t)(n_new - 1) * d; g.norm_g = G + c->gl.gf * c->es; g.norm_eps = s.rms_eps; }
         g.W = G + c->gl.head * c->es; g.M = B; g.N = V; g.K = d; g.epilogue = EPI_STORE_F32;
         g.w_panel = c->panels ? weight_panel_log2(V, d) : 0;
         float* z; int64_t ld;
@@ -1418,12 +1439,15 @@ int spec_verify(spec_ctx* c, int sub, const int32_t* draft_tokens, int k, int32_
     RowSource src{};
     src.s = sb.st; src.kind = RowSource::ROWS_VERIFY; src.embed = 1; src.draft_tokens = sb.draft_tokens; src.k = k;
     HIPCHK(c, launch_rows_prep(src, G + c->gl.emb * c->es, w.x, w.row_pos, w.cs, T, d, V, s.head_dim / 2, s.rope_theta, s.dtype, st));
-    if ((rc = target_layers(c, sb, w, T, k + 1, true))) {
+    const bool norm_in = head_norm_in(c, s, T);
+    if ((rc = target_layers(c, sb, w, T, k + 1, !norm_in))) {
         if (!c->items.empty() && c->uses_done % (int64_t)c->items.size() != 0) c->broken = true;   // stopped mid-pass
         return rc;
     }
     GemmArgs g{};
-    g.A = w.h; g.lda = d; g.W = G + c->gl.head * c->es; g.C = sb.logits; g.ldc = V; g.M = T; g.N = V; g.K = d;
+    g.A = w.h; g.lda = d;
+    if (norm_in) { g.A = w.x; g.norm_g = G + c->gl.gf * c->es; g.norm_eps = s.rms_eps; }
+    g.W = G + c->gl.head * c->es; g.C = sb.logits; g.ldc = V; g.M = T; g.N = V; g.K = d;
     g.epilogue = EPI_STORE_F32; g.w_panel = c->panels ? weight_panel_log2(V, d) : 0;
     { ProfScope ps(c, SPEC_PROF_HEAD, st); HIPCHK(c, gemm(c, g, s.dtype, st)); }
     AcceptArgs a{};

@@ -462,3 +462,32 @@ def test_prefill_groups_stay_below_4_gb_of_activations():
             P.spec_debug_logits(s.ctx, 0, out)
         ref = out if ref is None else ref
         assert torch.isfinite(out).all() and torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("d,hq,hkv,dh,F,V,B,k", [
+    (256, 4, 4, 64, 1024, 512, 4, 4),     # whole tiles, 20 rows
+    (264, 3, 1, 40, 72, 101, 3, 2),       # remainders: heads that straddle tiles of pairs, a row past one block of squares, odd vocabulary
+    (1032, 2, 2, 24, 40, 64, 1, 1),       # five blocks of squares, one sequence
+    (2048, 2, 1, 256, 64, 96, 2, 3),      # the longest row that the products normalise
+    (2056, 2, 1, 64, 64, 96, 2, 3),       # past it: norm and rotation as kernels of their own
+    (20, 2, 1, 8, 12, 16, 17, 1),         # rows not of whole 8s: the same, 34 rows
+    (18, 2, 1, 8, 12, 16, 2, 2),          # nor of whole 4s: no matrix cores
+])
+def test_small_f32_products_that_normalise_and_rotate(d, hq, hkv, dh, F, V, B, k):
+    """Small f32 models normalise and rotate inside their products: every logit and token of a run has the bits of the
+    plain-kernel mode, which keeps the separate kernels (the same sums in the same order)."""
+    import paper_2505_10259_amd as P
+    from gpu_common import GpuDecode, host_model_pinned
+    shp = synth.ModelShape(2, d, hq, hkv, dh, F, V, dtype="f32")
+    hm = host_model_pinned(shp, seed=3, std=0.05)
+    prompts = synth.make_prompts(B, (2, 40), V, seed=4)
+    runs = []
+    for flags in (0, P.SPEC_FLAG_SIMPLE_KERNELS):
+        g = GpuDecode(hm, 1, False, prompts, k, 6, flags=flags)
+        rounds = g.run()
+        runs.append((rounds, g.generated()))
+        g.close()
+    assert runs[0][1] == runs[1][1] and len(runs[0][0]) == len(runs[1][0]) > 0
+    for a, b in zip(*(r[0] for r in runs)):
+        assert np.isfinite(a["p_logits"]).all() and np.array_equal(a["p_logits"], b["p_logits"])
+        assert np.array_equal(a["draft"], b["draft"])

@@ -133,6 +133,22 @@ def test_layer_when_the_softmax_reference_has_to_move(B, n_new):
     assert np.abs(got2 - exp).max(axis=1)[ok].max() < 3e-2
 
 
+# chunks of 64 keys: none cached, one short, whole and one key over, two and a part; pages smaller and larger than a chunk
+@pytest.mark.parametrize("ctx,n_new,page_tokens", [(0, 1, 16), (0, 5, 64), (58, 6, 16), (63, 1, 64), (64, 1, 16), (61, 5, 128), (150, 3, 48)])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_f32_attention_matches_oracle_at_its_chunk_edges(head_dim, ctx, n_new, page_tokens):
+    from gpu_common import host_model_pinned
+    shp = synth.mini_moe_shape(dtype="f32", n_layers=1, head_dim=head_dim)
+    hm = host_model_pinned(shp, seed=3, std=0.05)
+    x, kc, vc = synth.make_layer_inputs(shp, 3, n_new, max(ctx, 1), seed=5)
+    kc, vc = (np.ascontiguousarray(t[:, :, :ctx]) for t in (kc, vc))
+    got, _ = _run_gpu(hm, x, kc, vc, 3, n_new, ctx, 0, page_tokens)
+    exp, gap = _oracle_layer(hm, x, kc, vc, range(3), n_new, ctx)
+    ok = gap > 1e-4
+    # f32 sums of at most 512 terms, some 2^-24 sqrt(512) = 1.4e-6 of their size each, five in a row
+    assert ok.any() and np.abs(got - exp)[ok].max() <= 1e-5 * np.abs(exp).max()
+
+
 def test_small_layer_f32_matches_oracle():
     from gpu_common import host_model_pinned
     shp = synth.mini_moe_shape(dtype="f32", n_layers=1, head_dim=64)
