@@ -110,10 +110,20 @@ __global__ void combine_norm_kernel(float* __restrict__ x, const float* __restri
     for (int c = threadIdx.x; c < d; c += blockDim.x) hr[c] = from_f32<T>(xr[c] * r * to_f32<T>(g[c]));
 }
 
+// the squares of 8 elements onto a sum (of none yet, if `first`), written out so that every kernel that normalises has the same bits
+__device__ inline float squares8(float ss, const float (&v)[8], bool first) {
+    ss = first ? fmaf(v[0], v[0], v[1] * v[1]) : fmaf(v[1], v[1], fmaf(v[0], v[0], ss));
+#pragma unroll
+    for (int e = 2; e < 8; ++e) ss = fmaf(v[e], v[e], ss);
+    return ss;
+}
+
 // Same operation with the row held in registers (8 consecutive elements per thread and chunk, 16-byte
-// loads and stores, one pass): for d % 8 == 0 and d <= 8 * 256 * COMBINE_CHUNKS.
+// loads and stores, one pass): for d % 8 == 0 and d <= 8 * 256 * COMBINE_CHUNKS; CH is the row's count of 2048-wide
+// chunks.  The gains are requested with the row, not behind the reduction (round of 32 sequences, 40
+// such launches of 32 and 224 rows: 3845 -> 3832 us).
 constexpr int COMBINE_CHUNKS = 4;
-template <typename T>
+template <typename T, int CH>
 __global__ void __launch_bounds__(256)
 combine_norm_vec_kernel(float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ wts,
                         const int32_t* __restrict__ slots, const T* __restrict__ g, T* __restrict__ h, int d,
@@ -121,23 +131,35 @@ combine_norm_vec_kernel(float* __restrict__ x, const float* __restrict__ y, cons
     __shared__ float red[4];
     const int t = blockIdx.x, tid = threadIdx.x;
     float* xr = x + (int64_t)t * d;
-    float v[COMBINE_CHUNKS][8];
+    float v[CH][8];
+    alignas(16) T gv[CH][8];
     float ss = 0.f;
     float w0 = 0.f, w1 = 0.f;
     const float* y0 = nullptr;
     const float* y1 = nullptr;
-    if (y) {
-        w0 = wts[2 * t]; w1 = wts[2 * t + 1];
-        if (w0 == 0.f && w1 == 0.f) y = nullptr;                   // a row without experts: nothing to add
-        else { y0 = y + (int64_t)slots[2 * t] * d; y1 = y + (int64_t)slots[2 * t + 1] * d; }
-    }
 #pragma unroll
-    for (int q = 0; q < COMBINE_CHUNKS; ++q) {
+    for (int q = 0; q < CH; ++q) {
         const int c = (q * 256 + tid) * 8;
         if (c < d) {
             const float4 a = *(const float4*)(xr + c), b = *(const float4*)(xr + c + 4);
             v[q][0] = a.x; v[q][1] = a.y; v[q][2] = a.z; v[q][3] = a.w;
             v[q][4] = b.x; v[q][5] = b.y; v[q][6] = b.z; v[q][7] = b.w;
+            if (g) {
+                *(uint4*)gv[q] = *(const uint4*)(g + c);
+                if (sizeof(T) == 4) *(uint4*)(gv[q] + 4) = *(const uint4*)(g + c + 4);
+            }
+        }
+    }
+    if (y) {
+        w0 = wts[2 * t]; w1 = wts[2 * t + 1];
+        const int s0 = slots[2 * t], s1 = slots[2 * t + 1];
+        if (w0 == 0.f && w1 == 0.f) y = nullptr;                   // a row without experts: nothing to add
+        else { y0 = y + (int64_t)s0 * d; y1 = y + (int64_t)s1 * d; }
+    }
+#pragma unroll
+    for (int q = 0; q < CH; ++q) {
+        const int c = (q * 256 + tid) * 8;
+        if (c < d) {
             if (y) {
                 const float4 p0 = *(const float4*)(y0 + c), p1 = *(const float4*)(y0 + c + 4);
                 const float4 q0 = *(const float4*)(y1 + c), q1 = *(const float4*)(y1 + c + 4);
@@ -148,8 +170,7 @@ combine_norm_vec_kernel(float* __restrict__ x, const float* __restrict__ y, cons
                 *(float4*)(xr + c) = make_float4(v[q][0], v[q][1], v[q][2], v[q][3]);
                 *(float4*)(xr + c + 4) = make_float4(v[q][4], v[q][5], v[q][6], v[q][7]);
             }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) ss += v[q][e] * v[q][e];
+            ss = squares8(ss, v[q], q == 0);
         }
     }
     if (!g) return;
@@ -159,14 +180,12 @@ combine_norm_vec_kernel(float* __restrict__ x, const float* __restrict__ y, cons
     const float r = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + eps);
     T* hr = h + (int64_t)t * d;
 #pragma unroll
-    for (int q = 0; q < COMBINE_CHUNKS; ++q) {
+    for (int q = 0; q < CH; ++q) {
         const int c = (q * 256 + tid) * 8;
         if (c < d) {
-            T gv[8], hv[8];
-            if (sizeof(T) == 2) *(uint4*)gv = *(const uint4*)(g + c);
-            else { *(uint4*)gv = *(const uint4*)(g + c); *(uint4*)(gv + 4) = *(const uint4*)(g + c + 4); }
+            alignas(16) T hv[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) hv[i] = from_f32<T>(v[q][i] * r * to_f32<T>(gv[i]));
+            for (int i = 0; i < 8; ++i) hv[i] = from_f32<T>(v[q][i] * r * to_f32<T>(gv[q][i]));
             if (sizeof(T) == 2) *(uint4*)(hr + c) = *(const uint4*)hv;
             else { *(uint4*)(hr + c) = *(const uint4*)hv; *(uint4*)(hr + c + 4) = *(const uint4*)(hv + 4); }
         }
@@ -178,8 +197,11 @@ hipError_t launch_combine_norm(float* x, const float* y, const float* wts, const
                                hipStream_t st) {
     if (T_ <= 0) return hipSuccess;
     if (d % 8 == 0 && d <= 8 * 256 * COMBINE_CHUNKS) {
-        DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(combine_norm_vec_kernel<T>, dim3(T_), dim3(256), 0, st, x, y,
-                                                 wts, slots, (const T*)g, (T*)h, d, eps));
+        DISPATCH_DTYPE(dtype, {
+            auto kern = d <= 2048 ? combine_norm_vec_kernel<T, 1> : d <= 4096 ? combine_norm_vec_kernel<T, 2>
+                      : d <= 6144 ? combine_norm_vec_kernel<T, 3> : combine_norm_vec_kernel<T, 4>;
+            hipLaunchKernelGGL(kern, dim3(T_), dim3(256), 0, st, x, y, wts, slots, (const T*)g, (T*)h, d, eps);
+        });
     } else {
         DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(combine_norm_kernel<T>, dim3(T_), dim3(256), 0, st, x, y,
                                                  wts, slots, (const T*)g, (T*)h, d, eps));
@@ -408,29 +430,52 @@ hipError_t launch_router(const void* h, const void* wr, int32_t* ids, float* wts
 // per row keeps the row in registers, writes h = norm(x) * g in the model dtype and multiplies the
 // rounded h by the E router rows on the way (same values the stand-alone router reads back from
 // memory), then reduces the E logits over the workgroup and picks top-2 as router_kernel does.
-// Needs d % 8 == 0 and d <= 8 * 256 * NORM_ROUTE_CHUNKS.
+// Needs d % 8 == 0 and d <= 8 * 256 * NORM_ROUTE_CHUNKS; CH is the row's count of 2048-wide chunks.  What bounds it is
+// latency, so a bf16 router's rows and the gains are requested with the row itself, in front of the reduction
+// that they would otherwise wait behind (layer of 5 rows 374.4 -> 371.8 us, of 40 rows 490.3 -> 486.0, of 896 874 -> 872.5, of 2304
+// the same; the registers that it takes cost nothing there).
 constexpr int NORM_ROUTE_CHUNKS = 4;
-template <typename T>
+template <typename T, int CH>
 __global__ void __launch_bounds__(256)
 norm_route_kernel(const float* __restrict__ x, const T* __restrict__ g, T* __restrict__ h,
                   const T* __restrict__ wr, int32_t* __restrict__ ids, float* __restrict__ wts, int d, int E,
                   float eps, const int32_t* __restrict__ forced, const int32_t* __restrict__ row_pos) {
+    constexpr bool AHEAD = sizeof(T) == 2;
     __shared__ float red[4];
     __shared__ float part[4][8];
     const int t = blockIdx.x, tid = threadIdx.x;
     const float* xr = x + (int64_t)t * d;
-    float v[NORM_ROUTE_CHUNKS][8];
-    float ss = 0.f;
+    auto load8 = [&](const T* p, T* to) {
+        *(uint4*)to = *(const uint4*)p;
+        if (sizeof(T) == 4) *(uint4*)(to + 4) = *(const uint4*)(p + 4);
+    };
+    float v[CH][8];
+    alignas(16) T gv[CH][8];
+    uint4 wv[AHEAD ? CH : 1][8];                      // (whole words: as elements they would take a register each)
 #pragma unroll
-    for (int q = 0; q < NORM_ROUTE_CHUNKS; ++q) {
+    for (int q = 0; q < CH; ++q) {
         const int c = (q * 256 + tid) * 8;
         if (c < d) {
             const float4 a = *(const float4*)(xr + c), b = *(const float4*)(xr + c + 4);
             v[q][0] = a.x; v[q][1] = a.y; v[q][2] = a.z; v[q][3] = a.w;
             v[q][4] = b.x; v[q][5] = b.y; v[q][6] = b.z; v[q][7] = b.w;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) ss += v[q][e] * v[q][e];
         }
+    }
+#pragma unroll
+    for (int q = 0; q < CH; ++q) {
+        const int c = (q * 256 + tid) * 8;
+        if (c < d) {
+            load8(g + c, gv[q]);
+            if constexpr (AHEAD) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) if (e < E) wv[q][e] = *(const uint4*)(wr + (int64_t)e * d + c);
+            }
+        }
+    }
+    float ss = 0.f;
+#pragma unroll
+    for (int q = 0; q < CH; ++q) {
+        if ((q * 256 + tid) * 8 < d) ss = squares8(ss, v[q], q == 0);
     }
     ss = wave_sum(ss);
     if ((tid & 63) == 0) red[tid >> 6] = ss;
@@ -441,26 +486,31 @@ norm_route_kernel(const float* __restrict__ x, const T* __restrict__ g, T* __res
     for (int e = 0; e < 8; ++e) acc[e] = 0.f;
     T* hr = h + (int64_t)t * d;
 #pragma unroll
-    for (int q = 0; q < NORM_ROUTE_CHUNKS; ++q) {
+    for (int q = 0; q < CH; ++q) {
         const int c = (q * 256 + tid) * 8;
         if (c < d) {
-            T gv[8], hv[8];
-            if (sizeof(T) == 2) *(uint4*)gv = *(const uint4*)(g + c);
-            else { *(uint4*)gv = *(const uint4*)(g + c); *(uint4*)(gv + 4) = *(const uint4*)(g + c + 4); }
+            alignas(16) T hv[8];
             float hf[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) { hv[i] = from_f32<T>(v[q][i] * r * to_f32<T>(gv[i])); hf[i] = to_f32<T>(hv[i]); }
+            for (int i = 0; i < 8; ++i) { hv[i] = from_f32<T>(v[q][i] * r * to_f32<T>(gv[q][i])); hf[i] = to_f32<T>(hv[i]); }
             if (sizeof(T) == 2) *(uint4*)(hr + c) = *(const uint4*)hv;
             else { *(uint4*)(hr + c) = *(const uint4*)hv; *(uint4*)(hr + c + 4) = *(const uint4*)(hv + 4); }
 #pragma unroll
             for (int e = 0; e < 8; ++e)
                 if (e < E) {
-                    T wv[8];
-                    const T* wp = wr + (int64_t)e * d + c;
-                    if (sizeof(T) == 2) *(uint4*)wv = *(const uint4*)wp;
-                    else { *(uint4*)wv = *(const uint4*)wp; *(uint4*)(wv + 4) = *(const uint4*)(wp + 4); }
+                    float w[8];
+                    if constexpr (AHEAD) {
+                        const uint32_t u[4] = {wv[q][e].x, wv[q][e].y, wv[q][e].z, wv[q][e].w};
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) acc[e] += hf[i] * to_f32<T>(wv[i]);
+                        for (int i = 0; i < 8; ++i) w[i] = __uint_as_float(i & 1 ? u[i >> 1] & 0xffff0000u : u[i >> 1] << 16);
+                    } else {
+                        alignas(16) T we[8];
+                        load8(wr + (int64_t)e * d + c, we);
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) w[i] = to_f32<T>(we[i]);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) acc[e] += hf[i] * w[i];
                 }
         }
     }
@@ -483,8 +533,11 @@ hipError_t launch_norm_route(const float* x, const void* g, void* h, const void*
                              int T_, int d, int E, float eps, const int32_t* forced, const int32_t* row_pos, int dtype,
                              hipStream_t st) {
     if (T_ <= 0) return hipSuccess;
-    DISPATCH_DTYPE(dtype, hipLaunchKernelGGL(norm_route_kernel<T>, dim3(T_), dim3(256), 0, st, x, (const T*)g, (T*)h,
-                                             (const T*)wr, ids, wts, d, E, eps, forced, row_pos));
+    DISPATCH_DTYPE(dtype, {
+        auto kern = d <= 2048 ? norm_route_kernel<T, 1> : d <= 4096 ? norm_route_kernel<T, 2> : d <= 6144 ? norm_route_kernel<T, 3>
+                                                                                                          : norm_route_kernel<T, 4>;
+        hipLaunchKernelGGL(kern, dim3(T_), dim3(256), 0, st, x, (const T*)g, (T*)h, (const T*)wr, ids, wts, d, E, eps, forced, row_pos);
+    });
     return hipGetLastError();
 }
 
@@ -853,7 +906,7 @@ gemm_f32_kernel(GemmArgs a) {
         // odd ones finish; 64 slots are a wavefront there, summed as its shuffles do: slots 32 apart, then 16, 8, ... 1.
         float s[16];
         auto squares = [&](int p, const f32x4_t& x, bool second) {
-            float t = fmaf(x[0], x[0], x[1] * x[1]);              // (as the norm kernel's sum is contracted)
+            float t = fmaf(x[0], x[0], x[1] * x[1]);              // (see squares8)
             t = fmaf(x[3], x[3], fmaf(x[2], x[2], t));
             t = __shfl_xor(t, 16, WAVE);
             t = fmaf(x[3], x[3], fmaf(x[2], x[2], fmaf(x[1], x[1], fmaf(x[0], x[0], t))));
