@@ -975,9 +975,8 @@ hipError_t launch_gemm_mfma_bf16(const GemmArgs& a, hipStream_t st) {
 // Whether a QKV projection of M rows is made as narrow tiles into an f32 buffer, with a rotary/append kernel behind it (6 us and
 // a round trip of the buffer).  Narrow tiles rotate themselves, which is faster at every size measured, us as buffer and kernel / in
 // the epilogue, K = 4096, 6144 columns: layer of 512 rows 644 / 637, 768 rows 726 / 722, prefill of 520 rows (8 layers) 3641 / 3570, of
-// 333 rows 3200 / 3130, round of 32 sequences (28 layers of 32 to 224 rows) 3918 / 3841.  Projections of fewer columns than a
-// launch of 128-column tiles can spread over half the units, with rows enough that the buffer's kernel spreads better, were
-// not measured and keep the cost model's choice.
+// 333 rows 3200 / 3130, round of 32 sequences (28 layers of 32 to 224 rows) 3918 / 3841.  Fewer than 4096 columns on more than
+// 448 rows were not measured and keep the cost model's choice against 256-column tiles.
 bool qkv_unfused_pays(int M, int N, int K) {
     if (M <= 448 || N >= 4096) return false;
     GemmArgs a{};
