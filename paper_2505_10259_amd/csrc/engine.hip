@@ -436,6 +436,9 @@ struct RowSet {
 inline bool small_fuses(const spec_ctx* c, int M, int N, int K, int dtype) {
     return !(c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS) && gemm_small_fuses(M, N, K, dtype);
 }
+// ... and take the residual stream as their operand where its rows lie on 16 bytes (spec_layer_forward's are the caller's, at any
+// address; the normalised rows of a norm kernel are the workspace's)
+inline bool takes_stream(const float* x) { return ((uintptr_t)x & 15) == 0; }
 
 inline void* kv_layer_ptr(void* pool, const KvGeom& g, int layer, size_t es) {
     return (char*)pool + (size_t)layer * (size_t)g.layer_elems() * es;
@@ -457,7 +460,7 @@ int layer_qkv(spec_ctx* c, const spec_model_shape& s, const Layout& L, const Wei
     const int qkv_rows = (s.n_q_heads + 2 * s.n_kv_heads) * s.head_dim;
     auto W = [&](int64_t off) { return Wb.at(off, es); };
 
-    const bool small = small_fuses(c, T, qkv_rows, d, dt), norm_in = small && !*pending;
+    const bool small = small_fuses(c, T, qkv_rows, d, dt), norm_in = small && !*pending && takes_stream(r.x);
     if (!norm_in) {
         ProfScope ps(c, SPEC_PROF_NORM, st);
         HIPCHK(c, launch_combine_norm(r.x, *pending ? w.y : nullptr, w.r_wts, w.slots, W(L.g1), w.h, T, d,
@@ -600,7 +603,7 @@ int layer_body(spec_ctx* c, const spec_model_shape& s, const Layout& L, const We
                const RowSet& r, void* kv_layer, const KvGeom& geom, const int32_t* page_table,
                bool* pending, bool defer, hipStream_t st) {
     // (the whole blob is there: a streamed FFN has lost its norm's weights with the piece in front of it)
-    const bool norm_in = !s.attn_only && s.n_experts == 0 && small_fuses(c, r.T, s.d_ff, s.d_model, s.dtype);
+    const bool norm_in = !s.attn_only && s.n_experts == 0 && small_fuses(c, r.T, s.d_ff, s.d_model, s.dtype) && takes_stream(r.x);
     int rc = norm_in ? layer_attn(c, s, L, Wb, w, r, kv_layer, geom, page_table, pending, st)
                      : layer_front(c, s, L, Wb, w, r, kv_layer, geom, page_table, pending, st);
     if (rc || s.attn_only) return rc;

@@ -161,6 +161,32 @@ def test_small_layer_f32_matches_oracle():
     assert np.abs(got - exp)[ok].max() < 2e-4
 
 
+@pytest.mark.parametrize("n_experts", [0, 4])
+@pytest.mark.parametrize("static", [False, True])
+def test_f32_layer_output_at_any_address(n_experts, static):
+    """x_out is the residual stream of the pass.  Where it does not lie on 16 bytes the products cannot take it as an operand and
+    normalise it themselves: the norm kernel does, with the same bits."""
+    import torch
+    import paper_2505_10259_amd as P
+    from gpu_common import dev, host_model_pinned
+    shp = synth.mini_moe_shape(dtype="f32", n_layers=1, head_dim=64, n_experts=n_experts)
+    hm = host_model_pinned(shp, seed=3, std=0.05)
+    B, n_new, ctx = 3, 4, 21
+    x, kc, vc = synth.make_layer_inputs(shp, B, n_new, ctx, seed=4)
+    call = P.spec_layer_forward_static if static else P.spec_layer_forward
+    out = []
+    for off in (0, 1, 2, 3):
+        with P.Session(hm, None, batch_max=B, k_max=n_new - 1, ctx_max=ctx + n_new + 2) as s:
+            P.spec_kv_import(s.ctx, 0, 0, dev(kc), dev(vc), B, ctx)
+            buf = torch.full((B * n_new * shp.d_model + 8,), -3.0, device="cuda")
+            xd, o = dev(x), buf[off:off + B * n_new * shp.d_model]
+            call(s.ctx, 0, 0, xd, n_new, o)
+            P.spec_sync(s.ctx, 0)
+            assert (buf[:off] == -3.0).all() and (buf[off + o.numel():] == -3.0).all()
+            out.append(o.clone())
+    assert torch.isfinite(out[0]).all() and all(torch.equal(o, out[0]) for o in out[1:])
+
+
 def test_cfg2_full_size_sampled_sequences():
     """The benchmark's launch configuration: d 4096, 32/8 heads x 128, 8 experts of 14336, B 256,
     k 8 (9 new tokens), 2048 cached positions.  The oracle recomputes a few whole sequences."""
