@@ -704,28 +704,29 @@ gemm_simple_kernel(GemmArgs a) {
 }
 
 // The same product for problems that 64x64 tiles would run on a handful of compute units, where the matrix cores do not take them
-// (bf16 in the plain-kernel mode, f32 rows not of whole 16 bytes: gemm_f32_kernel takes the others): 8x32 tiles, one output per
-// thread, the contraction in steps of 256 whose elements are requested a step ahead.  What bounds such a product is
+// (bf16 in the plain-kernel mode or onto outputs off 16 bytes, f32 rows not of whole 16 bytes: gemm_f32_kernel takes the others): 8x32
+// tiles, one output per thread, the contraction in steps of 256 whose elements are requested a step ahead.  What bounds such a product is
 // latency: 35-48 us per launch as 16-wide steps on one to sixteen workgroups (8 rows, 256 to 1024 columns,
-// K = 256 to 1024), 5-11 us so.  Every output is the same chain of fused multiply-adds over ascending k.
+// K = 256 to 1024), 5-11 us so.  Weights may be panels (a bf16 layer of 5 rows, d = 4096, whose output is off 16 bytes: 225 us, and
+// 1207 where panels left it to the 64x64 tiles).  Every output is the same chain of fused multiply-adds over ascending k.
 constexpr int F32_TILE = 16, F32_NORM_K = 2048;     // (longest row that NORM takes: one chunk of the norm kernel)
 constexpr int SMALL_BM = 8, SMALL_BN = 32, SMALL_BK = 256, SMALL_LK = SMALL_BK / 128;
 template <typename T>
-__device__ inline float4 load4_guarded(const T* __restrict__ row, int k, int K, bool vec) {     // zeros past K
+__device__ inline float4 load4_guarded(const T* __restrict__ p, int left, bool vec) {     // zeros past the `left` elements of the row
     float v[4] = {0.f, 0.f, 0.f, 0.f};
-    if (vec && k + 4 <= K) {
+    if (vec && left >= 4) {
         alignas(4 * sizeof(T)) T e[4];
-        if constexpr (sizeof(T) == 2) *(uint2*)e = *(const uint2*)(row + k);
-        else *(uint4*)e = *(const uint4*)(row + k);
+        if constexpr (sizeof(T) == 2) *(uint2*)e = *(const uint2*)p;
+        else *(uint4*)e = *(const uint4*)p;
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[q] = to_f32<T>(e[q]);
     } else {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) if (k + q < K) v[q] = to_f32<T>(row[k + q]);
+        for (int q = 0; q < 4; ++q) if (q < left) v[q] = to_f32<T>(p[q]);
     }
     return make_float4(v[0], v[1], v[2], v[3]);
 }
-template <typename T, bool SWIGLU>
+template <typename T, bool SWIGLU, bool PANELS>
 __global__ void __launch_bounds__(256)
 gemm_small_kernel(GemmArgs a, int vec) {
     constexpr int PITCH = SMALL_BK + 4, WQ = SMALL_BN / 8;      // weight rows per thread and 128 columns of a step
@@ -759,13 +760,13 @@ gemm_small_kernel(GemmArgs a, int vec) {
 #pragma unroll
         for (int j = 0; j < SMALL_LK; ++j) {
             const int k = k0 + lk + 128 * j;
-            ra[j] = a_on ? load4_guarded<T>(arow, k, a.K, vec) : z;
+            ra[j] = a_on ? load4_guarded<T>(arow + k, a.K - k, vec) : z;
 #pragma unroll
             for (int m = 0; m < (SWIGLU ? 2 : 1); ++m)
 #pragma unroll
                 for (int q = 0; q < WQ; ++q) {
                     const int n = col0 + lr + 8 * q;
-                    rw[m][q][j] = n < a.N ? load4_guarded<T>(W[m] + (int64_t)n * a.K, k, a.K, vec) : z;
+                    rw[m][q][j] = n < a.N ? load4_guarded<T>(W[m] + weight_elem(n, k, a.K, PANELS ? a.w_panel : 0), a.K - k, vec) : z;
                 }
         }
     };
@@ -1012,7 +1013,7 @@ gemm_f32_kernel(GemmArgs a) {
 // 64x64 tiles on fewer than half the compute units: small tiles (4 to 8 times the reads of a weight, from L2)
 static bool small_tiles(const GemmArgs& a) {
     const int rows = a.group_offsets ? a.m_upper : a.M;
-    return !a.w_panel && (int64_t)((rows + 63) / 64) * ((a.N + 63) / 64) < 128;
+    return (int64_t)((rows + 63) / 64) * ((a.N + 63) / 64) < 128;
 }
 bool gemm_small_fuses(int M, int N, int K, int dtype) {
     GemmArgs a{};
@@ -1045,8 +1046,13 @@ hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st) {
         }
         dim3 sgrid((a.N + SMALL_BN - 1) / SMALL_BN, (rows + SMALL_BM - 1) / SMALL_BM + (a.group_offsets ? a.n_groups : 0));
         DISPATCH_DTYPE(dtype, {
-            if (swiglu) hipLaunchKernelGGL((gemm_small_kernel<T, true>), sgrid, dim3(256), 0, st, a, vec);
-            else hipLaunchKernelGGL((gemm_small_kernel<T, false>), sgrid, dim3(256), 0, st, a, vec);
+            if (a.w_panel) {
+                if constexpr (sizeof(T) == 2) {
+                    if (swiglu) hipLaunchKernelGGL((gemm_small_kernel<T, true, true>), sgrid, dim3(256), 0, st, a, vec);
+                    else hipLaunchKernelGGL((gemm_small_kernel<T, false, true>), sgrid, dim3(256), 0, st, a, vec);
+                } else return hipErrorInvalidValue;
+            } else if (swiglu) hipLaunchKernelGGL((gemm_small_kernel<T, true, false>), sgrid, dim3(256), 0, st, a, vec);
+            else hipLaunchKernelGGL((gemm_small_kernel<T, false, false>), sgrid, dim3(256), 0, st, a, vec);
         });
         return hipGetLastError();
     }

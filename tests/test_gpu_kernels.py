@@ -202,6 +202,37 @@ def test_gemm_weight_panels_change_no_bit(epilogue, N, K, rows):
         assert ((plain - rows_out.float()).abs() <= tol).all()
 
 
+@pytest.mark.parametrize("M,N,K", [(5, 4096, 4096), (9, 40, 64), (20, 264, 320), (3, 520, 8256), (64, 8192, 128)])
+def test_plain_kernels_on_panels(M, N, K):
+    """The plain kernels on panels (a bf16 product onto an output off 16 bytes) have the bits of those on rows, and their tiles: small
+    ones where 64 x 64 tiles leave most compute units idle (the first size: 4 to 8 times as fast)."""
+    import torch
+    import paper_2505_10259_amd as P
+    g = torch.Generator("cuda").manual_seed(K)
+    A = torch.randn(M + 1, K, device="cuda", generator=g).bfloat16().reshape(-1)
+    W = (torch.randn(N, K, device="cuda", generator=g) * 0.05).bfloat16()
+    V = W.clone()
+    assert P.spec_debug_weight_panels(V, N, K) > 1
+    for a in (A[:M * K], A[1:M * K + 1]):                       # operand rows on 16 bytes and off
+        C, D = torch.full((M, N), 7.0, device="cuda"), torch.full((M, N), 9.0, device="cuda")
+        rows = lambda: P.spec_gemm(a, W, C, M, N, K, P.SPEC_BF16, P.SPEC_FLAG_SIMPLE_KERNELS)
+        panels = lambda: P.spec_debug_gemm_panels(a, V, None, D, None, 0, M, N, K, P.SPEC_GEMM_STORE, 1)
+        us = []
+        for f in (rows, panels):
+            best = float("inf")
+            for _ in range(3):
+                e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                e0.record()
+                for _ in range(20):
+                    f()
+                e1.record()
+                e1.synchronize()
+                best = min(best, e0.elapsed_time(e1) * 50)
+            us.append(best)
+        assert torch.equal(C, D)
+        assert us[1] < 2.5 * us[0], us
+
+
 # small plain tiles (8 x 32, steps of 256) with ragged rows, columns and contractions, unaligned rows (K odd), and
 # the sizes on either side of the line to the 64 x 64 tiles
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (8, 32, 128), (9, 33, 129), (20, 768, 256), (4, 256, 1024), (7, 100, 255), (3, 40, 257),
