@@ -56,7 +56,7 @@ enum { SPEC_F32 = 0, SPEC_BF16 = 1 };
 enum { SPEC_GREEDY = 0, SPEC_SAMPLE = 1 };
 enum {
     SPEC_FLAG_NO_OVERLAP = 1,      /* serialise weight copies and compute (time-breakdown runs) */
-    SPEC_FLAG_SIMPLE_KERNELS = 2,  /* use the plain (non-MFMA) kernels also for bf16 (debugging) */
+    SPEC_FLAG_SIMPLE_KERNELS = 2,  /* use the plain (non-MFMA) kernels for every product and attention, bf16 and f32 (debugging) */
     SPEC_FLAG_POISON_RELEASED = 4, /* checking aid for the streamer: a staging slot is overwritten with NaN
                                       bit patterns (by a kernel on the compute stream) as soon as the piece
                                       in it has been released, before the next copy may land there; results

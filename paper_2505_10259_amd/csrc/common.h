@@ -151,7 +151,8 @@ __host__ __device__ inline int64_t weight_elem(int64_t n, int64_t k, int64_t K, 
 hipError_t launch_weight_panels(void* W, int64_t N, int64_t K, int log2, hipStream_t st);
 
 // launchers (kernels_*.hip) -------------------------------------------------------------------
-hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st);
+// plain: f32 products stay off the matrix cores (the plain-kernel mode; same bits)
+hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st, bool plain = false);
 hipError_t launch_gemm_mfma_bf16(const GemmArgs& a, hipStream_t st);   // gemm_mfma.hip
 bool qkv_unfused_pays(int M, int N, int K);
 // whether an f32 product of this size takes the small tiles, which can normalise their rows (norm_g) and rotate (EPI_ROPE_KV)
@@ -167,7 +168,8 @@ struct AttnArgs {
     int B, n_new, n_q_heads;
     float scale;
 };
-hipError_t launch_attention_simple(const AttnArgs& a, int dtype, hipStream_t st);
+// plain: the general kernel at any size (the plain-kernel mode; same bits)
+hipError_t launch_attention_simple(const AttnArgs& a, int dtype, hipStream_t st, bool plain = false);
 hipError_t launch_attention_mfma_bf16(const AttnArgs& a, hipStream_t st);   // attn_mfma.hip
 
 hipError_t launch_fill_words(void* p, size_t n_words, uint32_t value, hipStream_t st);

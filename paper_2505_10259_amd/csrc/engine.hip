@@ -276,14 +276,12 @@ struct ProfScope {
 
 // ---- kernel selection ------------------------------------------------------------------------
 hipError_t gemm(spec_ctx* c, const GemmArgs& a, int dtype, hipStream_t st) {
-    if (dtype == SPEC_BF16 && !(c && (c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS)))
-        return launch_gemm_mfma_bf16(a, st);
-    return launch_gemm_simple(a, dtype, st);
+    const bool plain = c && (c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS);
+    return dtype == SPEC_BF16 && !plain ? launch_gemm_mfma_bf16(a, st) : launch_gemm_simple(a, dtype, st, plain);
 }
 hipError_t attention(spec_ctx* c, const AttnArgs& a, int dtype, hipStream_t st) {
-    if (dtype == SPEC_BF16 && !(c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS))
-        return launch_attention_mfma_bf16(a, st);
-    return launch_attention_simple(a, dtype, st);
+    const bool plain = c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS;
+    return dtype == SPEC_BF16 && !plain ? launch_attention_mfma_bf16(a, st) : launch_attention_simple(a, dtype, st, plain);
 }
 
 // ---- weight streamer ---------------------------------------------------------------------------
@@ -1726,9 +1724,9 @@ int spec_gemm(const void* A, const void* W, float* C, int M, int N, int K, int d
         return fail(nullptr, SPEC_ERR_ARG, "spec_gemm: bad arguments");
     GemmArgs g{};
     g.A = A; g.lda = K; g.W = W; g.C = C; g.ldc = N; g.M = M; g.N = N; g.K = K; g.epilogue = EPI_STORE_F32;
-    hipError_t e = (dtype == SPEC_BF16 && !(flags & SPEC_FLAG_SIMPLE_KERNELS)) ? launch_gemm_mfma_bf16(g, (hipStream_t)stream)
-                                                                              : launch_gemm_simple(g, dtype, (hipStream_t)stream);
-    HIPCHK(nullptr, e);
+    const bool plain = flags & SPEC_FLAG_SIMPLE_KERNELS;
+    HIPCHK(nullptr, dtype == SPEC_BF16 && !plain ? launch_gemm_mfma_bf16(g, (hipStream_t)stream)
+                                                 : launch_gemm_simple(g, dtype, (hipStream_t)stream, plain));
     return SPEC_OK;
 }
 

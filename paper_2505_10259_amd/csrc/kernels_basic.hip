@@ -1021,7 +1021,7 @@ bool gemm_small_fuses(int M, int N, int K, int dtype) {
     return dtype == SPEC_F32 && K % 8 == 0 && K <= F32_NORM_K && small_tiles(a);
 }
 
-hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st) {
+hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st, bool plain) {
     int rows = a.group_offsets ? a.m_upper : a.M;
     if (rows <= 0 || a.N <= 0) return hipSuccess;
     const bool swiglu = a.epilogue == EPI_SWIGLU_T;
@@ -1030,10 +1030,10 @@ hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st) {
         const size_t es = dtype == SPEC_F32 ? 4 : 2;
         const uintptr_t base = (uintptr_t)a.A | (uintptr_t)a.W | (swiglu ? (uintptr_t)a.W3 : 0) | (uintptr_t)(a.w_group_stride * es) | (uintptr_t)a.norm_g;
         const int vec = base % (4 * es) == 0 && a.lda % 4 == 0 && a.K % 4 == 0;
-        if ((rope || a.norm_g) && (dtype != SPEC_F32 || !vec || a.group_offsets)) return hipErrorInvalidValue;
+        if ((rope || a.norm_g) && (dtype != SPEC_F32 || !vec || a.group_offsets || plain)) return hipErrorInvalidValue;
         if (rope && a.N % a.rope.geom.head_dim != 0) return hipErrorInvalidValue;
         if (a.norm_g && (a.K % 8 != 0 || a.K > F32_NORM_K || a.epilogue == EPI_ADD_F32)) return hipErrorInvalidValue;
-        if (dtype == SPEC_F32 && vec) {
+        if (dtype == SPEC_F32 && vec && !plain) {
             const int cols = rope ? a.N / 2 : a.N;
             dim3 grid((cols + F32_TILE - 1) / F32_TILE, (rows + F32_TILE - 1) / F32_TILE + (a.group_offsets ? a.n_groups : 0));
             // (EPI_STORE_F32 stores or adds as a.epilogue says)
@@ -1271,11 +1271,11 @@ attention_f32_kernel(AttnArgs a) {
     for (int d = 0; d < ND; ++d) out[lane + 64 * d] = acc[d] * inv;
 }
 
-hipError_t launch_attention_simple(const AttnArgs& a, int dtype, hipStream_t st) {
+hipError_t launch_attention_simple(const AttnArgs& a, int dtype, hipStream_t st, bool plain) {
     int T_ = a.B * a.n_new;
     if (T_ <= 0) return hipSuccess;
     // (values are read in pieces of four positions: pages of whole fours; 16-byte rows)
-    if (dtype == SPEC_F32 && (a.geom.head_dim == 64 || a.geom.head_dim == 128) && a.geom.page_tokens % 4 == 0 && !((uintptr_t)a.kv_layer & 15)) {
+    if (!plain && dtype == SPEC_F32 && (a.geom.head_dim == 64 || a.geom.head_dim == 128) && a.geom.page_tokens % 4 == 0 && !((uintptr_t)a.kv_layer & 15)) {
         if (a.geom.head_dim == 64) hipLaunchKernelGGL(attention_f32_kernel<64>, dim3(T_ * a.n_q_heads), dim3(64), 0, st, a);
         else hipLaunchKernelGGL(attention_f32_kernel<128>, dim3(T_ * a.n_q_heads), dim3(64), 0, st, a);
         return hipGetLastError();

@@ -491,3 +491,30 @@ def test_small_f32_products_that_normalise_and_rotate(d, hq, hkv, dh, F, V, B, k
     for a, b in zip(*(r[0] for r in runs)):
         assert np.isfinite(a["p_logits"]).all() and np.array_equal(a["p_logits"], b["p_logits"])
         assert np.array_equal(a["draft"], b["draft"])
+
+
+def test_plain_kernel_flag_keeps_f32_models_off_the_matrix_cores():
+    """SPEC_FLAG_SIMPLE_KERNELS: no f32 product on the matrix cores, no attention kernel but the general one, and the logits have the
+    bits of a run without the flag."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    import paper_2505_10259_amd as P
+    from gpu_common import host_model_pinned
+    shp = synth.mini_moe_shape(dtype="f32", head_dim=64, n_experts=0)
+    hm = host_model_pinned(shp, seed=3, std=0.05)
+    prompts = synth.make_prompts(3, (2, 40), shp.vocab, seed=4)
+    kernels, logits = [], []
+    for flags in (0, P.SPEC_FLAG_SIMPLE_KERNELS):
+        with P.Session(hm, None, batch_max=3, k_max=2, ctx_max=60, flags=flags) as s:
+            with profile(activities=[ProfilerActivity.CUDA]) as prof:
+                P.spec_prefill(s.ctx, 0, prompts, 4)
+                P.spec_verify(s.ctx, 0, torch.ones(3, 2, dtype=torch.int32, device="cuda"), 2)
+                P.spec_sync(s.ctx, 0)
+                torch.cuda.synchronize()
+            kernels.append({e.key for e in prof.key_averages()})
+            logits.append(torch.empty(3, 3, shp.vocab, device="cuda"))
+            P.spec_debug_logits(s.ctx, 0, logits[-1])
+    for name in ("gemm_f32_kernel", "attention_f32_kernel"):
+        assert any(name in k for k in kernels[0]), kernels[0]
+        assert not any(name in k for k in kernels[1]), kernels[1]
+    assert torch.isfinite(logits[0]).all() and torch.equal(logits[0], logits[1])
