@@ -253,6 +253,51 @@ def test_gemm_plain_small_and_large_tiles(M, N, K, dtype):
     assert (C.double() - ref).abs().max().item() < max(2, K) * 2.0 ** -24 * 2 * K
 
 
+# one piece of 4, a tail of less than 16, one block of 256 and on either side of it, three blocks; 1 to 20 rows, ragged columns
+@pytest.mark.parametrize("M,N,K", [(1, 16, 4), (20, 48, 100), (16, 40, 256), (17, 33, 264), (4, 64, 600), (20, 100, 1024)])
+@pytest.mark.parametrize("values", ["ordinary", "subnormal", "special"])
+def test_gemm_f32_same_bits_on_every_kernel(M, N, K, values):
+    """f32 products of few tiles run on the matrix cores, which must give the chain of fused multiply-adds of the other kernels bit
+    for bit (a prefill's bits may not depend on its group's rows): against 8 x 32 tiles (operands off 16 bytes; the
+    plain-kernel flag) and 64 x 64 tiles (the same rows inside a matrix of 8200)."""
+    import torch
+    import paper_2505_10259_amd as P
+    g = torch.Generator("cuda").manual_seed(M * K + N)
+    A = torch.randn(8200, K, device="cuda", generator=g)
+    W = torch.randn(N, K, device="cuda", generator=g)
+    if values == "subnormal":              # operands, products and sums on both sides of 2^-126
+        A *= 2.0 ** -70
+        A[:, ::2] *= 2.0 ** -62
+        W *= 2.0 ** -56
+        W[:, ::2] *= 2.0 ** 66
+    elif values == "special":
+        A[torch.rand(A.shape, device="cuda", generator=g) < 0.3] = -0.0
+        W[torch.rand(W.shape, device="cuda", generator=g) < 0.3] = 0.0
+        A[0, K // 2] = float("inf")
+        if M > 4:
+            A[3, 1], W[5, 2], A[1, K - 1] = float("nan"), float("-inf"), 3.0e38
+
+    def call(a, w, rows, flags=0):
+        C = torch.full((rows, N), 7.0, device="cuda")
+        P.spec_gemm(a, w, C, rows, N, K, P.SPEC_F32, flags)
+        torch.cuda.synchronize()
+        return C[:M]
+
+    def off(t):
+        b = torch.empty(t.numel() + 1, device="cuda")
+        b[1:] = t.reshape(-1)
+        return b[1:]
+
+    ref = call(A, W, 8200)
+    if values == "subnormal":
+        assert ((ref != 0) & (ref.abs() < 2.0 ** -126)).any()
+    for name, C in (("matrix cores", call(A[:M], W, M)), ("off 16 bytes", call(off(A[:M]), W, M)),
+                    ("weights off 16 bytes", call(A[:M], off(W), M)), ("plain", call(A[:M], W, M, P.SPEC_FLAG_SIMPLE_KERNELS))):
+        nan = torch.isnan(ref)
+        assert torch.equal(torch.isnan(C), nan), name
+        assert torch.equal(C.view(torch.int32)[~nan], ref.view(torch.int32)[~nan]), name
+
+
 def test_gemm_f32_plain():
     import torch
     import paper_2505_10259_amd as P
