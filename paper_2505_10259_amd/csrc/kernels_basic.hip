@@ -1192,8 +1192,16 @@ attention_simple_kernel(AttnArgs a) {
 }
 // The same for an f32 model of head_dim 64 or 128, every key and value piece of a chunk requested before its first score (a
 // value's address does not wait for the softmax): the general kernel asks for 16 elements at a time, eight or
-// more round trips a chunk, and latency is all that bounds short contexts.  Same order of operations, same bits.
-// 16 workgroups, 33 to 100 keys 8.9 -> 6.8 us, the round of four sequences 415 -> 407.
+// more round trips a chunk, and latency is all that bounds a launch of few workgroups.  Same order of operations, same bits.
+// 16 workgroups, 33 to 100 keys 8.9 -> 6.8 us.  The pieces take 255 registers (64 dims) or 413 (128): two wavefronts or one a SIMD
+// where the general kernel has three, so with more workgroups than that occupancy counts for more.  us, 4 query heads, general kernel / this one:
+//   workgroups                256          512          640          768          1024         1280          3072
+//   64 dims, 100 keys      14.1 / 12.6  15.0 / 13.4  16.2 / 15.0  16.0 / 15.4  17.4 / 16.9  19.2 / 20.7   29.7 / 34.6
+//            1000 keys     85.0 / 74.8  90.0 / 78.6  94.5 / 94.7  96.1 / 95.9   101 / 107    115 / 118     255 / 274
+//   128 dims, 100 keys     21.8 / 15.6  24.2 / 18.9  26.2 / 22.8  25.0 / 25.8  29.4 / 30.3  31.1 / 47.2   54.4 / 75.2
+//            1000 keys      156 / 100    165 / 125    184 / 159    175 / 169    212 / 206    242 / 321     528 / 530
+// (16 query heads the same within 4 %; prefills of 4 x 257 and 16 x 1000 rows 47 / 48 and 1830 / 2056, 128 dims 85 / 98 and 3764 / 4282.)
+constexpr int F32_ATTN_GRID_64 = 768, F32_ATTN_GRID_128 = 640;
 template <int DH>
 __global__ void __launch_bounds__(64)
 attention_f32_kernel(AttnArgs a) {
@@ -1275,7 +1283,8 @@ hipError_t launch_attention_simple(const AttnArgs& a, int dtype, hipStream_t st,
     int T_ = a.B * a.n_new;
     if (T_ <= 0) return hipSuccess;
     // (values are read in pieces of four positions: pages of whole fours; 16-byte rows)
-    if (!plain && dtype == SPEC_F32 && (a.geom.head_dim == 64 || a.geom.head_dim == 128) && a.geom.page_tokens % 4 == 0 && !((uintptr_t)a.kv_layer & 15)) {
+    const int chunked = a.geom.head_dim == 64 ? F32_ATTN_GRID_64 : a.geom.head_dim == 128 ? F32_ATTN_GRID_128 : 0;
+    if (!plain && dtype == SPEC_F32 && (int64_t)T_ * a.n_q_heads <= chunked && a.geom.page_tokens % 4 == 0 && !((uintptr_t)a.kv_layer & 15)) {
         if (a.geom.head_dim == 64) hipLaunchKernelGGL(attention_f32_kernel<64>, dim3(T_ * a.n_q_heads), dim3(64), 0, st, a);
         else hipLaunchKernelGGL(attention_f32_kernel<128>, dim3(T_ * a.n_q_heads), dim3(64), 0, st, a);
         return hipGetLastError();

@@ -187,6 +187,34 @@ def test_f32_layer_output_at_any_address(n_experts, static):
     assert torch.isfinite(out[0]).all() and all(torch.equal(o, out[0]) for o in out[1:])
 
 
+# query rows x heads on either side of the lines between the two kernels (768 and 640), and far beyond
+@pytest.mark.parametrize("head_dim,B,n_new,ctx", [(64, 96, 2, 70), (64, 193, 1, 70), (128, 80, 2, 70), (128, 161, 1, 70), (128, 64, 5, 300)])
+def test_f32_attention_on_either_side_of_the_kernel_for_few_rows(head_dim, B, n_new, ctx):
+    """The f32 attention that holds a whole chunk in registers pays for few workgroups only: a layer has the bits of the general
+    kernel (plain-kernel flag) and its attention takes no longer (128 dims, 1280 workgroups: 1.5 times as long without that line)."""
+    import torch
+    import paper_2505_10259_amd as P
+    from gpu_common import dev, host_model_pinned
+    shp = synth.mini_moe_shape(dtype="f32", n_layers=1, n_kv_heads=4, head_dim=head_dim, n_experts=0)
+    hm = host_model_pinned(shp, seed=3, std=0.05)
+    x, kc, vc = (dev(a) for a in synth.make_layer_inputs(shp, B, n_new, ctx, seed=4))
+    out, ms = [], []
+    for flags in (0, P.SPEC_FLAG_SIMPLE_KERNELS):
+        with P.Session(hm, None, batch_max=B, k_max=max(1, n_new - 1), ctx_max=ctx + n_new + 2, flags=flags) as s:
+            P.spec_kv_import(s.ctx, 0, 0, kc, vc, B, ctx)
+            out.append(torch.empty(B * n_new, shp.d_model, device="cuda"))
+            torch.cuda.synchronize()
+            P.spec_profile_enable(s.ctx, ["attn"])
+            best = float("inf")
+            for _ in range(4):
+                for _ in range(10):
+                    P.spec_layer_forward(s.ctx, 0, 0, x, n_new, out[-1])
+                best = min(best, P.spec_profile_read(s.ctx)["attn"]["ms"])
+            ms.append(best)
+    assert torch.isfinite(out[0]).all() and torch.equal(out[0], out[1])
+    assert ms[0] < 1.25 * ms[1], ms
+
+
 def test_cfg2_full_size_sampled_sequences():
     """The benchmark's launch configuration: d 4096, 32/8 heads x 128, 8 experts of 14336, B 256,
     k 8 (9 new tokens), 2048 cached positions.  The oracle recomputes a few whole sequences."""
