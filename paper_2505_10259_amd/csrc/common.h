@@ -155,8 +155,9 @@ hipError_t launch_weight_panels(void* W, int64_t N, int64_t K, int log2, hipStre
 hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st, bool plain = false);
 hipError_t launch_gemm_mfma_bf16(const GemmArgs& a, hipStream_t st);   // gemm_mfma.hip
 bool qkv_unfused_pays(int M, int N, int K);
-// whether an f32 product of this size takes the small tiles, which can normalise their rows (norm_g) and rotate (EPI_ROPE_KV)
+// whether an f32 product of this size takes the small tiles and is to rotate (EPI_ROPE_KV), and whether it is to normalise its rows (norm_g) too
 bool gemm_small_fuses(int M, int N, int K, int dtype);
+bool gemm_small_norms(int K);
 
 struct AttnArgs {
     const void* q;            // [T, Hq*dh] model dtype

@@ -430,13 +430,15 @@ struct RowSet {
     const int32_t* forced = nullptr;   // [T, 2] expert ids forced on these rows in this layer, or null
 };
 
-// small f32 products normalise their rows and rotate themselves (the plain-kernel mode keeps the separate kernels)
+// small f32 products rotate (the plain-kernel mode keeps the separate kernels) ...
 inline bool small_fuses(const spec_ctx* c, int M, int N, int K, int dtype) {
     return !(c->cfg.flags & SPEC_FLAG_SIMPLE_KERNELS) && gemm_small_fuses(M, N, K, dtype);
 }
-// ... and take the residual stream as their operand where its rows lie on 16 bytes (spec_layer_forward's are the caller's, at any
-// address; the normalised rows of a norm kernel are the workspace's)
-inline bool takes_stream(const float* x) { return ((uintptr_t)x & 15) == 0; }
+// ... and those of short rows normalise them too, taking the residual stream x as their operand where it lies on 16 bytes
+// (spec_layer_forward's is the caller's, at any address; the rows of a norm kernel are the workspace's)
+inline bool small_norms(const spec_ctx* c, const float* x, int M, int N, int K, int dtype) {
+    return small_fuses(c, M, N, K, dtype) && gemm_small_norms(K) && ((uintptr_t)x & 15) == 0;
+}
 
 inline void* kv_layer_ptr(void* pool, const KvGeom& g, int layer, size_t es) {
     return (char*)pool + (size_t)layer * (size_t)g.layer_elems() * es;
@@ -458,7 +460,7 @@ int layer_qkv(spec_ctx* c, const spec_model_shape& s, const Layout& L, const Wei
     const int qkv_rows = (s.n_q_heads + 2 * s.n_kv_heads) * s.head_dim;
     auto W = [&](int64_t off) { return Wb.at(off, es); };
 
-    const bool small = small_fuses(c, T, qkv_rows, d, dt), norm_in = small && !*pending && takes_stream(r.x);
+    const bool small = small_fuses(c, T, qkv_rows, d, dt), norm_in = !*pending && small_norms(c, r.x, T, qkv_rows, d, dt);
     if (!norm_in) {
         ProfScope ps(c, SPEC_PROF_NORM, st);
         HIPCHK(c, launch_combine_norm(r.x, *pending ? w.y : nullptr, w.r_wts, w.slots, W(L.g1), w.h, T, d,
@@ -601,7 +603,7 @@ int layer_body(spec_ctx* c, const spec_model_shape& s, const Layout& L, const We
                const RowSet& r, void* kv_layer, const KvGeom& geom, const int32_t* page_table,
                bool* pending, bool defer, hipStream_t st) {
     // (the whole blob is there: a streamed FFN has lost its norm's weights with the piece in front of it)
-    const bool norm_in = !s.attn_only && s.n_experts == 0 && small_fuses(c, r.T, s.d_ff, s.d_model, s.dtype) && takes_stream(r.x);
+    const bool norm_in = !s.attn_only && s.n_experts == 0 && small_norms(c, r.x, r.T, s.d_ff, s.d_model, s.dtype);
     int rc = norm_in ? layer_attn(c, s, L, Wb, w, r, kv_layer, geom, page_table, pending, st)
                      : layer_front(c, s, L, Wb, w, r, kv_layer, geom, page_table, pending, st);
     if (rc || s.attn_only) return rc;
@@ -651,8 +653,8 @@ int target_layer(spec_ctx* c, int l, Workspace& w, const RowSet& r, void* kv_lay
 
 
 // whether an LM head of M rows takes the residual stream and the final norm with it (no expert outputs left to mix in)
-bool head_norm_in(const spec_ctx* c, const spec_model_shape& s, int M) {
-    return (s.attn_only || s.n_experts == 0) && small_fuses(c, M, s.vocab, s.d_model, s.dtype);
+bool head_norm_in(const spec_ctx* c, const spec_model_shape& s, const float* x, int M) {
+    return (s.attn_only || s.n_experts == 0) && small_norms(c, x, M, s.vocab, s.d_model, s.dtype);
 }
 
 // target pass over rows already embedded in w.x (row_pos/cs set); leaves normalised final
@@ -1382,7 +1384,7 @@ int spec_draft(spec_ctx* c, int sub, int k, int32_t* out_tokens) {
     const spec_model_shape& s = c->drf;
     const char* G = (const char*)c->d_draft_globals;
     const int B = sb.B, d = s.d_model, V = s.vocab, half = s.head_dim / 2;
-    const bool sample = c->cfg.mode == SPEC_SAMPLE, norm_in = head_norm_in(c, s, B);
+    const bool sample = c->cfg.mode == SPEC_SAMPLE, norm_in = head_norm_in(c, s, w.x, B);
     HIPCHK(c, hipStreamWaitEvent(st, sb.ev_committed, 0));
     ProfScope ps_draft(c, SPEC_PROF_DRAFT, st);
     // the draft pass is timed as one class: its kernels' own classes are masked until this call returns,
@@ -1440,7 +1442,7 @@ int spec_verify(spec_ctx* c, int sub, const int32_t* draft_tokens, int k, int32_
     RowSource src{};
     src.s = sb.st; src.kind = RowSource::ROWS_VERIFY; src.embed = 1; src.draft_tokens = sb.draft_tokens; src.k = k;
     HIPCHK(c, launch_rows_prep(src, G + c->gl.emb * c->es, w.x, w.row_pos, w.cs, T, d, V, s.head_dim / 2, s.rope_theta, s.dtype, st));
-    const bool norm_in = head_norm_in(c, s, T);
+    const bool norm_in = head_norm_in(c, s, w.x, T);
     if ((rc = target_layers(c, sb, w, T, k + 1, !norm_in))) {
         if (!c->items.empty() && c->uses_done % (int64_t)c->items.size() != 0) c->broken = true;   // stopped mid-pass
         return rc;

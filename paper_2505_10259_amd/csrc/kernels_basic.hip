@@ -709,7 +709,8 @@ gemm_simple_kernel(GemmArgs a) {
 // latency: 35-48 us per launch as 16-wide steps on one to sixteen workgroups (8 rows, 256 to 1024 columns,
 // K = 256 to 1024), 5-11 us so.  Weights may be panels (a bf16 layer of 5 rows, d = 4096, whose output is off 16 bytes: 225 us, and
 // 1207 where panels left it to the 64x64 tiles).  Every output is the same chain of fused multiply-adds over ascending k.
-constexpr int F32_TILE = 16, F32_NORM_K = 2048;     // (longest row that NORM takes: one chunk of the norm kernel)
+constexpr int F32_TILE = 16, F32_PIECES = 16;               // rows and columns of a tile; pieces of 16 k requested at once
+constexpr int F32_NORM_K = 16 * F32_PIECES, F32_ROPE_K = 2048;      // longest rows that are normalised and rotated inside (see gemm_small_fuses)
 constexpr int SMALL_BM = 8, SMALL_BN = 32, SMALL_BK = 256, SMALL_LK = SMALL_BK / 128;
 template <typename T>
 __device__ inline float4 load4_guarded(const T* __restrict__ p, int left, bool vec) {     // zeros past the `left` elements of the row
@@ -835,7 +836,7 @@ template <int EPI, bool NORM>
 __global__ void __launch_bounds__(EPI == EPI_SWIGLU_T || EPI == EPI_ROPE_KV ? 128 : 64)
 gemm_f32_kernel(GemmArgs a) {
     constexpr bool SWIGLU = EPI == EPI_SWIGLU_T, ROPE = EPI == EPI_ROPE_KV, DUAL = SWIGLU || ROPE;
-    constexpr int TILE = F32_TILE, P = 16;                       // pieces of 16 k requested at once
+    constexpr int TILE = F32_TILE, P = F32_PIECES;
     constexpr int NE = DUAL ? 2 : 4;                             // outputs that a lane finishes
     __shared__ f32x4_t part[2][64];
     int row_begin = blockIdx.y * TILE, row_end = a.M, group = 0;
@@ -904,42 +905,23 @@ gemm_f32_kernel(GemmArgs a) {
     float rs = 1.f;
     if constexpr (NORM) {
         // A slot is 8 consecutive elements (a thread of the norm kernel), its squares one chain that the even lane groups begin and the
-        // odd ones finish; 64 slots are a wavefront there, summed as its shuffles do: slots 32 apart, then 16, 8, ... 1.
+        // odd ones finish (see squares8); the row's at most 32 slots are half a wavefront there, summed as its shuffles do: slots 16
+        // apart, then 8, ... 1.
         float s[16];
-        auto squares = [&](int p, const f32x4_t& x, bool second) {
-            float t = fmaf(x[0], x[0], x[1] * x[1]);              // (see squares8)
+#pragma unroll
+        for (int p = 0; p < 16; ++p) {
+            const f32x4_t& x = fa[p];                             // (zeros past the row)
+            float t = fmaf(x[0], x[0], x[1] * x[1]);
             t = fmaf(x[3], x[3], fmaf(x[2], x[2], t));
             t = __shfl_xor(t, 16, WAVE);
-            t = fmaf(x[3], x[3], fmaf(x[2], x[2], fmaf(x[1], x[1], fmaf(x[0], x[0], t))));
-            s[p] = second ? s[p] + t : t;
-        };
-        float tot = 0.f;
-        for (int k0 = 0; k0 < a.K; k0 += 512) {
-#pragma unroll
-            for (int p = 0; p < 16; ++p) {
-                const int k = k0 + 16 * p + kq;
-                f32x4_t x = z;
-                if (k < a.K) x = k0 == 0 ? fa[p] : *(const f32x4_t*)(arow + k);
-                squares(p, x, false);
-            }
-            if (k0 + 256 < a.K) {
-                f32x4_t x[16];
-#pragma unroll
-                for (int p = 0; p < 16; ++p) {
-                    const int k = k0 + 256 + 16 * p + kq;
-                    x[p] = k < a.K ? *(const f32x4_t*)(arow + k) : z;
-                }
-#pragma unroll
-                for (int p = 0; p < 16; ++p) squares(p, x[p], true);
-            }
-#pragma unroll
-            for (int o = 8; o > 0; o >>= 1)
-#pragma unroll
-                for (int p = 0; p < o; ++p) s[p] += s[p + o];
-            s[0] += __shfl_xor(s[0], 32, WAVE);
-            tot = k0 == 0 ? s[0] : tot + s[0];
+            s[p] = fmaf(x[3], x[3], fmaf(x[2], x[2], fmaf(x[1], x[1], fmaf(x[0], x[0], t))));
         }
-        tot = __shfl(tot, 16 + fr, WAVE);
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1)
+#pragma unroll
+            for (int p = 0; p < o; ++p) s[p] += s[p + o];
+        s[0] += __shfl_xor(s[0], 32, WAVE);
+        const float tot = __shfl(s[0], 16 + fr, WAVE);
         rs = 1.0f / sqrtf(tot / (float)a.K + a.norm_eps);
     }
     f32x4_t acc = z;
@@ -1015,11 +997,23 @@ static bool small_tiles(const GemmArgs& a) {
     const int rows = a.group_offsets ? a.m_upper : a.M;
     return (int64_t)((rows + 63) / 64) * ((a.N + 63) / 64) < 128;
 }
+// Rotation inside pays at every size measured (a launch less): layer of 20 rows, us, as a launch of its own / inside, K = 512 62.9 / 60.9,
+// 1024 105 / 101, 2048 535 / 536, of one row 515 / 508.  The norm inside pays only where a row's squares come from the pieces that
+// the product holds anyway, up to 256 k: every column tile sums them again, and behind that each further chunk is
+// a round trip to memory in front of the product.  Layer of 1 / 20 / 80 rows, norm as a launch / inside (from 512 on with those trips):
+//   K = 128   32.2 / 35.4 / 36.0                          29.9 / 32.6 / 33.1
+//   K = 256   39.9 / 44.5 / 48.0                          38.2 / 42.0 / 46.1
+//   K = 512   54.0 / 60.9 / 73.0                          57.3 / 63.1 / 83.3
+//   K = 768   72.8 / 83.0 / 106                           84.2 / 92.6 / 128
+//   K = 1024  87.9 / 101 / 292                            103 / 116 / 300
+//   K = 2048  508 / 536 / 831                             529 / 550 / 842
+// Verify of a four-layer model, 1024 wide, 1 and 20 rows: 476 -> 415 and 521 -> 453 us with the line here and not at 2048.
 bool gemm_small_fuses(int M, int N, int K, int dtype) {
     GemmArgs a{};
     a.M = M; a.N = N;
-    return dtype == SPEC_F32 && K % 8 == 0 && K <= F32_NORM_K && small_tiles(a);
+    return dtype == SPEC_F32 && K % 8 == 0 && K <= F32_ROPE_K && small_tiles(a);
 }
+bool gemm_small_norms(int K) { return K <= F32_NORM_K; }
 
 hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st, bool plain) {
     int rows = a.group_offsets ? a.m_upper : a.M;

@@ -466,9 +466,10 @@ def test_prefill_groups_stay_below_4_gb_of_activations():
 
 @pytest.mark.parametrize("d,hq,hkv,dh,F,V,B,k", [
     (256, 4, 4, 64, 1024, 512, 4, 4),     # whole tiles, 20 rows
-    (264, 3, 1, 40, 72, 101, 3, 2),       # remainders: heads that straddle tiles of pairs, a row past one block of squares, odd vocabulary
-    (1032, 2, 2, 24, 40, 64, 1, 1),       # five blocks of squares, one sequence
-    (2048, 2, 1, 256, 64, 96, 2, 3),      # the longest row that the products normalise
+    (248, 3, 1, 40, 72, 101, 3, 2),       # remainders: heads that straddle tiles of pairs, a row short of a block of squares, odd vocabulary
+    (264, 3, 1, 40, 72, 101, 3, 2),       # past the longest row that the products normalise: the norm is a kernel of its own
+    (1032, 2, 2, 24, 40, 64, 1, 1),       # the same, one sequence
+    (2048, 2, 1, 256, 64, 96, 2, 3),      # the longest row that is rotated inside
     (2056, 2, 1, 64, 64, 96, 2, 3),       # past it: norm and rotation as kernels of their own
     (20, 2, 1, 8, 12, 16, 17, 1),         # rows not of whole 8s: the same, 34 rows
     (18, 2, 1, 8, 12, 16, 2, 2),          # nor of whole 4s: no matrix cores
@@ -491,6 +492,24 @@ def test_small_f32_products_that_normalise_and_rotate(d, hq, hkv, dh, F, V, B, k
     for a, b in zip(*(r[0] for r in runs)):
         assert np.isfinite(a["p_logits"]).all() and np.array_equal(a["p_logits"], b["p_logits"])
         assert np.array_equal(a["draft"], b["draft"])
+
+
+@pytest.mark.parametrize("d,norms", [(256, 0), (264, 2), (1024, 2)])
+def test_f32_rows_past_one_block_have_a_norm_kernel(d, norms):
+    """Products that normalise their rows sum the squares in every column tile: longer rows than a product requests at once (256) are
+    normalised by a launch of their own (a layer of 80 rows, 768 wide: 106 us so, 128 inside)."""
+    import torch
+    import paper_2505_10259_amd as P
+    from gpu_common import dev, host_model_pinned
+    shp = synth.ModelShape(1, d, 2, 2, 64, 512, 64, dtype="f32")
+    hm = host_model_pinned(shp, seed=3, std=0.05)
+    x, kc, vc = (dev(a) for a in synth.make_layer_inputs(shp, 2, 3, 5, seed=4))
+    with P.Session(hm, None, batch_max=2, k_max=2, ctx_max=10) as s:
+        P.spec_kv_import(s.ctx, 0, 0, kc, vc, 2, 5)
+        P.spec_profile_enable(s.ctx, ["norm", "rope"])
+        P.spec_layer_forward(s.ctx, 0, 0, x, 3, torch.empty(6, d, device="cuda"))
+        got = P.spec_profile_read(s.ctx)
+    assert got["norm"]["launches"] == norms and got["rope"]["launches"] == 0
 
 
 def test_plain_kernel_flag_keeps_f32_models_off_the_matrix_cores():
