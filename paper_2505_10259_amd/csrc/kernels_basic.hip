@@ -432,15 +432,17 @@ hipError_t launch_router(const void* h, const void* wr, int32_t* ids, float* wts
 // memory), then reduces the E logits over the workgroup and picks top-2 as router_kernel does.
 // Needs d % 8 == 0 and d <= 8 * 256 * NORM_ROUTE_CHUNKS; CH is the row's count of 2048-wide chunks.  What bounds it is
 // latency, so a bf16 router's rows and the gains are requested with the row itself, in front of the reduction
-// that they would otherwise wait behind (layer of 5 rows 374.4 -> 371.8 us, of 40 rows 490.3 -> 486.0, of 896 874 -> 872.5, of 2304
-// the same; the registers that it takes cost nothing there).
-constexpr int NORM_ROUTE_CHUNKS = 4;
-template <typename T, int CH>
+// that they would otherwise wait behind (AHEAD).  Of rows of four chunks that takes 212 registers, two workgroups a compute unit, and pays
+// while they are few: 8192 wide, 8 experts, us behind the reduction / with the row: 320 rows 17.0 / 11.2, 640 19.4 / 18.4, 768 19.7 / 19.0,
+// 1024 22.7 / 22.9, 1152 22.4 / 27.3, 2304 41.6 / 46.2, 4096 57.4 / 70.4.  6144 wide, 2304 rows 34.4 / 30.0.
+constexpr int NORM_ROUTE_CHUNKS = 4, NORM_ROUTE_AHEAD_ROWS = 768;
+template <typename T, int CH, bool AHEAD>
 __global__ void __launch_bounds__(256)
 norm_route_kernel(const float* __restrict__ x, const T* __restrict__ g, T* __restrict__ h,
                   const T* __restrict__ wr, int32_t* __restrict__ ids, float* __restrict__ wts, int d, int E,
                   float eps, const int32_t* __restrict__ forced, const int32_t* __restrict__ row_pos) {
-    constexpr bool AHEAD = sizeof(T) == 2;
+    static_assert(!AHEAD || sizeof(T) == 2, "a router's row as 16-byte words");
+    constexpr bool GAINS_AHEAD = AHEAD || sizeof(T) == 4;
     __shared__ float red[4];
     __shared__ float part[4][8];
     const int t = blockIdx.x, tid = threadIdx.x;
@@ -465,7 +467,7 @@ norm_route_kernel(const float* __restrict__ x, const T* __restrict__ g, T* __res
     for (int q = 0; q < CH; ++q) {
         const int c = (q * 256 + tid) * 8;
         if (c < d) {
-            load8(g + c, gv[q]);
+            if (GAINS_AHEAD) load8(g + c, gv[q]);
             if constexpr (AHEAD) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) if (e < E) wv[q][e] = *(const uint4*)(wr + (int64_t)e * d + c);
@@ -491,6 +493,7 @@ norm_route_kernel(const float* __restrict__ x, const T* __restrict__ g, T* __res
         if (c < d) {
             alignas(16) T hv[8];
             float hf[8];
+            if (!GAINS_AHEAD) load8(g + c, gv[q]);
 #pragma unroll
             for (int i = 0; i < 8; ++i) { hv[i] = from_f32<T>(v[q][i] * r * to_f32<T>(gv[q][i])); hf[i] = to_f32<T>(hv[i]); }
             if (sizeof(T) == 2) *(uint4*)(hr + c) = *(const uint4*)hv;
@@ -534,8 +537,9 @@ hipError_t launch_norm_route(const float* x, const void* g, void* h, const void*
                              hipStream_t st) {
     if (T_ <= 0) return hipSuccess;
     DISPATCH_DTYPE(dtype, {
-        auto kern = d <= 2048 ? norm_route_kernel<T, 1> : d <= 4096 ? norm_route_kernel<T, 2> : d <= 6144 ? norm_route_kernel<T, 3>
-                                                                                                          : norm_route_kernel<T, 4>;
+        constexpr bool B = sizeof(T) == 2;
+        auto kern = d <= 2048 ? norm_route_kernel<T, 1, B> : d <= 4096 ? norm_route_kernel<T, 2, B> : d <= 6144 ? norm_route_kernel<T, 3, B>
+                  : T_ <= NORM_ROUTE_AHEAD_ROWS ? norm_route_kernel<T, 4, B> : norm_route_kernel<T, 4, false>;
         hipLaunchKernelGGL(kern, dim3(T_), dim3(256), 0, st, x, (const T*)g, (T*)h, (const T*)wr, ids, wts, d, E, eps, forced, row_pos);
     });
     return hipGetLastError();

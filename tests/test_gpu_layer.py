@@ -215,6 +215,26 @@ def test_f32_attention_on_either_side_of_the_kernel_for_few_rows(head_dim, B, n_
     assert ms[0] < 1.25 * ms[1], ms
 
 
+def test_routing_of_wide_rows_by_few_and_by_many():
+    """Rows of more than 6144 are routed by one of two kernels (up to 768 rows and beyond): the same bits for a row either way."""
+    import torch
+    import paper_2505_10259_amd as P
+    from gpu_common import dev, host_model_pinned
+    shp = synth.mini_moe_shape(n_layers=1, d_model=8192, n_q_heads=1, n_kv_heads=1, d_ff=128, vocab=64)
+    hm = host_model_pinned(shp, seed=3)
+    x, kc, vc = (dev(a) for a in synth.make_layer_inputs(shp, 769, 1, 5, seed=4))
+    res = []
+    for B in (768, 769):
+        with P.Session(hm, None, batch_max=B, k_max=1, ctx_max=10) as s:
+            P.spec_kv_import(s.ctx, 0, 0, kc, vc, B, 5)
+            out, ids, wts = torch.empty(B, 8192, device="cuda"), torch.empty(B, 2, dtype=torch.int32, device="cuda"), torch.empty(B, 2, device="cuda")
+            P.spec_layer_forward(s.ctx, 0, 0, x, 1, out)
+            P.spec_debug_routing(s.ctx, 0, ids, wts, B)
+            res.append((out[:768], ids[:768], wts[:768]))
+    assert torch.isfinite(res[0][0]).all()
+    assert all(torch.equal(a, b) for a, b in zip(*res))
+
+
 def test_cfg2_full_size_sampled_sequences():
     """The benchmark's launch configuration: d 4096, 32/8 heads x 128, 8 experts of 14336, B 256,
     k 8 (9 new tokens), 2048 cached positions.  The oracle recomputes a few whole sequences."""
