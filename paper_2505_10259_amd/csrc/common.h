@@ -136,7 +136,10 @@ struct GemmArgs {
 //            K = 6144   20 rows 484 / 486 / 466 / 479 / 482              224 rows 728 / 690 / 675 / 698 / 690
 //   down     K = 14336  20 rows 155 / 141 / 138 / 138 / 140              80 rows 175 / 159 / 156 / 157 / 158
 //            K = 16384  20 rows 305 / 270 / 263 / 260 / 263              224 rows 380 / 346 / 353 / 355 / 359
-// so panels of 4 up to K = 4096 and of 8 above.  (Rotating the slabs of a panel by its position gave nothing.)
+// so panels of 4 up to K = 4096 and of 8 above (with 224 rows of K = 16384 the 4 would be 2 % better).  Single matrices of other widths, time as
+// panels over time as rows, 1 to 8192 rows: K = 256 to 1024 0.98-1.02 (one of 4.5 us 1.08), 2048 and 3072 0.95-1.02, 4096 0.86-1.03, 5120 0.92-0.98, 6144
+// 0.84-1.02, 8192 0.94-1.02, 14336 0.94-1.03, 16384 0.82-1.02; from 2304 rows on the matrix cores bound it and the layout counts
+// for nothing.  (Rotating the slabs of a panel by its position gave nothing.)
 constexpr int PANEL_MAX_K = 16384;     // a panel is turned in the registers of one workgroup
 __host__ __device__ inline int weight_panel_log2(int64_t N, int64_t K) {
     if (K % 64 != 0 || K > PANEL_MAX_K || N % 8 != 0) return 0;

@@ -861,7 +861,8 @@ struct TileChoice { int ni = 8, max_rows = 256; double cost = 0.0; };
 // takes a 64-wide slab of (mi + ni) x 32 operand rows at about 53 GB/s (0.076 us per 32 rows, measured
 // over tiles of (1, 1) to (8, 8)) or at the rate of its matrix instructions (32 cycles per mi x ni); a tile costs 3 us around
 // its slabs; a last round that fills at most half the units is cut in halves (256 columns); and the weights come from HBM
-// at 6.5 TB/s at best.  The second term of the result keeps the cheaper of two tilings that both wait for HBM.
+// at 6.5 TB/s at best.  (Fitted on weights as rows; panels of K = 4096 and more take 2 to 14 % less time up to 896 rows, which
+// moves all tilings of a product alike.)  The second term of the result keeps the cheaper of two tilings that both wait for HBM.
 double tile_cost(const GemmArgs& a, int ni, int max_rows) {
     const bool sw = a.epilogue == EPI_SWIGLU_T;
     const int groups = a.group_offsets ? (a.n_groups > 0 ? a.n_groups : 1) : 1, cols = sw ? 16 * ni : 32 * ni;
@@ -905,10 +906,12 @@ TileChoice choose_wide(const GemmArgs& a) {
 
 // The tiles of a product.  Every output's sum runs over the contraction in the same order whatever the tiles, so the choice
 // changes no bit of the result.  Narrow tiles give a product of few rows or few columns more tiles
-// than 256-column ones, hence more compute units that pull weights (us; 4096 x 4096 and 6144 x 4096 weights):
+// than 256-column ones, hence more compute units that pull weights (us; 4096 x 4096 and 6144 x 4096 weights, as rows and,
+// last line, as panels):
 //   rows        5          32         64         128        320        896
 //   256 cols    43 / 42    46 / 47    50 / 51    46 / 50    47 / 51    50 / 53
 //   chosen      11 / 12    14 / 14    14 / 19    17 / 24    25 / 33    39 / 51
+//   panels      11 / 13    13 / 15               17 / 22    23 / 31    37 / 44
 TileChoice choose_tiles(const GemmArgs& a) {
     TileChoice best = choose_wide(a);
     for (int ni = 4; ni >= (a.epilogue == EPI_SWIGLU_T ? 4 : 1); ni /= 2)
@@ -972,11 +975,16 @@ hipError_t launch_gemm_mfma_bf16(const GemmArgs& a, hipStream_t st) {
     return launch_gemm_tiles(a, t.ni, t.max_rows, expected_rows(a) <= t.max_rows, st);
 }
 
-// Whether a QKV projection of M rows is made as narrow tiles into an f32 buffer, with a rotary/append kernel behind it (6 us and
-// a round trip of the buffer).  Narrow tiles rotate themselves, which is faster at every size measured, us as buffer and kernel / in
-// the epilogue, K = 4096, 6144 columns: layer of 512 rows 644 / 637, 768 rows 726 / 722, prefill of 520 rows (8 layers) 3641 / 3570, of
-// 333 rows 3200 / 3130, round of 32 sequences (28 layers of 32 to 224 rows) 3918 / 3841.  Fewer than 4096 columns on more than
-// 448 rows were not measured and keep the cost model's choice against 256-column tiles.
+// Whether a QKV projection of M rows is made as tiles into an f32 buffer, with a rotary/append kernel behind it (6 us and a round
+// trip of the buffer), or rotates in its epilogue.  The epilogue is the better one or the same for few rows and for wide projections, us as
+// buffer and kernel / in the epilogue, K = 4096, 6144 columns: layer of 512 rows 644 / 637, 768 rows 726 / 722, prefill of 520 rows (8 layers)
+// 3641 / 3570, of 333 rows 3200 / 3130, round of 32 sequences (28 layers of 32 to 224 rows) 3918 / 3841.  Between 449 rows and the count from
+// which the wide epilogue wins in the cost model (960 rows of 1536 columns, 1024 of 2560, 1280 of 3072) neither is always ahead, and the
+// buffer keeps what it had.  Whole layers there, 256-wide experts:
+//   rows                       449        512        640        768        896        960        1024       1280
+//   K = 1024, 1536 columns  58.3/57.4  59.0/58.2  67.3/66.0  69.7/68.9  74.7/73.3  76.5/74.3
+//   K = 2048, 2560 columns  79.9/81.1  84.4/82.5  95.8/95.2   103/102    115/110    120/115    123/118
+//   K = 4096, 3072 columns   105/105    110/113    124/124    138/134    154/148    158/155    164/172    185/187
 bool qkv_unfused_pays(int M, int N, int K) {
     if (M <= 448 || N >= 4096) return false;
     GemmArgs a{};

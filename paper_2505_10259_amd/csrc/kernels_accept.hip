@@ -64,7 +64,7 @@ hipError_t launch_philox_uniforms(uint64_t seed, uint32_t round, uint32_t seq_ba
 // The maximum and the normaliser of the two rows of a candidate come from one pass (running maximum per thread), the
 // draw takes one pass for the sums of runs of 64 U granules and reads again only the run that holds the
 // crossing.  What bounds it is the exponentials of one compute unit per row pair: 24 sequences of 5 candidates,
-// 65537 ids, 1255 us as 256 threads with 4-byte loads and a pass per reduction, 93 as a launch of tests and one of draws, 66 with
+// 65537 ids, 1255 us as 256 threads with 4-byte loads and a pass per reduction, 93 as a launch of tests and one of draws, 71 with
 // the draw in the workgroup that rejects (accept_ahead_generic_kernel).  The normaliser's error is 1.0 x 2^-24 on average (256 threads: 3.7).
 // =================================================================================================
 constexpr int WIDE_THREADS = 1024, WIDE_WAVES = WIDE_THREADS / 64, WIDE_RUNS = 1024;
@@ -828,6 +828,10 @@ accept_sample_kernel(AcceptArgs a) {
 //   about half kept              42 / 24  30 / 27  66 / 29  69 / 46  127 / 70  77 / 59  80 / 88  117 / 161
 //   nearly all                   65 / 21  30 / 23  66 / 29  75 / 46  131 / 70  78 / 57  83 / 93  128 / 175
 //   nearly none                  27 / 27  29 / 28  36 / 30  45 / 39   50 / 42  53 / 47  59 / 75   70 / 99
+// A draft of which nothing at all is kept is the one case that at once is slower, up to twice (in turn every sequence ends at its first
+// candidate); device us, nothing kept / kept with probability 0.8 / all kept, in turn and at once:
+//   32000 ids   64, 8  27, 43 / 110, 64 / 111, 66    100, 4  28, 41 / 68, 54 / 69, 49    100, 8   28, 47 / 113, 84 / 116, 88
+//   512 ids     64, 8  24, 32 / 90, 46 / 90, 47      100, 4  24, 29 / 54, 38 / 53, 33    100, 16  24, 47 / 165, 87 / 164, 100
 // 65537 ids (general path): 16 sequences of 4 140 / 68, 64 of 8 287 / 138, 100 of 4 168 / 125, 160 of 4 173 / 166.
 // What bounds it is the exponentials of one compute unit: 4.2 us a row of 32000 ids (17 instructions each), and as much for a
 // row's bytes where all units load.  (Two workgroups per unit in half the registers spill and are slower; so is a next row

@@ -809,12 +809,16 @@ gemm_small_kernel(GemmArgs a, int vec) {
 }
 
 // f32 products of few tiles on the matrix cores: one wavefront makes 16 rows x 16 columns (of each of two weight matrices one).  What bounds such a product is
-// latency (a round of the 256-wide two-layer model is 60 of them, 4 to 20 rows), so every operand piece goes straight from memory to
+// latency (a round of the 256-wide two-layer model is 29 of them, 4 to 20 rows), so every operand piece goes straight from memory to
 // registers, 256 k in flight at once, with no LDS and no barrier in between.  A lane's four
 // consecutive k are turned (permlane swaps) so that v_mfma_f32_16x16x4_f32 takes them in ascending order: it is four
 // chained fused multiply-adds, so every output has the bits of the VALU kernels' chain, whatever the row count chooses.
-// Round of four sequences and four candidates, with the launches that NORM and EPI_ROPE_KV save: 420 -> 391 us; 16 sequences and
-// eight candidates 745 -> 703.
+// Round of four sequences and four candidates, with the launches that NORM and EPI_ROPE_KV save and the attention below: 433 -> 381 us.
+// A product alone, us, 8x32 VALU tiles / here, from 231 sizes of 1 to 512 rows (0.60 to 1.03 of the time, three at 1.04-1.06):
+//   K = 256    256 columns, 4 rows 4.4 / 4.4, 128 rows 4.6 / 4.7     8064 columns, 4 rows 5.3 / 5.6, 64 rows 15.8 / 11.9
+//   K = 1024  1024 columns, 1 row 11.5 / 10.6, 256 rows 27.7 / 18.5  8064 columns, 4 rows 14.1 / 14.9, 64 rows 55.6 / 36.6
+//   K = 2048   256 columns, 16 rows 20.1 / 21.1                      4096 columns, 20 rows 30.0 / 24.6
+//   K = 8192   256 columns, 4 rows 78.1 / 71.4                       4096 columns, 64 rows 190 / 115
 //
 // NORM: the rows are the residual stream and the product takes rmsnorm(row) * norm_g, with the row's squares summed in the
 // order of combine_norm_vec_kernel (same bits); EPI_ROPE_KV: a wavefront makes 16 rotary pairs (the second weight row of a
@@ -881,7 +885,7 @@ gemm_f32_kernel(GemmArgs a) {
     const float* wrow = (SWIGLU && w ? (const float*)a.W3 : (const float*)a.W) + (int64_t)group * a.w_group_stride +
                         (int64_t)(ROPE ? n / half * 2 * half + n % half + w * half : n) * a.K;
     // Chunks of 16 P: a whole one takes one address per operand and neither clamps nor branches (with them the dozen
-    // instructions more per piece outweigh its four MFMAs: round of four sequences 394 -> 382 us).
+    // instructions more per piece outweigh its four MFMAs: 3 % of a round of four sequences).
     f32x4_t fa[P], fw[P], fg[P];
     const float *pa = arow + kq, *pw = wrow + kq, *pg = (const float*)a.norm_g + kq;
     auto request = [&](auto whole_c, int k0, int p) __attribute__((always_inline)) {

@@ -418,8 +418,8 @@ def test_prefill_workspace_is_no_larger_than_its_rows_need(dtype):
 
 
 def test_prefill_on_either_side_of_the_projection_with_its_own_rotary_kernel():
-    """A QKV projection rotates and appends in its epilogue or, for few rows, leaves that to a kernel of its own
-    (1536 columns, K = 1024: up to 960 rows); both give the same bits, whichever takes which part of a prefill."""
+    """A QKV projection rotates and appends in its epilogue or leaves that to a kernel of its own (1536 columns, K = 1024: 449 to
+    960 rows); both give the same bits, whichever takes which part of a prefill."""
     import torch
     import paper_2505_10259_amd as P
     from gpu_common import host_model_pinned
