@@ -34,7 +34,7 @@
 //     ahead and the weights are fetched 2.7 times; with equal tiles 1.2 times);
 //   * tile width: 256 columns, or 128, 64 or 32 where wider tiles would leave compute units idle (see
 //     choose_tiles); the weights carry the non-temporal hint where no second row tile reads them (8x7B-shaped gate/up
-//     product, 40 rows: 308 -> 279 us, 6.74 TB/s; a streaming read of the same buffers: 6.2 TB/s
+//     product, 40 rows, weights as rows: 308 -> 279 us, 6.74 TB/s; a streaming read of the same buffers: 6.2 TB/s
 //     plain, 7.05 with the hint);
 //   * resident weights are panels of 4 or 8 rows (see common.h): a load then takes runs of 512 B or 1 KB of HBM;
 //   * tile order: group (expert), then bands of four row tiles, then column tile, then row tile
@@ -926,7 +926,7 @@ TileChoice choose_tiles(const GemmArgs& a) {
 
 // The kernel for tiles of 32*ni columns (ni 8, 4, 2, 1 as the epilogue has them); nt: no weight is read by two
 // row tiles of the expected height.  The hint is for weights that come from HBM, as those of a target or draft beyond the
-// 256 MB of last-level cache do: up to 32 rows, 100 to 200 MB of weights, 21 to 40 us with it and 24 to 44 without.  A
+// 256 MB of last-level cache do: up to 32 rows, 100 to 200 MB of weights (as rows), 21 to 40 us with it and 24 to 44 without.  A
 // single matrix of 100 to 250 MB used over and over by itself would stay in that cache without it (16384 x 4096 weights,
 // 5 rows: 27 against 23 us; below 64 MB no difference).  Routing that gives an expert more rows than expected, so that
 // two row tiles stream its weights with the hint, does not undo the gain: 320 rows, us per layer with routing uniform /
