@@ -212,7 +212,7 @@ def test_f32_attention_on_either_side_of_the_kernel_for_few_rows(head_dim, B, n_
                 best = min(best, P.spec_profile_read(s.ctx)["attn"]["ms"])
             ms.append(best)
     assert torch.isfinite(out[0]).all() and torch.equal(out[0], out[1])
-    assert ms[0] < 1.25 * ms[1], ms
+    assert ms[0] < 1.35 * ms[1], ms
 
 
 def test_routing_of_wide_rows_by_few_and_by_many():
