@@ -4,9 +4,11 @@
 // that equal the target's own argmax, then emit the target's argmax at the first mismatch (or after
 // all k).  Stochastic rule (the speculative-sampling works cited in Section 2.2): keep candidate i
 // while u * q_i(c_i) < p_{i-1}(c_i); then draw from max(0, p_n - q_{n+1}) renormalised, or from p_k
-// when all were kept.  All reductions over the vocabulary are wavefront shuffles + one LDS hop;
-// running sums for the inverse-CDF draw are taken in ascending token id (register path: 4096 ids per sweep; general path:
-// runs of 64 granules of four ids; short rows: 1024 ids per sweep).
+// when all were kept.  All reductions over the vocabulary are wavefront reductions + one LDS hop;
+// running sums for the inverse-CDF draw are taken in ascending token id (runs of 64 granules of four ids; draft picks from registers: 4096
+// ids per sweep).
+#include <type_traits>
+
 #include "common.h"
 
 namespace sv {
@@ -54,27 +56,329 @@ hipError_t launch_philox_uniforms(uint64_t seed, uint32_t round, uint32_t seq_ba
     return hipGetLastError();
 }
 
-// Softmax weights use the library's expf throughout.  One exp2 instruction on the rounded product x log2 e (its rounding
-// error added to first order) was 10 % faster for 256 sequences of 6 candidates over 32000 ids, 105 against 117 us, but up to
-// 2.3 x 2^-24 off where expf is 1.4, and it loses weights below 2^-126.
+// Single softmax weights use the library's expf.  (One exp2 instruction on the rounded product x log2 e is up to 2.3 x 2^-24 off where expf is
+// 1.4, and loses weights below 2^-126.)
+// In sums of many weights, of z under a maximum m, e^((z - m) / tau) = 2^t with t = (z - m) c, c = log2(e) / tau in two
+// parts, both positive so that -inf gives 0 (weight_scale).  t is rounded once, which for single weights is up to |t| 2^-25 off but
+// averages out in a sum, and weights below 2^-126 of the largest count as nothing.  Four instructions against expf's fourteen and the two in front: 256
+// sequences of 6 candidates over 32000 ids 85 us against 95 with a nine-instruction exponential as exact as expf.
+struct WeightScale { float hi, lo; };
+__device__ inline float sum_weight(float z, float m, const WeightScale& c) {
+    const float d = z - m;
+    return __builtin_amdgcn_exp2f(__builtin_fmaf(d, c.hi, d * c.lo));
+}
+__device__ inline WeightScale weight_scale(float inv_tau) {
+    const double c = (double)inv_tau * 1.44269504088896340736;
+    float hi = (float)c;
+    if ((double)hi > c) hi = __uint_as_float(__float_as_uint(hi) - 1u);       // (towards zero)
+    return {hi, fmaxf((float)(c - (double)hi), 1e-45f)};
+}
 
 // =================================================================================================
-// General path: long rows of any vocabulary size and alignment.  One workgroup of 1024 threads per sequence; a row is read in
-// aligned 16-byte granules (elements outside the row count as -inf), several granules per thread in flight.
-// The maximum and the normaliser of the two rows of a candidate come from one pass (running maximum per thread), the
-// draw takes one pass for the sums of runs of 64 U granules and reads again only the run that holds the
-// crossing.  What bounds it is the exponentials of one compute unit per row pair: 24 sequences of 5 candidates,
-// 65537 ids, 1255 us as 256 threads with 4-byte loads and a pass per reduction, 93 as a launch of tests and one of draws, 71 with
-// the draw in the workgroup that rejects (accept_ahead_generic_kernel).  The normaliser's error is 1.0 x 2^-24 on average (256 threads: 3.7).
+// Rows of 4 ids and more at any alignment, a workgroup of T threads per row or pair of rows.  A row passes through in granules of four ids: maximum and
+// normaliser in one pass (running maximum per thread), the draw in a pass for the sums of runs of 64 U granules, of which only the run that
+// holds the crossing is read again.  1 / normaliser of random rows (standard deviation 3, temperature
+// 0.8) is off by 0.96 x 2^-24 on average at 32000 and 65537 ids, 0.94 at 512 (library exponentials, rows in registers or 1024 threads: 1.05, 1.02, 0.88).
 // =================================================================================================
-constexpr int WIDE_THREADS = 1024, WIDE_WAVES = WIDE_THREADS / 64, WIDE_RUNS = 1024;
+// running maximum and sum of exp((z - m) / tau) over what a thread has seen
+struct MaxSum {
+    float m = -INFINITY, s = 0.f;
+    template <int N>
+    __device__ void take(const float4 (&v)[N], const WeightScale& c) {
+        float mx = m;
+#pragma unroll
+        for (int q = 0; q < N; ++q) mx = fmaxf(fmaxf(fmaxf(mx, v[q].x), fmaxf(v[q].y, v[q].z)), v[q].w);
+        if (mx > m) { s *= sum_weight(m, mx, c); m = mx; }
+        // (nothing but -inf and not-a-numbers so far: the former add nothing, one of the latter makes the sum one)
+        const float at = m == -INFINITY ? 0.f : m;
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+            s += (sum_weight(v[q].x, at, c) + sum_weight(v[q].y, at, c)) + (sum_weight(v[q].z, at, c) + sum_weight(v[q].w, at, c));
+    }
+};
 
-struct WideShared {
-    float red[2][WIDE_WAVES];
-    int redi[WIDE_WAVES];
-    float run[WIDE_RUNS];             // total of every run, then the sum in front of it
-    float wave_tot[WIDE_WAVES];
+template <int T>
+struct RowShared {
+    float red[2][2][T / 64];
+    float run[T];                 // total of every run, then the sum in front of it
+    float wave_tot[T / 64];
     int pick, last, stop;
+};
+// granule g of a row: ids 4 g .. 4 g + 3, loaded from the row's last four ids where it does not lie inside; row_ids makes of those
+// what the granule holds (-inf past the end)
+__device__ inline float4 row_load(const float* row, int V, int g) {
+    typedef float vec __attribute__((ext_vector_type(4), aligned(4)));
+    const vec x = *(const vec*)((const char*)row + min(16u * (uint32_t)g, 4u * (uint32_t)V - 16u));
+    return make_float4(x.x, x.y, x.z, x.w);
+}
+__device__ inline float4 row_ids(const float4& x, int V, int g) {
+    const int n = V - 4 * g;
+    const float I = -INFINITY;
+    float4 y = make_float4(n >= 4 ? x.x : I, n >= 4 ? x.y : I, n >= 4 ? x.z : I, n >= 4 ? x.w : I);
+    if (n > 0 && n < 4) y = n == 3 ? make_float4(x.y, x.z, x.w, I) : n == 2 ? make_float4(x.z, x.w, I, I) : make_float4(x.w, I, I, I);
+    return y;
+}
+// maxima and normalisers of the rows p and (if TWO) q
+template <int T, bool TWO>
+__device__ inline void row_stats(const float* p, const float* q, int V, float inv_tau, RowShared<T>& sh, float* pm, float* ps, float* qm, float* qs) {
+    constexpr int STEP = 4 * T;               // granules
+    const int t = (int)threadIdx.x, first = __builtin_amdgcn_readfirstlane(t & ~63);
+    const WeightScale c = weight_scale(inv_tau);
+    MaxSum x, y;
+    float4 a[2][4], b[2][4];
+    // (of a wavefront: whether all its granules of the step at g0 lie inside the row, whether its j-th ones do in part)
+    auto whole = [&](int g0) { return 4 * (g0 + 3 * T + first + 64) <= V; };
+    auto part = [&](int g0, int j) { return 4 * (g0 + j * T + first) < V; };
+    // (always all of a step's loads, so that the count of those in flight is known where their predecessors are waited for)
+    auto request = [&](int buf, int g0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            a[buf][j] = row_load(p, V, g0 + j * T + t);
+            if (TWO) b[buf][j] = row_load(q, V, g0 + j * T + t);
+        }
+    };
+    auto take = [&](int buf, int g0) {
+        if (whole(g0)) {
+            x.take(a[buf], c);
+            if (TWO) y.take(b[buf], c);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (part(g0, j)) {
+                    float4 v[1] = {row_ids(a[buf][j], V, g0 + j * T + t)};
+                    x.take(v, c);
+                    if (TWO) {
+                        v[0] = row_ids(b[buf][j], V, g0 + j * T + t);
+                        y.take(v, c);
+                    }
+                }
+        }
+    };
+    request(0, 0);
+    for (int g0 = 0; g0 < (V + 3) >> 2; g0 += 2 * STEP) {
+        request(1, g0 + STEP);
+        take(0, g0);
+        request(0, g0 + 2 * STEP);
+        take(1, g0 + STEP);
+    }
+    const int lane = t & 63, wv = t >> 6;
+    auto wave = [&](const MaxSum& v, int r) {
+        const float m = wave_max(v.m);
+        const float s = wave_sum(v.m == -INFINITY ? v.s : v.s * expf((v.m - m) * inv_tau));
+        if (lane == 0) { sh.red[r][0][wv] = m; sh.red[r][1][wv] = s; }
+    };
+    auto block = [&](int r, float* mo, float* so) {
+        float m = sh.red[r][0][0], s = 0.f;
+#pragma unroll
+        for (int w = 1; w < T / 64; ++w) m = fmaxf(m, sh.red[r][0][w]);
+#pragma unroll
+        for (int w = 0; w < T / 64; ++w) {
+            const float mw = sh.red[r][0][w], sw = sh.red[r][1][w];
+            s += mw == -INFINITY ? sw : sw * expf((mw - m) * inv_tau);
+        }
+        *mo = m; *so = s;
+    };
+    __syncthreads();
+    wave(x, 0);
+    if (TWO) wave(y, 1);
+    __syncthreads();
+    block(0, pm, ps);
+    if (TWO) block(1, qm, qs);
+}
+// sum over the lanes up to and with this one
+__device__ inline float wave_prefix(float v) {
+    auto up = [](float x, auto ctrl, auto rows) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, decltype(rows)::value, 0xf, false));
+    };
+    using All = std::integral_constant<int, 0xf>;
+    v += up(v, std::integral_constant<int, 0x111>{}, All{});                                  // row_shr:1, 2, 4, 8
+    v += up(v, std::integral_constant<int, 0x112>{}, All{});
+    v += up(v, std::integral_constant<int, 0x114>{}, All{});
+    v += up(v, std::integral_constant<int, 0x118>{}, All{});
+    v += up(v, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});     // row_bcast:15 to rows 1 and 3
+    v += up(v, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});     // row_bcast:31 to rows 2 and 3
+    return v;
+}
+// Inverse CDF over the residual weights max(0, p - q) of two rows, or (RES false) over the target's own: the smallest id whose running sum
+// (ascending ids) exceeds u * total; if rounding leaves none, the largest id of positive weight.  *total_out: the total (0: no
+// positive weight; result invalid).  One pass for the sums of runs of 64 U granules; the run that holds the crossing is read again.
+template <int T, bool RES>
+__device__ inline int row_draw(const float* p, const float* q, int V, float inv_tau, float pm, float pf, float qm, float qf, float u,
+                               RowShared<T>& sh, float* total_out) {
+    constexpr int W = T / 64;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = (V + 3) >> 2;
+    const int U = (n + 64 * T - 1) / (64 * T), runs = (n + 64 * U - 1) / (64 * U);
+    const WeightScale c = weight_scale(inv_tau);
+    auto weights = [&](const float4& zp, const float4& zq, int g, auto&& f) {
+        float4 a = zp, b = zq;
+        if (4 * (g - lane) + 256 > V) {                       // (the same for all lanes)
+            a = row_ids(zp, V, g);
+            if (RES) b = row_ids(zq, V, g);
+        }
+        float4 w = make_float4(f(a.x, pm) * pf, f(a.y, pm) * pf, f(a.z, pm) * pf, f(a.w, pm) * pf);
+        if (RES) w = make_float4(fmaxf(0.f, w.x - f(b.x, qm) * qf), fmaxf(0.f, w.y - f(b.y, qm) * qf),
+                                 fmaxf(0.f, w.z - f(b.z, qm) * qf), fmaxf(0.f, w.w - f(b.w, qm) * qf));
+        return w;
+    };
+    auto sum4 = [](const float4& w) { return (w.x + w.y) + (w.z + w.w); };
+    // four runs of a wavefront at a time, the next granules requested ahead
+    float4 zp[2][4], zq[2][4];
+    float t[4] = {0.f, 0.f, 0.f, 0.f};
+    auto request = [&](int buf, int r0, int i) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            zp[buf][j] = row_load(p, V, ((r0 + j * W) * U + i) * 64 + lane);
+            if (RES) zq[buf][j] = row_load(q, V, ((r0 + j * W) * U + i) * 64 + lane);
+        }
+    };
+    auto take = [&](int buf, int r0, int i) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (r0 + j * W >= runs) continue;                 // (the same for all lanes)
+            t[j] += sum4(weights(zp[buf][j], RES ? zq[buf][j] : zp[buf][j], ((r0 + j * W) * U + i) * 64 + lane,
+                                 [&](float z, float m) { return sum_weight(z, m, c); }));
+            if (i == U - 1) {
+                const float v = wave_sum(t[j]);
+                if (lane == 0) sh.run[r0 + j * W] = v;
+                t[j] = 0.f;
+            }
+        }
+    };
+    int r0 = wv, i0 = 0;
+    auto next = [&](int& r, int& i) { if (++i == U) { i = 0; r += 4 * W; } };
+    request(0, r0, i0);
+    if (threadIdx.x == 0) { sh.pick = 0x7fffffff; sh.last = -1; }
+    while (r0 < runs) {
+        int r1 = r0, i1 = i0;
+        next(r1, i1);
+        request(1, r1, i1);
+        take(0, r0, i0);
+        r0 = r1; i0 = i1;
+        next(r0, i0);
+        request(0, r0, i0);
+        take(1, r1, i1);
+    }
+    __syncthreads();
+    // the sum in front of every run, one per thread
+    const float mine = (int)threadIdx.x < runs ? sh.run[threadIdx.x] : 0.f;
+    const float incl = wave_prefix(mine);
+    if (lane == 63) sh.wave_tot[wv] = incl;
+    __syncthreads();
+    float before = 0.f, total = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) { if (w < wv) before += sh.wave_tot[w]; total += sh.wave_tot[w]; }
+    const float target = u * total, slack = 1e-4f * total;
+    const float front = before + (incl - mine);
+    // the run that holds the crossing, and its neighbours within the rounding of these sums
+    uint64_t near = __ballot(mine > 0.f && front <= target + slack && front + mine >= target - slack);
+    int found = 0x7fffffff;
+    auto exact = [&](float z, float m) { return expf((z - m) * inv_tau); };
+    for (; near; near &= near - 1) {
+        const int l = __ffsll((unsigned long long)near) - 1, r = wv * 64 + l;
+        float base = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(front), l));
+        for (int i = 0; i < U; ++i) {
+            const int g = (r * U + i) * 64 + lane;
+            const float4 za = row_load(p, V, g), zb = RES ? row_load(q, V, g) : za;
+            const float4 w = weights(za, zb, g, exact);
+            const float local = sum4(w), in = wave_prefix(local);
+            float s = base + (in - local);
+            const float x[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                s += x[j];
+                if (x[j] > 0.f && s > target) found = min(found, 4 * g + j);
+            }
+            base += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(in), 63));
+        }
+    }
+    if (found != 0x7fffffff) atomicMin(&sh.pick, found);
+    __syncthreads();
+    *total_out = total;
+    if (sh.pick != 0x7fffffff) return sh.pick;
+    int last = -1;
+    for (int g = threadIdx.x; g < (n + 63) / 64 * 64; g += T) {
+        const float4 za = row_load(p, V, g), zb = RES ? row_load(q, V, g) : za;
+        const float4 w = weights(za, zb, g, exact);
+        const float x[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) if (x[j] > 0.f) last = 4 * g + j;
+    }
+    if (last >= 0) atomicMax(&sh.last, last);
+    __syncthreads();
+    return sh.last >= 0 ? sh.last : 0;
+}
+// What the acceptance test of candidate i of sequence b needs of its rows, asked for ahead of their statistics, and the test: true = rejected
+struct Candidate {
+    float p = 0.f, q = 0.f, u = 0.f;
+    bool valid = false;
+};
+__device__ inline Candidate candidate(const AcceptArgs& a, int b, int i) {
+    Candidate t;
+    const int c = a.draft_tokens[b * a.k + i];
+    t.valid = c >= 0 && c < a.V;                      // an id outside the vocabulary is a rejected candidate
+    if (t.valid) {
+        t.p = a.p_logits[((int64_t)b * (a.k + 1) + i) * a.V + c];
+        t.q = a.q_logits[((int64_t)b * a.k + i) * a.V + c];
+    }
+    t.u = a.u_accept ? a.u_accept[b * a.k + i] : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)(i + 1), 1);
+    return t;
+}
+__device__ inline bool rejects(const Candidate& t, float inv_tau, float pm, float ps, float qm, float qs) {
+    const float pv = expf((t.p - pm) * inv_tau) / ps, qv = expf((t.q - qm) * inv_tau) / qs;
+    return !t.valid || !(t.u * qv < pv);
+}
+
+// =================================================================================================
+// Vocabularies of fewer than four ids: a thread per sequence.
+// =================================================================================================
+__device__ inline void tiny_stats(const float* z, int V, float inv_tau, float* m, float* s) {
+    *m = -INFINITY; *s = 0.f;
+    for (int c = 0; c < V; ++c) *m = fmaxf(*m, z[c]);
+    for (int c = 0; c < V; ++c) *s += expf((z[c] - *m) * inv_tau);
+}
+template <typename F>
+__device__ inline int tiny_inverse_cdf(F w, int V, float u, float* total_out) {
+    float total = 0.f, run = 0.f;
+    int last = 0;
+    for (int c = 0; c < V; ++c) total += w(c);
+    *total_out = total;
+    for (int c = 0; c < V; ++c) {
+        const float x = w(c);
+        run += x;
+        if (x > 0.f && run > u * total) return c;
+        if (x > 0.f) last = c;
+    }
+    return last;
+}
+__global__ void accept_sample_tiny_kernel(AcceptArgs a) {
+    const int b = blockIdx.x * blockDim.x + threadIdx.x, k = a.k, V = a.V;
+    if (b >= a.B) return;
+    const float* P = a.p_logits + (int64_t)b * (k + 1) * V;
+    const float* Q = a.q_logits + (int64_t)b * k * V;
+    const float it = a.inv_tau;
+    float pm, ps, qm = 0.f, qs = 1.f, tot = 0.f;
+    int n = 0, nxt = 0;
+    for (;; ++n) {
+        tiny_stats(P + n * V, V, it, &pm, &ps);
+        if (n == k) break;
+        tiny_stats(Q + n * V, V, it, &qm, &qs);
+        if (rejects(candidate(a, b, n), it, pm, ps, qm, qs)) break;
+    }
+    const float u = a.u_resample ? a.u_resample[b * (k + 1) + n] : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)n, 2);
+    auto wp = [&](int c) { return expf((P[n * V + c] - pm) * it) / ps; };
+    if (n < k) nxt = tiny_inverse_cdf([&](int c) { return fmaxf(0.f, wp(c) - expf((Q[n * V + c] - qm) * it) / qs); }, V, u, &tot);
+    if (n == k || !(tot > 0.f)) nxt = tiny_inverse_cdf(wp, V, u, &tot);       // (p == q everywhere: the target row)
+    if (a.n_accepted) a.n_accepted[b] = n;
+    if (a.next_token) a.next_token[b] = nxt;
+}
+
+// =================================================================================================
+// Greedy rule, a workgroup per sequence, for rows of any size and alignment (the kernels for some of them follow).
+// =================================================================================================
+constexpr int WIDE_THREADS = 1024, WIDE_WAVES = WIDE_THREADS / 64;
+struct WideShared {
+    float red[WIDE_WAVES];
+    int redi[WIDE_WAVES];
 };
 
 // a row of V floats at any alignment, as granules of four: granule g holds ids 4 g - off .. 4 g - off + 3
@@ -91,71 +395,6 @@ struct WideRow {
         return make_float4(v[0], v[1], v[2], v[3]);
     }
 };
-
-// running maximum and sum of exp((z - m) inv_tau) over what a thread has seen
-struct MaxSum {
-    float m = -INFINITY, s = 0.f;
-    __device__ void take(const float4 (&v)[4], float inv_tau) {
-        float mx = m;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) mx = fmaxf(fmaxf(fmaxf(mx, v[q].x), fmaxf(v[q].y, v[q].z)), v[q].w);
-        if (mx > m) { s *= expf((m - mx) * inv_tau); m = mx; }
-        // (nothing but -inf and not-a-numbers so far: the former add nothing, one of the latter makes the sum one)
-        const float at = m == -INFINITY ? 0.f : m;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            s += (expf((v[q].x - at) * inv_tau) + expf((v[q].y - at) * inv_tau)) +
-                 (expf((v[q].z - at) * inv_tau) + expf((v[q].w - at) * inv_tau));
-    }
-};
-
-// maximum and normaliser of one or two rows (b: may be the same row as a, then computed for nothing else)
-template <bool TWO>
-__device__ inline void wide_row_stats(const WideRow& a, const WideRow& b, float inv_tau, WideShared& sh, float* am, float* as,
-                                      float* bm, float* bs) {
-    constexpr int STEP = 4 * WIDE_THREADS;
-    const int n = TWO ? max(a.n, b.n) : a.n;
-    MaxSum x, y;
-    float4 va[2][4], vb[2][4];
-    auto request = [&](int buf, int g0) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            va[buf][q] = a.load(g0 + q * WIDE_THREADS + (int)threadIdx.x);
-            if (TWO) vb[buf][q] = b.load(g0 + q * WIDE_THREADS + (int)threadIdx.x);
-        }
-    };
-    request(0, 0);
-    for (int g0 = 0; g0 < n; g0 += 2 * STEP) {              // the next four granules are requested ahead
-        if (g0 + STEP < n) request(1, g0 + STEP);
-        x.take(va[0], inv_tau);
-        if (TWO) y.take(vb[0], inv_tau);
-        if (g0 + STEP < n) {
-            if (g0 + 2 * STEP < n) request(0, g0 + 2 * STEP);
-            x.take(va[1], inv_tau);
-            if (TWO) y.take(vb[1], inv_tau);
-        }
-    }
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    auto reduce = [&](const MaxSum& t, int slot, float* mo, float* so) {
-        float m = wave_max(t.m);
-        __syncthreads();
-        if (lane == 0) sh.red[slot][wv] = m;
-        __syncthreads();
-        m = sh.red[slot][0];
-#pragma unroll
-        for (int w = 1; w < WIDE_WAVES; ++w) m = fmaxf(m, sh.red[slot][w]);
-        float v = wave_sum(t.m == -INFINITY ? t.s : t.s * expf((t.m - m) * inv_tau));
-        __syncthreads();
-        if (lane == 0) sh.red[slot][wv] = v;
-        __syncthreads();
-        v = 0.f;
-#pragma unroll
-        for (int w = 0; w < WIDE_WAVES; ++w) v += sh.red[slot][w];
-        *mo = m; *so = v;
-    };
-    reduce(x, 0, am, as);
-    if (TWO) reduce(y, 1, bm, bs);
-}
 
 // argmax, lowest id on ties
 __device__ inline int wide_argmax(const WideRow& a, WideShared& sh) {
@@ -180,217 +419,16 @@ __device__ inline int wide_argmax(const WideRow& a, WideShared& sh) {
         if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
     }
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) { sh.red[0][threadIdx.x >> 6] = bv; sh.redi[threadIdx.x >> 6] = bi; }
+    if ((threadIdx.x & 63) == 0) { sh.red[threadIdx.x >> 6] = bv; sh.redi[threadIdx.x >> 6] = bi; }
     __syncthreads();
-    bv = sh.red[0][0]; bi = sh.redi[0];
+    bv = sh.red[0]; bi = sh.redi[0];
 #pragma unroll
     for (int w = 1; w < WIDE_WAVES; ++w)
-        if (sh.red[0][w] > bv || (sh.red[0][w] == bv && sh.redi[w] < bi)) { bv = sh.red[0][w]; bi = sh.redi[w]; }
+        if (sh.red[w] > bv || (sh.red[w] == bv && sh.redi[w] < bi)) { bv = sh.red[w]; bi = sh.redi[w]; }
     return bi;
 }
 
-// Inverse CDF over non-negative weights: weight(g) gives the weights of granule g (ids 4 g - off + 0..3; 0 outside
-// the row).  The smallest id whose running sum (ascending ids) exceeds u * total; if rounding leaves none, the
-// largest id of positive weight.  *total_out: the total (0: no positive weight; result invalid).
-template <typename F>
-__device__ inline int wide_inverse_cdf(F weight, int n, int off, float u, WideShared& sh, float* total_out) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int U = (n + 64 * WIDE_RUNS - 1) / (64 * WIDE_RUNS), runs = (n + 64 * U - 1) / (64 * U);
-    int last = -1;
-    auto sum4 = [](const float4& w) { return (w.x + w.y) + (w.z + w.w); };
-    auto see = [&](const float4& w, int g) {
-        if (w.x > 0.f) last = max(last, 4 * g - off);
-        if (w.y > 0.f) last = max(last, 4 * g - off + 1);
-        if (w.z > 0.f) last = max(last, 4 * g - off + 2);
-        if (w.w > 0.f) last = max(last, 4 * g - off + 3);
-    };
-    __syncthreads();
-    sh.run[threadIdx.x] = 0.f;
-    if (threadIdx.x == 0) { sh.pick = 0x7fffffff; sh.last = -1; }
-    __syncthreads();
-    for (int r0 = wv; r0 < runs; r0 += 4 * WIDE_WAVES) {             // four runs of a wavefront at a time
-        float t[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int i = 0; i < U; ++i) {
-            float4 w[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) w[q] = weight(((r0 + q * WIDE_WAVES) * U + i) * 64 + lane);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) { t[q] += sum4(w[q]); see(w[q], ((r0 + q * WIDE_WAVES) * U + i) * 64 + lane); }
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float v = wave_sum(t[q]);
-            if (lane == 0 && r0 + q * WIDE_WAVES < runs) sh.run[r0 + q * WIDE_WAVES] = v;
-        }
-    }
-    if (last >= 0) atomicMax(&sh.last, last);
-    __syncthreads();
-    // exclusive prefix of the runs' totals, one per thread
-    const float mine = sh.run[threadIdx.x];
-    float incl = mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const float up = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += up;
-    }
-    if (lane == 63) sh.wave_tot[wv] = incl;
-    __syncthreads();
-    float before = 0.f, total = 0.f;
-#pragma unroll
-    for (int w = 0; w < WIDE_WAVES; ++w) { if (w < wv) before += sh.wave_tot[w]; total += sh.wave_tot[w]; }
-    const float target = u * total, slack = 1e-4f * total;
-    const float front = before + (incl - mine);
-    // the run that holds the crossing, and its neighbours within the rounding of these sums
-    const bool near = mine > 0.f && front <= target + slack && front + mine >= target - slack;
-    __syncthreads();
-    sh.run[threadIdx.x] = near ? front : -1.f;
-    __syncthreads();
-    int found = 0x7fffffff;
-    for (int r = wv; r < runs; r += WIDE_WAVES) {
-        float base = sh.run[r];
-        if (base < 0.f) continue;                        // (wave-uniform)
-        for (int i = 0; i < U; ++i) {
-            const int g = (r * U + i) * 64 + lane;
-            const float4 w = weight(g);
-            const float local = sum4(w);
-            float in = local;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const float up = __shfl_up(in, o, 64);
-                if (lane >= o) in += up;
-            }
-            float c = base + (in - local);
-            const float x[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                c += x[j];
-                if (x[j] > 0.f && c > target) found = min(found, 4 * g - off + j);
-            }
-            base += __shfl(in, 63, 64);
-        }
-    }
-    if (found != 0x7fffffff) atomicMin(&sh.pick, found);
-    __syncthreads();
-    *total_out = total;
-    return sh.pick != 0x7fffffff ? sh.pick : (sh.last >= 0 ? sh.last : 0);
-}
-// the softmax weights of granule g of a row (0 for -inf entries, i.e. outside the row)
-__device__ inline float4 wide_weights(const WideRow& r, int g, float m, float inv_tau, float inv_norm) {
-    const float4 z = r.load(g);
-    return make_float4(expf((z.x - m) * inv_tau) * inv_norm, expf((z.y - m) * inv_tau) * inv_norm,
-                       expf((z.z - m) * inv_tau) * inv_norm, expf((z.w - m) * inv_tau) * inv_norm);
-}
-
-// the acceptance test of candidate i of sequence b (the rows' maxima and normalisers given): true = rejected
-__device__ inline bool rejects(const AcceptArgs& a, int b, int i, float pm, float ps, float qm, float qs) {
-    const int c = a.draft_tokens[b * a.k + i];
-    if (c < 0 || c >= a.V) return true;              // an id outside the vocabulary is a rejected candidate
-    const float pv = expf((a.p_logits[((int64_t)b * (a.k + 1) + i) * a.V + c] - pm) * a.inv_tau) / ps;
-    const float qv = expf((a.q_logits[((int64_t)b * a.k + i) * a.V + c] - qm) * a.inv_tau) / qs;
-    const float u = a.u_accept ? a.u_accept[b * a.k + i]
-                               : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)(i + 1), 1);
-    return !(u * qv < pv);
-}
-
-// greedy: early exit at the first mismatch
-__global__ void __launch_bounds__(WIDE_THREADS)
-accept_greedy_generic_kernel(AcceptArgs a) {
-    __shared__ WideShared sh;
-    const int b = blockIdx.x;
-    const float* P = a.p_logits + (int64_t)b * (a.k + 1) * a.V;
-    int n = 0, am;
-    while (true) {
-        am = wide_argmax(WideRow(P + (int64_t)n * a.V, a.V), sh);
-        if (n < a.k && a.draft_tokens[b * a.k + n] == am) ++n; else break;
-    }
-    if (threadIdx.x == 0) {
-        if (a.n_accepted) a.n_accepted[b] = n;
-        if (a.next_token) a.next_token[b] = am;
-    }
-}
-
-// the draw behind n kept candidates, from the residual of the two rows or (n == k) from the target's row
-__device__ inline int wide_draw(const AcceptArgs& a, int b, int n, const WideRow& pr, const WideRow& qr, float pm, float ps,
-                                float qm, float qs, WideShared& sh) {
-    const int k = a.k, V = a.V;
-    const float it = a.inv_tau, ipn = 1.0f / ps, iqn = 1.0f / qs;
-    const float u = a.u_resample ? a.u_resample[b * (k + 1) + n]
-                                 : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)n, 2);
-    // (granules of the two rows differ where their alignments do: the residual takes q element by element then)
-    auto wp = [&](int g) { return wide_weights(pr, g, pm, it, ipn); };
-    auto wres = [&](int g) {
-        float4 w = wide_weights(pr, g, pm, it, ipn), q;
-        if (pr.off == qr.off) q = wide_weights(qr, g, qm, it, iqn);
-        else {
-            float z[4];
-            const int id = 4 * g - pr.off;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bool in = id + j >= 0 && id + j < V;
-                z[j] = in ? expf((qr.row[in ? id + j : 0] - qm) * it) * iqn : 0.f;
-            }
-            q = make_float4(z[0], z[1], z[2], z[3]);
-        }
-        return make_float4(fmaxf(0.f, w.x - q.x), fmaxf(0.f, w.y - q.y), fmaxf(0.f, w.z - q.z), fmaxf(0.f, w.w - q.w));
-    };
-    float tot = 0.f;
-    int nxt = 0;
-    if (n < k) nxt = wide_inverse_cdf(wres, pr.n, pr.off, u, sh, &tot);
-    if (n == k || !(tot > 0.f)) nxt = wide_inverse_cdf(wp, pr.n, pr.off, u, sh, &tot);    // (p == q everywhere: the target row)
-    return nxt;
-}
-
-__global__ void __launch_bounds__(WIDE_THREADS)
-accept_sample_generic_kernel(AcceptArgs a) {
-    __shared__ WideShared sh;
-    const int b = blockIdx.x, k = a.k, V = a.V;
-    const float* P = a.p_logits + (int64_t)b * (k + 1) * V;
-    const float* Q = a.q_logits + (int64_t)b * k * V;
-    const float it = a.inv_tau;
-    int n = 0;
-    float pm = 0.f, ps = 1.f, qm = 0.f, qs = 1.f;
-    // candidates are tested in order; each test needs the softmax normalisers of two rows
-    while (true) {
-        const WideRow p(P + (int64_t)n * V, V);
-        if (n == k) { wide_row_stats<false>(p, p, it, sh, &pm, &ps, nullptr, nullptr); break; }
-        wide_row_stats<true>(p, WideRow(Q + (int64_t)n * V, V), it, sh, &pm, &ps, &qm, &qs);
-        if (threadIdx.x == 0) sh.stop = rejects(a, b, n, pm, ps, qm, qs);
-        __syncthreads();
-        const int stop = sh.stop;
-        __syncthreads();
-        if (stop) break;
-        ++n;
-    }
-    const int nxt = wide_draw(a, b, n, WideRow(P + (int64_t)n * V, V), WideRow(Q + (int64_t)(n < k ? n : 0) * V, V), pm, ps, qm, qs, sh);
-    if (threadIdx.x == 0) {
-        if (a.n_accepted) a.n_accepted[b] = n;
-        if (a.next_token) a.next_token[b] = nxt;
-    }
-}
-
-// =================================================================================================
-// Short rows of any vocabulary size and alignment: one workgroup of 256 threads per sequence, an element per thread and
-// load, a pass over the row (in L1) per reduction.  Bound by the latency of its few steps, which four wavefronts
-// go through faster than the sixteen of the general path: 16 sequences, 4 candidates, us per call as this and as
-// the general path, first candidate rejected / all kept: 1001 ids 9 / 20 and 17 / 33, 2001 ids 14 / 30 and 18 / 36, 3001 ids
-// 18 / 40 and 19 / 40, 4097 ids 24 / 51 and 21 / 44.
-// =================================================================================================
-constexpr int NARROW_THREADS = 256, NARROW_MAX_V = 3072;
-
-__device__ inline float narrow_sum(float v, float* sh /*>=4*/) {
-    v = wave_sum(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return sh[0] + sh[1] + sh[2] + sh[3];
-}
-__device__ inline float narrow_max(float v, float* sh) {
-    v = wave_max(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
-}
+constexpr int NARROW_THREADS = 256, NARROW_MAX_V = 3072;       // (short rows: a quarter of the wavefronts to meet)
 // argmax with lowest-index tie-break
 __device__ inline int narrow_argmax(const float* __restrict__ z, int V, float* shv, int* shi) {
     float bv = -INFINITY;
@@ -415,143 +453,28 @@ __device__ inline int narrow_argmax(const float* __restrict__ z, int V, float* s
     return bi;
 }
 
-// Smallest id whose running sum of w(id) (ascending ids) exceeds target; if rounding leaves none,
-// the largest id with positive weight.
-template <typename F>
-__device__ inline int narrow_inverse_cdf(F w, int V, float target, float* shf, int* shi) {
-    float run = 0.f;
-    int last_pos = -1;
-    int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int base = 0; base < V; base += NARROW_THREADS * 4) {
-        int id0 = base + threadIdx.x * 4;
-        float x[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            x[j] = id0 + j < V ? w(id0 + j) : 0.f;
-            if (x[j] > 0.f) last_pos = id0 + j;
-        }
-        float local = (x[0] + x[1]) + (x[2] + x[3]);
-        float incl = local;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            float up = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += up;
-        }
-        __syncthreads();
-        if (lane == 63) shf[wv] = incl;
-        __syncthreads();
-        float wave_base = 0.f;
-        for (int q = 0; q < wv; ++q) wave_base += shf[q];
-        float seg_total = shf[0] + shf[1] + shf[2] + shf[3];
-        incl += wave_base;
-        bool over = run + incl > target;
-        // lowest thread over the target
-        unsigned long long bal = __ballot(over);
-        __syncthreads();
-        if (lane == 0) shi[wv] = bal ? (wv * 64 + (int)__ffsll((long long)bal) - 1) : 0x7fffffff;
-        __syncthreads();
-        int first = min(min(shi[0], shi[1]), min(shi[2], shi[3]));
-        if (first != 0x7fffffff) {
-            __syncthreads();
-            if ((int)threadIdx.x == first) {
-                float c = run + (incl - local);
-                int pick = -1, lastp = -1;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    c += x[j];
-                    if (x[j] > 0.f) lastp = id0 + j;
-                    if (pick < 0 && c > target && x[j] > 0.f) pick = id0 + j;
-                }
-                shi[4] = pick >= 0 ? pick : (lastp >= 0 ? lastp : id0);
-            }
-            __syncthreads();
-            return shi[4];
-        }
-        run += seg_total;
-    }
-    // no crossing found (target >= total after rounding): largest id of positive weight
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) last_pos = max(last_pos, __shfl_xor(last_pos, o, 64));
-    __syncthreads();
-    if (lane == 0) shi[wv] = last_pos;
-    __syncthreads();
-    int r = max(max(shi[0], shi[1]), max(shi[2], shi[3]));
-    return r < 0 ? 0 : r;
-}
-
-// max and sum of exp((z - max) * inv_tau) of one row
-__device__ inline void narrow_row_stats(const float* __restrict__ z, int V, float inv_tau, float* sh,
-                                       float* out_max, float* out_sum) {
-    float m = -INFINITY;
-    for (int c = threadIdx.x; c < V; c += NARROW_THREADS) m = fmaxf(m, z[c]);
-    m = narrow_max(m, sh);
-    float s = 0.f;
-    for (int c = threadIdx.x; c < V; c += NARROW_THREADS) s += expf((z[c] - m) * inv_tau);
-    s = narrow_sum(s, sh);
-    *out_max = m; *out_sum = s;
-}
-
-__global__ void __launch_bounds__(NARROW_THREADS)
-accept_sample_narrow_kernel(AcceptArgs a) {
-    __shared__ float shf[4];
-    __shared__ int shi[5];
-    __shared__ int sh_stop;
-    int b = blockIdx.x, k = a.k, V = a.V;
-    const float* P = a.p_logits + (int64_t)b * (k + 1) * V;
-    const float* Q = a.q_logits + (int64_t)b * k * V;
-    float it = a.inv_tau;
-    int n = 0;
-    float pm = 0.f, ps = 1.f, qm = 0.f, qs = 1.f;
-    // candidates are tested in order; each test needs the softmax normalisers of two rows
+// greedy: early exit at the first mismatch
+__global__ void __launch_bounds__(WIDE_THREADS)
+accept_greedy_generic_kernel(AcceptArgs a) {
+    __shared__ WideShared sh;
+    const int b = blockIdx.x;
+    const float* P = a.p_logits + (int64_t)b * (a.k + 1) * a.V;
+    int n = 0, am;
     while (true) {
-        narrow_row_stats(P + (int64_t)n * V, V, it, shf, &pm, &ps);
-        if (n == k) break;
-        narrow_row_stats(Q + (int64_t)n * V, V, it, shf, &qm, &qs);
-        if (threadIdx.x == 0) sh_stop = rejects(a, b, n, pm, ps, qm, qs);
-        __syncthreads();
-        int stop = sh_stop;
-        __syncthreads();
-        if (stop) break;
-        ++n;
-    }
-    const float* pr = P + (int64_t)n * V;
-    const float* qr = n < k ? Q + (int64_t)n * V : nullptr;
-    float ipn = 1.0f / ps, iqn = 1.0f / qs;
-    auto wres = [&](int id) -> float {
-        float pv = expf((pr[id] - pm) * it) * ipn;
-        if (!qr) return pv;
-        float qv = expf((qr[id] - qm) * it) * iqn;
-        return fmaxf(0.f, pv - qv);
-    };
-    auto wp = [&](int id) -> float { return expf((pr[id] - pm) * it) * ipn; };
-    float tot = 0.f;
-    for (int c = threadIdx.x; c < V; c += NARROW_THREADS) tot += wres(c);
-    tot = narrow_sum(tot, shf);
-    float u = a.u_resample ? a.u_resample[b * (k + 1) + n]
-                           : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)n, 2);
-    int nxt;
-    if (tot > 0.f) nxt = narrow_inverse_cdf(wres, V, u * tot, shf, shi);
-    else {                                  // p == q everywhere: fall back to the target row
-        float tp = 0.f;
-        for (int c = threadIdx.x; c < V; c += NARROW_THREADS) tp += wp(c);
-        tp = narrow_sum(tp, shf);
-        nxt = narrow_inverse_cdf(wp, V, u * tp, shf, shi);
+        am = wide_argmax(WideRow(P + (int64_t)n * a.V, a.V), sh);
+        if (n < a.k && a.draft_tokens[b * a.k + n] == am) ++n; else break;
     }
     if (threadIdx.x == 0) {
         if (a.n_accepted) a.n_accepted[b] = n;
-        if (a.next_token) a.next_token[b] = nxt;
+        if (a.next_token) a.next_token[b] = am;
     }
 }
 
 // =================================================================================================
-// Fast path: vocabularies of up to 32768 ids (a multiple of 4, rows 16-byte aligned).  One workgroup
+// Rows in registers: vocabularies of up to 32768 ids (a multiple of 4, rows 16-byte aligned), greedy rule and draft picks.  One workgroup
 // of 1024 threads per sequence; a logits row is loaded once, 32 values per thread as 8 float4 (thread
 // t of sweep s holds ids 4096 s + 4 t .. + 3, so running sums stay in ascending id order), and every
-// reduction of that row (max, normaliser, residual total, inverse CDF) runs on the registers.  Candidates
-// tested in turn, with early exit at the first rejected one, read each row they need exactly once: (2 n + 2) rows of V
-// floats per sequence when n are kept (2 k + 1 when all are).  In turn a call is bound by the dependent chain of the sequence
-// that keeps most, about 8 us a candidate at 32000 ids, not by bytes (256 sequences of 6 candidates: 117 us, 2.2 TB/s); with
-// fewer sequences the candidates are tested at once (accept_ahead_kernel).
+// reduction of that row runs on the registers.
 // =================================================================================================
 constexpr int FAST_THREADS = 1024, FAST_WAVES = FAST_THREADS / 64, FAST_SWEEPS = 8;
 constexpr int FAST_MAX_V = FAST_THREADS * 4 * FAST_SWEEPS;
@@ -591,10 +514,7 @@ __device__ inline float fast_block_max(float v, FastShared& sh) {
     for (int w = 1; w < FAST_WAVES; ++w) t = fmaxf(t, sh.red[w]);
     return t;
 }
-// max and sum of exp((z - max) * inv_tau) of a row held in registers (padding is -inf: adds 0).  KEEP: the row becomes those
-// exponentials, which a draw that follows needs again (not where candidates are tested in turn: most tests are not
-// followed by one, and writing them back costs 2 % of a call of 256 sequences)
-template <bool KEEP>
+// max and sum of exp((z - max) * inv_tau) of a row held in registers, which becomes those exponentials (padding is -inf: adds 0)
 __device__ inline void fast_row_stats(float4 (&v)[FAST_SWEEPS], float inv_tau, FastShared& sh, float* out_max, float* out_sum) {
     float m = -INFINITY;
 #pragma unroll
@@ -603,10 +523,9 @@ __device__ inline void fast_row_stats(float4 (&v)[FAST_SWEEPS], float inv_tau, F
     float sum = 0.f;
 #pragma unroll
     for (int s = 0; s < FAST_SWEEPS; ++s) {
-        const float4 e = make_float4(expf((v[s].x - m) * inv_tau), expf((v[s].y - m) * inv_tau), expf((v[s].z - m) * inv_tau),
-                                     expf((v[s].w - m) * inv_tau));
-        if (KEEP) v[s] = e;
-        sum += (e.x + e.y) + (e.z + e.w);
+        v[s] = make_float4(expf((v[s].x - m) * inv_tau), expf((v[s].y - m) * inv_tau), expf((v[s].z - m) * inv_tau),
+                           expf((v[s].w - m) * inv_tau));
+        sum += (v[s].x + v[s].y) + (v[s].z + v[s].w);
     }
     *out_max = m;
     *out_sum = fast_block_sum(sum, sh);
@@ -694,40 +613,6 @@ __device__ inline int fast_inverse_cdf(const float4 (&wt)[FAST_SWEEPS], float u,
     *total_out = total;
     return sh.pick != 0x7fffffff ? sh.pick : (sh.last >= 0 ? sh.last : 0);
 }
-__device__ inline float4 fast_softmax_weights(const float4& z, float m, float inv_tau, float inv_norm) {
-    return make_float4(expf((z.x - m) * inv_tau) * inv_norm, expf((z.y - m) * inv_tau) * inv_norm,
-                       expf((z.z - m) * inv_tau) * inv_norm, expf((z.w - m) * inv_tau) * inv_norm);
-}
-__device__ inline float4 fast_scaled(const float4& e, float f) { return make_float4(e.x * f, e.y * f, e.z * f, e.w * f); }
-
-// The draw behind n kept candidates: from the residual of the rows p and q (n < k) or from p, with the rows' maxima and
-// normalisers; KEPT: the rows are their exponentials already
-template <bool KEPT>
-__device__ inline int fast_draw(const AcceptArgs& a, int b, int n, const float4 (&p)[FAST_SWEEPS], const float4 (&q)[FAST_SWEEPS],
-                                float pm, float ps, float qm, float qs, FastShared& sh) {
-    const float it = a.inv_tau, ipn = 1.0f / ps, iqn = 1.0f / qs;
-    auto weights = [&](const float4& v, float m, float inv) { return KEPT ? fast_scaled(v, inv) : fast_softmax_weights(v, m, it, inv); };
-    float4 w[FAST_SWEEPS];
-#pragma unroll
-    for (int s = 0; s < FAST_SWEEPS; ++s) {
-        w[s] = weights(p[s], pm, ipn);
-        if (n < a.k) {
-            const float4 x = weights(q[s], qm, iqn);
-            w[s] = make_float4(fmaxf(0.f, w[s].x - x.x), fmaxf(0.f, w[s].y - x.y), fmaxf(0.f, w[s].z - x.z), fmaxf(0.f, w[s].w - x.w));
-        }
-    }
-    const float u = a.u_resample ? a.u_resample[b * (a.k + 1) + n]
-                                 : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)n, 2);
-    float tot;
-    int nxt = fast_inverse_cdf(w, u, sh, &tot);
-    if (!(tot > 0.f)) {                     // p == q everywhere: fall back to the target row
-#pragma unroll
-        for (int s = 0; s < FAST_SWEEPS; ++s) w[s] = weights(p[s], pm, ipn);
-        nxt = fast_inverse_cdf(w, u, sh, &tot);
-    }
-    return nxt;
-}
-
 __global__ void __launch_bounds__(FAST_THREADS)
 accept_greedy_kernel(AcceptArgs a) {
     __shared__ FastShared sh;
@@ -784,59 +669,41 @@ accept_greedy_rows_kernel(AcceptArgs a) {
     }
 }
 
-__global__ void __launch_bounds__(FAST_THREADS)
-accept_sample_kernel(AcceptArgs a) {
-    __shared__ FastShared sh;
-    const int b = blockIdx.x, k = a.k, V = a.V;
-    const float* P = a.p_logits + (int64_t)b * (k + 1) * V;
-    const float* Q = a.q_logits + (int64_t)b * k * V;
-    const float it = a.inv_tau;
-    int n = 0;
-    float pm = 0.f, ps = 1.f, qm = 0.f, qs = 1.f;
-    float4 pz[FAST_SWEEPS], qz[FAST_SWEEPS];
-    // candidates are tested in order; each test needs the softmax normalisers of two rows, which stay
-    // in registers for the draw that follows the first rejection
-    while (true) {
-        fast_load_row(P + (int64_t)n * V, V, pz);
-        if (n < k) fast_load_row(Q + (int64_t)n * V, V, qz);
-        fast_row_stats<false>(pz, it, sh, &pm, &ps);
-        if (n == k) break;
-        fast_row_stats<false>(qz, it, sh, &qm, &qs);
-        if (threadIdx.x == 0) sh.stop = rejects(a, b, n, pm, ps, qm, qs);
-        __syncthreads();
-        const int stop = sh.stop;
-        __syncthreads();
-        if (stop) break;
-        ++n;
-    }
-    const int nxt = fast_draw<false>(a, b, n, pz, qz, pm, ps, qm, qs, sh);
-    if (threadIdx.x == 0) {
-        if (a.n_accepted) a.n_accepted[b] = n;
-        if (a.next_token) a.next_token[b] = nxt;
-    }
-}
-
-// All candidates at once: a workgroup for each of the k + 1 rows of a sequence tests its candidate and, where it is rejected (or
-// the row is the one behind the last candidate), draws the sequence's next token.  The outputs serve as the meeting
-// point: next_token[b] holds the smallest (row << 27 | token) of those that would draw, announced without a token before
+// The sampling rule on rows of 4 ids and more, at any alignment.  At once: a workgroup for each of the k + 1 rows of a sequence tests its candidate
+// and, where it is rejected (or the row is the one behind the last candidate), draws the sequence's next token.  The outputs serve as the
+// meeting point: next_token[b] holds the smallest (row << 27 | token) of those that would draw, announced without a token before
 // the draw, n_accepted[b] counts the workgroups that are through, and the last one turns both into the results.  Nobody waits.
 // A workgroup leaves as soon as it sees a rejection in front of it; those of the first candidates start first, so with more
-// workgroups than the chip holds few rows are read for nothing.
+// workgroups than the chip holds few rows are read for nothing.  In turn: a workgroup per sequence.
 //
-// us per call, in turn / at once (32000 ids; candidates of which the given number is kept on average):
-//   sequences, candidates        1, 4     16, 1    16, 4    64, 4    64, 8    100, 4   160, 4   256, 6
-//   about half kept              42 / 24  30 / 27  66 / 29  69 / 46  127 / 70  77 / 59  80 / 88  117 / 161
-//   nearly all                   65 / 21  30 / 23  66 / 29  75 / 46  131 / 70  78 / 57  83 / 93  128 / 175
-//   nearly none                  27 / 27  29 / 28  36 / 30  45 / 39   50 / 42  53 / 47  59 / 75   70 / 99
-// A draft of which nothing at all is kept is the one case that at once is slower, up to twice (in turn every sequence ends at its first
-// candidate); device us, nothing kept / kept with probability 0.8 / all kept, in turn and at once:
-//   32000 ids   64, 8  27, 43 / 110, 64 / 111, 66    100, 4  28, 41 / 68, 54 / 69, 49    100, 8   28, 47 / 113, 84 / 116, 88
-//   512 ids     64, 8  24, 32 / 90, 46 / 90, 47      100, 4  24, 29 / 54, 38 / 53, 33    100, 16  24, 47 / 165, 87 / 164, 100
-// 65537 ids (general path): 16 sequences of 4 140 / 68, 64 of 8 287 / 138, 100 of 4 168 / 125, 160 of 4 173 / 166.
-// What bounds it is the exponentials of one compute unit: 4.2 us a row of 32000 ids (17 instructions each), and as much for a
-// row's bytes where all units load.  (Two workgroups per unit in half the registers spill and are slower; so is a next row
-// requested into LDS while the draft's is summed.)
-constexpr int AHEAD_MAX_B = 100;
+// Bound by HBM where many rows are read (256 sequences of 6 candidates over 32000 ids, all kept: 432 MB, 86 us), else by the latency of a
+// workgroup's few steps, so: several granules of both rows requested ahead of those being summed, in every step as many (their
+// predecessors are waited for by count), two workgroups and more to a compute unit so that one's loads run under another's exponentials,
+// nothing of a row kept for the draw (it reads the rows again, from the caches), four-instruction exponentials in the
+// sums.  us per call (calls in a graph), candidates of which about 0.8 are kept / none / all, rows in registers of a 1024-thread workgroup or
+// library exponentials in 1024 threads before -> 256 threads up to 24576 ids, 512 above:
+//   ids     sequences, candidates   before                 at once               in turn
+//   32000   1, 4                    21.9 / 26.2 / 21.4     14.5 / 20.1 / 13.4    34.7 / 15.1 / 33.6
+//   32000   64, 8                   64.2 / 43.1 / 66.2     35.1 / 39.5 / 34.1    62.1 / 16.6 / 62.3
+//   32768   100, 4                  55.4 / 40.7 / 48.6     35.9 / 37.1 / 28.6    37.9 / 16.8 / 39.0
+//   32000   160, 3                  60.2 / 30.1 / 62.4     39.6 / 36.3 / 34.6    36.0 / 19.2 / 36.4
+//   32000   256, 1                  39.3 / 34.6 / 39.6     29.1 / 33.0 / 28.5    25.7 / 26.9 / 25.5
+//   32000   256, 6                  108 / 35.6 / 131       66.0 / 38.1 / 85.8    66.4 / 27.1 / 87.5
+//   65537   24, 5                   71.0 / 73.9 / 40.5     31.2 / 34.9 / 21.5    67.3 / 25.4 / 68.2
+//   99999   8, 2                    86.1 / 86.1 / 48.4     37.3 / 38.1 / 24.8    48.6 / 34.0 / 48.0
+//   20001   60, 8                   62.2 / 48.5 / 62.8     27.2 / 32.4 / 26.2    49.8 / 15.1 / 50.9
+//   9001    200, 8                  77.5 / 22.6 / 79.7     30.9 / 27.3 / 29.2    38.7 / 11.2 / 42.4
+//   3001    256, 8                  85.2 / 18.5 / 98.1     22.4 / 15.4 / 21.3    28.6 / 8.9 / 31.2
+//   1001    64, 4                   20.7 / 9.2 / 20.4      12.5 / 15.4 / 12.0    15.0 / 7.8 / 15.0
+//   512     4, 3                    23.0 / 23.3 / 18.0     10.4 / 11.0 / 9.3     11.6 / 7.5 / 12.2
+// (256 against 512 threads at once: 9001 ids 30.9 / 32.0, 20001 ids 27.2 / 28.4, 32000 ids, 256 sequences 81 / 66.)  A draft of which nothing at
+// all is kept is the one case in which at once is the slower way.  Tried and not kept: the non-temporal hint on the rows (66 -> 68, 35.9 -> 32.5),
+// asking for a rejection in front with every step (66 -> 75: the word of a sequence is in memory, and all ask for few lines of it).
+constexpr int IN_TURN_MIN_B = 128, IN_TURN_MAX_K = 3, ROWS_256_MAX_V = 24576;
+// Greedy at once: where all rows are few enough to read, 0.8 of the candidates agree / none / all, us, in turn -> at once: 32000 ids 16, 4
+// 17.9 / 5.5 / 18.0 -> 9.5 / 9.8 / 9.5, 64, 8 (74 MB) 33 / 5.7 / 35 -> 18.5 / 18.6 / 18.3, 256, 6 (229 MB) 34.7 / 7.3 / 43 -> 41 / 33 / 41; one
+// candidate, 256 sequences 15.4 / 7.9 / 16 -> 17.2; 65537 ids 24, 5 38 / 8.4 / 57 -> 20; 5003 ids 100, 5 20.8 / 5.6 / 20.8 -> 9.7.
+constexpr int64_t GREEDY_AHEAD_MAX_IDS = 20 << 20;
 constexpr int PICK_BITS = 27;
 constexpr uint32_t PICK_NO_TOKEN = (1u << PICK_BITS) - 1;
 __global__ void accept_begin_kernel(AcceptArgs a) {
@@ -847,141 +714,197 @@ __global__ void accept_begin_kernel(AcceptArgs a) {
 __device__ inline bool rejected_before(const AcceptArgs& a, int b, int i) {
     return (int)(__hip_atomic_load((uint32_t*)a.next_token + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> PICK_BITS) < i;
 }
-__device__ inline void offer_pick(const AcceptArgs& a, int b, int i, uint32_t token) {
-    __hip_atomic_fetch_min((uint32_t*)a.next_token + b, ((uint32_t)i << PICK_BITS) | token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ inline void announce_pick(const AcceptArgs& a, int b, int i) {
+    __hip_atomic_fetch_min((uint32_t*)a.next_token + b, ((uint32_t)i << PICK_BITS) | PICK_NO_TOKEN, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// (one thread) this workgroup is through; the last of the sequence writes the results
+// (the wait is for the value that the minimum gives back: it has been done then)
+__device__ inline void offer_pick(const AcceptArgs& a, int b, int i, uint32_t token) {
+    const uint32_t was = __hip_atomic_fetch_min((uint32_t*)a.next_token + b, ((uint32_t)i << PICK_BITS) | token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" :: "v"(was) : "memory");
+}
+// (one thread) this workgroup is through; the last of the sequence writes the results.  All that the workgroups of a sequence tell each
+// other are these atomics, so it is enough that a workgroup's offer has been done (offer_pick waits for it) in front of its count.  (A
+// release and an acquire at device scope would write back and invalidate the whole L2 every time: 20 ns of the whole chip's
+// time a workgroup, 52 against 9 us for 256 sequences of 8 candidates over 512 ids.)
 __device__ inline void report(const AcceptArgs& a, int b) {
-    if (__hip_atomic_fetch_add(a.n_accepted + b, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != a.k) return;
+    if (__hip_atomic_fetch_add(a.n_accepted + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != a.k) return;
     const uint32_t v = __hip_atomic_load((uint32_t*)a.next_token + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     a.n_accepted[b] = (int)(v >> PICK_BITS);
     a.next_token[b] = (int)(v & PICK_NO_TOKEN);
 }
-__global__ void __launch_bounds__(FAST_THREADS)
-accept_ahead_kernel(AcceptArgs a) {
-    __shared__ FastShared sh;
-    const int b = blockIdx.x % a.B, i = blockIdx.x / a.B, k = a.k, V = a.V;
-    if (threadIdx.x == 0) sh.stop = rejected_before(a, b, i);
-    __syncthreads();
-    bool go = !sh.stop;
-    if (go) {
-        float4 pz[FAST_SWEEPS], qz[FAST_SWEEPS];
-        float pm, ps, qm = 0.f, qs = 1.f;
-        fast_load_row(a.p_logits + ((int64_t)b * (k + 1) + i) * V, V, pz);
-        if (i < k) fast_load_row(a.q_logits + ((int64_t)b * k + i) * V, V, qz);
-        fast_row_stats<true>(pz, a.inv_tau, sh, &pm, &ps);
-        if (i < k) fast_row_stats<true>(qz, a.inv_tau, sh, &qm, &qs);
+// AHEAD: a workgroup per row, else one per sequence that tests its candidates in turn (where a caller leaves out an output)
+template <int T, bool AHEAD>
+__global__ void __launch_bounds__(T, 4)
+accept_rows_kernel(AcceptArgs a) {
+    __shared__ RowShared<T> sh;
+    const int b = AHEAD ? blockIdx.x % a.B : blockIdx.x, k = a.k, V = a.V;
+    int i = AHEAD ? blockIdx.x / a.B : 0;
+    const float it = a.inv_tau;
+    if (AHEAD) {
+        if (threadIdx.x == 0) sh.stop = rejected_before(a, b, i);
+        __syncthreads();
+        if (sh.stop) {
+            if (threadIdx.x == 0) report(a, b);
+            return;
+        }
+    }
+    const float *p, *q;
+    float pm, ps, qm = 0.f, qs = 1.f;
+    while (true) {
+        p = a.p_logits + ((int64_t)b * (k + 1) + i) * V;
+        q = a.q_logits + ((int64_t)b * k + (i < k ? i : 0)) * V;
+        Candidate cand;
+        if (i < k && threadIdx.x == 0) cand = candidate(a, b, i);
+        if (i < k) row_stats<T, true>(p, q, V, it, sh, &pm, &ps, &qm, &qs);
+        else row_stats<T, false>(p, p, V, it, sh, &pm, &ps, nullptr, nullptr);
         if (threadIdx.x == 0) {
-            const bool draws = (i == k || rejects(a, b, i, pm, ps, qm, qs)) && !rejected_before(a, b, i);
-            if (draws) offer_pick(a, b, i, PICK_NO_TOKEN);
-            sh.stop = !draws;
+            bool draws = i == k || rejects(cand, it, pm, ps, qm, qs);
+            if (AHEAD) {
+                draws = draws && !rejected_before(a, b, i);
+                if (draws) announce_pick(a, b, i);
+            }
+            sh.stop = draws;
         }
         __syncthreads();
-        go = !sh.stop;
-        if (go) {
-            const int nxt = fast_draw<true>(a, b, i, pz, qz, pm, ps, qm, qs, sh);
-            if (threadIdx.x == 0) offer_pick(a, b, i, (uint32_t)nxt);
+        if (AHEAD || sh.stop) break;
+        __syncthreads();
+        ++i;
+    }
+    if (sh.stop) {
+        // the draw behind i kept candidates: from the residual of the two rows or (i == k) from the target's
+        const float u = a.u_resample ? a.u_resample[b * (k + 1) + i] : philox_uniform(a.seed, a.round, a.seq_base + b, (uint32_t)i, 2);
+        float tot = 0.f;
+        int nxt = 0;
+        if (i < k) nxt = row_draw<T, true>(p, q, V, it, pm, 1.0f / ps, qm, 1.0f / qs, u, sh, &tot);
+        if (i == k || !(tot > 0.f)) nxt = row_draw<T, false>(p, p, V, it, pm, 1.0f / ps, 0.f, 0.f, u, sh, &tot);    // (p == q everywhere: the target row)
+        if (threadIdx.x == 0) {
+            if (AHEAD) offer_pick(a, b, i, (uint32_t)nxt);
+            else {
+                if (a.n_accepted) a.n_accepted[b] = i;
+                if (a.next_token) a.next_token[b] = nxt;
+            }
+        }
+    }
+    if (AHEAD && threadIdx.x == 0) report(a, b);
+}
+// greedy: a workgroup per row; a row whose argmax is not its candidate (or the one behind the last candidate) offers the argmax
+__global__ void __launch_bounds__(512)
+accept_greedy_ahead_kernel(AcceptArgs a) {
+    constexpr int T = 512;
+    __shared__ float red[T / 64];
+    __shared__ int redi[T / 64], stop;
+    const int b = blockIdx.x % a.B, i = blockIdx.x / a.B, V = a.V, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    if (threadIdx.x == 0) stop = rejected_before(a, b, i);
+    __syncthreads();
+    if (!stop) {
+        const float* row = a.p_logits + ((int64_t)b * (a.k + 1) + i) * V;
+        float bv = -INFINITY;
+        int bi = 0x7fffffff;
+        float4 v[2][4];
+        auto request = [&](int buf, int g0) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[buf][q] = row_load(row, V, g0 + q * T + (int)threadIdx.x);
+        };
+        auto take = [&](int buf, int g0) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int g = g0 + q * T + (int)threadIdx.x;
+                const float4 z = 4 * (g - lane) + 256 <= V ? v[buf][q] : row_ids(v[buf][q], V, g);
+                const float x[4] = {z.x, z.y, z.z, z.w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) if (x[j] > bv) { bv = x[j]; bi = 4 * g + j; }
+            }
+        };
+        request(0, 0);
+        for (int g0 = 0; g0 < (V + 3) >> 2; g0 += 8 * T) {
+            request(1, g0 + 4 * T);
+            take(0, g0);
+            request(0, g0 + 8 * T);
+            take(1, g0 + 4 * T);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const float ov = __shfl_xor(bv, o, 64);
+            const int oi = __shfl_xor(bi, o, 64);
+            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+        }
+        if (lane == 0) { red[wv] = bv; redi[wv] = bi; }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            bv = red[0]; bi = redi[0];
+#pragma unroll
+            for (int w = 1; w < T / 64; ++w) if (red[w] > bv || (red[w] == bv && redi[w] < bi)) { bv = red[w]; bi = redi[w]; }
+            if (i == a.k || a.draft_tokens[b * a.k + i] != bi) offer_pick(a, b, i, (uint32_t)bi);
         }
     }
     if (threadIdx.x == 0) report(a, b);
 }
-__global__ void __launch_bounds__(WIDE_THREADS)
-accept_ahead_generic_kernel(AcceptArgs a) {
-    __shared__ WideShared sh;
-    const int b = blockIdx.x % a.B, i = blockIdx.x / a.B, k = a.k, V = a.V;
-    if (threadIdx.x == 0) sh.stop = rejected_before(a, b, i);
-    __syncthreads();
-    bool go = !sh.stop;
-    if (go) {
-        const WideRow p(a.p_logits + ((int64_t)b * (k + 1) + i) * V, V), q(a.q_logits + ((int64_t)b * k + (i < k ? i : 0)) * V, V);
-        float pm, ps, qm = 0.f, qs = 1.f;
-        if (i < k) wide_row_stats<true>(p, q, a.inv_tau, sh, &pm, &ps, &qm, &qs);
-        else wide_row_stats<false>(p, p, a.inv_tau, sh, &pm, &ps, nullptr, nullptr);
-        if (threadIdx.x == 0) {
-            const bool draws = (i == k || rejects(a, b, i, pm, ps, qm, qs)) && !rejected_before(a, b, i);
-            if (draws) offer_pick(a, b, i, PICK_NO_TOKEN);
-            sh.stop = !draws;
-        }
-        __syncthreads();
-        go = !sh.stop;
-        if (go) {
-            const int nxt = wide_draw(a, b, i, p, q, pm, ps, qm, qs, sh);
-            if (threadIdx.x == 0) offer_pick(a, b, i, (uint32_t)nxt);
-        }
-    }
-    if (threadIdx.x == 0) report(a, b);
-}
-
 static inline bool fast_rows_ok(const float* base, int V) {
     return V % 4 == 0 && V <= FAST_MAX_V && ((uintptr_t)base & 15) == 0;
+}
+
+template <int T>
+static void launch_accept_rows(const AcceptArgs& a, bool ahead, hipStream_t st) {
+    if (ahead) hipLaunchKernelGGL(accept_begin_kernel, dim3((a.B + 255) / 256), dim3(256), 0, st, a);
+    if (ahead) hipLaunchKernelGGL((accept_rows_kernel<T, true>), dim3(a.B * (a.k + 1)), dim3(T), 0, st, a);
+    else hipLaunchKernelGGL((accept_rows_kernel<T, false>), dim3(a.B), dim3(T), 0, st, a);
 }
 
 hipError_t launch_accept(const AcceptArgs& a, hipStream_t st) {
     if (a.B <= 0) return hipSuccess;
     const bool fast = fast_rows_ok(a.p_logits, a.V) && (!a.q_logits || fast_rows_ok(a.q_logits, a.V));
+    const bool can = a.n_accepted && a.next_token && a.V >= 4 && a.V < (int)PICK_NO_TOKEN;      // (the outputs are the meeting point)
+    const int64_t ids = (int64_t)a.B * (a.k + 1) * a.V;
     if (a.q_logits) {
-        // Candidates at once or in turn (accept_ahead_kernel has the figures).  At once a sequence takes one test and one draw, but
-        // the rows behind its first rejection are read as well and a workgroup holds a compute unit: from about 100
-        // sequences on, whose first candidates alone come near to filling the chip, in turn is faster again.  Rows off the register
-        // path: one candidate is tested in turn (65537 ids, 16 sequences: 63 us, at once 65), and so are short rows, whose test
-        // costs only V / 430 us, unless there are several candidates and sequences.
-        const bool short_rows = a.V <= 2 * NARROW_MAX_V;
-        const bool pays = fast               ? a.B <= AHEAD_MAX_B
-                          : a.V <= NARROW_MAX_V ? a.k >= 3 && a.B >= 4 && a.B <= 256 / a.k && (int64_t)a.k * a.V >= 4 * NARROW_MAX_V
-                                             : a.B <= AHEAD_MAX_B && a.k >= 2 && (!short_rows || (a.B >= 4 && (int64_t)a.k * a.V >= 4 * NARROW_MAX_V));
-        const bool ahead = pays && a.n_accepted && a.next_token && a.V < (int)PICK_NO_TOKEN;
-        if (ahead) {
-            hipLaunchKernelGGL(accept_begin_kernel, dim3((a.B + 255) / 256), dim3(256), 0, st, a);
-            if (fast) hipLaunchKernelGGL(accept_ahead_kernel, dim3(a.B * (a.k + 1)), dim3(FAST_THREADS), 0, st, a);
-            else hipLaunchKernelGGL(accept_ahead_generic_kernel, dim3(a.B * (a.k + 1)), dim3(WIDE_THREADS), 0, st, a);
-        } else if (fast) hipLaunchKernelGGL(accept_sample_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
-        else if (a.V <= NARROW_MAX_V) hipLaunchKernelGGL(accept_sample_narrow_kernel, dim3(a.B), dim3(NARROW_THREADS), 0, st, a);
-        else hipLaunchKernelGGL(accept_sample_generic_kernel, dim3(a.B), dim3(WIDE_THREADS), 0, st, a);
+        // Rows at once but for many sequences of few candidates, where the chip is full in turn as well (figures at the kernel)
+        const bool ahead = can && !(a.B >= IN_TURN_MIN_B && a.k <= IN_TURN_MAX_K);
+        if (a.V < 4) hipLaunchKernelGGL(accept_sample_tiny_kernel, dim3((a.B + 63) / 64), dim3(64), 0, st, a);
+        else if (a.V <= ROWS_256_MAX_V) launch_accept_rows<256>(a, ahead, st);
+        else launch_accept_rows<512>(a, ahead, st);
+    } else if (a.V <= ROWS_MAX_V && (!fast || ids <= ROWS_MAX_IDS)) {
+        hipLaunchKernelGGL(accept_greedy_rows_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
+    } else if (can && a.k >= 2 && ids <= GREEDY_AHEAD_MAX_IDS) {
+        hipLaunchKernelGGL(accept_begin_kernel, dim3((a.B + 255) / 256), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(accept_greedy_ahead_kernel, dim3(a.B * (a.k + 1)), dim3(512), 0, st, a);
+    } else if (fast) {
+        hipLaunchKernelGGL(accept_greedy_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
     } else {
-        const bool rows = a.V <= ROWS_MAX_V && (!fast || (int64_t)a.B * (a.k + 1) * a.V <= ROWS_MAX_IDS);
-        if (rows) hipLaunchKernelGGL(accept_greedy_rows_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
-        else if (fast) hipLaunchKernelGGL(accept_greedy_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
-        else hipLaunchKernelGGL(accept_greedy_generic_kernel, dim3(a.B), dim3(WIDE_THREADS), 0, st, a);
+        hipLaunchKernelGGL(accept_greedy_generic_kernel, dim3(a.B), dim3(WIDE_THREADS), 0, st, a);
     }
     return hipGetLastError();
 }
 
 // ---- draft token pick ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(WIDE_THREADS)
-draft_pick_generic_kernel(const float* __restrict__ z, int64_t ld, int V, int mode, float inv_tau, uint64_t seed,
-                          uint32_t round, uint32_t seq_base, int step, int32_t* __restrict__ draft_tokens, int k) {
-    __shared__ WideShared sh;
+template <int T>
+__global__ void __launch_bounds__(T)
+draft_sample_kernel(const float* __restrict__ z, int64_t ld, int V, float inv_tau, uint64_t seed, uint32_t round, uint32_t seq_base, int step,
+                    int32_t* __restrict__ draft_tokens, int k) {
+    __shared__ RowShared<T> sh;
     const int b = blockIdx.x;
-    const WideRow row(z + (int64_t)b * ld, V);
+    const float* row = z + (int64_t)b * ld;
+    const float u = philox_uniform(seed, round, seq_base + b, (uint32_t)step, 0);
+    float m, s, tot;
     int pick;
-    if (mode == SPEC_GREEDY) {
-        pick = wide_argmax(row, sh);
+    if (V < 4) {
+        tiny_stats(row, V, inv_tau, &m, &s);
+        pick = tiny_inverse_cdf([&](int c) { return expf((row[c] - m) * inv_tau); }, V, u, &tot);
     } else {
-        float m, s, tot;
-        wide_row_stats<false>(row, row, inv_tau, sh, &m, &s, nullptr, nullptr);
-        auto w = [&](int g) { return wide_weights(row, g, m, inv_tau, 1.0f); };
-        const float u = philox_uniform(seed, round, seq_base + b, (uint32_t)step, 0);
-        pick = wide_inverse_cdf(w, row.n, row.off, u, sh, &tot);
+        row_stats<T, false>(row, row, V, inv_tau, sh, &m, &s, nullptr, nullptr);
+        pick = row_draw<T, false>(row, row, V, inv_tau, m, 1.0f, 0.f, 0.f, u, sh, &tot);
     }
     if (threadIdx.x == 0) draft_tokens[b * k + step - 1] = pick;
 }
+__global__ void __launch_bounds__(WIDE_THREADS)
+draft_argmax_kernel(const float* __restrict__ z, int64_t ld, int V, int step, int32_t* __restrict__ draft_tokens, int k) {
+    __shared__ WideShared sh;
+    const int b = blockIdx.x, pick = wide_argmax(WideRow(z + (int64_t)b * ld, V), sh);
+    if (threadIdx.x == 0) draft_tokens[b * k + step - 1] = pick;
+}
 __global__ void __launch_bounds__(NARROW_THREADS)
-draft_pick_narrow_kernel(const float* __restrict__ z, int64_t ld, int V, int mode, float inv_tau, uint64_t seed,
-                          uint32_t round, uint32_t seq_base, int step, int32_t* __restrict__ draft_tokens, int k) {
+draft_argmax_narrow_kernel(const float* __restrict__ z, int64_t ld, int V, int step, int32_t* __restrict__ draft_tokens, int k) {
     __shared__ float shf[4];
-    __shared__ int shi[5];
-    int b = blockIdx.x;
-    const float* row = z + (int64_t)b * ld;
-    int pick;
-    if (mode == SPEC_GREEDY) {
-        pick = narrow_argmax(row, V, shf, shi);
-    } else {
-        float m, s;
-        narrow_row_stats(row, V, inv_tau, shf, &m, &s);
-        auto w = [&](int id) -> float { return expf((row[id] - m) * inv_tau); };
-        float u = philox_uniform(seed, round, seq_base + b, (uint32_t)step, 0);
-        pick = narrow_inverse_cdf(w, V, u * s, shf, shi);
-    }
+    __shared__ int shi[4];
+    const int b = blockIdx.x, pick = narrow_argmax(z + (int64_t)b * ld, V, shf, shi);
     if (threadIdx.x == 0) draft_tokens[b * k + step - 1] = pick;
 }
 // fast path (see above): the row is read once
@@ -997,7 +920,7 @@ draft_pick_kernel(const float* __restrict__ z, int64_t ld, int V, int mode, floa
         pick = fast_argmax(row, sh);
     } else {
         float m, s, tot;
-        fast_row_stats<true>(row, inv_tau, sh, &m, &s);        // (the row is its exponentials now)
+        fast_row_stats(row, inv_tau, sh, &m, &s);        // (the row is its exponentials now)
         const float u = philox_uniform(seed, round, seq_base + b, (uint32_t)step, 0);
         pick = fast_inverse_cdf(row, u, sh, &tot);
     }
@@ -1010,12 +933,14 @@ hipError_t launch_draft_pick(const float* z, int64_t ld, int V, int B, int mode,
     if (fast_rows_ok(z, V) && ld % 4 == 0)
         hipLaunchKernelGGL(draft_pick_kernel, dim3(B), dim3(FAST_THREADS), 0, st, z, ld, V, mode, inv_tau, seed,
                            round, seq_base, step, draft_tokens, k);
-    else if (V <= NARROW_MAX_V)
-        hipLaunchKernelGGL(draft_pick_narrow_kernel, dim3(B), dim3(NARROW_THREADS), 0, st, z, ld, V, mode, inv_tau, seed,
-                           round, seq_base, step, draft_tokens, k);
+    else if (mode == SPEC_GREEDY && V <= NARROW_MAX_V)
+        hipLaunchKernelGGL(draft_argmax_narrow_kernel, dim3(B), dim3(NARROW_THREADS), 0, st, z, ld, V, step, draft_tokens, k);
+    else if (mode == SPEC_GREEDY)
+        hipLaunchKernelGGL(draft_argmax_kernel, dim3(B), dim3(WIDE_THREADS), 0, st, z, ld, V, step, draft_tokens, k);
+    else if (V <= ROWS_256_MAX_V)
+        hipLaunchKernelGGL(draft_sample_kernel<256>, dim3(B), dim3(256), 0, st, z, ld, V, inv_tau, seed, round, seq_base, step, draft_tokens, k);
     else
-        hipLaunchKernelGGL(draft_pick_generic_kernel, dim3(B), dim3(WIDE_THREADS), 0, st, z, ld, V, mode, inv_tau,
-                           seed, round, seq_base, step, draft_tokens, k);
+        hipLaunchKernelGGL(draft_sample_kernel<512>, dim3(B), dim3(512), 0, st, z, ld, V, inv_tau, seed, round, seq_base, step, draft_tokens, k);
     return hipGetLastError();
 }
 

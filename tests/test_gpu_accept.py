@@ -196,6 +196,70 @@ def test_accept_sample_wide_rows_and_both_test_orders(B, k, V, tau):
     assert torch.equal(out[0], out[1])
 
 
+# edges of the row kernels: granules that the row ends in, workgroups of 256 and 512 threads (24576 ids), rows at once and in turn (128
+# sequences, 3 candidates), one wavefront's and one workgroup's granules and one id more
+@pytest.mark.parametrize("B,k,V,tau", [(4, 2, 4, 0.8), (4, 2, 5, 0.8), (4, 2, 7, 0.8), (4, 2, 257, 0.8), (4, 2, 1023, 0.8), (4, 2, 1025, 0.8),
+                                       (4, 2, 4097, 0.8), (4, 3, 24576, 0.8), (4, 3, 24577, 0.8), (4, 2, 24579, 0.8), (4, 2, 131073, 0.8),
+                                       (127, 3, 130, 0.8), (128, 3, 130, 0.8), (128, 4, 130, 0.8)])
+def test_accept_sample_row_kernels(B, k, V, tau):
+    test_accept_sample_wide_rows_and_both_test_orders(B, k, V, tau)
+
+
+# greedy rows at once (from two candidates and 4097 ids on) and, without n_accepted, in turn
+@pytest.mark.parametrize("B,k,V", [(5, 2, 4097), (5, 2, 4098), (5, 2, 4100), (5, 3, 8195), (3, 2, 65537), (5, 1, 8195), (40, 16, 4100),
+                                   (300, 16, 4112)])
+def test_accept_greedy_at_once_and_in_turn(B, k, V):
+    import torch
+    import paper_2505_10259_amd as P
+    from gpu_common import dev
+    test_accept_greedy(B, k, V)
+    p, _, d = _logits(B, k, V, seed=V, agree=0.9)
+    p[:, :, V - 1] = p.max(-1) * (np.arange(B) % 3 == 0)[:, None]              # the last id, of equal value, wins over none
+    exp = [ospec.accept_greedy(p[b], d[b]) for b in range(B)]
+    p, d = dev(p), dev(d)
+    for n in (torch.full((B,), -1, dtype=torch.int32, device="cuda"), None):
+        nx = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+        P.spec_accept(p, None, d, None, None, 1.0, 0, 0, 0, B, k, V, n, nx)
+        torch.cuda.synchronize()
+        assert nx.cpu().tolist() == [e[1] for e in exp]
+        if n is not None:
+            assert n.cpu().tolist() == [e[0] for e in exp]
+
+
+@pytest.mark.parametrize("V,ahead", [(300, True), (9001, True), (24577, True), (65537, True), (9001, False)])
+def test_normaliser_error(V, ahead):
+    """With a draft row of one id the candidate is kept exactly while u < p(c), so bisecting u gives p(c) to the bit; the id of the largest
+    logit makes it 1 / normaliser.  Bound in units of 2^-24: a sum behind another in a thread (16 ids a step) and in the reduction over
+    lanes and wavefronts, each rounded once, three levels inside a step, half a unit for the rounded exponent of weights that average
+    over the row, one for the division."""
+    import torch
+    import paper_2505_10259_amd as P
+    B, T = 8, 256 if V <= 24576 else 512
+    g = torch.Generator("cuda").manual_seed(V)
+    p = torch.randn(B, 2, V, device="cuda", generator=g) * 3
+    d = p[:, :1].argmax(-1).to(torch.int32).contiguous()
+    q = torch.full((B, 1, V), -float("inf"), device="cuda").scatter_(2, d.long().unsqueeze(-1), 0.0)
+    n = torch.empty(B, dtype=torch.int32, device="cuda") if ahead else None
+    nx = torch.empty(B, dtype=torch.int32, device="cuda")
+    ur = torch.full((B, 2), 0.5, device="cuda")
+    # (in turn there is no count: behind a kept candidate the draw is of a row that is all token 0, behind a rejected one never token 0)
+    p[:, 1] = -float("inf")
+    p[:, 1, 0] = 0.0
+    p[:, 0, 0] = -float("inf")
+    lo = torch.zeros(B, dtype=torch.int32, device="cuda")
+    hi = torch.full((B,), 0x3f800000, dtype=torch.int32, device="cuda")
+    for _ in range(31):
+        mid = lo + (hi - lo) // 2
+        P.spec_accept(p, q, d, mid.view(torch.float32).reshape(B, 1).contiguous(), ur, 0.8, 0, 0, 0, B, 1, V, n, nx)
+        torch.cuda.synchronize()
+        kept = n == 1 if ahead else nx == 0
+        lo, hi = torch.where(kept, mid, lo), torch.where(kept, hi, mid)
+    got = hi.view(torch.float32).double()
+    ref = torch.softmax(p[:, 0].double() * float(np.float32(1.0) / np.float32(0.8)), -1).max(-1).values
+    bound = -(-V // (16 * T)) + 6 + (T // 64) + 3 + 0.5 + 1
+    assert ((got / ref - 1).abs() * 2 ** 24).max().item() <= bound
+
+
 @pytest.mark.parametrize("V", [512, 40001])
 def test_accept_at_once_under_capture(V):
     """The outputs are the meeting point of the workgroups of a sequence: every replay starts it afresh, whatever they hold."""
