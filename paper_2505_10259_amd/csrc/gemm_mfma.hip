@@ -43,6 +43,7 @@
 //     4 row tiles x 8 column tiles and share both operands in its L2 (measured on an 8192^3 product:
 //     L2 hit rate 48 % -> 79 % against column-major tile order).
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -855,6 +856,16 @@ int expected_rows(const GemmArgs& a) {
     return a.m_expected > 0 ? (int)((int64_t)a.m_expected * 26 / 25) + 1 : (int)((int64_t)a.m_upper * 26 / (25 * groups)) + 1;
 }
 
+// Groups that the rows of a routed product (two experts each) are expected to reach.  Few rows leave most experts without any, and tiles
+// chosen as for all of them leave the chip idle: down product of layers with 1 / 2 / 3 / 5 rows, us, 4096 x 14336 78 / 93 / 94 / 101 as for all
+// eight and 41 / 79 / 95 / 101 so, 6144 x 16384 162 / 201 / 192 / 194 and 65 / 126 / 157 / 197.
+double live_groups(const GemmArgs& a) {
+    if (!a.group_offsets) return 1.0;
+    const double g = a.n_groups > 0 ? a.n_groups : 1;
+    if (g < 3 || a.m_upper < 2) return std::min(g, (double)std::max(1, a.m_upper));
+    return g * (1.0 - std::pow(1.0 - 2.0 / g, a.m_upper / 2));
+}
+
 struct TileChoice { int ni = 8, max_rows = 256; double cost = 0.0; };
 
 // Time (microseconds) of a product cut into tiles of at most max_rows rows and 32*ni columns.  A compute unit
@@ -865,17 +876,18 @@ struct TileChoice { int ni = 8, max_rows = 256; double cost = 0.0; };
 // moves all tilings of a product alike.)  The second term of the result keeps the cheaper of two tilings that both wait for HBM.
 double tile_cost(const GemmArgs& a, int ni, int max_rows) {
     const bool sw = a.epilogue == EPI_SWIGLU_T;
-    const int groups = a.group_offsets ? (a.n_groups > 0 ? a.n_groups : 1) : 1, cols = sw ? 16 * ni : 32 * ni;
+    const int cols = sw ? 16 * ni : 32 * ni;
+    const double groups = live_groups(a);
     int nt, rt;
     split_rows(expected_rows(a), max_rows, nt, rt);
     const int mi = (rt + 31) / 32, slabs = a.K / 64;
-    const int64_t jobs = (int64_t)groups * nt * ((a.N + cols - 1) / cols);
+    const int64_t jobs = (int64_t)(groups * nt * ((a.N + cols - 1) / cols) + 0.5);
     double slab = std::max(0.076 * (mi + ni) + 0.02, 0.0168 * mi * ni);
     if (nt > 1) slab *= 1.05;              // (the row tiles of one weight slab do not all find it in L2)
     const int64_t full = jobs / 256, rem = jobs % 256;
     const double rounds = full + (rem == 0 ? 0.0 : ni == 8 && full > 0 && rem <= 128 ? 0.6 : 1.0);
     const double t = rounds * (slabs * slab + 3.0);
-    const double hbm = (double)groups * (sw ? 2 : 1) * a.N * a.K * 2.0 / 6.5e6;
+    const double hbm = groups * (sw ? 2 : 1) * a.N * a.K * 2.0 / 6.5e6;
     return std::max(t, hbm) + 0.2 * t;
 }
 

@@ -125,6 +125,31 @@ def test_gemm_narrow_tiles_with_every_epilogue_change_no_bit(tile_rows, epilogue
 
 # 36 column tiles for each of the groups that have rows: an XCD's list is longer than its 32 units by a few tiles, which are cut
 # into column halves where one row tile reads the weights; the last column tile is ragged on either side of its middle
+# few rows that reach few of the groups: narrower tiles than for all groups
+@pytest.mark.parametrize("epilogue", ["store", "swiglu"])
+@pytest.mark.parametrize("sizes", [(0, 1, 0, 0, 0, 0, 0, 1), (1, 0, 0, 1, 0, 2, 0, 0), (0, 0, 0, 3, 0, 0, 0, 3), (2, 1, 1, 0, 2, 0, 1, 1)])
+def test_gemm_few_live_groups_change_no_bit(epilogue, sizes):
+    import torch
+    import paper_2505_10259_amd as P
+    epi = {"store": P.SPEC_GEMM_STORE, "swiglu": P.SPEC_GEMM_SWIGLU}[epilogue]
+    g = torch.Generator("cuda").manual_seed(sum(sizes))
+    N, M, K, G = 4096 + 40, sum(sizes), 320, len(sizes)
+    A = torch.randn(M, K, device="cuda", generator=g).bfloat16()
+    W = (torch.randn(2, G, N, K, device="cuda", generator=g) * 0.05).bfloat16()
+    W3 = W[1] if epilogue == "swiglu" else None
+    off = torch.tensor([0] + list(np.cumsum(sizes)), dtype=torch.int32, device="cuda")
+    C = torch.full((M, N), 0.25, device="cuda", dtype=torch.bfloat16 if epilogue == "swiglu" else torch.float32)
+    D = C.clone()
+    P.spec_debug_gemm_epilogue(A, W[0], W3, C, off, G, M, N, K, epi, 0, 0)
+    b = 0
+    for i, n in enumerate(sizes):
+        if n:
+            P.spec_debug_gemm_epilogue(A[b:b + n], W[0, i], W[1, i] if W3 is not None else None, D[b:b + n], None, 0, n, N, K, epi, 256, 256)
+        b += n
+    torch.cuda.synchronize()
+    assert torch.equal(C, D)
+
+
 @pytest.mark.parametrize("epilogue", ["store", "add", "swiglu"])
 @pytest.mark.parametrize("short_by", [32, 160])
 @pytest.mark.parametrize("sizes", [(80, 80, 80, 80, 80, 80, 80, 80), (5, 128, 0, 97, 64, 17, 33, 96),
