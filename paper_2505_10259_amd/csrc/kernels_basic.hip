@@ -619,11 +619,18 @@ hipError_t launch_moe_sort(const int32_t* ids, int32_t* offsets, int32_t* perm, 
 // ---------------------------------------------------------------------------------------------
 // Plain tiled GEMM (any dtype, any size): 64x64 output tile, 256 threads, 4x4 outputs each.
 // Used for f32 models; bf16 models use the MFMA kernels.
+// What bounds it is the wait for a step of 16 k, so the next step's elements are requested before this one is multiplied
+// (registers: 120 with SwiGLU, four wavefronts a SIMD).  f32 layer of 80 / 576 rows, us, requested when needed / a step ahead:
+// 1024 wide 292 / 243 and 1346 / 965, 2048 wide 832 / 664 and 3604 / 2700.
 // ---------------------------------------------------------------------------------------------
+// f32 sums: four segments of the contraction, each a chain of fused multiply-adds over ascending k, added in ascending order,
+// so that four wavefronts can share an output (gemm_f32_kernel) and every f32 kernel gives the same bits.  (bf16 here: one chain.)
+__host__ __device__ inline int f32_segment(int K) { return (K + 63) / 64 * 16; }
 template <typename T, bool SWIGLU, bool PANELS>
 __global__ void __launch_bounds__(256)
 gemm_simple_kernel(GemmArgs a) {
     constexpr int BM = 64, BN = 64, BK = 16;
+    constexpr bool SEGS = std::is_same<T, float>::value;
     __shared__ float As[BK][BM + 1];
     __shared__ float Ws[BK][BN + 1];
     __shared__ float W3s[SWIGLU ? BK : 1][BN + 1];
@@ -655,22 +662,37 @@ gemm_simple_kernel(GemmArgs a) {
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) { acc[i][j] = 0.f; acc3[i][j] = 0.f; }
+    float tot[4][4] = {}, tot3[4][4] = {};            // (SEGS: the segments behind the running one)
     // loader mapping: thread loads (row = tid/4, k = (tid%4)*4 .. +3)
     int lr = tid >> 2, lk = (tid & 3) * 4;
     int arow = row_begin + lr;
     int64_t asrc = -1;
     if (arow < row_end) asrc = a.a_rows ? a.a_rows[arow] : arow;
     int wrow = col0 + lr;
-    for (int k0 = 0; k0 < a.K; k0 += BK) {
+    float ra[4], rw[4], rw3[4];
+    auto request = [&](int k0) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            int kk = k0 + lk + q;
-            As[lk + q][lr] = (asrc >= 0 && kk < a.K) ? to_f32<T>(A[asrc * a.lda + kk]) : 0.f;
-            bool wv = wrow < a.N && kk < a.K;
-            Ws[lk + q][lr] = wv ? to_f32<T>(W[weight_elem(wrow, kk, a.K, PANELS ? a.w_panel : 0)]) : 0.f;
-            if (SWIGLU) W3s[lk + q][lr] = wv ? to_f32<T>(W3[weight_elem(wrow, kk, a.K, PANELS ? a.w_panel : 0)]) : 0.f;
+            const int kk = k0 + lk + q;
+            const bool wv = wrow < a.N && kk < a.K;
+            ra[q] = (asrc >= 0 && kk < a.K) ? to_f32<T>(A[asrc * a.lda + kk]) : 0.f;
+            rw[q] = wv ? to_f32<T>(W[weight_elem(wrow, kk, a.K, PANELS ? a.w_panel : 0)]) : 0.f;
+            if (SWIGLU) rw3[q] = wv ? to_f32<T>(W3[weight_elem(wrow, kk, a.K, PANELS ? a.w_panel : 0)]) : 0.f;
+        }
+    };
+    request(0);
+    const int seg = SEGS ? f32_segment(a.K) : a.K;
+    for (int k_beg = 0; k_beg < a.K; k_beg += seg) {
+    const int k_end = min(k_beg + seg, a.K);
+    for (int k0 = k_beg; k0 < k_end; k0 += BK) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            As[lk + q][lr] = ra[q];
+            Ws[lk + q][lr] = rw[q];
+            if (SWIGLU) W3s[lk + q][lr] = rw3[q];
         }
         __syncthreads();
+        request(k0 + BK);
 #pragma unroll
         for (int kk = 0; kk < BK; ++kk) {
             float av[4], wv[4], w3v[4];
@@ -687,6 +709,22 @@ gemm_simple_kernel(GemmArgs a) {
                 }
         }
         __syncthreads();
+    }
+    if (SEGS && k_end < a.K) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                tot[i][j] += acc[i][j]; acc[i][j] = 0.f;
+                if (SWIGLU) { tot3[i][j] += acc3[i][j]; acc3[i][j] = 0.f; }
+            }
+    }
+    }
+    if (SEGS) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { acc[i][j] = tot[i][j] + acc[i][j]; acc3[i][j] = tot3[i][j] + acc3[i][j]; }
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -712,9 +750,12 @@ gemm_simple_kernel(GemmArgs a) {
 // tiles, one output per thread, the contraction in steps of 256 whose elements are requested a step ahead.  What bounds such a product is
 // latency: 35-48 us per launch as 16-wide steps on one to sixteen workgroups (8 rows, 256 to 1024 columns,
 // K = 256 to 1024), 5-11 us so.  Weights may be panels (a bf16 layer of 5 rows, d = 4096, whose output is off 16 bytes: 225 us, and
-// 1207 where panels left it to the 64x64 tiles).  Every output is the same chain of fused multiply-adds over ascending k.
+// 1207 where panels left it to the 64x64 tiles).  Every output is the same sum as there.
 constexpr int F32_TILE = 16, F32_PIECES = 16;               // rows and columns of a tile; pieces of 16 k requested at once
 constexpr int F32_NORM_K = 16 * F32_PIECES, F32_ROPE_K = 2048;      // longest rows that are normalised and rotated inside (see gemm_small_fuses)
+// Tiles (of one weight matrix) up to which four wavefronts share one, K over 256: 0.42 to 0.91 of one wavefront's time up to 512
+// tiles, 1.01 to 1.16 of it from 1008 to 2016.
+constexpr int F32_SEGMENT_TILES = 512;
 constexpr int SMALL_BM = 8, SMALL_BN = 32, SMALL_BK = 256, SMALL_LK = SMALL_BK / 128;
 template <typename T>
 __device__ inline float4 load4_guarded(const T* __restrict__ p, int left, bool vec) {     // zeros past the `left` elements of the row
@@ -776,7 +817,10 @@ gemm_small_kernel(GemmArgs a, int vec) {
         }
     };
     const int n_in = tid & 31, m_in = tid >> 5;
-    float acc = 0.f, acc3 = 0.f;
+    constexpr bool SEGS = std::is_same<T, float>::value;
+    float acc = 0.f, acc3 = 0.f, tot = 0.f, tot3 = 0.f;
+    const int seg = f32_segment(a.K);
+    int fold = seg;
     request(0);
     for (int k0 = 0; k0 < a.K; k0 += SMALL_BK) {
         __syncthreads();
@@ -790,16 +834,41 @@ gemm_small_kernel(GemmArgs a, int vec) {
         }
         __syncthreads();
         if (k0 + SMALL_BK < a.K) request(k0 + SMALL_BK);
-#pragma unroll 8
-        for (int k = 0; k < SMALL_BK; k += 4) {
+        auto four = [&](int k) __attribute__((always_inline)) {
             const float4 x = *(const float4*)&As[m_in][k], w = *(const float4*)&Ws[0][n_in][k];
             acc = fmaf(x.x, w.x, acc); acc = fmaf(x.y, w.y, acc); acc = fmaf(x.z, w.z, acc); acc = fmaf(x.w, w.w, acc);
             if (SWIGLU) {
                 const float4 u = *(const float4*)&Ws[SWIGLU ? 1 : 0][n_in][k];
                 acc3 = fmaf(x.x, u.x, acc3); acc3 = fmaf(x.y, u.y, acc3); acc3 = fmaf(x.z, u.z, acc3); acc3 = fmaf(x.w, u.w, acc3);
             }
+        };
+        auto behind = [&](int k) {                           // a segment's sum is whole behind its last k
+            if (SEGS && k0 + k == fold) {
+                fold += seg;
+                tot += acc; acc = 0.f;
+                if (SWIGLU) { tot3 += acc3; acc3 = 0.f; }
+            }
+        };
+        if (!SEGS || seg % SMALL_BK == 0) {
+#pragma unroll 8
+            for (int k = 0; k < SMALL_BK; k += 4) four(k);
+            behind(SMALL_BK);
+        } else if (seg % 64 == 0) {
+            for (int k1 = 0; k1 < SMALL_BK; k1 += 64) {
+#pragma unroll
+                for (int k = 0; k < 64; k += 4) four(k1 + k);
+                behind(k1 + 64);
+            }
+        } else {
+#pragma unroll 2
+            for (int k1 = 0; k1 < SMALL_BK; k1 += 16) {
+#pragma unroll
+                for (int k = 0; k < 16; k += 4) four(k1 + k);
+                behind(k1 + 16);
+            }
         }
     }
+    if (SEGS) { acc = tot + acc; acc3 = tot3 + acc3; }
     const int r = row_begin + m_in, c = col0 + n_in;
     if (r >= row_end || c >= a.N) return;
     const int64_t o = (int64_t)r * a.ldc + c;
@@ -808,17 +877,21 @@ gemm_small_kernel(GemmArgs a, int vec) {
     else ((float*)a.C)[o] = acc;
 }
 
-// f32 products of few tiles on the matrix cores: one wavefront makes 16 rows x 16 columns (of each of two weight matrices one).  What bounds such a product is
-// latency (a round of the 256-wide two-layer model is 29 of them, 4 to 20 rows), so every operand piece goes straight from memory to
-// registers, 256 k in flight at once, with no LDS and no barrier in between.  A lane's four
+// f32 products of few tiles on the matrix cores: a tile is 16 rows x 16 columns (of each of two weight matrices one).  What bounds such a product is
+// latency (a round of the 256-wide two-layer model is 29 of them, 4 to 20 rows): round trips to memory and the chain of matrix
+// instructions (16 cycles for four k).  So every operand piece goes straight from memory to registers, up to 256 k in flight at once,
+// and the four segments of a sum go to four wavefronts, which meet once, in LDS.  A lane's four
 // consecutive k are turned (permlane swaps) so that v_mfma_f32_16x16x4_f32 takes them in ascending order: it is four
-// chained fused multiply-adds, so every output has the bits of the VALU kernels' chain, whatever the row count chooses.
-// Round of four sequences and four candidates, with the launches that NORM and EPI_ROPE_KV save and the attention below: 433 -> 381 us.
-// A product alone, us, 8x32 VALU tiles / here, from 231 sizes of 1 to 512 rows (0.60 to 1.03 of the time, three at 1.04-1.06):
-//   K = 256    256 columns, 4 rows 4.4 / 4.4, 128 rows 4.6 / 4.7     8064 columns, 4 rows 5.3 / 5.6, 64 rows 15.8 / 11.9
-//   K = 1024  1024 columns, 1 row 11.5 / 10.6, 256 rows 27.7 / 18.5  8064 columns, 4 rows 14.1 / 14.9, 64 rows 55.6 / 36.6
-//   K = 2048   256 columns, 16 rows 20.1 / 21.1                      4096 columns, 20 rows 30.0 / 24.6
-//   K = 8192   256 columns, 4 rows 78.1 / 71.4                       4096 columns, 64 rows 190 / 115
+// chained fused multiply-adds, so every output has the bits of the VALU kernels' sums, whatever the row count chooses.
+// Where the tiles alone fill the chip four wavefronts only add traffic and one makes all segments (SEGS = 1).
+// Round of four sequences and four candidates: 433 us with 8x32 VALU tiles, 376 with one wavefront a tile, 329 here (the error of its
+// probabilities against 64 bits: 2.6e-7 with one chain a sum, 1.6e-7 with four).
+// A product alone, us, one wavefront and one chain / here, from 229 sizes of 1 to 512 rows (0.42 to 1.04 of the time, mean 0.70):
+//   K = 256    256 columns, 4 rows 4.4 / 3.4, 128 rows 4.7 / 3.7     8064 columns, 4 rows 5.7 / 4.6, 64 rows 12.0 / 10.9
+//   K = 1024  1024 columns, 1 row 10.7 / 6.4                         8064 columns, 4 rows 14.8 / 10.3
+//   K = 2048   256 columns, 16 rows 21.0 / 12.5                      4096 columns, 20 rows 25.0 / 20.0
+//   K = 8192   256 columns, 4 rows 71.4 / 31.9
+// (SEGS = 1 holds 8 pieces at once: 16 took 219 registers and up to 1.17 of the time, 19.9 -> 23.3 for 64 rows, 8064 columns, K = 512.)
 //
 // NORM: the rows are the residual stream and the product takes rmsnorm(row) * norm_g, with the row's squares summed in the
 // order of combine_norm_vec_kernel (same bits); EPI_ROPE_KV: a wavefront makes 16 rotary pairs (the second weight row of a
@@ -840,13 +913,14 @@ template <typename F, int... I>
 __device__ __forceinline__ void static_for_p_impl(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
 template <int N, typename F>
 __device__ __forceinline__ void static_for_p(F&& f) { static_for_p_impl(f, std::make_integer_sequence<int, N>{}); }
-template <int EPI, bool NORM>
-__global__ void __launch_bounds__(EPI == EPI_SWIGLU_T || EPI == EPI_ROPE_KV ? 128 : 64)
+template <int EPI, bool NORM, int P, int SEGS>
+__global__ void __launch_bounds__((EPI == EPI_SWIGLU_T || EPI == EPI_ROPE_KV ? 128 : 64) * SEGS)
 gemm_f32_kernel(GemmArgs a) {
     constexpr bool SWIGLU = EPI == EPI_SWIGLU_T, ROPE = EPI == EPI_ROPE_KV, DUAL = SWIGLU || ROPE;
-    constexpr int TILE = F32_TILE, P = F32_PIECES;
+    constexpr int TILE = F32_TILE;
     constexpr int NE = DUAL ? 2 : 4;                             // outputs that a lane finishes
-    __shared__ f32x4_t part[2][64];
+    __shared__ f32x4_t part[DUAL ? 2 : 1][SEGS][64];
+    __shared__ __attribute__((aligned(16))) float squares[NORM ? TILE : 1][NORM ? 2 * F32_PIECES + 4 : 1];
     int row_begin = blockIdx.y * TILE, row_end = a.M, group = 0;
     if (a.group_offsets) {
         int tiles = 0;
@@ -860,7 +934,10 @@ gemm_f32_kernel(GemmArgs a) {
         }
         if (!found) return;
     }
-    const int lane = threadIdx.x & 63, w = DUAL ? threadIdx.x >> 6 : 0, fr = lane & 15, kq = (lane >> 4) * 4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, w = DUAL ? wave & 1 : 0, s = DUAL ? wave >> 1 : wave;
+    const int fr = lane & 15, kq = (lane >> 4) * 4;
+    const int seg = f32_segment(a.K);
+    const int k_beg = SEGS > 1 ? min(s * seg, a.K) : 0, k_end = SEGS > 1 ? min(k_beg + seg, a.K) : a.K;     // this wavefront's segment, or all
     const int col0 = blockIdx.x * TILE;
     // ROPE: columns are rotary pairs, `half` of them a head
     const int half = ROPE ? a.rope.geom.head_dim >> 1 : 0, n_cols = ROPE ? a.N >> 1 : a.N;
@@ -890,7 +967,7 @@ gemm_f32_kernel(GemmArgs a) {
     const float *pa = arow + kq, *pw = wrow + kq, *pg = (const float*)a.norm_g + kq;
     auto request = [&](auto whole_c, int k0, int p) __attribute__((always_inline)) {
         const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
-        const bool in = decltype(whole_c)::value || k0 + 16 * p + kq < a.K;          // pieces past the end become zeros
+        const bool in = decltype(whole_c)::value || k0 + 16 * p + kq < k_end;        // pieces past the end become zeros
         f32x4_t x = z, g = z, wv = z;
         if (in) {
             x = *(const f32x4_t*)(pa + k0 + 16 * p);
@@ -902,8 +979,8 @@ gemm_f32_kernel(GemmArgs a) {
     };
     using Yes = std::true_type;
     using No = std::false_type;
-    if (a.K >= 16 * P) static_for_p<P>([&](auto p_c) __attribute__((always_inline)) { request(Yes(), 0, decltype(p_c)::value); });
-    else static_for_p<P>([&](auto p_c) __attribute__((always_inline)) { request(No(), 0, decltype(p_c)::value); });
+    if (k_end - k_beg >= 16 * P) static_for_p<P>([&](auto p_c) __attribute__((always_inline)) { request(Yes(), k_beg, decltype(p_c)::value); });
+    else static_for_p<P>([&](auto p_c) __attribute__((always_inline)) { request(No(), k_beg, decltype(p_c)::value); });
     if (ROPE) {
         const int lp = pos / a.rope.geom.page_tokens;
         if (pos < 0 || lp >= a.rope.geom.pages_per_seq) pos = -1;
@@ -915,30 +992,47 @@ gemm_f32_kernel(GemmArgs a) {
         // A slot is 8 consecutive elements (a thread of the norm kernel), its squares one chain that the even lane groups begin and the
         // odd ones finish (see squares8); the row's at most 32 slots are half a wavefront there, summed as its shuffles do: slots 16
         // apart, then 8, ... 1.
-        float s[16];
+        static_assert(!NORM || 4 * P == F32_PIECES, "a row's pieces lie in the four wavefronts' first chunks");
 #pragma unroll
-        for (int p = 0; p < 16; ++p) {
-            const f32x4_t& x = fa[p];                             // (zeros past the row)
+        for (int p = 0; p < P; ++p) {
+            const f32x4_t& x = fa[p];                             // (zeros past the segment)
             float t = fmaf(x[0], x[0], x[1] * x[1]);
             t = fmaf(x[3], x[3], fmaf(x[2], x[2], t));
             t = __shfl_xor(t, 16, WAVE);
-            s[p] = fmaf(x[3], x[3], fmaf(x[2], x[2], fmaf(x[1], x[1], fmaf(x[0], x[0], t))));
+            t = fmaf(x[3], x[3], fmaf(x[2], x[2], fmaf(x[1], x[1], fmaf(x[0], x[0], t))));
+            const int slot = (k_beg + 16 * p) / 8 + (lane >> 5);
+            if (w == 0 && (lane & 16) && slot < 2 * F32_PIECES && k_beg + 16 * p < k_end) squares[fr][slot] = t;
+        }
+        if (threadIdx.x < TILE) {                                 // slots past the row
+            for (int q = (a.K + 15) / 16 * 2; q < 2 * F32_PIECES; ++q) squares[threadIdx.x][q] = 0.f;
+        }
+        __syncthreads();
+        float v[2 * F32_PIECES];
+#pragma unroll
+        for (int q = 0; q < 2 * F32_PIECES; q += 4) {
+            const f32x4_t x = *(const f32x4_t*)&squares[fr][q];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[q + e] = x[e];
         }
 #pragma unroll
-        for (int o = 8; o > 0; o >>= 1)
+        for (int o = F32_PIECES; o > 0; o >>= 1)
 #pragma unroll
-            for (int p = 0; p < o; ++p) s[p] += s[p + o];
-        s[0] += __shfl_xor(s[0], 32, WAVE);
-        const float tot = __shfl(s[0], 16 + fr, WAVE);
-        rs = 1.0f / sqrtf(tot / (float)a.K + a.norm_eps);
+            for (int q = 0; q < o; ++q) v[q] += v[q + o];
+        rs = 1.0f / sqrtf(v[0] / (float)a.K + a.norm_eps);
     }
-    f32x4_t acc = z;
+    f32x4_t acc = z, tot = z;
+    int fold = seg;
     // the chunk in the registers, with the requests of the next one (NEXT: 0 none, 1 whole, 2 the rest) as they fall free
     auto chunk = [&](auto next_c, int k0) __attribute__((always_inline)) {
         constexpr int NEXT = decltype(next_c)::value;
         static_for_p<P>([&](auto p_c) __attribute__((always_inline)) {
             constexpr int p = decltype(p_c)::value;
-            if (NEXT == 0 && k0 + 16 * p >= a.K) return;
+            if (NEXT == 0 && k0 + 16 * p >= k_end) return;
+            if (SEGS == 1 && k0 + 16 * p == fold) {
+                fold += seg;
+                tot += acc;
+                acc = z;
+            }
             f32x4_t av = fa[p], wv = fw[p];
             if (NORM) {
 #pragma unroll
@@ -952,16 +1046,27 @@ gemm_f32_kernel(GemmArgs a) {
             for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], av[e], acc, 0, 0, 0);
         });
     };
-    int k0 = 0;
-    for (; k0 + 32 * P <= a.K; k0 += 16 * P) chunk(std::integral_constant<int, 1>(), k0);
-    if (k0 + 16 * P < a.K) { chunk(std::integral_constant<int, 2>(), k0); k0 += 16 * P; }
+    int k0 = k_beg;
+    for (; k0 + 32 * P <= k_end; k0 += 16 * P) chunk(std::integral_constant<int, 1>(), k0);
+    if (k0 + 16 * P < k_end) { chunk(std::integral_constant<int, 2>(), k0); k0 += 16 * P; }
     chunk(std::integral_constant<int, 0>(), k0);
+    if (SEGS == 1) acc = tot + acc;
     float v0[NE], v1[NE];
-    if constexpr (DUAL) {                                 // each wavefront finishes half of the columns
-        part[w][lane] = acc;
+    if constexpr (SEGS > 1 || DUAL) {
+        part[w][s][lane] = acc;
         __syncthreads();
+        if (s != 0) return;                               // the first segment's wavefronts add them (DUAL: each finishes half of the columns)
+        auto sum = [&](int m, int e) {
+            float v = part[m][0][lane][e];
 #pragma unroll
-        for (int e = 0; e < NE; ++e) { v0[e] = part[0][lane][w * NE + e]; v1[e] = part[1][lane][w * NE + e]; }
+            for (int q = 1; q < SEGS; ++q) v += part[m][q][lane][e];
+            return v;
+        };
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            v0[e] = sum(0, DUAL ? w * NE + e : e);
+            if constexpr (DUAL) v1[e] = sum(1, w * NE + e);
+        }
     } else {
 #pragma unroll
         for (int e = 0; e < NE; ++e) v0[e] = acc[e];
@@ -1008,7 +1113,8 @@ static bool small_tiles(const GemmArgs& a) {
 // Rotation inside pays at every size measured (a launch less): layer of 20 rows, us, as a launch of its own / inside, K = 512 62.9 / 60.9,
 // 1024 105 / 101, 2048 535 / 536, of one row 515 / 508.  The norm inside pays only where a row's squares come from the pieces that
 // the product holds anyway, up to 256 k: every column tile sums them again, and behind that each further chunk is
-// a round trip to memory in front of the product.  Layer of 1 / 20 / 80 rows, norm as a launch / inside (from 512 on with those trips):
+// a round trip to memory in front of the product.  Layer of 1 / 20 / 80 rows, norm as a launch / inside (from 512 on with those trips;
+// measured with one wavefront a tile, and with four the trips weigh more):
 //   K = 128   32.2 / 35.4 / 36.0                          29.9 / 32.6 / 33.1
 //   K = 256   39.9 / 44.5 / 48.0                          38.2 / 42.0 / 46.1
 //   K = 512   54.0 / 60.9 / 73.0                          57.3 / 63.1 / 83.3
@@ -1039,11 +1145,21 @@ hipError_t launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st, bool
             const int cols = rope ? a.N / 2 : a.N;
             dim3 grid((cols + F32_TILE - 1) / F32_TILE, (rows + F32_TILE - 1) / F32_TILE + (a.group_offsets ? a.n_groups : 0));
             // (EPI_STORE_F32 stores or adds as a.epilogue says)
-            auto kern = a.norm_g ? (rope ? gemm_f32_kernel<EPI_ROPE_KV, true> : swiglu ? gemm_f32_kernel<EPI_SWIGLU_T, true>
-                                                                                        : gemm_f32_kernel<EPI_STORE_F32, true>)
-                                 : (rope ? gemm_f32_kernel<EPI_ROPE_KV, false> : swiglu ? gemm_f32_kernel<EPI_SWIGLU_T, false>
-                                                                                         : gemm_f32_kernel<EPI_STORE_F32, false>);
-            hipLaunchKernelGGL(kern, grid, dim3(rope || swiglu ? 128 : 64), 0, st, a);
+            // A wavefront per segment and tile, with all pieces of a row of up to 256 k in flight; one for all segments where the tiles alone
+            // fill the chip (figures at F32_SEGMENT_TILES).
+            const bool all = a.K > 256 && (int64_t)grid.x * grid.y * (rope || swiglu ? 2 : 1) > F32_SEGMENT_TILES;
+            auto pick = [&](auto p_c, auto segs_c) {
+                constexpr int P = decltype(p_c)::value, SEGS = decltype(segs_c)::value;
+                return rope ? gemm_f32_kernel<EPI_ROPE_KV, false, P, SEGS> : swiglu ? gemm_f32_kernel<EPI_SWIGLU_T, false, P, SEGS>
+                                                                                   : gemm_f32_kernel<EPI_STORE_F32, false, P, SEGS>;
+            };
+            using C1 = std::integral_constant<int, 1>;
+            using C4 = std::integral_constant<int, 4>;
+            using CP = std::integral_constant<int, F32_PIECES>;
+            auto kern = a.norm_g ? (rope ? gemm_f32_kernel<EPI_ROPE_KV, true, 4, 4> : swiglu ? gemm_f32_kernel<EPI_SWIGLU_T, true, 4, 4>
+                                                                                              : gemm_f32_kernel<EPI_STORE_F32, true, 4, 4>)
+                        : a.K <= 256 ? pick(C4(), C4()) : all ? pick(std::integral_constant<int, F32_PIECES / 2>(), C1()) : pick(CP(), C4());
+            hipLaunchKernelGGL(kern, grid, dim3((rope || swiglu ? 128 : 64) * (all ? 1 : 4)), 0, st, a);
             return hipGetLastError();
         }
         dim3 sgrid((a.N + SMALL_BN - 1) / SMALL_BN, (rows + SMALL_BM - 1) / SMALL_BM + (a.group_offsets ? a.n_groups : 0));

@@ -323,6 +323,40 @@ def test_gemm_f32_same_bits_on_every_kernel(M, N, K, values):
         assert torch.equal(C.view(torch.int32)[~nan], ref.view(torch.int32)[~nan]), name
 
 
+# segments of 16 k, empty and ragged ones, pieces of 8 and of 16 on either side of a fold; the last three are tiles enough for one wavefront each
+@pytest.mark.parametrize("M,N,K", [(3, 24, 16), (16, 40, 68), (16, 40, 132), (5, 33, 1028), (20, 64, 2052),
+                                   (64, 8064, 260), (64, 8100, 1028), (33, 8192, 2064)])
+def test_gemm_f32_four_segments(M, N, K):
+    """An f32 sum is four chains over consecutive segments of the contraction, added in ascending order, whichever kernel makes it: the
+    matrix cores with a wavefront per segment or for all four, 8 x 32 tiles (operands off 16 bytes) and 64 x 64 tiles (the same rows
+    inside 1024) agree bit for bit, and the error is that of chains of a quarter of K."""
+    import torch
+    import paper_2505_10259_amd as P
+    g = torch.Generator("cuda").manual_seed(M + N + K)
+    A = torch.randn(1024, K, device="cuda", generator=g)
+    W = torch.randn(N, K, device="cuda", generator=g)
+
+    def call(a, w, rows):
+        C = torch.full((rows, N), 7.0, device="cuda")
+        P.spec_gemm(a, w, C, rows, N, K, P.SPEC_F32)
+        torch.cuda.synchronize()
+        return C[:M]
+
+    off = torch.empty(M * K + 1, device="cuda")
+    off[1:] = A[:M].reshape(-1)
+    W_all = torch.cat([W, torch.zeros(max(0, 1024 - N), K, device="cuda")])        # (1024 rows and columns are 256 tiles of 64 x 64)
+    C_all = torch.empty(1024, W_all.shape[0], device="cuda")
+    P.spec_gemm(A, W_all, C_all, 1024, W_all.shape[0], K, P.SPEC_F32)
+    torch.cuda.synchronize()
+    ref = C_all[:M, :N]
+    assert torch.equal(call(A[:M], W, M), ref)
+    assert torch.equal(call(off[1:], W, M), ref)
+    seg = (K + 63) // 64 * 16
+    terms = A[:M].double().abs() @ W.double().abs().t()
+    # a segment's chain rounds seg times, the sum of four three times more
+    assert ((ref.double() - A[:M].double() @ W.double().t()).abs() <= 1.01 * (seg + 3) * 2.0 ** -24 * terms).all()
+
+
 def test_gemm_f32_plain():
     import torch
     import paper_2505_10259_amd as P
