@@ -274,8 +274,9 @@ int spec_profile_read(spec_ctx* ctx, double* ms_out, int64_t* launches_out, int 
  *   (sampling only; both NULL = draw them from Philox4x32-10 with key `seed`, counter
  *   (round, seq_base + b, position, 0), word 1 -> accept, word 2 -> resample);
  *   outputs n_accepted [B], next_token [B] int32: ordinary device memory (hipMalloc), apart from each other and from the inputs.
- *   Both are scratch of the call until it has completed: with q_logits the workgroups of a sequence meet in them by atomic
- *   minimum and add, which memory of the host or of another device need not offer.  Runs on `stream` (hipStream_t or NULL). */
+ *   Both are scratch of the call until it has completed: the workgroups of a sequence meet in them by atomic
+ *   minimum and add, which memory of the host or of another device need not offer.  A row of p_logits that is -inf or not-a-number
+ *   throughout keeps no candidate, and its token is 0.  Runs on `stream` (hipStream_t or NULL). */
 int spec_accept(const float* p_logits, const float* q_logits, const int32_t* draft_tokens,
                 const float* u_accept, const float* u_resample, float temperature, uint64_t seed,
                 uint32_t round, uint32_t seq_base, int B, int k, int V, int32_t* n_accepted,

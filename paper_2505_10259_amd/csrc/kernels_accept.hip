@@ -375,6 +375,11 @@ __global__ void accept_sample_tiny_kernel(AcceptArgs a) {
 // =================================================================================================
 // Greedy rule, a workgroup per sequence, for rows of any size and alignment (the kernels for some of them follow).
 // =================================================================================================
+// The argmax kernels give NO_ID for a row that holds nothing above -inf (all -inf or not-a-number).  Such a row keeps no candidate and its
+// token is 0, as in the sampling rule: no id outside the vocabulary is emitted, and none meets the row number of offer_pick.
+constexpr int NO_ID = 0x7fffffff;
+__device__ inline bool greedy_keeps(int am, int candidate) { return am != NO_ID && am == candidate; }
+__device__ inline int greedy_token(int am) { return am == NO_ID ? 0 : am; }
 constexpr int WIDE_THREADS = 1024, WIDE_WAVES = WIDE_THREADS / 64;
 struct WideShared {
     float red[WIDE_WAVES];
@@ -399,7 +404,7 @@ struct WideRow {
 // argmax, lowest id on ties
 __device__ inline int wide_argmax(const WideRow& a, WideShared& sh) {
     float bv = -INFINITY;
-    int bi = 0x7fffffff;
+    int bi = NO_ID;
     for (int g0 = 0; g0 < a.n; g0 += 4 * WIDE_THREADS) {
         float4 v[4];
 #pragma unroll
@@ -432,7 +437,7 @@ constexpr int NARROW_THREADS = 256, NARROW_MAX_V = 3072;       // (short rows: a
 // argmax with lowest-index tie-break
 __device__ inline int narrow_argmax(const float* __restrict__ z, int V, float* shv, int* shi) {
     float bv = -INFINITY;
-    int bi = 0x7fffffff;
+    int bi = NO_ID;
     for (int c = threadIdx.x; c < V; c += NARROW_THREADS) {
         float v = z[c];
         if (v > bv) { bv = v; bi = c; }
@@ -462,11 +467,11 @@ accept_greedy_generic_kernel(AcceptArgs a) {
     int n = 0, am;
     while (true) {
         am = wide_argmax(WideRow(P + (int64_t)n * a.V, a.V), sh);
-        if (n < a.k && a.draft_tokens[b * a.k + n] == am) ++n; else break;
+        if (n < a.k && greedy_keeps(am, a.draft_tokens[b * a.k + n])) ++n; else break;
     }
     if (threadIdx.x == 0) {
         if (a.n_accepted) a.n_accepted[b] = n;
-        if (a.next_token) a.next_token[b] = am;
+        if (a.next_token) a.next_token[b] = greedy_token(am);
     }
 }
 
@@ -533,7 +538,7 @@ __device__ inline void fast_row_stats(float4 (&v)[FAST_SWEEPS], float inv_tau, F
 // argmax of a row held in registers, lowest id on ties
 __device__ inline int fast_argmax(const float4 (&v)[FAST_SWEEPS], FastShared& sh) {
     float bv = -INFINITY;
-    int bi = 0x7fffffff;
+    int bi = NO_ID;
 #pragma unroll
     for (int s = 0; s < FAST_SWEEPS; ++s) {
         const int id = (s * FAST_THREADS + (int)threadIdx.x) * 4;
@@ -623,11 +628,11 @@ accept_greedy_kernel(AcceptArgs a) {
         float4 z[FAST_SWEEPS];
         fast_load_row(P + (int64_t)n * a.V, a.V, z);
         am = fast_argmax(z, sh);
-        if (n < a.k && a.draft_tokens[b * a.k + n] == am) ++n; else break;
+        if (n < a.k && greedy_keeps(am, a.draft_tokens[b * a.k + n])) ++n; else break;
     }
     if (threadIdx.x == 0) {
         if (a.n_accepted) a.n_accepted[b] = n;
-        if (a.next_token) a.next_token[b] = am;
+        if (a.next_token) a.next_token[b] = greedy_token(am);
     }
 }
 
@@ -646,7 +651,7 @@ accept_greedy_rows_kernel(AcceptArgs a) {
     for (int r = threadIdx.x >> 6; r <= a.k; r += FAST_WAVES) {
         const float* row = P + (int64_t)r * a.V;
         float bv = -INFINITY;
-        int bi = 0x7fffffff;
+        int bi = NO_ID;
 #pragma unroll 8
         for (int c = lane; c < a.V; c += 64) {
             const float v = row[c];
@@ -663,9 +668,9 @@ accept_greedy_rows_kernel(AcceptArgs a) {
     __syncthreads();
     if (threadIdx.x == 0) {
         int n = 0;
-        while (n < a.k && a.draft_tokens[b * a.k + n] == am[n]) ++n;
+        while (n < a.k && greedy_keeps(am[n], a.draft_tokens[b * a.k + n])) ++n;
         if (a.n_accepted) a.n_accepted[b] = n;
-        if (a.next_token) a.next_token[b] = am[n];
+        if (a.next_token) a.next_token[b] = greedy_token(am[n]);
     }
 }
 
@@ -799,7 +804,7 @@ accept_greedy_ahead_kernel(AcceptArgs a) {
     if (!stop) {
         const float* row = a.p_logits + ((int64_t)b * (a.k + 1) + i) * V;
         float bv = -INFINITY;
-        int bi = 0x7fffffff;
+        int bi = NO_ID;
         float4 v[2][4];
         auto request = [&](int buf, int g0) {
 #pragma unroll
@@ -834,7 +839,7 @@ accept_greedy_ahead_kernel(AcceptArgs a) {
             bv = red[0]; bi = redi[0];
 #pragma unroll
             for (int w = 1; w < T / 64; ++w) if (red[w] > bv || (red[w] == bv && redi[w] < bi)) { bv = red[w]; bi = redi[w]; }
-            if (i == a.k || a.draft_tokens[b * a.k + i] != bi) offer_pick(a, b, i, (uint32_t)bi);
+            if (i == a.k || !greedy_keeps(bi, a.draft_tokens[b * a.k + i])) offer_pick(a, b, i, (uint32_t)greedy_token(bi));
         }
     }
     if (threadIdx.x == 0) report(a, b);
@@ -897,14 +902,14 @@ draft_sample_kernel(const float* __restrict__ z, int64_t ld, int V, float inv_ta
 __global__ void __launch_bounds__(WIDE_THREADS)
 draft_argmax_kernel(const float* __restrict__ z, int64_t ld, int V, int step, int32_t* __restrict__ draft_tokens, int k) {
     __shared__ WideShared sh;
-    const int b = blockIdx.x, pick = wide_argmax(WideRow(z + (int64_t)b * ld, V), sh);
+    const int b = blockIdx.x, pick = greedy_token(wide_argmax(WideRow(z + (int64_t)b * ld, V), sh));
     if (threadIdx.x == 0) draft_tokens[b * k + step - 1] = pick;
 }
 __global__ void __launch_bounds__(NARROW_THREADS)
 draft_argmax_narrow_kernel(const float* __restrict__ z, int64_t ld, int V, int step, int32_t* __restrict__ draft_tokens, int k) {
     __shared__ float shf[4];
     __shared__ int shi[4];
-    const int b = blockIdx.x, pick = narrow_argmax(z + (int64_t)b * ld, V, shf, shi);
+    const int b = blockIdx.x, pick = greedy_token(narrow_argmax(z + (int64_t)b * ld, V, shf, shi));
     if (threadIdx.x == 0) draft_tokens[b * k + step - 1] = pick;
 }
 // fast path (see above): the row is read once
@@ -917,7 +922,7 @@ draft_pick_kernel(const float* __restrict__ z, int64_t ld, int V, int mode, floa
     fast_load_row(z + (int64_t)b * ld, V, row);
     int pick;
     if (mode == SPEC_GREEDY) {
-        pick = fast_argmax(row, sh);
+        pick = greedy_token(fast_argmax(row, sh));
     } else {
         float m, s, tot;
         fast_row_stats(row, inv_tau, sh, &m, &s);        // (the row is its exponentials now)

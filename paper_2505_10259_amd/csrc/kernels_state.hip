@@ -15,7 +15,7 @@ __global__ void commit_kernel(SeqState s, const int32_t* __restrict__ d, int k,
     if (b >= B) return;
     int remaining = s.max_new[b] - s.n_new[b];
     if (remaining <= 0) return;
-    int n = n_acc[b];
+    const int n = min(max(n_acc[b], 0), k);        // (what is read and counted below has room for k)
     int c = min(n + 1, remaining);
     int len = s.len[b];
     int32_t* toks = s.tokens + (int64_t)b * s.tok_cap;

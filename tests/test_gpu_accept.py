@@ -226,6 +226,57 @@ def test_accept_greedy_at_once_and_in_turn(B, k, V):
             assert n.cpu().tolist() == [e[0] for e in exp]
 
 
+# rows at once (4097, 32000, 65537), a wavefront per row (1001) and, without n_accepted or of one candidate, in turn
+@pytest.mark.parametrize("bad", [float("nan"), -float("inf")])
+@pytest.mark.parametrize("B,k,V", [(9, 2, 4097), (9, 16, 4097), (9, 2, 32000), (9, 16, 32000), (9, 3, 65537), (9, 1, 32000), (9, 4, 1001)])
+def test_greedy_row_without_a_number_keeps_nothing(B, k, V, bad):
+    """A row that is -inf or not-a-number throughout keeps no candidate, whatever the rows behind it say, and its token is 0."""
+    import torch
+    import paper_2505_10259_amd as P
+    g = torch.Generator("cuda").manual_seed(V + k)
+    p = torch.randn(B, k + 1, V, device="cuda", generator=g)
+    p[:, :, 0] = -5.0                            # (no other row's choice)
+    d = p[:, :k].argmax(-1).to(torch.int32).contiguous()
+    tokens = p.argmax(-1)
+    row = [0, k // 2, k - 1, k, None]            # the bad row of each sequence: first, middle, last candidate's, the one behind them, none
+    exp = []
+    for b in range(B):
+        r = row[b % 5]
+        if r is not None:
+            p[b, r] = bad
+        if b == 8:                               # no good row at all
+            p[b], r = bad, 0
+        if b == 5:                               # the bad row's candidate is the number that says so inside the kernels
+            d[b, 0] = 0x7fffffff
+        exp.append((k, tokens[b, k].item()) if r is None else (r, 0))
+    for n in (torch.full((B,), -1, dtype=torch.int32, device="cuda"), None):
+        nx = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+        P.spec_accept(p, None, d, None, None, 1.0, 0, 0, 0, B, k, V, n, nx)
+        torch.cuda.synchronize()
+        assert nx.cpu().tolist() == [e[1] for e in exp]
+        if n is not None:
+            assert n.cpu().tolist() == [e[0] for e in exp]
+
+
+@pytest.mark.parametrize("vocab", [512, 4100])
+def test_greedy_round_of_a_model_without_numbers_commits_tokens_of_the_vocabulary(vocab):
+    """An LM head of not-a-numbers: every round of both models commits one token 0 per sequence and counts no kept candidate."""
+    import paper_2505_10259_amd as P
+    from gpu_common import GpuDecode, host_model_pinned
+    from synth import ModelShape
+    hm = host_model_pinned(ModelShape(2, 256, 4, 4, 64, 512, vocab, dtype="f32"))
+    hm.globals()["head"][:] = np.nan
+    prompts = synth.make_prompts(3, (5, 9), vocab, seed=1)
+    g = GpuDecode(hm, 1, False, prompts, 4, 6)
+    rounds = g.run(want_logits=False)
+    stats = P.spec_get_stats(g.s.ctx)
+    assert all((r["draft"] == 0).all() and (r["n_acc"] == 0).all() and (r["next"] == 0).all() for r in rounds)
+    # (the first of the 6 tokens may come with the prefill)
+    assert g.generated() == [[0] * 6] * 3
+    assert sum(stats["accept_hist"][1:]) == 0
+    g.close()
+
+
 @pytest.mark.parametrize("V,ahead", [(300, True), (9001, True), (24577, True), (65537, True), (9001, False)])
 def test_normaliser_error(V, ahead):
     """With a draft row of one id the candidate is kept exactly while u < p(c), so bisecting u gives p(c) to the bit; the id of the largest
