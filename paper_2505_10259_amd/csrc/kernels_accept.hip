@@ -56,16 +56,16 @@ hipError_t launch_philox_uniforms(uint64_t seed, uint32_t round, uint32_t seq_ba
     return hipGetLastError();
 }
 
-// Single softmax weights use the library's expf.  (One exp2 instruction on the rounded product x log2 e is up to 2.3 x 2^-24 off where expf is
-// 1.4, and loses weights below 2^-126.)
-// In sums of many weights, of z under a maximum m, e^((z - m) / tau) = 2^t with t = (z - m) c, c = log2(e) / tau in two
-// parts, both positive so that -inf gives 0 (weight_scale).  t is rounded once, which for single weights is up to |t| 2^-25 off but
-// averages out in a sum, and weights below 2^-126 of the largest count as nothing.  Four instructions against expf's fourteen and the two in front: 256
-// sequences of 6 candidates over 32000 ids 85 us against 95 with a nine-instruction exponential as exact as expf.
+// Softmax weights e^((z - m) / tau) = 2^(d c), d = z - m <= 0, c = log2(e) / tau in two parts, both positive so that -inf gives 0
+// (weight_scale).  A weight is the library's expf with the division by tau inside the product: 2^n * exp2 of the rest, eleven instructions against
+// sixteen, and weights below 2^-126 are there.  (Far below, n stays and the rest underflows.)  Error over every f32 argument, in units of half the
+// last place, mean / largest: 0.51 / 1.8 at any temperature; expf of the rounded d / tau 0.51 / 1.8 at temperature 1 and, at
+// 0.8, 2.4 / 33 down to e^-17, 24 / 129 below.
 struct WeightScale { float hi, lo; };
-__device__ inline float sum_weight(float z, float m, const WeightScale& c) {
-    const float d = z - m;
-    return __builtin_amdgcn_exp2f(__builtin_fmaf(d, c.hi, d * c.lo));
+__device__ inline float weight(float z, float m, const WeightScale& c) {
+    const float d = z - m, h = fmaxf(d * c.hi, -200.f), n = __builtin_rintf(h);
+    const float l = __builtin_fmaf(d, c.lo, __builtin_fmaf(d, c.hi, -h));
+    return __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f((h - n) + l), (int)n);
 }
 __device__ inline WeightScale weight_scale(float inv_tau) {
     const double c = (double)inv_tau * 1.44269504088896340736;
@@ -77,24 +77,41 @@ __device__ inline WeightScale weight_scale(float inv_tau) {
 // =================================================================================================
 // Rows of 4 ids and more at any alignment, a workgroup of T threads per row or pair of rows.  A row passes through in granules of four ids: maximum and
 // normaliser in one pass (running maximum per thread), the draw in a pass for the sums of runs of 64 U granules, of which only the run that
-// holds the crossing is read again.  1 / normaliser of random rows (standard deviation 3, temperature
-// 0.8) is off by 0.96 x 2^-24 on average at 32000 and 65537 ids, 0.94 at 512 (library exponentials, rows in registers or 1024 threads: 1.05, 1.02, 0.88).
+// holds the crossing is read again.  1 / normaliser, mean error in 2^-24 at temperature 0.8 / 1, expf and one chain a thread (256 threads up to 3072
+// ids, else 1024) -> here: random rows (standard deviation 3) 1001 ids 0.89 / 0.78 -> 0.89 / 0.81, 32000 ids 1.02 / 0.97 -> 0.90 / 0.82, 131073 ids
+// 1.05 / 0.96 -> 0.86 / 0.74; one large logit and the rest equal, far below 32000 ids 2.7 / 2.1 -> 2.3 / 1.6, 131073 ids 10.5 / 7.3 -> 2.4 / 1.8.
 // =================================================================================================
-// running maximum and sum of exp((z - m) / tau) over what a thread has seen
+// Running maximum and sum of the weights over what a thread has seen.  With h the rounded d c and l what it lacks, a weight is
+// 2^h (1 + l ln 2): the sum takes the 2^h and a second one their corrections, eight instructions and no rounding of the exponent.  (Those
+// below 2^-126 of the maximum's weight count as nothing: the sum does not see them.)  What rounding takes from the sum at every step of N
+// granules is kept beside it: equal weights would lose in the same direction every time.
 struct MaxSum {
-    float m = -INFINITY, s = 0.f;
+    float m = -INFINITY, s = 0.f, r = 0.f, lost = 0.f;
+    __device__ float add(float z, float at, const WeightScale& c) {
+        const float d = z - at, h = d * c.hi, e = __builtin_amdgcn_exp2f(h);
+        // (far below what h lacks is no number, or as large, where the weight is 0; a not-a-number is one in e)
+        r = __builtin_fmaf(e, __builtin_amdgcn_fmed3f(__builtin_fmaf(d, c.lo, __builtin_fmaf(d, c.hi, -h)), -1.f, 1.f), r);
+        return e;
+    }
     template <int N>
     __device__ void take(const float4 (&v)[N], const WeightScale& c) {
+        static_assert(N == 1 || N == 4, "granules of a step");
         float mx = m;
 #pragma unroll
         for (int q = 0; q < N; ++q) mx = fmaxf(fmaxf(fmaxf(mx, v[q].x), fmaxf(v[q].y, v[q].z)), v[q].w);
-        if (mx > m) { s *= sum_weight(m, mx, c); m = mx; }
+        if (mx > m) { const float f = weight(m, mx, c); s *= f; r *= f; lost *= f; m = mx; }
         // (nothing but -inf and not-a-numbers so far: the former add nothing, one of the latter makes the sum one)
         const float at = m == -INFINITY ? 0.f : m;
+        float t[N];
 #pragma unroll
-        for (int q = 0; q < N; ++q)
-            s += (sum_weight(v[q].x, at, c) + sum_weight(v[q].y, at, c)) + (sum_weight(v[q].z, at, c) + sum_weight(v[q].w, at, c));
+        for (int q = 0; q < N; ++q) t[q] = (add(v[q].x, at, c) + add(v[q].y, at, c)) + (add(v[q].z, at, c) + add(v[q].w, at, c));
+        const float step = N == 1 ? t[0] : (t[0] + t[1 % N]) + (t[2 % N] + t[3 % N]);
+        const float now = s + step, b = now - s;              // (Knuth's sum of two and its error)
+        lost += (s - (now - b)) + (step - b);
+        s = now;
     }
+    // the sum under the maximum of more threads, whose weight f this one's has
+    __device__ float under(float f) const { return __builtin_fmaf(s, f, __builtin_fmaf(r, 0.693147181f, lost) * f); }
 };
 
 template <int T>
@@ -164,7 +181,7 @@ __device__ inline void row_stats(const float* p, const float* q, int V, float in
     const int lane = t & 63, wv = t >> 6;
     auto wave = [&](const MaxSum& v, int r) {
         const float m = wave_max(v.m);
-        const float s = wave_sum(v.m == -INFINITY ? v.s : v.s * expf((v.m - m) * inv_tau));
+        const float s = wave_sum(v.under(v.m == -INFINITY ? 1.f : weight(v.m, m, c)));
         if (lane == 0) { sh.red[r][0][wv] = m; sh.red[r][1][wv] = s; }
     };
     auto block = [&](int r, float* mo, float* so) {
@@ -174,7 +191,7 @@ __device__ inline void row_stats(const float* p, const float* q, int V, float in
 #pragma unroll
         for (int w = 0; w < T / 64; ++w) {
             const float mw = sh.red[r][0][w], sw = sh.red[r][1][w];
-            s += mw == -INFINITY ? sw : sw * expf((mw - m) * inv_tau);
+            s += mw == -INFINITY ? sw : sw * weight(mw, m, c);
         }
         *mo = m; *so = s;
     };
@@ -201,7 +218,8 @@ __device__ inline float wave_prefix(float v) {
 }
 // Inverse CDF over the residual weights max(0, p - q) of two rows, or (RES false) over the target's own: the smallest id whose running sum
 // (ascending ids) exceeds u * total; if rounding leaves none, the largest id of positive weight.  *total_out: the total (0: no
-// positive weight; result invalid).  One pass for the sums of runs of 64 U granules; the run that holds the crossing is read again.
+// positive weight; result invalid).  One pass for the sums of runs of 64 U granules; the run that holds the crossing is read again.  Both
+// passes take the same weights to the bit, so that what the sums see as positive is found (and rows that are equal leave nothing).
 template <int T, bool RES>
 __device__ inline int row_draw(const float* p, const float* q, int V, float inv_tau, float pm, float pf, float qm, float qf, float u,
                                RowShared<T>& sh, float* total_out) {
@@ -209,7 +227,9 @@ __device__ inline int row_draw(const float* p, const float* q, int V, float inv_
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = (V + 3) >> 2;
     const int U = (n + 64 * T - 1) / (64 * T), runs = (n + 64 * U - 1) / (64 * U);
     const WeightScale c = weight_scale(inv_tau);
-    auto weights = [&](const float4& zp, const float4& zq, int g, auto&& f) {
+    auto weights = [&](const float4& zp, const float4& zq, int g) {
+#pragma clang fp contract(off)
+        auto f = [&](float z, float m) { return weight(z, m, c); };
         float4 a = zp, b = zq;
         if (4 * (g - lane) + 256 > V) {                       // (the same for all lanes)
             a = row_ids(zp, V, g);
@@ -235,8 +255,7 @@ __device__ inline int row_draw(const float* p, const float* q, int V, float inv_
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (r0 + j * W >= runs) continue;                 // (the same for all lanes)
-            t[j] += sum4(weights(zp[buf][j], RES ? zq[buf][j] : zp[buf][j], ((r0 + j * W) * U + i) * 64 + lane,
-                                 [&](float z, float m) { return sum_weight(z, m, c); }));
+            t[j] += sum4(weights(zp[buf][j], RES ? zq[buf][j] : zp[buf][j], ((r0 + j * W) * U + i) * 64 + lane));
             if (i == U - 1) {
                 const float v = wave_sum(t[j]);
                 if (lane == 0) sh.run[r0 + j * W] = v;
@@ -272,14 +291,13 @@ __device__ inline int row_draw(const float* p, const float* q, int V, float inv_
     // the run that holds the crossing, and its neighbours within the rounding of these sums
     uint64_t near = __ballot(mine > 0.f && front <= target + slack && front + mine >= target - slack);
     int found = 0x7fffffff;
-    auto exact = [&](float z, float m) { return expf((z - m) * inv_tau); };
     for (; near; near &= near - 1) {
         const int l = __ffsll((unsigned long long)near) - 1, r = wv * 64 + l;
         float base = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(front), l));
         for (int i = 0; i < U; ++i) {
             const int g = (r * U + i) * 64 + lane;
             const float4 za = row_load(p, V, g), zb = RES ? row_load(q, V, g) : za;
-            const float4 w = weights(za, zb, g, exact);
+            const float4 w = weights(za, zb, g);
             const float local = sum4(w), in = wave_prefix(local);
             float s = base + (in - local);
             const float x[4] = {w.x, w.y, w.z, w.w};
@@ -298,14 +316,15 @@ __device__ inline int row_draw(const float* p, const float* q, int V, float inv_
     int last = -1;
     for (int g = threadIdx.x; g < (n + 63) / 64 * 64; g += T) {
         const float4 za = row_load(p, V, g), zb = RES ? row_load(q, V, g) : za;
-        const float4 w = weights(za, zb, g, exact);
+        const float4 w = weights(za, zb, g);
         const float x[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
         for (int j = 0; j < 4; ++j) if (x[j] > 0.f) last = 4 * g + j;
     }
     if (last >= 0) atomicMax(&sh.last, last);
     __syncthreads();
-    return sh.last >= 0 ? sh.last : 0;
+    if (sh.last < 0) *total_out = 0.f;
+    return max(sh.last, 0);
 }
 // What the acceptance test of candidate i of sequence b needs of its rows, asked for ahead of their statistics, and the test: true = rejected
 struct Candidate {

@@ -277,6 +277,99 @@ def test_greedy_round_of_a_model_without_numbers_commits_tokens_of_the_vocabular
     g.close()
 
 
+# rows at once, in turn (without n_accepted) and, for fewer than four ids, a thread per sequence
+@pytest.mark.parametrize("V,B", [(3, 4096), (4, 4096), (8, 4096), (32, 4096), (1001, 512), (9001, 256), (32000, 256), (65537, 128)])
+@pytest.mark.parametrize("tau", [0.8, 1.0])
+def test_draw_from_rows_that_are_equal_up_to_rounding(V, B, tau):
+    """The draft's row is the target's plus a constant, or with one logit a unit in the last place up: the residual is rounding, or nothing
+    at all.  A candidate outside the vocabulary forces the draw, which must give an id of positive target probability, and for one
+    pair of rows must not fall while u rises."""
+    import torch
+    import paper_2505_10259_amd as P
+    g = torch.Generator("cuda").manual_seed(V)
+    masked = torch.arange(V, device="cuda") % 3 == 0          # id 0 among them
+    for same in (False, True):                                # a pair of rows each; one pair for all
+        p = (torch.randn(1 if same else B, 1, V, device="cuda", generator=g) * 2).masked_fill(masked, -float("inf"))
+        up = p.clone()
+        up[:, 0, V - 1 - int(masked[V - 1])] = torch.nextafter(p[:, 0, V - 1 - int(masked[V - 1])], torch.tensor(9.0, device="cuda"))
+        for q in (p + 0.37, p + torch.rand(p.shape[0], 1, 1, device="cuda", generator=g) * 3, up):
+            pb = p.expand(B, 1, V).repeat(1, 2, 1).contiguous()
+            qb = q.expand(B, 1, V).contiguous()
+            d = torch.full((B, 1), V, dtype=torch.int32, device="cuda")
+            ua = torch.full((B, 1), 0.5, device="cuda")
+            ur = ((torch.arange(B, device="cuda") + 0.5) / B).reshape(B, 1).repeat(1, 2).contiguous()
+            for n in (torch.full((B,), -1, dtype=torch.int32, device="cuda"), None):
+                nx = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+                P.spec_accept(pb, qb, d, ua, ur, tau, 0, 0, 0, B, 1, V, n, nx)
+                torch.cuda.synchronize()
+                t = nx.cpu().long()
+                assert ((t >= 0) & (t < V)).all() and not masked.cpu()[t].any(), (V, tau, same)
+                if n is not None:
+                    assert (n == 0).all()
+                if same:
+                    assert (t[1:] >= t[:-1]).all(), (V, tau)
+
+
+@pytest.mark.parametrize("V", [512, 4096, 40001])
+def test_weights_below_the_smallest_normal_number_are_drawn(V):
+    """A bonus row whose first id has the weight exp(x), subnormal, and whose last has 1, a long way behind: id 0 is drawn exactly while
+    u < exp(x) (the total is 1 in f32).  u half and twice the weight."""
+    import torch
+    import paper_2505_10259_amd as P
+    B = 64
+    x = torch.linspace(-101.0, -87.5, B, dtype=torch.float64).float()
+    p = torch.full((B, 2, V), -float("inf"), device="cuda")
+    p[:, 0, 1] = 0.0                             # the candidate, token 1, is certain on both sides: kept
+    q = p[:, :1].contiguous()
+    p[:, 1, 0], p[:, 1, V - 1] = x.cuda(), 0.0
+    d = torch.ones(B, 1, dtype=torch.int32, device="cuda")
+    ua = torch.full((B, 1), 0.5, device="cuda")
+    for factor, token in ((0.5, 0), (2.0, V - 1)):
+        u = (x.double().exp() * factor).float().cuda().reshape(B, 1).repeat(1, 2).contiguous()
+        for n in (torch.zeros(B, dtype=torch.int32, device="cuda"), None):
+            nx = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+            P.spec_accept(p, q, d, ua, u, 1.0, 0, 0, 0, B, 1, V, n, nx)
+            torch.cuda.synchronize()
+            assert nx.cpu().tolist() == [token] * B, factor
+
+
+@pytest.mark.parametrize("rows", ["random", "far"])
+@pytest.mark.parametrize("tau", [0.8, 1.0, 1.3])
+@pytest.mark.parametrize("V", [300, 4097, 32000, 65537, 131073])
+def test_normaliser_error_at_any_length(V, tau, rows):
+    """1 / normaliser as in test_normaliser_error, of random rows and of rows of one large logit and many equal ones far below it.  Bound in
+    units of 2^-24, of the value: an exponential (1.8, the library's), four levels of sums inside a step, one rounding of the thread's sum and its
+    corrections, an exponential and a product where threads and wavefronts meet (twice), six levels of lanes, the wavefronts one behind the other,
+    one for the division and one for the quotient that u is compared with: whatever the length.  On average (of 64) rounding takes no more than
+    a sixth of that."""
+    import torch
+    import paper_2505_10259_amd as P
+    B = 64
+    g = torch.Generator("cuda").manual_seed(V)
+    if rows == "random":
+        p = torch.randn(B, 2, V, device="cuda", generator=g) * 3
+    else:
+        p = (-torch.rand(B, 1, 1, device="cuda", generator=g) * 4 - float(np.log(V)) + 1).expand(B, 2, V).contiguous()
+        p[:, :, V // 3] = 0.0
+    d = p[:, :1].argmax(-1).to(torch.int32).contiguous()
+    q = torch.full((B, 1, V), -float("inf"), device="cuda").scatter_(2, d.long().unsqueeze(-1), 0.0)
+    n = torch.empty(B, dtype=torch.int32, device="cuda")
+    nx = torch.empty(B, dtype=torch.int32, device="cuda")
+    ur = torch.full((B, 2), 0.5, device="cuda")
+    lo = torch.zeros(B, dtype=torch.int32, device="cuda")
+    hi = torch.full((B,), 0x3f800000, dtype=torch.int32, device="cuda")
+    for _ in range(31):
+        mid = lo + (hi - lo) // 2
+        P.spec_accept(p, q, d, mid.view(torch.float32).reshape(B, 1).contiguous(), ur, tau, 0, 0, 0, B, 1, V, n, nx)
+        torch.cuda.synchronize()
+        lo, hi = torch.where(n == 1, mid, lo), torch.where(n == 1, hi, mid)
+    z = p[:, 0].double()                         # (torch's softmax of doubles is off by several units of 2^-24 itself)
+    ref = 1.0 / torch.exp((z - z.max(-1, keepdim=True).values) * float(np.float32(1.0) / np.float32(tau))).sum(-1)
+    err = (hi.view(torch.float32).double() / ref - 1).abs() * 2 ** 24
+    bound = 1.8 + 4 + 1 + 2 * 2.8 + 6 + 8 + 2
+    assert err.max().item() <= bound and err.mean().item() <= bound / 6, (err.max().item(), err.mean().item())
+
+
 @pytest.mark.parametrize("V,ahead", [(300, True), (9001, True), (24577, True), (65537, True), (9001, False)])
 def test_normaliser_error(V, ahead):
     """With a draft row of one id the candidate is kept exactly while u < p(c), so bisecting u gives p(c) to the bit; the id of the largest
