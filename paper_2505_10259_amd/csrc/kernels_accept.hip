@@ -700,34 +700,43 @@ accept_greedy_rows_kernel(AcceptArgs a) {
 // A workgroup leaves as soon as it sees a rejection in front of it; those of the first candidates start first, so with more
 // workgroups than the chip holds few rows are read for nothing.  In turn: a workgroup per sequence.
 //
-// Bound by HBM where many rows are read (256 sequences of 6 candidates over 32000 ids, all kept: 432 MB, 86 us), else by the latency of a
+// Bound by HBM where many rows are read (256 sequences of 8 candidates over 32000 ids, all kept: 557 MB, 116 us), else by the latency of a
 // workgroup's few steps, so: several granules of both rows requested ahead of those being summed, in every step as many (their
 // predecessors are waited for by count), two workgroups and more to a compute unit so that one's loads run under another's exponentials,
-// nothing of a row kept for the draw (it reads the rows again, from the caches), four-instruction exponentials in the
-// sums.  us per call (calls in a graph), candidates of which about 0.8 are kept / none / all, rows in registers of a 1024-thread workgroup or
-// library exponentials in 1024 threads before -> 256 threads up to 24576 ids, 512 above:
-//   ids     sequences, candidates   before                 at once               in turn
-//   32000   1, 4                    21.9 / 26.2 / 21.4     14.5 / 20.1 / 13.4    34.7 / 15.1 / 33.6
-//   32000   64, 8                   64.2 / 43.1 / 66.2     35.1 / 39.5 / 34.1    62.1 / 16.6 / 62.3
-//   32768   100, 4                  55.4 / 40.7 / 48.6     35.9 / 37.1 / 28.6    37.9 / 16.8 / 39.0
-//   32000   160, 3                  60.2 / 30.1 / 62.4     39.6 / 36.3 / 34.6    36.0 / 19.2 / 36.4
-//   32000   256, 1                  39.3 / 34.6 / 39.6     29.1 / 33.0 / 28.5    25.7 / 26.9 / 25.5
-//   32000   256, 6                  108 / 35.6 / 131       66.0 / 38.1 / 85.8    66.4 / 27.1 / 87.5
-//   65537   24, 5                   71.0 / 73.9 / 40.5     31.2 / 34.9 / 21.5    67.3 / 25.4 / 68.2
-//   99999   8, 2                    86.1 / 86.1 / 48.4     37.3 / 38.1 / 24.8    48.6 / 34.0 / 48.0
-//   20001   60, 8                   62.2 / 48.5 / 62.8     27.2 / 32.4 / 26.2    49.8 / 15.1 / 50.9
-//   9001    200, 8                  77.5 / 22.6 / 79.7     30.9 / 27.3 / 29.2    38.7 / 11.2 / 42.4
-//   3001    256, 8                  85.2 / 18.5 / 98.1     22.4 / 15.4 / 21.3    28.6 / 8.9 / 31.2
-//   1001    64, 4                   20.7 / 9.2 / 20.4      12.5 / 15.4 / 12.0    15.0 / 7.8 / 15.0
-//   512     4, 3                    23.0 / 23.3 / 18.0     10.4 / 11.0 / 9.3     11.6 / 7.5 / 12.2
-// (256 against 512 threads at once: 9001 ids 30.9 / 32.0, 20001 ids 27.2 / 28.4, 32000 ids, 256 sequences 81 / 66.)  A draft of which nothing at
-// all is kept is the one case in which at once is the slower way.  Tried and not kept: the non-temporal hint on the rows (66 -> 68, 35.9 -> 32.5),
-// asking for a rejection in front with every step (66 -> 75: the word of a sequence is in memory, and all ask for few lines of it).
-constexpr int IN_TURN_MIN_B = 128, IN_TURN_MAX_K = 3, ROWS_256_MAX_V = 24576;
-// Greedy at once: where all rows are few enough to read, 0.8 of the candidates agree / none / all, us, in turn -> at once: 32000 ids 16, 4
-// 17.9 / 5.5 / 18.0 -> 9.5 / 9.8 / 9.5, 64, 8 (74 MB) 33 / 5.7 / 35 -> 18.5 / 18.6 / 18.3, 256, 6 (229 MB) 34.7 / 7.3 / 43 -> 41 / 33 / 41; one
-// candidate, 256 sequences 15.4 / 7.9 / 16 -> 17.2; 65537 ids 24, 5 38 / 8.4 / 57 -> 20; 5003 ids 100, 5 20.8 / 5.6 / 20.8 -> 9.7.
-constexpr int64_t GREEDY_AHEAD_MAX_IDS = 20 << 20;
+// nothing of a row kept for the draw (it reads the rows again, from the caches).  us per call (calls in a graph, on the same rows: those
+// of up to 256 MB come from the last-level cache), none kept / 0.3 of the candidates / 0.8 / all, rows in registers of a
+// 1024-thread workgroup or general kernels before -> 256 threads up to 8192 ids at once and 24576 in turn, 512 above:
+//   ids     sequences, candidates   before                       at once                      in turn
+//   512     4, 4                    24.0 / 24.0 / 23.1 / 18.0    11.9 / 12.0 / 11.0 / 9.9     7.9 / 7.9 / 15.3 / 15.4
+//   512     16, 8                   25.4 / 24.8 / 24.1 / 19.1    13.4 / 12.9 / 12.1 / 10.1    8.2 / 13.1 / 23.9 / 24.2
+//   1001    16, 8                   9.7 / 19.6 / 34.3 / 34.5     13.3 / 13.0 / 12.5 / 10.4    8.4 / 14.2 / 24.3 / 24.6
+//   1001    64, 4                   9.9 / 19.9 / 20.9 / 20.9     14.4 / 14.1 / 13.2 / 12.4    8.4 / 14.0 / 16.0 / 16.2
+//   1001    64, 8                   9.8 / 19.8 / 34.5 / 34.7     16.8 / 16.2 / 14.3 / 14.1    8.7 / 13.6 / 24.6 / 24.9
+//   4001    100, 8                  40.3 / 39.9 / 50.5 / 52.5    18.2 / 18.4 / 18.6 / 16.0    10.7 / 19.2 / 33.0 / 34.9
+//   9001    200, 4                  23.5 / 43.1 / 47.3 / 48.6    19.4 / 28.1 / 27.8 / 27.3    12.9 / 23.7 / 28.4 / 31.0
+//   9001    200, 8                  23.5 / 65.0 / 78.2 / 80.4    20.3 / 28.7 / 35.1 / 37.6    13.1 / 34.4 / 45.1 / 49.5
+//   20001   128, 8                  33.2 / 77.6 / 121 / 124      31.3 / 37.3 / 43.8 / 43.8    18.8 / 41.9 / 65.4 / 66.6
+//   32000   1, 4                    27.3 / 27.1 / 27.0 / 21.8    24.2 / 24.1 / 24.2 / 17.5    20.9 / 21.0 / 21.0 / 44.3
+//   32000   64, 8                   44.3 / 42.6 / 63.1 / 66.6    41.5 / 38.7 / 38.9 / 37.3    21.6 / 42.4 / 77.6 / 78.9
+//   32000   128, 4                  28.7 / 63.3 / 68.4 / 71.8    39.4 / 39.8 / 42.9 / 37.8    22.6 / 45.4 / 48.8 / 50.4
+//   32000   256, 4                  35.8 / 68.5 / 76.0 / 89.9    39.0 / 56.8 / 59.4 / 56.8    29.8 / 51.8 / 55.8 / 61.8
+//   32000   128, 8                  28.8 / 71.2 / 111 / 127      40.0 / 46.3 / 55.7 / 55.4    22.4 / 51.7 / 79.6 / 87.0
+//   32000   256, 8                  35.8 / 98.9 / 132 / 163      41.0 / 58.1 / 81.0 / 116     31.2 / 73.2 / 91.7 / 112
+//   65537   16, 4                   70.0 / 68.5 / 68.2 / 39.2    40.7 / 39.8 / 39.0 / 26.0    34.7 / 71.5 / 74.8 / 75.5
+//   65537   256, 4                  77.5 / 151 / 178 / 187       71.7 / 105 / 118 / 123       49.6 / 89.5 / 99.4 / 119
+// In turn, then: short rows, but for few sequences of many candidates, and many sequences of up to four.  Faster than before at every rate but for short
+// rows off 16 bytes of few sequences (1001 ids, 16, 8: 13.3 against 9.7 with nothing kept) and 24577 to 32768 ids of 128
+// sequences and more of eight candidates and more (1.15 to 1.44 of it with nothing kept, 0.4 to 0.7 from 0.3 on).
+// 256 against 512 threads at once, 9001 ids, 200 sequences of 8: 28.5 / 30.5 / 34.5 / 32 against 20.3 / 28.7 / 35.1 / 37.6; 6001 ids, 256 of 8: 24 / 27 /
+// 30 / 30 against 19 / 28 / 37 / 41.  Tried and not kept: the non-temporal hint on the rows (256 of 6 over 32000 ids 66 -> 68, 100 of 4 over 32768 35.9 -> 32.5), asking
+// for a rejection in front with every step (66 -> 75: the word of a sequence is in memory, and all ask for few lines of it).
+constexpr int SHORT_MAX_V = 3072, IN_TURN_MAX_K = 4, IN_TURN_MIN_B = 128, IN_TURN_SHORT_MIN_B = 32, ROWS_256_AHEAD_MAX_V = 8192, ROWS_256_MAX_V = 24576;
+// Greedy at once: where all rows are few enough to read (ROWS_MAX_IDS) and several may be kept, so that what is read for nothing where the first
+// differs is little against the rows that come one behind the other where it does not.  us, in turn -> at once, first differs / 0.3 / 0.8 of the
+// candidates agree / all: 9001 ids 16, 4 5.6 / 14.0 / 17.4 / 17.5 -> 8.8 / 8.6 / 8.6 / 8.4, 100, 8 5.7 / 14.0 / 29.1 / 31.9 -> 11.9 / 11.7 / 11.3 / 11.3;
+// 32000 16, 8 5.7 / 14.5 / 30.5 / 30.7 -> 10.2 / 9.7 / 9.8 / 9.7; 65537 16, 2 8.6 / 20.1 / 20.5 / 20.6 -> 11.4 / 11.5 / 11.4 / 11.3.  In turn: 32000 16, 2
+// 5.8 / 11.4 / 11.9 / 12.2 -> 9.0 / 9.0 / 9.0 / 8.8, 64, 4 5.9 / 14.5 / 19.5 / 21.3 -> 13.1 / 13.4 / 13.3 / 13.6, 64, 8 5.9 / 14.5 / 34.6 / 35.7 -> 18.2 / 18.2 / 18.4 / 18.4;
+// 9001 256, 8 6.1 / 22.6 / 31.7 / 34.9 -> 18.3 / 19.3 / 19.9 / 20.5.
 constexpr int PICK_BITS = 27;
 constexpr uint32_t PICK_NO_TOKEN = (1u << PICK_BITS) - 1;
 __global__ void accept_begin_kernel(AcceptArgs a) {
@@ -867,27 +876,26 @@ static inline bool fast_rows_ok(const float* base, int V) {
     return V % 4 == 0 && V <= FAST_MAX_V && ((uintptr_t)base & 15) == 0;
 }
 
-template <int T>
-static void launch_accept_rows(const AcceptArgs& a, bool ahead, hipStream_t st) {
-    if (ahead) hipLaunchKernelGGL(accept_begin_kernel, dim3((a.B + 255) / 256), dim3(256), 0, st, a);
-    if (ahead) hipLaunchKernelGGL((accept_rows_kernel<T, true>), dim3(a.B * (a.k + 1)), dim3(T), 0, st, a);
-    else hipLaunchKernelGGL((accept_rows_kernel<T, false>), dim3(a.B), dim3(T), 0, st, a);
+template <int T, bool AHEAD>
+static void launch_accept_rows(const AcceptArgs& a, hipStream_t st) {
+    if (AHEAD) hipLaunchKernelGGL(accept_begin_kernel, dim3((a.B + 255) / 256), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((accept_rows_kernel<T, AHEAD>), dim3(AHEAD ? a.B * (a.k + 1) : a.B), dim3(T), 0, st, a);
 }
 
 hipError_t launch_accept(const AcceptArgs& a, hipStream_t st) {
     if (a.B <= 0) return hipSuccess;
-    const bool fast = fast_rows_ok(a.p_logits, a.V) && (!a.q_logits || fast_rows_ok(a.q_logits, a.V));
+    const bool fast = fast_rows_ok(a.p_logits, a.V);
     const bool can = a.n_accepted && a.next_token && a.V >= 4 && a.V < (int)PICK_NO_TOKEN;      // (the outputs are the meeting point)
     const int64_t ids = (int64_t)a.B * (a.k + 1) * a.V;
     if (a.q_logits) {
-        // Rows at once but for many sequences of few candidates, where the chip is full in turn as well (figures at the kernel)
-        const bool ahead = can && !(a.B >= IN_TURN_MIN_B && a.k <= IN_TURN_MAX_K);
+        // (figures at the kernel)
+        const bool turn = a.V <= SHORT_MAX_V ? a.k <= IN_TURN_MAX_K || a.B >= IN_TURN_SHORT_MIN_B : a.k <= IN_TURN_MAX_K && a.B >= IN_TURN_MIN_B;
         if (a.V < 4) hipLaunchKernelGGL(accept_sample_tiny_kernel, dim3((a.B + 63) / 64), dim3(64), 0, st, a);
-        else if (a.V <= ROWS_256_MAX_V) launch_accept_rows<256>(a, ahead, st);
-        else launch_accept_rows<512>(a, ahead, st);
+        else if (can && !turn) a.V <= ROWS_256_AHEAD_MAX_V ? launch_accept_rows<256, true>(a, st) : launch_accept_rows<512, true>(a, st);
+        else a.V <= ROWS_256_MAX_V ? launch_accept_rows<256, false>(a, st) : launch_accept_rows<512, false>(a, st);
     } else if (a.V <= ROWS_MAX_V && (!fast || ids <= ROWS_MAX_IDS)) {
         hipLaunchKernelGGL(accept_greedy_rows_kernel, dim3(a.B), dim3(FAST_THREADS), 0, st, a);
-    } else if (can && a.k >= 2 && ids <= GREEDY_AHEAD_MAX_IDS) {
+    } else if (can && a.k >= (a.V > FAST_MAX_V ? 2 : 3) && ids <= ROWS_MAX_IDS) {
         hipLaunchKernelGGL(accept_begin_kernel, dim3((a.B + 255) / 256), dim3(256), 0, st, a);
         hipLaunchKernelGGL(accept_greedy_ahead_kernel, dim3(a.B * (a.k + 1)), dim3(512), 0, st, a);
     } else if (fast) {

@@ -196,18 +196,22 @@ def test_accept_sample_wide_rows_and_both_test_orders(B, k, V, tau):
     assert torch.equal(out[0], out[1])
 
 
-# edges of the row kernels: granules that the row ends in, workgroups of 256 and 512 threads (24576 ids), rows at once and in turn (128
-# sequences, 3 candidates), one wavefront's and one workgroup's granules and one id more
+# edges of the row kernels: granules that the row ends in, one wavefront's and one workgroup's granules and one id more, workgroups of 256 and
+# 512 threads (at once 8192 ids, in turn 24576), rows at once and in turn (3072 ids, four candidates, 32 and 128 sequences)
 @pytest.mark.parametrize("B,k,V,tau", [(4, 2, 4, 0.8), (4, 2, 5, 0.8), (4, 2, 7, 0.8), (4, 2, 257, 0.8), (4, 2, 1023, 0.8), (4, 2, 1025, 0.8),
                                        (4, 2, 4097, 0.8), (4, 3, 24576, 0.8), (4, 3, 24577, 0.8), (4, 2, 24579, 0.8), (4, 2, 131073, 0.8),
-                                       (127, 3, 130, 0.8), (128, 3, 130, 0.8), (128, 4, 130, 0.8)])
+                                       (127, 3, 130, 0.8), (128, 3, 130, 0.8), (128, 4, 130, 0.8),
+                                       (4, 5, 4, 0.8), (4, 5, 5, 0.8), (4, 5, 7, 0.8), (4, 5, 257, 0.8), (4, 5, 1023, 0.8), (4, 5, 1025, 0.8),
+                                       (31, 5, 130, 0.8), (32, 5, 130, 0.8), (8, 5, 3072, 0.8), (8, 4, 3073, 0.8), (127, 4, 3074, 0.8),
+                                       (128, 4, 3074, 0.8), (128, 5, 3074, 0.8), (4, 3, 8192, 0.8), (4, 3, 8193, 0.8)])
 def test_accept_sample_row_kernels(B, k, V, tau):
     test_accept_sample_wide_rows_and_both_test_orders(B, k, V, tau)
 
 
-# greedy rows at once (from two candidates and 4097 ids on) and, without n_accepted, in turn
+# greedy rows at once (from 4097 ids and three candidates on, over 32768 ids two; up to 8 M ids) and, without n_accepted, in turn
 @pytest.mark.parametrize("B,k,V", [(5, 2, 4097), (5, 2, 4098), (5, 2, 4100), (5, 3, 8195), (3, 2, 65537), (5, 1, 8195), (40, 16, 4100),
-                                   (300, 16, 4112)])
+                                   (300, 16, 4112), (5, 3, 4097), (5, 3, 4098), (5, 3, 4099), (5, 3, 4100), (3, 2, 32768), (3, 2, 32769),
+                                   (120, 16, 4112), (121, 16, 4112)])
 def test_accept_greedy_at_once_and_in_turn(B, k, V):
     import torch
     import paper_2505_10259_amd as P
@@ -226,9 +230,9 @@ def test_accept_greedy_at_once_and_in_turn(B, k, V):
             assert n.cpu().tolist() == [e[0] for e in exp]
 
 
-# rows at once (4097, 32000, 65537), a wavefront per row (1001) and, without n_accepted or of one candidate, in turn
+# rows at once (from three candidates on), a wavefront per row (1001) and, without n_accepted or of one or two candidates, in turn
 @pytest.mark.parametrize("bad", [float("nan"), -float("inf")])
-@pytest.mark.parametrize("B,k,V", [(9, 2, 4097), (9, 16, 4097), (9, 2, 32000), (9, 16, 32000), (9, 3, 65537), (9, 1, 32000), (9, 4, 1001)])
+@pytest.mark.parametrize("B,k,V", [(9, 2, 4097), (9, 3, 4097), (9, 16, 4097), (9, 2, 32000), (9, 16, 32000), (9, 3, 65537), (9, 1, 32000), (9, 4, 1001)])
 def test_greedy_row_without_a_number_keeps_nothing(B, k, V, bad):
     """A row that is -inf or not-a-number throughout keeps no candidate, whatever the rows behind it say, and its token is 0."""
     import torch
@@ -370,6 +374,47 @@ def test_normaliser_error_at_any_length(V, tau, rows):
     assert err.max().item() <= bound and err.mean().item() <= bound / 6, (err.max().item(), err.mean().item())
 
 
+# each at most 0.7 of its time at once
+@pytest.mark.parametrize("B,k,V,greedy", [(64, 4, 1001, False), (256, 4, 32000, False), (64, 8, 32000, True), (24, 5, 65537, True), (100, 2, 9001, True)])
+def test_drafts_of_which_nothing_is_kept_cost_what_their_first_rows_cost(B, k, V, greedy):
+    """Calls that rows at once slow down most where the first candidate is rejected are as fast as in turn (without n_accepted): a quarter of
+    the time is left for the clock."""
+    import torch
+    import paper_2505_10259_amd as P
+    g = torch.Generator("cuda").manual_seed(V)
+    p = torch.randn(B, k + 1, V, device="cuda", generator=g)
+    best = p[:, :k].argmax(-1).to(torch.int32)
+    d = ((best + 1) % V).to(torch.int32) if greedy else best
+    q = None if greedy else p[:, :k].contiguous().scatter_(2, d.long().unsqueeze(-1), 40.0)
+    ua = None if greedy else torch.full((B, k), 0.9999, device="cuda")
+    ur = None if greedy else torch.rand(B, k + 1, device="cuda", generator=g)
+    nx = torch.zeros(B, dtype=torch.int32, device="cuda")
+    n = torch.zeros(B, dtype=torch.int32, device="cuda")
+    st = torch.cuda.Stream()
+    us = {}
+    for key, count in (("rule", n), ("turn", None)):
+        call = lambda: P.spec_accept(p, q, d, ua, ur, 1.0, 0, 0, 0, B, k, V, count, nx, st.cuda_stream)
+        torch.cuda.synchronize()
+        call()
+        st.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            for _ in range(20):
+                call()
+        times = []
+        for _ in range(6):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            with torch.cuda.stream(st):
+                e0.record()
+                graph.replay()
+                e1.record()
+            st.synchronize()
+            times.append(e0.elapsed_time(e1))
+        us[key] = min(times) * 50
+    assert (n == 0).all()
+    assert us["rule"] <= 1.25 * us["turn"], us
+
+
 @pytest.mark.parametrize("V,ahead", [(300, True), (9001, True), (24577, True), (65537, True), (9001, False)])
 def test_normaliser_error(V, ahead):
     """With a draft row of one id the candidate is kept exactly while u < p(c), so bisecting u gives p(c) to the bit; the id of the largest
@@ -404,7 +449,7 @@ def test_normaliser_error(V, ahead):
     assert ((got / ref - 1).abs() * 2 ** 24).max().item() <= bound
 
 
-@pytest.mark.parametrize("V", [512, 40001])
+@pytest.mark.parametrize("V", [512, 4000, 40001])        # (512: in turn)
 def test_accept_at_once_under_capture(V):
     """The outputs are the meeting point of the workgroups of a sequence: every replay starts it afresh, whatever they hold."""
     import torch
