@@ -323,9 +323,10 @@ def test_gemm_f32_same_bits_on_every_kernel(M, N, K, values):
         assert torch.equal(C.view(torch.int32)[~nan], ref.view(torch.int32)[~nan]), name
 
 
-# segments of 16 k, empty and ragged ones, pieces of 8 and of 16 on either side of a fold; the last three are tiles enough for one wavefront each
+# segments of 16 k, empty and ragged ones, pieces of 8 and of 16 on either side of a fold; the three in front of the last are tiles enough for
+# one wavefront each (127 of 64 x 64 at most, more than 512 of 16 x 16); the last is 128 of 64 x 64
 @pytest.mark.parametrize("M,N,K", [(3, 24, 16), (16, 40, 68), (16, 40, 132), (5, 33, 1028), (20, 64, 2052),
-                                   (64, 8064, 260), (64, 8100, 1028), (33, 8192, 2064)])
+                                   (64, 8064, 260), (64, 8100, 1028), (33, 8100, 2064), (33, 8192, 2064)])
 def test_gemm_f32_four_segments(M, N, K):
     """An f32 sum is four chains over consecutive segments of the contraction, added in ascending order, whichever kernel makes it: the
     matrix cores with a wavefront per segment or for all four, 8 x 32 tiles (operands off 16 bytes) and 64 x 64 tiles (the same rows

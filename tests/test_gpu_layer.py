@@ -187,6 +187,36 @@ def test_f32_layer_output_at_any_address(n_experts, static):
     assert torch.isfinite(out[0]).all() and all(torch.equal(o, out[0]) for o in out[1:])
 
 
+# rotated projection of 126 heads and gate/up of 8064 columns (dense), gate/up of 8 experts: with 5 rows 504 tiles of two matrices for the
+# projection (a wavefront per segment) and more than 512 for gate/up (one for all four), with 20 rows more than 512 for both, with 130 tiles of 64 x 64
+@pytest.mark.parametrize("n_experts,heads,d_ff", [(0, (112, 7), 8064), (8, (8, 2), 2048)])
+def test_f32_layer_rows_have_the_same_bits_whatever_the_products_tiles(n_experts, heads, d_ff):
+    """One wavefront for all four segments of a sum, a wavefront for each, 8 x 32 tiles (plain-kernel flag) and 64 x 64 tiles: gated and rotated
+    products have the same bits, contractions of 512 and more."""
+    import torch
+    import paper_2505_10259_amd as P
+    from gpu_common import dev, host_model_pinned
+    shp = synth.mini_moe_shape(dtype="f32", n_layers=1, d_model=512, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=64, d_ff=d_ff,
+                               n_experts=n_experts)
+    hm = host_model_pinned(shp, seed=3, std=0.05)
+    n_new, ctx = 5, 13
+    x, kc, vc = synth.make_layer_inputs(shp, 26, n_new, ctx, seed=4)
+
+    def run(B, flags=0):
+        with P.Session(hm, None, batch_max=B, k_max=n_new - 1, ctx_max=ctx + n_new + 2, flags=flags) as s:
+            P.spec_kv_import(s.ctx, 0, 0, dev(kc[:B]), dev(vc[:B]), B, ctx)
+            xd, out = dev(x[:B * n_new]), torch.empty(B * n_new, shp.d_model, device="cuda")
+            P.spec_layer_forward(s.ctx, 0, 0, xd, n_new, out)
+            P.spec_sync(s.ctx, 0)
+            return out
+
+    ref = run(26)
+    assert torch.isfinite(ref).all()
+    # (with the flag a router kernel of its own sums in another order)
+    for B, flags in ((1, 0), (4, 0), (12, 0)) + (() if n_experts else ((4, P.SPEC_FLAG_SIMPLE_KERNELS),)):
+        assert torch.equal(run(B, flags), ref[:B * n_new]), (B, flags)
+
+
 # query rows x heads on either side of the lines between the two kernels (768 and 640), and far beyond
 @pytest.mark.parametrize("head_dim,B,n_new,ctx", [(64, 96, 2, 70), (64, 193, 1, 70), (128, 80, 2, 70), (128, 161, 1, 70), (128, 64, 5, 300)])
 def test_f32_attention_on_either_side_of_the_kernel_for_few_rows(head_dim, B, n_new, ctx):
