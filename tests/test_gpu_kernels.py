@@ -123,8 +123,6 @@ def test_gemm_narrow_tiles_with_every_epilogue_change_no_bit(tile_rows, epilogue
             assert (out[1].double() - x).abs().max().item() < 2e-4 * np.sqrt(K) * 0.05 + 2.0 ** -22
 
 
-# 36 column tiles for each of the groups that have rows: an XCD's list is longer than its 32 units by a few tiles, which are cut
-# into column halves where one row tile reads the weights; the last column tile is ragged on either side of its middle
 # few rows that reach few of the groups: narrower tiles than for all groups
 @pytest.mark.parametrize("epilogue", ["store", "swiglu"])
 @pytest.mark.parametrize("sizes", [(0, 1, 0, 0, 0, 0, 0, 1), (1, 0, 0, 1, 0, 2, 0, 0), (0, 0, 0, 3, 0, 0, 0, 3), (2, 1, 1, 0, 2, 0, 1, 1)])
@@ -150,6 +148,8 @@ def test_gemm_few_live_groups_change_no_bit(epilogue, sizes):
     assert torch.equal(C, D)
 
 
+# 36 column tiles for each of the groups that have rows: an XCD's list is longer than its 32 units by a few tiles, which are cut
+# into column halves where one row tile reads the weights; the last column tile is ragged on either side of its middle
 @pytest.mark.parametrize("epilogue", ["store", "add", "swiglu"])
 @pytest.mark.parametrize("short_by", [32, 160])
 @pytest.mark.parametrize("sizes", [(80, 80, 80, 80, 80, 80, 80, 80), (5, 128, 0, 97, 64, 17, 33, 96),
