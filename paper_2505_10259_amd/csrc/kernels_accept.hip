@@ -508,7 +508,7 @@ struct FastShared {
     int redi[FAST_WAVES];
     float tot[FAST_SWEEPS * FAST_WAVES];     // wave totals of every sweep, then their exclusive prefix
     float total;
-    int pick, last, stop;
+    int pick, last;
 };
 
 __device__ inline void fast_load_row(const float* __restrict__ row, int V, float4 (&v)[FAST_SWEEPS]) {
