@@ -865,6 +865,8 @@ double live_groups(const GemmArgs& a) {
     if (g < 3 || a.m_upper < 2) return std::min(g, (double)std::max(1, a.m_upper));
     return g * (1.0 - std::pow(1.0 - 2.0 / g, a.m_upper / 2));
 }
+// tiles of a product of which `groups` matrices are cut into nt row tiles and columns of `cols`
+int64_t expected_tiles(const GemmArgs& a, double groups, int nt, int cols) { return (int64_t)(groups * nt * ((a.N + cols - 1) / cols) + 0.5); }
 
 struct TileChoice { int ni = 8, max_rows = 256; double cost = 0.0; };
 
@@ -874,14 +876,13 @@ struct TileChoice { int ni = 8, max_rows = 256; double cost = 0.0; };
 // its slabs; a last round that fills at most half the units is cut in halves (256 columns); and the weights come from HBM
 // at 6.5 TB/s at best.  (Fitted on weights as rows; panels of K = 4096 and more take 2 to 14 % less time up to 896 rows, which
 // moves all tilings of a product alike.)  The second term of the result keeps the cheaper of two tilings that both wait for HBM.
-double tile_cost(const GemmArgs& a, int ni, int max_rows) {
+double tile_cost(const GemmArgs& a, double groups, int ni, int max_rows) {
     const bool sw = a.epilogue == EPI_SWIGLU_T;
     const int cols = sw ? 16 * ni : 32 * ni;
-    const double groups = live_groups(a);
     int nt, rt;
     split_rows(expected_rows(a), max_rows, nt, rt);
     const int mi = (rt + 31) / 32, slabs = a.K / 64;
-    const int64_t jobs = (int64_t)(groups * nt * ((a.N + cols - 1) / cols) + 0.5);
+    const int64_t jobs = expected_tiles(a, groups, nt, cols);
     double slab = std::max(0.076 * (mi + ni) + 0.02, 0.0168 * mi * ni);
     if (nt > 1) slab *= 1.05;              // (the row tiles of one weight slab do not all find it in L2)
     const int64_t full = jobs / 256, rem = jobs % 256;
@@ -895,16 +896,14 @@ double tile_cost(const GemmArgs& a, int ni, int max_rows) {
 // its accumulator height in 32-row units plus about three units for the column operand and the
 // per-slab overheads (fitted to measurements of the projection shapes).  Each group is then cut into
 // equal tiles of at most that height on the device.
-TileChoice choose_wide(const GemmArgs& a) {
-    const bool sw = a.epilogue == EPI_SWIGLU_T;
-    const int tiles_n = (a.N + (sw ? 127 : 255)) / (sw ? 128 : 256), r = expected_rows(a);
-    const int groups = a.group_offsets ? (a.n_groups > 0 ? a.n_groups : 1) : 1;
+TileChoice choose_wide(const GemmArgs& a, double groups) {
+    const int cols = a.epilogue == EPI_SWIGLU_T ? 128 : 256, r = expected_rows(a);
     TileChoice t;
     double best = 0;
     for (int cand = 256; cand >= 96; cand -= 32) {
         int nt, rt;
         split_rows(r, cand, nt, rt);
-        const int64_t jobs = (int64_t)groups * nt * tiles_n;
+        const int64_t jobs = expected_tiles(a, groups, nt, cols);
         const double cost = (double)((jobs + 255) / 256) * ((rt + 31) / 32 + 3);
         if (best == 0 || cost < best - 1e-9) { best = cost; t.max_rows = cand; }
     }
@@ -912,7 +911,7 @@ TileChoice choose_wide(const GemmArgs& a) {
     // the largest of eight passes 128 rows often where r does, and each one that does adds a round of tiles (8x22B shape,
     // 495 rows, r = 128: gate/up and down 730 + 398 us with this limit, 639 + 356 with the one found above).
     if (r <= (a.group_offsets ? 112 : 128)) t.max_rows = 128;
-    t.cost = tile_cost(a, 8, t.max_rows);
+    t.cost = tile_cost(a, groups, 8, t.max_rows);
     return t;
 }
 
@@ -925,10 +924,11 @@ TileChoice choose_wide(const GemmArgs& a) {
 //   chosen      11 / 12    14 / 14    14 / 19    17 / 24    25 / 33    39 / 51
 //   panels      11 / 13    13 / 15               17 / 22    23 / 31    37 / 44
 TileChoice choose_tiles(const GemmArgs& a) {
-    TileChoice best = choose_wide(a);
+    const double groups = live_groups(a);
+    TileChoice best = choose_wide(a, groups);
     for (int ni = 4; ni >= (a.epilogue == EPI_SWIGLU_T ? 4 : 1); ni /= 2)
         for (int rows = 256; rows >= 32; rows -= 32) {
-            const double c = tile_cost(a, ni, rows);
+            const double c = tile_cost(a, groups, ni, rows);
             if (c < 0.97 * best.cost) best = TileChoice{ni, rows, c};
         }
     return best;
