@@ -1001,7 +1001,7 @@ bool qkv_unfused_pays(int M, int N, int K) {
     if (M <= 448 || N >= 4096) return false;
     GemmArgs a{};
     a.M = M; a.N = N; a.K = K; a.epilogue = EPI_STORE_F32;
-    const TileChoice t = choose_tiles(a), w = choose_wide(a);
+    const TileChoice t = choose_tiles(a), w = choose_wide(a, live_groups(a));
     return t.ni < 8 && t.cost + 6.0 + 2.0 * M * N * 4.0 / 4.0e6 < w.cost;
 }
 
