@@ -725,8 +725,8 @@ accept_greedy_rows_kernel(AcceptArgs a) {
 //   65537   16, 4                   70.0 / 68.5 / 68.2 / 39.2    40.7 / 39.8 / 39.0 / 26.0    34.7 / 71.5 / 74.8 / 75.5
 //   65537   256, 4                  77.5 / 151 / 178 / 187       71.7 / 105 / 118 / 123       49.6 / 89.5 / 99.4 / 119
 // In turn, then: short rows, but for few sequences of many candidates, and many sequences of up to four.  Faster than before at every rate but for short
-// rows off 16 bytes of few sequences (1001 ids, 16, 8: 13.3 against 9.7 with nothing kept) and 24577 to 32768 ids of 128
-// sequences and more of eight candidates and more (1.15 to 1.44 of it with nothing kept, 0.4 to 0.7 from 0.3 on).
+// rows off 16 bytes of few sequences (1001 ids, 16, 8: 13.3 against 9.7 with nothing kept) and, of 128 sequences and more, 24577 to 32768 ids and more
+// than four candidates (1.1 to 1.44 of it with nothing kept, 0.4 to 0.75 from 0.3 on) and 5000 to 8192 ids and 16 (1.1 to 1.27, 0.2 to 0.45).
 // 256 against 512 threads at once, 9001 ids, 200 sequences of 8: 28.5 / 30.5 / 34.5 / 32 against 20.3 / 28.7 / 35.1 / 37.6; 6001 ids, 256 of 8: 24 / 27 /
 // 30 / 30 against 19 / 28 / 37 / 41.  Tried and not kept: the non-temporal hint on the rows (256 of 6 over 32000 ids 66 -> 68, 100 of 4 over 32768 35.9 -> 32.5), asking
 // for a rejection in front with every step (66 -> 75: the word of a sequence is in memory, and all ask for few lines of it).
